@@ -10,10 +10,17 @@
 // that match the digits fixed so far, of (count, sum of the 23-bit mantissas);
 // all candidates of a bin share their exponent, so the bin's score mass is
 // (count * 2^23 + mantissa sum) * 2^(e - 150) EXACTLY, from integer sums whose
-// order cannot matter.  One thread then walks the bins from the top, adding
-// their masses in fp64 in that fixed order, until the running sum reaches the
-// target.  Nothing in the kernel adds floating-point numbers atomically:
-// repeated runs give identical lists.
+// order cannot matter.  One wave then walks the bins from the top: a lane holds
+// four bins, the running sums come from an fp64 scan over the lanes in a fixed
+// order, and the first bin whose running sum reaches the target is the digit.
+// Nothing in the kernel adds floating-point numbers atomically: repeated runs
+// give identical lists.  (One thread walking the 256 bins pays an LDS round trip
+// per bin and was 17 us in each of the four passes.)
+//
+// Measured, both directions of a layer in one launch: 1 head of 1024 candidates
+// 76 -> 13 us, 32 heads of 8192 88 -> 19 us, of 32768 112 -> 45 us, of 131072
+// 211 -> 145 us.  The small ones are four passes of three barriers; the large ones
+// are bound by the LDS atomics (about one per clock and CU, 64 CUs at work).
 //
 // The histogram lives in LDS and is updated with one 64-bit integer atomic per
 // candidate (count in the upper bits, mantissa sum below).  Scores of one head
@@ -37,6 +44,7 @@ constexpr int NW = NT / 64;
 constexpr int kCopies = 32;                 // copies of every histogram bin
 constexpr int kCntShift = 43;               // packed bin: count << 43 | mantissa sum (2^24 candidates at most:
                                             // a copy sees 2^19 of them, mantissa sum < 2^42, count < 2^20)
+constexpr unsigned int kNoKey = 0xFFFFFFFFu;
 constexpr int kBatch = 16;                  // scores a lane requests before it uses the first
 constexpr size_t kSelectLds = 256 * kCopies * sizeof(unsigned long long);
 
@@ -49,7 +57,6 @@ __device__ __forceinline__ unsigned int score_key(float v) {
 
 __global__ __launch_bounds__(NT) void select_kernel(SelectParams P) {
   extern __shared__ __attribute__((aligned(16))) unsigned long long hist[];   // [256 bins][kCopies]
-  __shared__ unsigned long long hms[256];     // sum of the mantissas per bin
   __shared__ unsigned int hcnt[256];
   __shared__ double bsum[256];                // mass per bin
   __shared__ double sh_above, sh_target;
@@ -77,86 +84,141 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectParams P) {
   const int n_groups = (S + 63) / 64;
   const int g_lo = (int)((long long)n_groups * wave / NW), g_hi = (int)((long long)n_groups * (wave + 1) / NW);
 
+  // kBatch loads in flight per lane: a wave that waits for every score before it asks for
+  // the next spends the pass waiting.  Up to 16384 candidates a wave's run is one batch: it
+  // is read once and stays in registers for all six sweeps.
+  unsigned int key[kBatch];                  // kNoKey past the end: matches no digit, exceeds no cut (as a signed number)
+  auto load_batch = [&](int g0) {
+    float v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = (g0 + u) * 64 + lane;
+      v[u] = (g0 + u < g_hi && i < S) ? sc[i] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = (g0 + u) * 64 + lane;
+      key[u] = (g0 + u < g_hi && i < S) ? score_key(v[u]) : kNoKey;
+    }
+  };
+  const bool resident = n_groups <= NW * kBatch;
+  if (resident) load_batch(g_lo);
+
   if (tid == 0) { sh_above = 0.0; sh_prefix = 0u; sh_done = 0u; sh_m = 0u; }
+  for (int x = tid; x < 256 * kCopies; x += NT) hist[x] = 0ull;
+  __syncthreads();
   // digit p: bits [shift, shift + width) of the 31-bit key
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = (pass == 3) ? 0 : 23 - 8 * pass;
     const int above_shift = (pass == 0) ? 31 : 31 - 8 * pass;    // bits from here up are fixed
     const unsigned int dmask = (pass == 3) ? 127u : 255u;
-    for (int x = tid; x < 256 * kCopies; x += NT) hist[x] = 0ull;
-    __syncthreads();
     const unsigned int prefix = sh_prefix;
+    const unsigned int fixed = prefix >> above_shift;
     unsigned long long* my_hist = hist + (lane & (kCopies - 1));
-    // kBatch loads in flight per lane: a wave that waits for every score before it asks
-    // for the next spends the pass waiting
     for (int g0 = g_lo; g0 < g_hi; g0 += kBatch) {
-      float v[kBatch];
+      if (!resident) load_batch(g0);
+      auto credit = [&](unsigned int x) {
+        if ((x >> above_shift) == fixed) {
+          const unsigned int b = (x >> shift) & dmask;
+          atomicAdd(my_hist + b * kCopies, (1ull << kCntShift) | (unsigned long long)(x & 0x7FFFFFu));
+        }
+      };
+      if (g0 + kBatch <= g_hi) {
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = (g0 + u) * 64 + lane;
-        v[u] = (g0 + u < g_hi && i < S) ? sc[i] : 0.0f;
-      }
+        for (int u = 0; u < kBatch; ++u) credit(key[u]);
+      } else {
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const unsigned int key = score_key(v[u]);
-        const bool in = g0 + u < g_hi && (g0 + u) * 64 + lane < S;
-        const bool live = in && (pass == 0 || (key >> above_shift) == (prefix >> above_shift));
-        const unsigned int b = (key >> shift) & dmask;
-        if (live) atomicAdd(my_hist + b * kCopies, (1ull << kCntShift) | (unsigned long long)(key & 0x7FFFFFu));
+        for (int u = 0; u < kBatch; ++u) {
+          if (g0 + u >= g_hi) break;                           // (wave-uniform: short problems skip the empty steps)
+          credit(key[u]);
+        }
       }
     }
     __syncthreads();
-    if (tid < 256) {
-      // the copies of bin tid, each thread starting at another copy (spreads the LDS banks)
+    {
+      // four threads per bin, eight copies each (started at different copies, to spread the
+      // LDS banks), left cleared for the next pass
+      const int bin = tid >> 2;
+      unsigned long long* part = hist + bin * kCopies + (tid & 3) * (kCopies / 4);
       unsigned long long c = 0ull, ms = 0ull;
-      for (int x = 0; x < kCopies; ++x) {
-        const unsigned long long v = hist[tid * kCopies + ((x + tid) & (kCopies - 1))];
+#pragma unroll
+      for (int x = 0; x < kCopies / 4; ++x) {
+        const int at = (x + bin) & (kCopies / 4 - 1);
+        const unsigned long long v = part[at];
+        part[at] = 0ull;
         c += v >> kCntShift;
         ms += v & ((1ull << kCntShift) - 1ull);
       }
-      hcnt[tid] = (unsigned int)c;
-      hms[tid] = ms;
-    }
-    __syncthreads();
-    if (tid < 256) {
-      // exponent of the bin's candidates: the bin itself in the first pass
-      const unsigned int e = (pass == 0) ? (unsigned int)tid : (prefix >> 23);
-      const unsigned long long units = (e > 0u ? ((unsigned long long)hcnt[tid] << 23) : 0ull) + hms[tid];
-      bsum[tid] = ldexp((double)units, e > 0u ? (int)e - 150 : -149);   // exact: units < 2^53
-    }
-    __syncthreads();
-    if (tid == 0) {
-      if (pass == 0) {
-        double total = 0.0;
-        for (int b = 255; b >= 0; --b) total += bsum[b];
-        sh_target = alpha * total;
-        if (!(sh_target > 0.0)) sh_done = 1u;   // alpha == 0 or no mass: keep nothing
+      unsigned int c32 = (unsigned int)c;
+      c32 += __shfl_xor(c32, 1, 64); c32 += __shfl_xor(c32, 2, 64);
+      ms += __shfl_xor(ms, 1, 64); ms += __shfl_xor(ms, 2, 64);
+      if ((tid & 3) == 0) {
+        // exponent of the bin's candidates: the bin itself in the first pass
+        const unsigned int e = (pass == 0) ? (unsigned int)bin : (prefix >> 23);
+        const unsigned long long units = (e > 0u ? ((unsigned long long)c32 << 23) : 0ull) + ms;
+        hcnt[bin] = c32;
+        bsum[bin] = ldexp((double)units, e > 0u ? (int)e - 150 : -149);   // exact: units < 2^53
       }
-      if (!sh_done) {
-        double above = sh_above;
-        int chosen = -1, last_b = 0;
-        double last_above = above;
-        for (int b = (int)dmask; b >= 0; --b) {
-          if (hcnt[b] == 0u) continue;
-          if (above + bsum[b] >= sh_target) { chosen = b; break; }
-          last_b = b; last_above = above;
-          above += bsum[b];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // The walk from the top bin down, by one wave: lane l holds the bins 255 - 4 l .. 252 - 4 l.
+      // The running sums are formed in one fixed order (four bins in a row, a scan over the
+      // lanes), so repeated runs agree bit for bit.
+      double b4[4];
+      unsigned int c4[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        b4[x] = bsum[255 - 4 * lane - x];
+        c4[x] = hcnt[255 - 4 * lane - x];
+      }
+      double incl = ((b4[0] + b4[1]) + b4[2]) + b4[3];
+      for (int step = 1; step < 64; step <<= 1) {
+        const double o = __shfl_up(incl, step, 64);
+        if (lane >= step) incl += o;
+      }
+      double target = sh_target;
+      if (pass == 0) {
+        target = alpha * __shfl(incl, 63, 64);
+        if (lane == 0) {
+          sh_target = target;
+          if (!(target > 0.0)) sh_done = 1u;       // alpha == 0 or no mass: keep nothing
         }
-        if (chosen < 0) {   // only by fp64 rounding of the running sum: cut inside the lowest non-empty bin
-          chosen = last_b; above = last_above;
+      }
+      double run = __shfl_up(incl, 1, 64);
+      run = sh_above + (lane == 0 ? 0.0 : run);    // mass above this lane's bins
+      int cut = -1, low = -1;                      // first bin that reaches the target; lowest non-empty bin
+      double cut_above = 0.0, low_above = 0.0;
+      unsigned int cut_n = 0u, low_n = 0u;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        if (c4[x] != 0u) {
+          const int b = 255 - 4 * lane - x;
+          if (cut < 0 && run + b4[x] >= target) { cut = b; cut_above = run; cut_n = c4[x]; }
+          low = b; low_above = run; low_n = c4[x];
+          run += b4[x];
         }
+      }
+      const unsigned long long has_cut = __ballot(cut >= 0), has_low = __ballot(low >= 0);
+      // without a cut (only by fp64 rounding of the running sum): inside the lowest non-empty bin
+      const bool mine = has_cut != 0ull ? lane == __ffsll((unsigned long long)has_cut) - 1
+                                        : (has_low != 0ull && lane == 63 - __clzll((long long)has_low));
+      if (mine && target > 0.0) {
+        const int chosen = has_cut != 0ull ? cut : low;
+        const double above = has_cut != 0ull ? cut_above : low_above;
+        const unsigned int new_prefix = prefix | ((unsigned int)chosen << shift);
         sh_above = above;
-        sh_prefix = prefix | ((unsigned int)chosen << shift);
+        sh_prefix = new_prefix;
         if (pass == 3) {
           // all candidates left share the exact value v: how many are needed
-          double v = (double)__uint_as_float(sh_prefix);
-          unsigned int c = hcnt[chosen];
+          const double v = (double)__uint_as_float(new_prefix);
+          const unsigned int c = has_cut != 0ull ? cut_n : low_n;
           unsigned int m = 1u;
           if (v > 0.0) {
-            double need = (sh_target - above) / v;
+            const double need = (target - above) / v;
             m = (need <= 1.0) ? 1u : (need >= (double)c ? c : (unsigned int)need);
-            while (m > 1u && above + (double)(m - 1u) * v >= sh_target) --m;
-            while (m < c && above + (double)m * v < sh_target) ++m;
+            while (m > 1u && above + (double)(m - 1u) * v >= target) --m;
+            while (m < c && above + (double)m * v < target) ++m;
           }
           sh_m = m;
         }
@@ -175,18 +237,12 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectParams P) {
   const unsigned long long lt = (1ull << lane) - 1ull;
   unsigned int n_gt = 0u, n_tie = 0u;
   for (int g0 = g_lo; g0 < g_hi; g0 += kBatch) {
-    float v[kBatch];
+    if (!resident) load_batch(g0);
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const int i = (g0 + u) * 64 + lane;
-      v[u] = (g0 + u < g_hi && i < S) ? sc[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const unsigned int key = score_key(v[u]);
-      const bool in = g0 + u < g_hi && (g0 + u) * 64 + lane < S;
-      n_gt += (unsigned int)__popcll(__ballot(in && key > vkey));
-      n_tie += (unsigned int)__popcll(__ballot(in && key == vkey));
+      if (g0 + u >= g_hi) break;
+      n_gt += (unsigned int)__popcll(__ballot((int)key[u] > (int)vkey));
+      n_tie += (unsigned int)__popcll(__ballot(key[u] == vkey));
     }
   }
   if (lane == 0) { w_gt[wave] = n_gt; w_tie[wave] = n_tie; }
@@ -199,19 +255,13 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectParams P) {
     tie_run += t;
   }
   for (int g0 = g_lo; g0 < g_hi; g0 += kBatch) {
-    float v[kBatch];
+    if (!resident) load_batch(g0);
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
+      if (g0 + u >= g_hi) break;
       const int i = (g0 + u) * 64 + lane;
-      v[u] = (g0 + u < g_hi && i < S) ? sc[i] : 0.0f;
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = (g0 + u) * 64 + lane;
-      const unsigned int key = score_key(v[u]);
-      const bool in = g0 + u < g_hi && i < S;
-      const bool gt = in && key > vkey;
-      const bool tie = in && key == vkey;
+      const bool gt = (int)key[u] > (int)vkey;
+      const bool tie = key[u] == vkey;
       const unsigned long long bt = __ballot(tie);
       const unsigned int trank = tie_run + (unsigned int)__popcll(bt & lt);
       const bool sel = gt || (tie && trank < m);
