@@ -1,8 +1,8 @@
 // Small data-movement kernels around the attention kernels:
-//  - gather_transpose: V -> V^T (so the PV product reads 16-byte MFMA operands)
-//    and, for the strip-masked path, K/V rows gathered by selected column index
-//    into compact per-head arrays (Algorithm 1, merge_index: column strips);
-//  - mask_prep: the selected columns and offsets (plus the local window) as
+//  - transpose: V -> V^T (so the PV product reads 16-byte MFMA operands);
+//  - gather_strips: K rows and V^T columns gathered by selected column index into
+//    compact per-head arrays (Algorithm 1, merge_index: column strips);
+//  - strip_prep: the selected columns and offsets (plus the local window) as
 //    bitmaps, and the list of 64-key tile diagonals that hold at least one kept
 //    offset (Algorithm 1, merge_index: slash strips extended over the matrix);
 //  - block granularity (Algorithm 1, block_reduction with blk > 1): token scores
@@ -16,44 +16,8 @@ namespace {
 
 constexpr int GT_ROW_B = 260;   // bytes per gathered row in LDS (256 + 4 pad)
 
-__global__ __launch_bounds__(256) void gather_transpose_kernel(GatherParams P) {
-  __shared__ __attribute__((aligned(16))) char tile[64 * GT_ROW_B];
-  const int g = blockIdx.y;
-  const int c0 = blockIdx.x * 64;
-  const int cnt = P.cnt ? min(max(P.cnt[g], 0), P.S) : P.S;
-  const int tid = threadIdx.x;
-  if (P.idx_pad != nullptr) {
-    // padded copy of the index list: INT_MAX marks "no column"
-    if (tid < 64) {
-      int c = c0 + tid;
-      if (c < P.idx_pad_stride)
-        P.idx_pad[(size_t)g * P.idx_pad_stride + c] = (c < cnt) ? P.idx[(size_t)g * P.idx_stride + c] : 0x7FFFFFFF;
-    }
-  }
-  if (P.out_t == nullptr && P.out_rows == nullptr) return;   // only the padded index list was wanted
-  if (c0 >= ((cnt + 63) & ~63)) return;   // nothing reads beyond the last partial tile
-  // rows of an earlier segment see no key at or after their end: a tile of the ascending
-  // list that starts there is left alone
-  if (P.key_limit > 0 && P.idx != nullptr && P.idx[(size_t)g * P.idx_stride + c0] >= P.key_limit) return;
-  const uint16_t* src = P.src + (size_t)((P.head0 + g) / P.group) * P.S * kHeadDim;
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    int c = tid + 256 * n;
-    int row = c >> 4, col = c & 15;
-    int cc = c0 + row;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (cc < cnt) {
-      int j = P.idx ? P.idx[(size_t)g * P.idx_stride + cc] : cc;
-      j = min(max(j, 0), P.S - 1);   // a malformed list must not read out of bounds
-      v = *reinterpret_cast<const uint4*>(src + (size_t)j * kHeadDim + col * 8);
-    }
-    if (P.out_rows != nullptr)
-      *reinterpret_cast<uint4*>(P.out_rows + ((size_t)g * P.C_pad + cc) * kHeadDim + col * 8) = v;
-    uint32_t* dst = reinterpret_cast<uint32_t*>(tile + row * GT_ROW_B + col * 16);
-    dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-  }
-  if (P.out_t == nullptr) return;   // rows-only gather
-  __syncthreads();
+// 64 rows staged in LDS -> 128 transposed rows of 64 entries (128 bytes each)
+__device__ __forceinline__ void store_transposed(const char* tile, uint16_t* out, size_t out_stride, int tid) {
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
     int c = tid + 256 * n;
@@ -67,36 +31,82 @@ __global__ __launch_bounds__(256) void gather_transpose_kernel(GatherParams P) {
     v.y = e[2] | ((uint32_t)e[3] << 16);
     v.z = e[4] | ((uint32_t)e[5] << 16);
     v.w = e[6] | ((uint32_t)e[7] << 16);
-    *reinterpret_cast<uint4*>(P.out_t + ((size_t)g * kHeadDim + drow) * P.C_pad + c0 + 8 * kc) = v;
+    *reinterpret_cast<uint4*>(out + (size_t)drow * out_stride + 8 * kc) = v;
   }
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  size_t stride = (size_t)gridDim.x * blockDim.x;
-  for (; i < n; i += stride) p[i] = v;
+__device__ __forceinline__ void stage_chunk(char* tile, int row, int col, uint4 v) {
+  uint32_t* dst = reinterpret_cast<uint32_t*>(tile + row * GT_ROW_B + col * 16);
+  dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
 }
 
-__global__ __launch_bounds__(256) void set_bits_kernel(MaskPrepParams P) {
-  const int h = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  uint32_t* cb = P.col_bits + (size_t)h * P.cb_words;
-  uint32_t* ob = P.off_bits + (size_t)h * P.rb_words;
-  if (c < P.S && c < P.col_cnt[h]) {
-    int j = P.col_idx[(size_t)h * P.S + c];
-    if (j >= 0 && j < P.S) atomicOr(cb + (j >> 5), 1u << (j & 31));
+// V -> V^T, zero padded to S_pad keys
+__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* v, uint16_t* vt, int S, int S_pad) {
+  __shared__ __attribute__((aligned(16))) char tile[64 * GT_ROW_B];
+  const int g = blockIdx.y, c0 = blockIdx.x * 64, tid = threadIdx.x;
+  if (c0 >= ((S + 63) & ~63)) return;   // nothing reads beyond the last partial tile
+  const uint16_t* src = v + (size_t)g * S * kHeadDim;
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const int c = tid + 256 * n, row = c >> 4, col = c & 15;
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    if (c0 + row < S) x = *reinterpret_cast<const uint4*>(src + (size_t)(c0 + row) * kHeadDim + col * 8);
+    stage_chunk(tile, row, col, x);
   }
-  if (P.slash_idx != nullptr && c < P.S && c < P.slash_cnt[h]) {
-    int o = P.slash_idx[(size_t)h * P.S + c];
-    if (o >= 0 && o < P.S) {
-      int x = P.off_max - o;
-      atomicOr(ob + (x >> 5), 1u << (x & 31));
+  __syncthreads();
+  store_transposed(tile, vt + (size_t)g * kHeadDim * S_pad + c0, S_pad, tid);
+}
+
+// The column side of the strip mask: a workgroup takes 64 entries of one head's list, writes
+// the padded copy of them (INT_MAX marks "no column"), their K rows and, transposed through
+// LDS, their V rows.  K and V go in one launch: both read the list, and a launch of its own
+// costs 5 us, as much as the whole gather of a short sequence.
+__global__ __launch_bounds__(256) void gather_strips_kernel(GatherParams P) {
+  __shared__ __attribute__((aligned(16))) char tile[64 * GT_ROW_B];
+  const int g = blockIdx.y;
+  const int c0 = blockIdx.x * 64;
+  const int cnt = min(max(P.cnt[g], 0), P.S);
+  const int tid = threadIdx.x;
+  const int32_t* list = P.idx + (size_t)g * P.S;
+  if (tid < 64) P.idx_pad[(size_t)g * P.S_pad + c0 + tid] = (c0 + tid < cnt) ? list[c0 + tid] : 0x7FFFFFFF;
+  if (c0 >= ((cnt + 63) & ~63)) return;   // nothing reads beyond the last partial tile
+  // rows of an earlier segment see no key at or after their end: a tile of the ascending
+  // list that starts there is left alone
+  if (P.key_limit > 0 && list[c0] >= P.key_limit) return;
+  const size_t kv = (size_t)((P.head0 + g) / P.group) * P.S * kHeadDim;
+  uint4 kr[4], vr[4];
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const int c = tid + 256 * n, cc = c0 + (c >> 4), col = c & 15;
+    kr[n] = vr[n] = make_uint4(0u, 0u, 0u, 0u);
+    if (cc < cnt) {
+      const int j = min(max(list[cc], 0), P.S - 1);   // a malformed list must not read out of bounds
+      const size_t at = kv + (size_t)j * kHeadDim + col * 8;
+      kr[n] = *reinterpret_cast<const uint4*>(P.k + at);
+      vr[n] = *reinterpret_cast<const uint4*>(P.v + at);
     }
   }
-  if (c < P.window && c < P.S) {
-    int x = P.off_max - c;
-    atomicOr(ob + (x >> 5), 1u << (x & 31));
+#pragma unroll
+  for (int n = 0; n < 4; ++n) {
+    const int c = tid + 256 * n, row = c >> 4, col = c & 15;
+    *reinterpret_cast<uint4*>(P.kc + ((size_t)g * P.S_pad + c0 + row) * kHeadDim + col * 8) = kr[n];
+    stage_chunk(tile, row, col, vr[n]);
   }
+  __syncthreads();
+  store_transposed(tile, P.vct + (size_t)g * kHeadDim * P.S_pad + c0, P.S_pad, tid);
+}
+
+constexpr int PT = 1024;               // threads of the metadata kernels
+constexpr int kBitSegWords = 32768;    // bitmap words a workgroup holds in LDS: 1M keys or offsets
+
+// word w of a bitmap whose set bits are the run [lo, hi]
+__device__ __forceinline__ uint32_t run_word(int w, int lo, int hi) {
+  const int x0 = w << 5;
+  if (x0 > hi || x0 + 31 < lo) return 0u;
+  uint32_t m = 0xFFFFFFFFu;
+  if (lo > x0) m &= 0xFFFFFFFFu << (lo - x0);
+  if (hi < x0 + 31) m &= 0xFFFFFFFFu >> (x0 + 31 - hi);
+  return m;
 }
 
 // any kept offset in [lo, hi] (0 <= lo <= hi)?  offset o sits at bit off_max - o
@@ -116,37 +126,103 @@ __device__ bool any_offset(const uint32_t* ob, int off_max, int lo, int hi) {
 // [64 d - 255, 64 d + 63], the 32 rows of wave w (of 8) the 95 offsets from
 // 64 d - 255 + 32 w on.  dlist = ascending d with at least one kept offset; an
 // entry is d | (mask << 24), bit w of mask set when wave w sees a kept offset.
-__global__ __launch_bounds__(256) void dlist_kernel(MaskPrepParams P) {
-  __shared__ int wave_cnt[4];
-  __shared__ int base;
+//
+// Written by one workgroup: `active(d, w)` says whether wave w has work on diagonal d.  A
+// thread takes one (d, w) pair, a wave eight diagonals at a time (one ballot is eight
+// masks), and every wave owns a contiguous run of diagonals: it counts its entries, the
+// counts are exchanged once, and it forms the masks again to write them in order.
+template <typename F>
+__device__ __forceinline__ void write_dlist(int nd, int32_t* dl, int32_t* dcnt, int* wave_cnt, F&& active) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_groups = (nd + 7) / 8;
+  const int g_lo = n_groups * wave / (PT / 64), g_hi = n_groups * (wave + 1) / (PT / 64);
+  auto mask_of = [&](int g) {                      // mask of diagonal 8 g + lane / 8
+    const int d = 8 * g + (lane >> 3);
+    const unsigned long long b = __ballot(d < nd && active(d, lane & 7));
+    return (uint32_t)(b >> (lane & ~7)) & 0xFFu;
+  };
+  int n = 0;
+  for (int g = g_lo; g < g_hi; ++g) {
+    const uint32_t mask = mask_of(g);
+    n += __popcll(__ballot((lane & 7) == 0 && mask != 0u));
+  }
+  if (lane == 0) wave_cnt[wave] = n;
+  __syncthreads();
+  int at = 0, total = 0;
+  for (int w = 0; w < PT / 64; ++w) {
+    at += w < wave ? wave_cnt[w] : 0;
+    total += wave_cnt[w];
+  }
+  for (int g = g_lo; g < g_hi; ++g) {
+    const uint32_t mask = mask_of(g);
+    const bool mine = (lane & 7) == 0 && mask != 0u;
+    const unsigned long long b = __ballot(mine);
+    if (mine) dl[at + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)((uint32_t)(8 * g + (lane >> 3)) | (mask << 24));
+    at += __popcll(b);
+  }
+  if (tid == 0) *dcnt = total;
+}
+
+// The metadata of a strip mask in one launch.  One workgroup builds a head's offset bitmap in
+// LDS (the window first, then the listed offsets), stores it and lists the tile diagonals it
+// touches; another builds the head's column bitmap.  Two fills, a bit-setting launch over
+// global atomics (12 us for one head of 1K tokens, 41 us for 32 heads of 8K: neighbouring
+// list entries hit the same word) and a list launch became this one.  A bitmap longer than
+// kBitSegWords (1M tokens) is cut into segments, each of which goes through the whole list;
+// the tile diagonals are then listed by dlist_kernel.
+__global__ __launch_bounds__(PT) void strip_prep_kernel(MaskPrepParams P, int n_seg) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
+  __shared__ int wave_cnt[PT / 64];
+  const int h = blockIdx.y, tid = threadIdx.x;
+  const bool cols = (int)blockIdx.x >= n_seg;
+  const int w0 = ((int)blockIdx.x - (cols ? n_seg : 0)) * kBitSegWords;
+  const int words = cols ? P.cb_words : P.rb_words;
+  const int nw = min(kBitSegWords, words - w0);
+  if (nw <= 0) return;
+  if (blockIdx.x == 0 && tid == 0 && P.tiles != nullptr) P.tiles[h] = 0ull;
+  const int32_t* list = (cols ? P.col_idx : P.slash_idx) + (size_t)h * P.S;
+  const int n = min(max((cols ? P.col_cnt : P.slash_cnt)[h], 0), P.S);
+  // bit x of the offset bitmap is offset off_max - x: the window is the run of bits up to off_max
+  const int win_lo = cols ? 0x7FFFFFFF : P.off_max - (min(P.window, P.S) - 1);
+  for (int x = tid; x < nw; x += PT) bits[x] = run_word(w0 + x, win_lo, P.off_max);
+  __syncthreads();
+  constexpr int B = 8;                      // entries a thread requests before it uses the first
+  for (int c0 = 0; c0 < n; c0 += B * PT) {
+    int v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int c = c0 + u * PT + tid;
+      v[u] = c < n ? list[c] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (v[u] < 0 || v[u] >= P.S) continue;          // (also entries a malformed list may hold)
+      const int x = cols ? v[u] : P.off_max - v[u];
+      const int at = (x >> 5) - w0;
+      if (at >= 0 && at < nw) atomicOr(bits + at, 1u << (x & 31));
+    }
+  }
+  __syncthreads();
+  uint32_t* out = cols ? P.col_bits + (size_t)h * P.cb_words : P.off_bits + (size_t)h * P.rb_words;
+  for (int x = tid; x < nw; x += PT) out[w0 + x] = bits[x];
+  if (cols || n_seg != 1) return;
+  write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
+              [&](int d, int w) {
+                const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
+                return lo <= hi && any_offset(bits, P.off_max, lo, hi);
+              });
+}
+
+// the tile diagonals of a head whose offset bitmap was written in several segments
+__global__ __launch_bounds__(PT) void dlist_kernel(MaskPrepParams P) {
+  __shared__ int wave_cnt[PT / 64];
   const int h = blockIdx.x;
   const uint32_t* ob = P.off_bits + (size_t)h * P.rb_words;
-  int32_t* dl = P.dlist + (size_t)h * P.dlist_stride;
-  const int nd = (P.S + 63) / 64 + 3;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) base = 0;
-  __syncthreads();
-  for (int d0 = 0; d0 < nd; d0 += 256) {
-    int d = d0 + tid;
-    uint32_t mask = 0;
-    if (d < nd) {
-      for (int w = 0; w < 8; ++w) {
-        int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
-        if (lo <= hi && any_offset(ob, P.off_max, lo, hi)) mask |= 1u << w;
-      }
-    }
-    const bool f = mask != 0;
-    unsigned long long b = __ballot(f);
-    if (lane == 0) wave_cnt[wave] = __popcll(b);
-    __syncthreads();
-    int pre = base;
-    for (int w = 0; w < wave; ++w) pre += wave_cnt[w];
-    if (f) dl[pre + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)((uint32_t)d | (mask << 24));
-    __syncthreads();
-    if (tid == 0) base += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-    __syncthreads();
-  }
-  if (tid == 0) P.dcnt[h] = base;
+  write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
+              [&](int d, int w) {
+                const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
+                return lo <= hi && any_offset(ob, P.off_max, lo, hi);
+              });
 }
 
 // ---- block granularity ----------------------------------------------------------
@@ -167,108 +243,76 @@ __global__ __launch_bounds__(256) void block_reduce_kernel(const float* in, floa
   if (lane == 0) out[(size_t)g * nb + b] = (float)acc;
 }
 
-// every offset 0 .. S-1 kept: bits off_max - (S-1) .. off_max of each head's bitmap
-__global__ void all_offsets_kernel(uint32_t* off_bits, int n_bh, int rb_words, int S, int off_max) {
-  const int x_lo = off_max - (S - 1), x_hi = off_max;
-  size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (size_t)n_bh * rb_words) return;
-  const int w = (int)(i % rb_words);
-  uint32_t m = 0u;
-  if (w >= (x_lo >> 5) && w <= (x_hi >> 5)) {
-    m = 0xFFFFFFFFu;
-    if (w == (x_lo >> 5)) m &= 0xFFFFFFFFu << (x_lo & 31);
-    if (w == (x_hi >> 5)) m &= 0xFFFFFFFFu >> (31 - (x_hi & 31));
-  }
-  off_bits[i] = m;
-}
-
 __device__ __forceinline__ int floor_div(int x, int y) { return x >= 0 ? x / y : -((-x + y - 1) / y); }
 
-// selected key blocks -> the token columns they hold (ascending, as the strip path
-// wants them).  Only the last block of the sequence can be short, and an ascending
-// list has it last, so token slot c belongs to list entry c / blk.
-__global__ __launch_bounds__(256) void expand_blocks_kernel(BlockPrepParams P) {
-  const int h = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  const int cnt = min(max(P.col_bcnt[h], 0), P.nb);
-  const int32_t* bl = P.col_blk + (size_t)h * P.nb;
-  if (c == 0) {
-    int n = 0;
-    if (cnt > 0) {
-      int last = min(max(bl[cnt - 1], 0), P.nb - 1);
-      n = (cnt - 1) * P.blk + min(P.blk, P.S - last * P.blk);
-    }
-    P.tok_cnt[h] = min(n, P.S);
-  }
-  if (c >= P.S) return;
-  const int r = c / P.blk;
-  int j = 0x7FFFFFFF;
-  if (r < cnt) {
-    int J = min(max(bl[r], 0), P.nb - 1);   // a malformed list must not lead out of bounds
-    j = min(J * P.blk + c % P.blk, P.S - 1);
-  }
-  P.tok_idx[(size_t)h * P.S + c] = j;
-}
-
-// kept block diagonals (block row minus block column): a full block on diagonal
-// delta spans the offsets blk*delta - (blk-1) .. blk*delta + (blk-1), so a selected
-// block b of offsets [blk*b, blk*b + blk) lies on diagonals b and b + 1, and the
-// window [0, w) on every diagonal with blk*delta - (blk-1) <= w - 1.
-__global__ __launch_bounds__(256) void diag_bits_kernel(BlockPrepParams P) {
-  const int h = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  uint32_t* db = P.diag_bits + (size_t)h * P.db_words;
-  const int cnt = min(max(P.slash_bcnt[h], 0), P.nb);
-  if (c < cnt) {
-    int b = P.slash_blk[(size_t)h * P.nb + c];
-    if (b >= 0 && b < P.nb) {
-      atomicOr(db + (b >> 5), 1u << (b & 31));
-      atomicOr(db + ((b + 1) >> 5), 1u << ((b + 1) & 31));
-    }
-  }
-  if (c <= P.nb && (long long)c * P.blk - (P.blk - 1) <= (long long)P.window - 1)
-    atomicOr(db + (c >> 5), 1u << (c & 31));
-}
-
-// The tile-diagonal list of the block mask.  With 256-row query tiles, 64-key tiles
-// and blk in {64, 128, 256}, the 32 rows of wave w lie in one row block and the key
-// tile of tile diagonal d in one column block, floor(32 w / blk) - floor((192 - 64 d)
-// / blk) block diagonals apart whatever the query tile: the entry format is that of
-// dlist_kernel, the per-wave bit now saying "this wave's block is kept".
-__global__ __launch_bounds__(256) void dlist_block_kernel(BlockPrepParams P) {
-  __shared__ int wave_cnt[4];
-  __shared__ int base;
-  const int h = blockIdx.x;
-  const uint32_t* db = P.diag_bits + (size_t)h * P.db_words;
-  int32_t* dl = P.dlist + (size_t)h * P.dlist_stride;
-  const int nd = (P.S + 63) / 64 + 3;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid == 0) base = 0;
+// The metadata of a block mask in one launch, in the format of the strip path.
+//
+// Job 0 of a head lists the tile diagonals.  Kept block diagonals (block row minus block
+// column): a full block on diagonal delta spans the offsets blk*delta - (blk-1) ..
+// blk*delta + (blk-1), so a selected block b of offsets [blk*b, blk*b + blk) lies on
+// diagonals b and b + 1, and the window [0, w) on every diagonal with blk*delta - (blk-1)
+// <= w - 1.  With 256-row query tiles, 64-key tiles and blk in {64, 128, 256}, the 32 rows
+// of wave w lie in one row block and the key tile of tile diagonal d in one column block,
+// floor(32 w / blk) - floor((192 - 64 d) / blk) block diagonals apart whatever the query
+// tile: the per-wave bit of a list entry says "this wave's block is kept".
+//
+// The other jobs take kBlockSpan keys each and write, for the selected key blocks seen as
+// the token columns they hold, their part of the padded index list (only the last block of
+// the sequence can be short, and an ascending list has it last, so slot c belongs to list
+// entry c / blk) and of the column bitmap, and their part of the offset bitmap, in which
+// every offset 0 .. S-1 is kept (kept blocks are kept whole).
+constexpr int kBlockSpan = 8192;
+__global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
+  extern __shared__ __attribute__((aligned(16))) uint32_t bits[];   // block diagonals / key blocks
+  __shared__ int wave_cnt[PT / 64];
+  const int h = blockIdx.y, tid = threadIdx.x;
+  const bool diag = blockIdx.x == 0;
+  if (diag && tid == 0 && P.tiles != nullptr) P.tiles[h] = 0ull;
+  const int32_t* list = (diag ? P.slash_blk : P.col_blk) + (size_t)h * P.nb;
+  const int n = min(max((diag ? P.slash_bcnt : P.col_bcnt)[h], 0), P.nb);
+  const int n_words = (P.nb + 1) / 32 + 1;
+  // the window's diagonals are the run [0, (w + blk - 2) / blk]
+  const int win_hi = diag ? (int)min(((long long)P.window + P.blk - 2) / P.blk, (long long)P.nb) : -1;
+  for (int x = tid; x < n_words; x += PT) bits[x] = run_word(x, 0, win_hi);
   __syncthreads();
-  for (int d0 = 0; d0 < nd; d0 += 256) {
-    int d = d0 + tid;
-    uint32_t mask = 0;
-    if (d < nd) {
-      const int kb = floor_div(192 - 64 * d, P.blk);
-      for (int w = 0; w < 8; ++w) {
-        const int delta = (32 * w) / P.blk - kb;
-        const int o_lo = 64 * d - 255 + 32 * w, o_hi = o_lo + 94;   // offsets the wave meets on this tile
-        if (delta >= 0 && delta <= P.nb && o_hi >= 0 && o_lo <= P.S - 1 && ((db[delta >> 5] >> (delta & 31)) & 1u))
-          mask |= 1u << w;
-      }
-    }
-    const bool f = mask != 0;
-    unsigned long long b = __ballot(f);
-    if (lane == 0) wave_cnt[wave] = __popcll(b);
-    __syncthreads();
-    int pre = base;
-    for (int w = 0; w < wave; ++w) pre += wave_cnt[w];
-    if (f) dl[pre + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)((uint32_t)d | (mask << 24));
-    __syncthreads();
-    if (tid == 0) base += wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-    __syncthreads();
+  for (int c = tid; c < n; c += PT) {
+    const int b = list[c];
+    if (b < 0 || b >= P.nb) continue;
+    atomicOr(bits + (b >> 5), 1u << (b & 31));
+    if (diag) atomicOr(bits + ((b + 1) >> 5), 1u << ((b + 1) & 31));
   }
-  if (tid == 0) P.dcnt[h] = base;
+  __syncthreads();
+  auto has = [&](int b) { return ((bits[b >> 5] >> (b & 31)) & 1u) != 0u; };
+  if (diag) {
+    write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
+                [&](int d, int w) {
+                  const int delta = (32 * w) / P.blk - floor_div(192 - 64 * d, P.blk);
+                  const int o_lo = 64 * d - 255 + 32 * w, o_hi = o_lo + 94;   // offsets the wave meets on this tile
+                  return delta >= 0 && delta <= P.nb && o_hi >= 0 && o_lo <= P.S - 1 && has(delta);
+                });
+    return;
+  }
+  const int span = (int)blockIdx.x - 1, n_span = (int)gridDim.x - 1;
+  int n_tok = 0;
+  if (n > 0) n_tok = min((n - 1) * P.blk + min(P.blk, P.S - min(max(list[n - 1], 0), P.nb - 1) * P.blk), P.S);
+  if (span == 0 && tid == 0) P.tok_cnt[h] = n_tok;
+  const int c_lo = span * kBlockSpan, c_hi = min(c_lo + kBlockSpan, P.idx_pad_stride);
+  for (int c = c_lo + tid; c < c_hi; c += PT) {
+    const int r = c / P.blk;
+    int j = 0x7FFFFFFF;
+    if (c < n_tok) j = min(min(max(list[r], 0), P.nb - 1) * P.blk + c % P.blk, P.S - 1);   // (a malformed list must not lead out of bounds)
+    P.idx_pad[(size_t)h * P.idx_pad_stride + c] = j;
+  }
+  // words of the two bitmaps: kBlockSpan / 32 a job, the last job takes the few beyond
+  const int w_lo = span * (kBlockSpan / 32);
+  const int cw_hi = span + 1 < n_span ? w_lo + kBlockSpan / 32 : P.cb_words;
+  for (int x = w_lo + tid; x < cw_hi; x += PT) {
+    const int b = x * 32 / P.blk;
+    P.col_bits[(size_t)h * P.cb_words + x] = (b < P.nb && has(b)) ? run_word(x, 0, P.S - 1) : 0u;
+  }
+  const int ow_hi = span + 1 < n_span ? w_lo + kBlockSpan / 32 : P.rb_words;
+  for (int x = w_lo + tid; x < ow_hi; x += PT)
+    P.off_bits[(size_t)h * P.rb_words + x] = run_word(x, P.off_max - (P.S - 1), P.off_max);
 }
 
 }  // namespace
@@ -280,49 +324,44 @@ hipError_t launch_block_reduce(const float* in, float* out, int n_rows, int S, i
   return hipGetLastError();
 }
 
-// Block lists -> the metadata of the strip path: token columns of the selected key
-// blocks (tok_idx / tok_cnt), their bitmap, every offset >= 0 kept inside a computed
-// tile (the kept blocks are kept whole), and the tile-diagonal list.
+// kernels with a sequence-sized LDS array: the limit is raised to what the launch asks for
+template <typename K>
+static hipError_t allow_lds(K kernel, size_t bytes) {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 hipError_t launch_block_prep(const BlockPrepParams& P, hipStream_t st) {
-  size_t ncb = (size_t)P.n_bh * P.cb_words, nob = (size_t)P.n_bh * P.rb_words, ndb = (size_t)P.n_bh * P.db_words;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, st, P.col_bits, ncb, 0u);
-  hipLaunchKernelGGL(all_offsets_kernel, dim3((unsigned)((nob + 255) / 256)), dim3(256), 0, st, P.off_bits, P.n_bh,
-                     P.rb_words, P.S, P.off_max);
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, P.diag_bits, ndb, 0u);
-  dim3 grid((P.S + 255) / 256, P.n_bh);
-  hipLaunchKernelGGL(expand_blocks_kernel, grid, dim3(256), 0, st, P);
-  hipLaunchKernelGGL(diag_bits_kernel, dim3((P.nb + 256) / 256, P.n_bh), dim3(256), 0, st, P);
-  MaskPrepParams M;
-  M.col_idx = P.tok_idx; M.col_cnt = P.tok_cnt; M.slash_idx = nullptr; M.slash_cnt = nullptr;
-  M.col_bits = P.col_bits; M.off_bits = P.off_bits; M.dlist = P.dlist; M.dcnt = P.dcnt;
-  M.n_bh = P.n_bh; M.S = P.S; M.window = 0;     // (the offset bitmap is already complete)
-  M.cb_words = P.cb_words; M.rb_words = P.rb_words; M.dlist_stride = P.dlist_stride; M.off_max = P.off_max;
-  hipLaunchKernelGGL(set_bits_kernel, grid, dim3(256), 0, st, M);
-  hipLaunchKernelGGL(dlist_block_kernel, dim3(P.n_bh), dim3(256), 0, st, P);
+  const size_t lds = (size_t)((P.nb + 1) / 32 + 1) * 4;
+  hipError_t e = allow_lds(&block_prep_kernel, lds);
+  if (e != hipSuccess) return e;
+  dim3 grid(1 + (P.idx_pad_stride + kBlockSpan - 1) / kBlockSpan, P.n_bh);
+  hipLaunchKernelGGL(block_prep_kernel, grid, dim3(PT), lds, st, P);
   return hipGetLastError();
 }
 
-hipError_t launch_gather_transpose(const GatherParams& P, hipStream_t st) {
-  dim3 grid(P.C_pad / 64, P.n_out);
+hipError_t launch_transpose(const uint16_t* v, uint16_t* vt, int n, int S, int S_pad, hipStream_t st) {
+  dim3 grid(S_pad / 64, n);
   if (grid.x == 0 || grid.y == 0) return hipSuccess;
-  hipLaunchKernelGGL(gather_transpose_kernel, grid, dim3(256), 0, st, P);
+  hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, st, v, vt, S, S_pad);
   return hipGetLastError();
 }
 
-hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  int blocks = (int)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks), dim3(256), 0, st, p, n, v);
+hipError_t launch_gather_strips(const GatherParams& P, hipStream_t st) {
+  dim3 grid(P.S_pad / 64, P.n_heads);
+  if (grid.x == 0 || grid.y == 0) return hipSuccess;
+  hipLaunchKernelGGL(gather_strips_kernel, grid, dim3(256), 0, st, P);
   return hipGetLastError();
 }
 
 hipError_t launch_mask_prep(const MaskPrepParams& P, hipStream_t st) {
-  size_t ncb = (size_t)P.n_bh * P.cb_words, nob = (size_t)P.n_bh * P.rb_words;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, st, P.col_bits, ncb, 0u);
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1024), dim3(256), 0, st, P.off_bits, nob, 0u);
-  dim3 grid((P.S + 255) / 256, P.n_bh);
-  hipLaunchKernelGGL(set_bits_kernel, grid, dim3(256), 0, st, P);
-  hipLaunchKernelGGL(dlist_kernel, dim3(P.n_bh), dim3(256), 0, st, P);
+  const int n_seg = (P.rb_words + kBitSegWords - 1) / kBitSegWords;   // (the column bitmap is the shorter one)
+  const size_t lds = (size_t)(n_seg == 1 ? P.rb_words : kBitSegWords) * 4;
+  hipError_t e = allow_lds(&strip_prep_kernel, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(strip_prep_kernel, dim3(2 * n_seg, P.n_bh), dim3(PT), lds, st, P, n_seg);
+  if (n_seg > 1) {
+    hipLaunchKernelGGL(dlist_kernel, dim3(P.n_bh), dim3(PT), 0, st, P);
+  }
   return hipGetLastError();
 }
 

@@ -139,16 +139,13 @@ SparseWs sparse_ws(const Dims& d, int n_heads, bool gathered = true) {
   return w;
 }
 
-struct BlockWs { SparseWs sp; size_t tok_idx, tok_cnt, dbits, total; int nb, db_words; };
+struct BlockWs { SparseWs sp; size_t tok_cnt, total; int nb; };
 BlockWs block_ws(const Dims& d, int blk, int n_heads) {
   BlockWs w;
   w.sp = sparse_ws(d, n_heads, false);
   w.nb = (d.S + blk - 1) / blk;
-  w.db_words = (w.nb + 1) / 32 + 1;
   size_t at = w.sp.total;
-  w.tok_idx = at; at += align_up((size_t)n_heads * d.S * 4);
   w.tok_cnt = at; at += align_up((size_t)n_heads * 4);
-  w.dbits = at;   at += align_up((size_t)n_heads * w.db_words * 4);
   w.total = at;
   return w;
 }
@@ -234,13 +231,7 @@ sa::FlashParams base_flash(const Dims& d, const void* q, const void* k) {
 }
 
 hipError_t transpose_v(const Dims& d, const void* v, uint16_t* vt, hipStream_t st) {
-  sa::GatherParams G;
-  memset(&G, 0, sizeof(G));
-  G.src = static_cast<const uint16_t*>(v);
-  G.out_t = vt;
-  G.n_out = d.n_bkv; G.group = 1;
-  G.S = d.S; G.C_pad = d.S_pad;
-  return sa::launch_gather_transpose(G, st);
+  return sa::launch_transpose(static_cast<const uint16_t*>(v), vt, d.n_bkv, d.S, d.S_pad, st);
 }
 
 }  // namespace
@@ -458,7 +449,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
                         const void* k, const void* v,
                         const int32_t* col_idx, const int32_t* col_cnt,
                         const int32_t* slash_idx, const int32_t* slash_cnt, int32_t local_window, int row_hi,
-                        char* ws, hipStream_t st, const int32_t** cnt_used) {
+                        uint64_t* tiles_to_clear, char* ws, hipStream_t st, const int32_t** cnt_used) {
   const SparseWs& w = bw.sp;
   const bool blocks = granularity != 1;
   Scope sc(SA_K_MASK_PREP, st);
@@ -466,6 +457,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
   col_idx += (size_t)h0 * n_cand; slash_idx += (size_t)h0 * n_cand;
   col_cnt += h0; slash_cnt += h0;
   sa_status s = SA_OK;
+  unsigned long long* tiles = tiles_to_clear ? reinterpret_cast<unsigned long long*>(tiles_to_clear) + h0 : nullptr;
   uint32_t* col_bits = reinterpret_cast<uint32_t*>(ws + w.cbits);
   uint32_t* off_bits = reinterpret_cast<uint32_t*>(ws + w.obits);
   int32_t* dlist = reinterpret_cast<int32_t*>(ws + w.dlist);
@@ -476,6 +468,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     memset(&M, 0, sizeof(M));
     M.col_bits = col_bits; M.off_bits = off_bits; M.dlist = dlist; M.dcnt = dcnt;
     M.col_idx = col_idx; M.col_cnt = col_cnt; M.slash_idx = slash_idx; M.slash_cnt = slash_cnt;
+    M.tiles = tiles;
     M.n_bh = nh; M.S = d.S; M.window = local_window;
     M.cb_words = w.cb_words; M.rb_words = w.rb_words; M.dlist_stride = w.dlist_stride; M.off_max = w.off_max;
     s = dev(sa::launch_mask_prep(M, st));
@@ -485,39 +478,30 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     sa::BlockPrepParams B;
     memset(&B, 0, sizeof(B));
     B.col_blk = col_idx; B.col_bcnt = col_cnt; B.slash_blk = slash_idx; B.slash_bcnt = slash_cnt;
-    B.tok_idx = reinterpret_cast<int32_t*>(ws + bw.tok_idx);
+    B.idx_pad = reinterpret_cast<int32_t*>(ws + w.cidx); B.idx_pad_stride = d.S_pad;
     B.tok_cnt = reinterpret_cast<int32_t*>(ws + bw.tok_cnt);
-    B.diag_bits = reinterpret_cast<uint32_t*>(ws + bw.dbits);
     B.col_bits = col_bits; B.off_bits = off_bits; B.dlist = dlist; B.dcnt = dcnt;
+    B.tiles = tiles;
     B.n_bh = nh; B.S = d.S; B.window = local_window;
     B.cb_words = w.cb_words; B.rb_words = w.rb_words; B.dlist_stride = w.dlist_stride; B.off_max = w.off_max;
-    B.blk = granularity; B.nb = bw.nb; B.db_words = bw.db_words;
-    s = dev(sa::launch_block_prep(B, st));
-    col_idx = B.tok_idx; col_cnt = B.tok_cnt;
+    B.blk = granularity; B.nb = bw.nb;
+    *cnt_used = B.tok_cnt;
+    // (key blocks are runs of consecutive keys and are read in place: nothing to gather)
+    return dev(sa::launch_block_prep(B, st));
   }
   if (s != SA_OK) return s;
   *cnt_used = col_cnt;
 
-  // column side: compact K rows and V^T columns of the kept keys, per query head.  Key
-  // blocks are runs of consecutive keys and are read in place: only the padded index
-  // list (the tiles' key indices) is written then.
+  // column side: compact K rows and V^T columns of the kept keys, per query head
   sa::GatherParams G;
   memset(&G, 0, sizeof(G));
-  G.idx = col_idx; G.cnt = col_cnt; G.idx_stride = d.S;
-  G.idx_pad = reinterpret_cast<int32_t*>(ws + w.cidx); G.idx_pad_stride = d.S_pad;
-  G.n_out = nh; G.group = d.group; G.head0 = h0; G.S = d.S; G.C_pad = d.S_pad;
+  G.k = static_cast<const uint16_t*>(k); G.v = static_cast<const uint16_t*>(v);
+  G.idx = col_idx; G.cnt = col_cnt;
+  G.kc = reinterpret_cast<uint16_t*>(ws + w.kc); G.vct = reinterpret_cast<uint16_t*>(ws + w.vct);
+  G.idx_pad = reinterpret_cast<int32_t*>(ws + w.cidx);
+  G.n_heads = nh; G.group = d.group; G.head0 = h0; G.S = d.S; G.S_pad = d.S_pad;
   G.key_limit = row_hi < d.S ? row_hi : 0;     // the rows of this segment end at row_hi: later keys are never read
-  if (blocks) return dev(sa::launch_gather_transpose(G, st));
-  G.src = static_cast<const uint16_t*>(v);
-  G.out_t = reinterpret_cast<uint16_t*>(ws + w.vct);
-  s = dev(sa::launch_gather_transpose(G, st));
-  if (s != SA_OK) return s;
-  // K rows: gather only
-  G.src = static_cast<const uint16_t*>(k);
-  G.out_rows = reinterpret_cast<uint16_t*>(ws + w.kc);
-  G.out_t = nullptr;
-  G.idx_pad = nullptr;
-  return dev(sa::launch_gather_transpose(G, st));
+  return dev(sa::launch_gather_strips(G, st));
 }
 
 // the strip-masked kernel on query tiles [qtile0, qtile0 + n_qtiles) of the heads [h0, h0 + nh)
@@ -589,10 +573,6 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
   if (s != SA_OK) return s;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  if (tiles != nullptr) {
-    s = dev(sa::launch_fill_u32(reinterpret_cast<uint32_t*>(tiles), 2 * (size_t)d.n_bh, 0u, st));
-    if (s != SA_OK) return s;
-  }
   {
     // V^T for the contiguous (slash / window) tiles: once per call
     Scope sc(SA_K_TRANSPOSE_V, st);
@@ -612,7 +592,7 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
       s = prepare_heads(d, bw, granularity, h0, nh, n_cand, k, v,
                         col_idx_all + chunk_off * n_cand, col_cnt_all + chunk_off,
                         slash_idx_all + chunk_off * n_cand, slash_cnt_all + chunk_off,
-                        local_window, row_hi, ws, st, &cnt_used);
+                        local_window, row_hi, m == 0 ? tiles : nullptr, ws, st, &cnt_used);
       if (s != SA_OK) return s;
       const int segs = (n_segments < qtile1 - qtile0) ? n_segments : (qtile1 - qtile0);
       for (int g = 0; g < segs; ++g) {

@@ -47,43 +47,47 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
 int lse_key_splits(int row_first, int n_s, int n_bh);
 hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hipStream_t st);
 
-// out[g][d][c] = src[kv(g)][idx ? idx[g][c] : c][d] for c < cnt (zero beyond, up to C_pad);
-// optionally also rows_out[g][c][:] = src[kv(g)][idx[g][c]][:]
+// vt[g][d][c] = v[g][c][d], zero up to the 64-key tile that ends the sequence
+hipError_t launch_transpose(const uint16_t* v, uint16_t* vt, int n, int S, int S_pad, hipStream_t st);
+
+// per head g of the pass, c < cnt[g] (zero up to the end of the 64-entry tile):
+//   kc[g][c][:] = k[kv(g)][idx[g][c]][:],  vct[g][:][c] = v[kv(g)][idx[g][c]][:]
 struct GatherParams {
-  const uint16_t* src;      // [n_src, S, 128]; may be null when only idx_pad is wanted
-  const int32_t* idx;       // nullable [n_out, idx_stride]
-  const int32_t* cnt;       // nullable [n_out]; null -> S
-  uint16_t* out_t;          // [n_out, 128, C_pad]
-  uint16_t* out_rows;       // nullable [n_out, C_pad, 128]
-  int32_t* idx_pad;         // nullable [n_out, idx_pad_stride]: copy of idx padded with INT_MAX
-  int n_out, group;         // source head of output g is (head0 + g) / group
+  const uint16_t* k; const uint16_t* v;   // [n_kv, S, 128]
+  const int32_t* idx;       // [n_heads, S] ascending
+  const int32_t* cnt;       // [n_heads]
+  uint16_t* kc;             // [n_heads, S_pad, 128]
+  uint16_t* vct;            // [n_heads, 128, S_pad]
+  int32_t* idx_pad;         // [n_heads, S_pad]: copy of idx padded with INT_MAX
+  int n_heads, group;       // source head of head g is (head0 + g) / group
   int head0;
-  int S, C_pad, idx_stride, idx_pad_stride;
-  int key_limit;            // > 0: the list ascends and no reader looks at a key >= key_limit; tiles of 64 list entries
+  int S, S_pad;
+  int key_limit;            // > 0: no reader looks at a key >= key_limit; tiles of 64 list entries
                             // that start there are not gathered (their idx_pad entries still are written)
 };
-hipError_t launch_gather_transpose(const GatherParams& P, hipStream_t st);
+hipError_t launch_gather_strips(const GatherParams& P, hipStream_t st);
 
 struct MaskPrepParams {
   const int32_t* col_idx; const int32_t* col_cnt;      // [n_bh, S], [n_bh]
   const int32_t* slash_idx; const int32_t* slash_cnt;
-  uint32_t* col_bits; uint32_t* off_bits;              // zero-filled by the launcher
+  uint32_t* col_bits; uint32_t* off_bits;
   int32_t* dlist; int32_t* dcnt;
+  unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
 };
 hipError_t launch_mask_prep(const MaskPrepParams& P, hipStream_t st);
-hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 
 // block granularity: lists of selected key blocks / offset blocks of blk tokens
 struct BlockPrepParams {
   const int32_t* col_blk; const int32_t* col_bcnt;     // [n_bh, nb], [n_bh]
   const int32_t* slash_blk; const int32_t* slash_bcnt;
-  int32_t* tok_idx; int32_t* tok_cnt;                  // [n_bh, S], [n_bh]: the key blocks as token columns
-  uint32_t* diag_bits;                                 // [n_bh, db_words]: kept block diagonals
+  int32_t* idx_pad; int32_t* tok_cnt;                  // [n_bh, idx_pad_stride], [n_bh]: the key blocks as token
+                                                       // columns, padded with INT_MAX
   uint32_t* col_bits; uint32_t* off_bits;
   int32_t* dlist; int32_t* dcnt;
+  unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
-  int blk, nb, db_words;
+  int blk, nb, idx_pad_stride;
 };
 hipError_t launch_block_prep(const BlockPrepParams& P, hipStream_t st);
 // out[r][b] = sum of in[r][b*blk .. (b+1)*blk), r < n_rows, rows of S floats
