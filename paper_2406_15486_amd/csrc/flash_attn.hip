@@ -39,7 +39,7 @@ constexpr int BK = kFlashBK;          // 64 keys per tile
 constexpr int NT = 512;               // two groups of four waves
 constexpr int NSTAGE = 4;             // K and V^T tiles resident in LDS
 constexpr int NAUX = 8;               // ring of aux-word slots
-constexpr int kDiagMask = 0x00FFFFFF;  // a tile-diagonal list entry: diagonal in bits 0..23, one bit per wave above
+constexpr int kDiagMask = 0x007FFFFF;  // a tile-diagonal list entry: diagonal in bits 0..22, kSweepBit, one bit per wave above
 // LDS tiles are unpadded (the direct global->LDS loads write 1 KB runs); bank
 // conflicts are avoided by XOR-swizzling the 16-byte chunk index with the row.
 constexpr int KROW_B = 256;           // bytes per K row in LDS: 16 chunks, chunk c of row p stored at c ^ (p & 15)
@@ -129,8 +129,14 @@ __device__ __forceinline__ void wg_barrier() {
 // consecutive keys (blocks of 64, 128 or 256 keys), so they are read from K and V^T
 // themselves instead of from gathered copies; the padded index list still travels with
 // every tile (causal edge, short last block).
-template <int MODE, bool OUT_F32, bool IN_PLACE = false>
-__global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
+// SWEEP (strip-masked mode, heads whose lists are nearly full): one causal sweep over every
+// key tile in order, as in the dense mode, with columns and offsets joined in one mask; no
+// gathered tiles.  The kernel below picks the body by head.  As a run-time flag inside one
+// body the choice cost the long unswept launches 2.5 % (128K tokens, alpha = 0.95); as a
+// body of its own it knows at compile time that interior tiles are active.
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP>
+__device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, const int a, const int split) {
+  static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool WITH_V = (MODE != 1);
@@ -149,43 +155,6 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   const int hf = lane >> 5;   // which half of the contraction block this lane feeds
   const uint32_t smem_lds = __builtin_amdgcn_readfirstlane((int)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
 
-  // ---- which (head, query tile) this workgroup owns ------------------------
-  // (the log-sum-exp sweep may also cut the keys of a query tile into k_splits
-  // equal parts, one workgroup each, to even out the last round of the launch)
-  int bh, a, split = 0;
-  {
-    const int bid = blockIdx.x;
-    if (MODE == 2) {
-      // heads are sliced over the 8 XCDs (workgroups go round-robin to XCDs) and an
-      // XCD works through one head at a time, heavy (late) query tiles first: the
-      // workgroups resident on it then stream the gathered columns of the same head,
-      // a working set (tens of MB per XCD) that the memory-side cache can hold.
-      if (P.n_bh >= 8) {
-        int xcd = bid & 7, slot = bid >> 3;
-        a = P.n_qtiles - 1 - slot % P.n_qtiles;
-        bh = xcd + 8 * (slot / P.n_qtiles);
-        if (bh >= P.n_bh) return;
-      } else {
-        a = P.n_qtiles - 1 - bid / P.n_bh;
-        bh = bid % P.n_bh;
-        if (a < 0) return;
-      }
-      a += P.qtile0;
-    } else {
-      // a bundle = the query heads sharing one KV head at one query tile; the
-      // bundle's workgroups land on one XCD so the K/V stream is shared in L2.
-      int xcd = bid & 7, slot = bid >> 3;
-      int bl = slot / P.group, hg = slot % P.group;
-      int bundle = bl * 8 + xcd;
-      const int ks = (MODE == 1) ? P.k_splits : 1;
-      if (bundle >= P.n_qtiles * ks * P.n_bkv) return;
-      const int av = P.n_qtiles * ks - 1 - bundle / P.n_bkv;
-      a = av / ks;
-      split = av % ks;
-      int bkv = bundle % P.n_bkv;
-      bh = bkv * P.group + hg;
-    }
-  }
   const int bkv = ((MODE == 2 ? P.head0 : 0) + bh) / P.group;
   const int S = P.S;
   const int i0 = P.q_row0 + a * BQ;                     // first query row of the workgroup
@@ -206,7 +175,11 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   const uint16_t* kc = nullptr;
   const uint16_t* vct = nullptr;
   int n_col_tiles = 0, n_rng = 0;
-  if (MODE == 2) {
+  if (SWEEP) {
+    dl = P.dlist + (size_t)bh * P.dlist_stride;
+    cbits = P.col_bits + (size_t)bh * P.cb_words;
+    obits = P.off_bits + (size_t)bh * P.rb_words;
+  } else if (MODE == 2) {
     cidx = P.col_idx_pad + (size_t)bh * P.cidx_stride;
     int cnt = min(max(P.col_cnt[bh], 0), S);
     int lo = 0, hi = cnt;          // selected columns j <= last row of the tile (ascending list)
@@ -237,13 +210,13 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
     n_sweep = (int)((long long)n_sweep * (split + 1) / P.k_splits) - t_base;
   }
   t_base = __builtin_amdgcn_readfirstlane(t_base);
-  const int n_tiles = __builtin_amdgcn_readfirstlane((MODE == 2) ? (n_col_tiles + n_rng) : n_sweep);
+  const int n_tiles = __builtin_amdgcn_readfirstlane((MODE == 2 && !SWEEP) ? (n_col_tiles + n_rng) : n_sweep);
 
   // Kind of tile t (wave-uniform; no memory access), and whether t lies inside the schedule.
   // `kc` is the Stretch the calling iteration belongs to: what it knows at compile time.
   auto is_col = [&](auto kc, int t) __attribute__((always_inline)) -> bool {
     constexpr int KIND = decltype(kc)::KIND;
-    return MODE == 2 && (KIND == 1 || (KIND == 0 && t < n_col_tiles));
+    return MODE == 2 && !SWEEP && (KIND == 1 || (KIND == 0 && t < n_col_tiles));
   };
   auto is_real = [&](auto kc, int t) __attribute__((always_inline)) -> bool { return decltype(kc)::REAL || t < n_tiles; };
   // Descriptor of tile t.  A range tile is named by its tile diagonal d: key tile
@@ -258,6 +231,11 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
     typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
     if (IN_PLACE && is_col(kc, t))
       return ((const_i32_ptr)(uintptr_t)cidx)[BK * t];                       // first key of the tile's block
+    if (SWEEP) {
+      // the list holds every diagonal; only block masks need its entry (which waves keep the tile)
+      if (IN_PLACE && is_real(kc, t)) return ((const_i32_ptr)(uintptr_t)dl)[a64 + 3 - t];
+      return 0;
+    }
     if (MODE == 2 && !is_col(kc, t) && is_real(kc, t))
       return ((const_i32_ptr)(uintptr_t)dl)[n_rng - 1 - (t - n_col_tiles)];   // far to near
     return 0;
@@ -265,7 +243,7 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   // first key of tile t
   auto first_key = [&](auto kc, int t, int d) __attribute__((always_inline)) -> int {  // contiguous tiles only; d = list entry
     if (IN_PLACE && is_col(kc, t)) return d;         // the entry of an in-place column tile is its first key
-    return (MODE == 2) ? (a64 + 3 - (d & kDiagMask)) * BK : (t + (MODE == 1 ? t_base : 0)) * BK;
+    return (MODE == 2 && !SWEEP) ? (a64 + 3 - (d & kDiagMask)) * BK : (t + (MODE == 1 ? t_base : 0)) * BK;
   };
   // array bases as scalars, once
   const uint64_t s_kbase = scalar_ptr(kbase), s_vtbase = scalar_ptr(vtbase);
@@ -379,7 +357,7 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   // The aux words are read early (act_words) and looked at later (tile_active), so
   // that the wait for them hides behind MFMAs.
   auto act_words = [&](auto kc, int t, uint32_t& w0, uint32_t& w1) __attribute__((always_inline)) {
-    if (MODE != 2 || decltype(kc)::INTERIOR) return;
+    if (MODE != 2 || decltype(kc)::INTERIOR || (SWEEP && !IN_PLACE)) return;
     const uint32_t* ax = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
     if (is_col(kc, t)) {
       w0 = ax[0];
@@ -394,7 +372,10 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
     const int j0 = first_key(kc, t, d);
     if (is_col(kc, t)) {
       act = (int)w0 <= iw0 + 31;
-    } else if (MODE == 2) {
+    } else if (SWEEP && IN_PLACE) {
+      // the wave's block diagonal is kept, or the tile lies in a selected key block
+      act = ((((uint32_t)d >> (24 + wave)) & 1u) || (w0 & w1) == 0xFFFFFFFFu) && j0 <= iw0 + 31;
+    } else if (MODE == 2 && !SWEEP) {
       act = (((uint32_t)d >> (24 + wave)) & 1u) && ((w0 & w1) != 0xFFFFFFFFu) && (j0 < S);
     } else {
       act = j0 <= iw0 + 31;                        // else every key of the tile lies after the wave's rows
@@ -490,7 +471,7 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   auto step_softmax = [&](auto kc, int t, int d) __attribute__((always_inline)) {
     const int j0 = first_key(kc, t, d);
     constexpr bool INTERIOR = decltype(kc)::INTERIOR;
-    const int kind = is_col(kc, t) ? TK_COLIDX : (MODE == 2) ? TK_RANGE : (!INTERIOR && j0 + BK - 1 > i0) ? TK_CAUSAL : TK_PLAIN;
+    const int kind = is_col(kc, t) ? TK_COLIDX : (MODE == 2 && !(SWEEP && IN_PLACE)) ? TK_RANGE : (!INTERIOR && j0 + BK - 1 > i0) ? TK_CAUSAL : TK_PLAIN;
     const int buf = t & (NSTAGE - 1);
     // Mask: one 32-bit pattern per lane and 32-key half, bit b <-> key
     // j0 + 32 sb + 8 hf + b of the lane's 16 (b = 0..7, 16..23), set = keep.  The
@@ -537,7 +518,10 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
         uint32_t lo = mw[k], hi = mw[k + 1];
         uint32_t ow = __builtin_amdgcn_alignbit(hi, lo, x0 & 31);  // bit b <-> offset tl - b
         uint32_t cw = mw[16 + sb] >> (8 * hf);                     // bit 16u+e <-> key is a selected column
-        km[sb] = ow & ~cw;
+        // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
+        // column bit, unlike an offset bit, says nothing about j <= i)
+        km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
+        if (SWEEP && !INTERIOR) km[sb] &= tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u);
       }
       // a tile that keeps every pair (a whole block of the block mask, the inside of a
       // band of offsets) needs no masking at all
@@ -754,9 +738,9 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   // general form.  Dense and log-sum-exp sweeps: the tiles below key tile a64 (the one
   // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
   // past the end of the schedule.
-  const int n_gen0 = (MODE == 2) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
+  const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
                                  : max(min(a64 - t_base - 1, n_tiles - 4), 0);
-  const int n_gen1 = (MODE == 2) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
+  const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
   const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
   if (grp == 0) {
     auto iteration = [&](auto kc, int n) __attribute__((always_inline)) {
@@ -770,7 +754,10 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       dq0 = dq1; dq1 = dq2; dq2 = dq3; dq3 = dq4;
     };
     int n = 0;
-    if (MODE == 2) {
+    if (SWEEP && IN_PLACE) {
+      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+    } else if (MODE == 2 && !SWEEP) {
       for (; n < n_gen0; ++n) iteration(ColTiles{}, n);
       for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
       for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
@@ -790,7 +777,10 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       dprev = dq0; dq0 = dq1; dq1 = dq2; dq2 = dq3; dq3 = dq4;
     };
     int n = 0;
-    if (MODE == 2) {
+    if (SWEEP && IN_PLACE) {
+      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+    } else if (MODE == 2 && !SWEEP) {
       for (; n < n_gen0; ++n) iteration(ColTiles{}, n);
       for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
       for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
@@ -829,6 +819,56 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
         }
       }
   }
+}
+
+template <int MODE, bool OUT_F32, bool IN_PLACE = false>
+__global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
+  // ---- which (head, query tile) this workgroup owns ------------------------
+  // (the log-sum-exp sweep may also cut the keys of a query tile into k_splits
+  // equal parts, one workgroup each, to even out the last round of the launch)
+  int bh, a, split = 0;
+  {
+    const int bid = blockIdx.x;
+    if (MODE == 2) {
+      // heads are sliced over the 8 XCDs (workgroups go round-robin to XCDs) and an
+      // XCD works through one head at a time, heavy (late) query tiles first: the
+      // workgroups resident on it then stream the gathered columns of the same head,
+      // a working set (tens of MB per XCD) that the memory-side cache can hold.
+      if (P.n_bh >= 8) {
+        int xcd = bid & 7, slot = bid >> 3;
+        a = P.n_qtiles - 1 - slot % P.n_qtiles;
+        bh = xcd + 8 * (slot / P.n_qtiles);
+        if (bh >= P.n_bh) return;
+      } else {
+        a = P.n_qtiles - 1 - bid / P.n_bh;
+        bh = bid % P.n_bh;
+        if (a < 0) return;
+      }
+      a += P.qtile0;
+    } else {
+      // a bundle = the query heads sharing one KV head at one query tile; the
+      // bundle's workgroups land on one XCD so the K/V stream is shared in L2.
+      int xcd = bid & 7, slot = bid >> 3;
+      int bl = slot / P.group, hg = slot % P.group;
+      int bundle = bl * 8 + xcd;
+      const int ks = (MODE == 1) ? P.k_splits : 1;
+      if (bundle >= P.n_qtiles * ks * P.n_bkv) return;
+      const int av = P.n_qtiles * ks - 1 - bundle / P.n_bkv;
+      a = av / ks;
+      split = av % ks;
+      int bkv = bundle % P.n_bkv;
+      bh = bkv * P.group + hg;
+    }
+  }
+  if (MODE == 2) {
+    // (diagonal 0 is in every list, and its entry is the first)
+    const int first = P.dlist[(size_t)bh * P.dlist_stride];
+    if (__builtin_amdgcn_readfirstlane(first) & kSweepBit) {
+      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2>(P, bh, a, split);
+      return;
+    }
+  }
+  flash_body<MODE, OUT_F32, IN_PLACE, false>(P, bh, a, split);
 }
 
 // out[i] = log sum_s exp(part[s][i]): the key splits of the log-sum-exp sweep, in fixed order

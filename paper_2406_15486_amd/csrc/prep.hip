@@ -67,6 +67,7 @@ __global__ __launch_bounds__(256) void gather_strips_kernel(GatherParams P) {
   const int c0 = blockIdx.x * 64;
   const int cnt = min(max(P.cnt[g], 0), P.S);
   const int tid = threadIdx.x;
+  if (P.dlist[(size_t)g * P.dlist_stride] & kSweepBit) return;
   const int32_t* list = P.idx + (size_t)g * P.S;
   if (tid < 64) P.idx_pad[(size_t)g * P.S_pad + c0 + tid] = (c0 + tid < cnt) ? list[c0 + tid] : 0x7FFFFFFF;
   if (c0 >= ((cnt + 63) & ~63)) return;   // nothing reads beyond the last partial tile
@@ -127,12 +128,42 @@ __device__ bool any_offset(const uint32_t* ob, int off_max, int lo, int hi) {
 // 64 d - 255 + 32 w on.  dlist = ascending d with at least one kept offset; an
 // entry is d | (mask << 24), bit w of mask set when wave w sees a kept offset.
 //
+// Sum of x over the workgroup, known to every thread.
+__device__ __forceinline__ long long block_sum(long long x, long long* scratch) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = x;
+  __syncthreads();
+  long long t = 0;
+  for (int w = 0; w < PT / 64; ++w) t += scratch[w];
+  return t;
+}
+
+// Whether a head is swept: every causal key tile visited once, columns and offsets kept in
+// one mask, instead of the gathered columns first and then every tile diagonal with a kept
+// offset, columns masked out.  Where the lists are full the two passes visit nearly every
+// key twice (8K tokens of a diffuse head at alpha = 0.95: 1.9 x the tiles of a sweep).
+//
+// The rule compares tile costs in 1/128 of a tile of the dense kernel, fitted at 2K, 16K and
+// 64K tokens (32 heads, 5-90 % of the columns, 0.4-20 runs of four offsets per 2000):
+// a gathered tile 132, a range tile 76 + 7 per wave that works on it (idle waves are cheaper,
+// but the tile's loads and barrier are paid), a swept tile 134 to 144.  At 64K, 60 % columns:
+// 32 runs 19.2 ms in two passes / 30.9 swept, 218 runs 29.7 / 30.9, 436 runs 35.7 / 30.9,
+// 1638 runs 45.2 / 31.1.
+constexpr int kColTileCost = 132, kRangeTileCost = 76, kRangeWaveCost = 7, kSweepTileCost = 140;
+
 // Written by one workgroup: `active(d, w)` says whether wave w has work on diagonal d.  A
 // thread takes one (d, w) pair, a wave eight diagonals at a time (one ballot is eight
 // masks), and every wave owns a contiguous run of diagonals: it counts its entries, the
-// counts are exchanged once, and it forms the masks again to write them in order.
-template <typename F>
-__device__ __forceinline__ void write_dlist(int nd, int32_t* dl, int32_t* dcnt, int* wave_cnt, F&& active) {
+// counts are exchanged once, and it forms the masks again to write them in order.  The
+// list of a head that is swept holds every diagonal, with the bits of `swept(d, w)`.
+// `col_tiles`: the gathered tiles this thread counted.
+template <typename F, typename G>
+__device__ __forceinline__ void write_dlist(int nd, int q_lo, int q_hi, long long col_tiles, int32_t* dl, int32_t* dcnt,
+                                            F&& active, G&& swept) {
+  __shared__ int wave_cnt[PT / 64];
+  __shared__ long long sums[PT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_groups = (nd + 7) / 8;
   const int g_lo = n_groups * wave / (PT / 64), g_hi = n_groups * (wave + 1) / (PT / 64);
@@ -141,13 +172,31 @@ __device__ __forceinline__ void write_dlist(int nd, int32_t* dl, int32_t* dcnt, 
     const unsigned long long b = __ballot(d < nd && active(d, lane & 7));
     return (uint32_t)(b >> (lane & ~7)) & 0xFFu;
   };
+  // diagonal d is met by the query tiles a with 4 a + 3 >= d
+  auto met = [&](int d) { return (long long)max(q_hi - max(q_lo, d / 4), 0); };
   int n = 0;
+  long long two_pass = kColTileCost * col_tiles, sweep = 0;
   for (int g = g_lo; g < g_hi; ++g) {
     const uint32_t mask = mask_of(g);
-    n += __popcll(__ballot((lane & 7) == 0 && mask != 0u));
+    const int d = 8 * g + (lane >> 3);
+    const bool first = (lane & 7) == 0 && d < nd;
+    n += __popcll(__ballot(first && mask != 0u));
+    if (first) {
+      sweep += kSweepTileCost * met(d);
+      if (mask != 0u) two_pass += (kRangeTileCost + kRangeWaveCost * __popc(mask)) * met(d);
+    }
   }
   if (lane == 0) wave_cnt[wave] = n;
-  __syncthreads();
+  if (block_sum(two_pass - sweep, sums) > 0) {
+    for (int g = g_lo; g < g_hi; ++g) {
+      const int d = 8 * g + (lane >> 3);
+      const unsigned long long b = __ballot(d < nd && swept(d, lane & 7));
+      const uint32_t mask = (uint32_t)(b >> (lane & ~7)) & 0xFFu;
+      if ((lane & 7) == 0 && d < nd) dl[d] = (int32_t)((uint32_t)(d | kSweepBit) | (mask << 24));
+    }
+    if (tid == 0) *dcnt = nd;
+    return;
+  }
   int at = 0, total = 0;
   for (int w = 0; w < PT / 64; ++w) {
     at += w < wave ? wave_cnt[w] : 0;
@@ -163,6 +212,32 @@ __device__ __forceinline__ void write_dlist(int nd, int32_t* dl, int32_t* dcnt, 
   if (tid == 0) *dcnt = total;
 }
 
+// gathered tiles of the query tiles this thread takes: 64 listed columns each, up to the last row
+__device__ __forceinline__ long long count_col_tiles(const int32_t* list, int n, int q_lo, int q_hi, int row_hi) {
+  long long tiles = 0;
+  for (int a = q_lo + (int)threadIdx.x; a < q_hi; a += PT) {
+    const int last = min(a * kFlashBQ + kFlashBQ, row_hi) - 1;
+    int lo = 0, hi = n;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (list[mid] <= last) lo = mid + 1; else hi = mid;
+    }
+    tiles += (lo + kFlashBK - 1) / kFlashBK;
+  }
+  return tiles;
+}
+
+// Strip masks: wave w meets the offsets [64 d - 255 + 32 w, 64 d - 161 + 32 w] on diagonal d.
+__device__ __forceinline__ void write_strip_dlist(const MaskPrepParams& P, int h, const uint32_t* ob) {
+  const long long col = count_col_tiles(P.col_idx + (size_t)h * P.S, min(max(P.col_cnt[h], 0), P.S), P.qtile_lo, P.qtile_hi, P.row_hi);
+  write_dlist((P.S + 63) / 64 + 3, P.qtile_lo, P.qtile_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h,
+              [&](int d, int w) {
+                const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
+                return lo <= hi && any_offset(ob, P.off_max, lo, hi);
+              },
+              [&](int d, int w) { return 64 * d - 255 + 32 * w + 94 >= 0 && 64 * d - 255 + 32 * w <= P.S - 1; });
+}
+
 // The metadata of a strip mask in one launch.  One workgroup builds a head's offset bitmap in
 // LDS (the window first, then the listed offsets), stores it and lists the tile diagonals it
 // touches; another builds the head's column bitmap.  Two fills, a bit-setting launch over
@@ -172,7 +247,6 @@ __device__ __forceinline__ void write_dlist(int nd, int32_t* dl, int32_t* dcnt, 
 // the tile diagonals are then listed by dlist_kernel.
 __global__ __launch_bounds__(PT) void strip_prep_kernel(MaskPrepParams P, int n_seg) {
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];
-  __shared__ int wave_cnt[PT / 64];
   const int h = blockIdx.y, tid = threadIdx.x;
   const bool cols = (int)blockIdx.x >= n_seg;
   const int w0 = ((int)blockIdx.x - (cols ? n_seg : 0)) * kBitSegWords;
@@ -206,23 +280,12 @@ __global__ __launch_bounds__(PT) void strip_prep_kernel(MaskPrepParams P, int n_
   uint32_t* out = cols ? P.col_bits + (size_t)h * P.cb_words : P.off_bits + (size_t)h * P.rb_words;
   for (int x = tid; x < nw; x += PT) out[w0 + x] = bits[x];
   if (cols || n_seg != 1) return;
-  write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
-              [&](int d, int w) {
-                const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
-                return lo <= hi && any_offset(bits, P.off_max, lo, hi);
-              });
+  write_strip_dlist(P, h, bits);
 }
 
 // the tile diagonals of a head whose offset bitmap was written in several segments
 __global__ __launch_bounds__(PT) void dlist_kernel(MaskPrepParams P) {
-  __shared__ int wave_cnt[PT / 64];
-  const int h = blockIdx.x;
-  const uint32_t* ob = P.off_bits + (size_t)h * P.rb_words;
-  write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
-              [&](int d, int w) {
-                const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
-                return lo <= hi && any_offset(ob, P.off_max, lo, hi);
-              });
+  write_strip_dlist(P, blockIdx.x, P.off_bits + (size_t)blockIdx.x * P.rb_words);
 }
 
 // ---- block granularity ----------------------------------------------------------
@@ -264,7 +327,6 @@ __device__ __forceinline__ int floor_div(int x, int y) { return x >= 0 ? x / y :
 constexpr int kBlockSpan = 8192;
 __global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];   // block diagonals / key blocks
-  __shared__ int wave_cnt[PT / 64];
   const int h = blockIdx.y, tid = threadIdx.x;
   const bool diag = blockIdx.x == 0;
   if (diag && tid == 0 && P.tiles != nullptr) P.tiles[h] = 0ull;
@@ -284,12 +346,21 @@ __global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
   __syncthreads();
   auto has = [&](int b) { return ((bits[b >> 5] >> (b & 31)) & 1u) != 0u; };
   if (diag) {
-    write_dlist((P.S + 63) / 64 + 3, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, wave_cnt,
-                [&](int d, int w) {
-                  const int delta = (32 * w) / P.blk - floor_div(192 - 64 * d, P.blk);
-                  const int o_lo = 64 * d - 255 + 32 * w, o_hi = o_lo + 94;   // offsets the wave meets on this tile
-                  return delta >= 0 && delta <= P.nb && o_hi >= 0 && o_lo <= P.S - 1 && has(delta);
-                });
+    // column tiles: the selected key blocks as runs of blk columns
+    long long col = 0;
+    const int32_t* cb = P.col_blk + (size_t)h * P.nb;
+    const int nc = min(max(P.col_bcnt[h], 0), P.nb);
+    for (int c = tid; c < nc; c += PT)
+      col += (long long)(P.blk / kFlashBK) * max(P.qtile_hi - max(P.qtile_lo, (int)((long long)cb[c] * P.blk / kFlashBQ)), 0);
+    auto meets = [&](int d, int w) {       // the offsets of the wave on this tile reach into [0, S)
+      const int o_lo = 64 * d - 255 + 32 * w;
+      return o_lo + 94 >= 0 && o_lo <= P.S - 1;
+    };
+    auto kept = [&](int d, int w) {
+      const int delta = (32 * w) / P.blk - floor_div(192 - 64 * d, P.blk);
+      return delta >= 0 && delta <= P.nb && meets(d, w) && has(delta);
+    };
+    write_dlist((P.S + 63) / 64 + 3, P.qtile_lo, P.qtile_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, kept, kept);
     return;
   }
   const int span = (int)blockIdx.x - 1, n_span = (int)gridDim.x - 1;

@@ -448,7 +448,7 @@ namespace {
 sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h0, int nh, size_t n_cand,
                         const void* k, const void* v,
                         const int32_t* col_idx, const int32_t* col_cnt,
-                        const int32_t* slash_idx, const int32_t* slash_cnt, int32_t local_window, int row_hi,
+                        const int32_t* slash_idx, const int32_t* slash_cnt, int32_t local_window, int row_lo, int row_hi,
                         uint64_t* tiles_to_clear, char* ws, hipStream_t st, const int32_t** cnt_used) {
   const SparseWs& w = bw.sp;
   const bool blocks = granularity != 1;
@@ -471,6 +471,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     M.tiles = tiles;
     M.n_bh = nh; M.S = d.S; M.window = local_window;
     M.cb_words = w.cb_words; M.rb_words = w.rb_words; M.dlist_stride = w.dlist_stride; M.off_max = w.off_max;
+    M.qtile_lo = row_lo / sa::kFlashBQ; M.qtile_hi = (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ; M.row_hi = row_hi;
     s = dev(sa::launch_mask_prep(M, st));
   } else {
     // the same metadata from block lists; from here on the selected key blocks are
@@ -485,6 +486,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     B.n_bh = nh; B.S = d.S; B.window = local_window;
     B.cb_words = w.cb_words; B.rb_words = w.rb_words; B.dlist_stride = w.dlist_stride; B.off_max = w.off_max;
     B.blk = granularity; B.nb = bw.nb;
+    B.qtile_lo = row_lo / sa::kFlashBQ; B.qtile_hi = (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ; B.row_hi = row_hi;
     *cnt_used = B.tok_cnt;
     // (key blocks are runs of consecutive keys and are read in place: nothing to gather)
     return dev(sa::launch_block_prep(B, st));
@@ -500,6 +502,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
   G.kc = reinterpret_cast<uint16_t*>(ws + w.kc); G.vct = reinterpret_cast<uint16_t*>(ws + w.vct);
   G.idx_pad = reinterpret_cast<int32_t*>(ws + w.cidx);
   G.n_heads = nh; G.group = d.group; G.head0 = h0; G.S = d.S; G.S_pad = d.S_pad;
+  G.dlist = dlist; G.dlist_stride = w.dlist_stride;
   G.key_limit = row_hi < d.S ? row_hi : 0;     // the rows of this segment end at row_hi: later keys are never read
   return dev(sa::launch_gather_strips(G, st));
 }
@@ -592,7 +595,7 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
       s = prepare_heads(d, bw, granularity, h0, nh, n_cand, k, v,
                         col_idx_all + chunk_off * n_cand, col_cnt_all + chunk_off,
                         slash_idx_all + chunk_off * n_cand, slash_cnt_all + chunk_off,
-                        local_window, row_hi, m == 0 ? tiles : nullptr, ws, st, &cnt_used);
+                        local_window, row_lo, row_hi, m == 0 ? tiles : nullptr, ws, st, &cnt_used);
       if (s != SA_OK) return s;
       const int segs = (n_segments < qtile1 - qtile0) ? n_segments : (qtile1 - qtile0);
       for (int g = 0; g < segs; ++g) {

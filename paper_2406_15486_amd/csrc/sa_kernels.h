@@ -8,6 +8,7 @@ namespace sa {
 constexpr int kHeadDim = 128;  // the only supported head dimension
 constexpr int kFlashBQ = 256;  // query rows per workgroup of the flash kernels
 constexpr int kFlashBK = 64;   // keys per tile
+constexpr int kSweepBit = 1 << 23;   // in every entry of a tile-diagonal list: the head is swept
 
 struct FlashParams {
   const uint16_t* q;        // [n_bh, S, 128] bf16
@@ -62,6 +63,8 @@ struct GatherParams {
   int n_heads, group;       // source head of head g is (head0 + g) / group
   int head0;
   int S, S_pad;
+  const int32_t* dlist;     // [n_heads, dlist_stride]: nothing is gathered for a head that is swept
+  int dlist_stride;
   int key_limit;            // > 0: no reader looks at a key >= key_limit; tiles of 64 list entries
                             // that start there are not gathered (their idx_pad entries still are written)
 };
@@ -74,6 +77,7 @@ struct MaskPrepParams {
   int32_t* dlist; int32_t* dcnt;
   unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
+  int qtile_lo, qtile_hi, row_hi;                      // the query tiles this mask is for, and the end of their rows
 };
 hipError_t launch_mask_prep(const MaskPrepParams& P, hipStream_t st);
 
@@ -87,6 +91,7 @@ struct BlockPrepParams {
   int32_t* dlist; int32_t* dcnt;
   unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
+  int qtile_lo, qtile_hi, row_hi;                      // the query tiles this mask is for, and the end of their rows
   int blk, nb, idx_pad_stride;
 };
 hipError_t launch_block_prep(const BlockPrepParams& P, hipStream_t st);

@@ -6,7 +6,9 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from gpu_progress import say as _say              # noqa: E402
-from test_gpu_parity import _select_case          # noqa: E402
+from oracle import sample_attention as O           # noqa: E402
+from test_gpu_block import _block_case            # noqa: E402
+from test_gpu_parity import _check_out, _dev, _f64, _inputs, _select_case, _sparse_case   # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +49,57 @@ def test_sparse_attn_bitmap_in_several_segments():
         s = kk @ q[0, 0, i].double().cpu() / np.sqrt(128.0)
         assert abs(float(torch.logsumexp(s, 0)) - float(lse[0, i])) < 2e-3, i
         assert (torch.softmax(s, 0) @ vv - out[0, 0, i].double().cpu()).abs().max() < 2e-2, i
+
+
+def _fill(rng, n, share):
+    return np.sort(rng.choice(n, int(round(share * n)), replace=False))
+
+
+@pytest.mark.parametrize("S", [1, 63, 65, 255, 257, 320, 321, 1279, 1281])
+def test_swept_heads_beside_two_pass_heads(S):
+    """Heads with nearly full lists are swept once, the others take the two passes, in one
+    launch: per-key lists of every mixture, at lengths around the key and query tiles."""
+    _say(f"swept heads S={S}")
+    wl, x = _inputs("glm8k", S=S, Hq=4, Hkv=2, n_sinks=min(8, S))
+    rng = np.random.default_rng(S)
+    Ic = [_fill(rng, S, f) for f in (0.9, 0.02, 1.0, 0.5)]
+    Is = [_fill(rng, S, f) for f in (0.9, 0.01, 0.3, 0.97)]
+    _sparse_case(wl, x, Ic, Is, 1, "swept", f32_out=S % 2 == 1)
+
+
+@pytest.mark.parametrize("S,blk", [(1280, 64), (1333, 128), (2100, 256)])
+def test_swept_heads_block_lists(S, blk):
+    _say(f"swept heads S={S} blk={blk}")
+    _, x = _inputs("glm8k", S=S, Hq=4, Hkv=2, n_sinks=8)
+    nb = (S + blk - 1) // blk
+    rng = np.random.default_rng(S)
+    Ic = [_fill(rng, nb, f) for f in (0.9, 0.1, 1.0, 0.6)]
+    Is = [_fill(rng, nb, f) for f in (0.8, 0.0, 0.3, 1.0)]
+    _block_case(x, Ic, Is, 1, blk, "swept blocks")
+
+
+@pytest.mark.parametrize("S,C,blk", [(1000, 3, 1), (1901, 5, 128)])
+def test_swept_segments(S, C, blk):
+    """Segments that end inside a query tile, full lists next to short ones."""
+    import paper_2406_15486_amd as sa
+    _say(f"swept segments S={S} C={C} blk={blk}")
+    _, x = _inputs("glm8k", S=S, Hq=2, Hkv=1, n_sinks=8)
+    n = (S + blk - 1) // blk
+    rng = np.random.default_rng(S)
+    lists = [[[_fill(rng, n, 0.9 if (m + h) % 2 else 0.05) for h in range(2)] for m in range(C)] for _ in range(2)]
+    idx = [torch.zeros(C, 2, n, dtype=torch.int32) for _ in range(2)]
+    cnt = [torch.zeros(C, 2, dtype=torch.int32) for _ in range(2)]
+    for t in range(2):
+        for m in range(C):
+            for h in range(2):
+                cnt[t][m, h] = len(lists[t][m][h])
+                idx[t][m, h, :len(lists[t][m][h])] = torch.from_numpy(lists[t][m][h].astype(np.int32))
+    out, lse, _ = sa.sa_sparse_attn_chunked(_dev(x["q"]), _dev(x["k"]), _dev(x["v"]), idx[0].cuda(), cnt[0].cuda(),
+                                            idx[1].cuda(), cnt[1].cuda(), 1, C, granularity=blk, want_lse=True)
+    torch.cuda.synchronize()
+    qf, kf, vf = _f64(x["q"]), _f64(x["k"]), _f64(x["v"])
+    for h in range(2):
+        want, wlse = O.chunked_masked_attn(qf[h], kf[0], vf[0], [lists[0][m][h] for m in range(C)],
+                                           [lists[1][m][h] for m in range(C)], 1, C, blk=blk)
+        _check_out(out[0, h].float().cpu().numpy(), want, f"swept segments h{h}")
+        assert np.abs(lse[h].cpu().numpy() - wlse).max() < 2e-3
