@@ -888,20 +888,25 @@ hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hi
   return hipGetLastError();
 }
 
-// How many key splits even out the log-sum-exp launch: W workgroups of equal length cut
-// k ways take ceil(W k / 512) / k rounds on 256 CUs x 2 workgroups; a split keeps at least 64 tiles, and
-// every row must see a key in every split (the sampled rows start at row_first).
-int lse_key_splits(int row_first, int n_s, int n_bh) {
+// How many workgroups share the keys of a query tile of the log-sum-exp launch (a power of
+// two, at most k_max).  Two things ask for a split: W workgroups fill the 512 slots (256 CUs x
+// 2) unevenly, and a chunk of 128 sampled rows gives one workgroup per head, a serial chain
+// over every key on a chip that is nearly idle.  A part costs its tiles and kPartTiles tiles'
+// worth of start, end and combination; a workgroup that has a CU to itself runs its tiles in
+// 0.6 of the time.  A part keeps kMinPartTiles tiles, more than the four that a query tile
+// spans, so that every row sees a key in every part.
+constexpr int kPartTiles = 6, kMinPartTiles = 8;
+int lse_key_splits(int row_first, int n_s, int n_bh, int k_max) {
   const int n_qtiles = (n_s + kFlashBQ - 1) / kFlashBQ;
   const long long W = (long long)n_qtiles * n_bh;
   const int min_tiles = row_first / kFlashBK;       // key tiles the first sampled row sees, at least
+  auto cost = [&](int k) {
+    const long long n = W * k;
+    return (n <= 256 ? 0.6 : (double)((n + 511) / 512)) * ((double)min_tiles / k + kPartTiles);
+  };
   int best = 1;
-  double best_t = (double)((W + 511) / 512);
-  for (int k = 2; k <= 8; k *= 2) {
-    if (min_tiles / k < 64) break;
-    double t = (double)((W * k + 511) / 512) / k;
-    if (t < best_t - 1e-9) { best_t = t; best = k; }
-  }
+  for (int k = 2; k <= k_max && min_tiles / k >= kMinPartTiles; k *= 2)
+    if (cost(k) < cost(best)) best = k;
   return best;
 }
 

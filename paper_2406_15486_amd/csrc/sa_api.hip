@@ -75,13 +75,17 @@ sa_status check_chunks(const Dims& d, int n_chunks, int granularity) {
 }
 
 // ---- workspace layouts --------------------------------------------------------
-constexpr int kMaxKeySplits = 8;
+// The partial log-sum-exps of more than kRoomKeySplits key splits run on into the region of the
+// slash partials, which are written after they have been combined: a part keeps at least eight
+// key tiles, so that k splits need S >= 512 k, and there are more than S / 205 slash partials
+// per sampled row.
+constexpr int kRoomKeySplits = 8, kMaxKeySplits = 64;
 struct SampleWs { size_t lse, lse_part, partial, tok_col, tok_slash, total; };
 SampleWs sample_ws(const Dims& d, int n_s, int granularity) {
   SampleWs w;
   size_t at = 0;
   w.lse = at;      at += align_up((size_t)d.n_bh * n_s * sizeof(float));
-  w.lse_part = at; at += align_up((size_t)kMaxKeySplits * d.n_bh * n_s * sizeof(float));
+  w.lse_part = at; at += align_up((size_t)kRoomKeySplits * d.n_bh * n_s * sizeof(float));
   w.partial = at; at += align_up(sa::score_partial_floats(d.S, n_s, d.n_bh) * sizeof(float));
   w.tok_col = w.tok_slash = at;
   if (granularity > 1) {   // per-token scores, reduced to blocks afterwards
@@ -309,8 +313,7 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
 
       // pass 1: log-sum-exp of every sampled row (flash sweep without V)
       sa::FlashParams P = base_flash(pd, q_pass, k_pass);
-      P.k_splits = sa::lse_key_splits(row_first, n_s, pd.n_bh);
-      if (P.k_splits > kMaxKeySplits) P.k_splits = kMaxKeySplits;
+      P.k_splits = sa::lse_key_splits(row_first, n_s, pd.n_bh, kMaxKeySplits);
       P.lse = P.k_splits > 1 ? reinterpret_cast<float*>(ws + w.lse_part) : lse;
       P.q_row0 = row_first;
       P.n_qrows = n_s;

@@ -45,7 +45,7 @@ struct FlashParams {
 
 // mode 0: dense causal; 1: row log-sum-exp of rows [q_row0, q_row0+n_qrows); 2: strip mask
 hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_t st);
-int lse_key_splits(int row_first, int n_s, int n_bh);
+int lse_key_splits(int row_first, int n_s, int n_bh, int k_max);
 hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hipStream_t st);
 
 // vt[g][d][c] = v[g][c][d], zero up to the 64-key tile that ends the sequence

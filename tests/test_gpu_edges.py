@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 from gpu_progress import say as _say              # noqa: E402
 from oracle import sample_attention as O           # noqa: E402
 from test_gpu_block import _block_case            # noqa: E402
-from test_gpu_parity import _check_out, _dev, _f64, _inputs, _select_case, _sparse_case   # noqa: E402
+from test_gpu_parity import _check_out, _dev, _f64, _inputs, _score_tol, _select_case, _sparse_case   # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -103,3 +103,20 @@ def test_swept_segments(S, C, blk):
                                            [lists[1][m][h] for m in range(C)], 1, C, blk=blk)
         _check_out(out[0, h].float().cpu().numpy(), want, f"swept segments h{h}")
         assert np.abs(lse[h].cpu().numpy() - wlse).max() < 2e-3
+
+
+@pytest.mark.parametrize("S,n_s,Hq", [(1087, 64, 1), (1088, 64, 1), (1111, 65, 2), (4224, 128, 2), (4500, 300, 2), (32896, 128, 1)])
+def test_sample_scores_around_the_key_splits(S, n_s, Hq):
+    """Few sampled rows: the keys of a query tile are cut into parts of eight tiles or more
+    (S - n_s = 1024: the first split; 32768: the most of them)."""
+    import paper_2406_15486_amd as sa
+    _say(f"key splits S={S} n_s={n_s}")
+    _, x = _inputs("glm8k", S=S, Hq=Hq, Hkv=1, n_sinks=8)
+    col, slash, lse = sa.sa_sample_scores(_dev(x["q"]), _dev(x["k"]), n_s, want_lse=True)
+    torch.cuda.synchronize()
+    qf, kf = _f64(x["q"]), _f64(x["k"])
+    for h in range(Hq):
+        wc, ws, wl = O.sample_scores(qf[h], kf[0], n_s)
+        _score_tol(col[h].cpu().numpy(), wc, f"col h{h}")
+        _score_tol(slash[h].cpu().numpy(), ws, f"slash h{h}")
+        assert np.abs(lse[h].cpu().numpy() - wl).max() < 2e-3
