@@ -270,8 +270,12 @@ sa_status sa_sparse_attn(const sa_shape* shape, const void* q, const void* k, co
  * consecutive launches of (nearly) equal numbers of 256-row query tiles.
  * Values larger than the number of heads / query tiles are clamped; both must
  * be >= 1.  The result (out, out_lse, tiles) is bit-identical to
- * sa_sparse_attn's: every (head, query tile) is computed by one workgroup in
- * the same order of operations whatever the partition.
+ * sa_sparse_attn's where both calls bring workspaces of the sizes that the
+ * library asks for: every (head, query tile) is computed in the same order of
+ * operations whatever the partition.  (Of a small problem, fewer query tiles
+ * than CUs, a tile's keys are cut into parts by a rule on the shape; a
+ * workspace that lacks the room for the partial sums is accepted, the tiles
+ * are then not cut, and the last bits of the result differ.)
  * Workspace: sa_partitioned_workspace_bytes(shape, partition) (0 for invalid
  * arguments; host only).
  */
@@ -303,7 +307,8 @@ sa_status sa_dense_attn(const sa_shape* shape, const void* q, const void* k, con
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc.  Same arguments, results and kernels as sa_dense_attn, but
  * the transposed copy of V lives in a device array that is part of the library
- * (SA_STATIC_SCRATCH_BYTES per GPU, held until the process ends) instead of a
+ * (SA_STATIC_SCRATCH_BYTES and, for the partial sums of small problems, 34 MB
+ * more per GPU, held until the process ends) instead of a
  * caller workspace, and the call allocates nothing.
  * Limit: batch * n_kv_heads * head_dim * roundup(seq_len, 256) * 2 bytes must
  * fit the array, i.e. batch * n_kv_heads * roundup(seq_len, 256) <= 65536 -

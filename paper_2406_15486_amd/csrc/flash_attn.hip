@@ -122,6 +122,10 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Parts of the query tiles [q0, q1) of a head, ceil((a + 1) / m) for tile a.
+__host__ __device__ inline int parts_upto(int m, int n) { return m * (n / m) * (n / m + 1) / 2 + (n % m) * (n / m + 1); }
+__host__ __device__ inline int parts_before(int m, int q0, int q1) { return parts_upto(m, q1) - parts_upto(m, q0); }
+
 }  // namespace
 
 // MODE: 0 dense causal, 1 row log-sum-exp only (no V), 2 strip-masked sparse.
@@ -134,8 +138,10 @@ __device__ __forceinline__ void wg_barrier() {
 // gathered tiles.  The kernel below picks the body by head.  As a run-time flag inside one
 // body the choice cost the long unswept launches 2.5 % (128K tokens, alpha = 0.95); as a
 // body of its own it knows at compile time that interior tiles are active.
-template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP>
-__device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, const int a, const int split) {
+// PARTS (dense and strip-masked modes): the workgroup takes part `split` of the `n_parts` equal
+// parts of its query tile's schedule and leaves unnormalised sums for parts_combine_kernel.
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP, bool PARTS>
+__device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, const int a, const int split, const int n_parts) {
   static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -201,16 +207,30 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     kc = P.kc + (size_t)bh * P.S_pad * kHeadDim;
     vct = P.vct + (size_t)bh * kHeadDim * P.S_pad;
   }
-  n_col_tiles = __builtin_amdgcn_readfirstlane(n_col_tiles);
-  n_rng = __builtin_amdgcn_readfirstlane(n_rng);
   int t_base = 0;                        // first key tile of this workgroup's share of the causal sweep
   int n_sweep = min(i_last_wg, S - 1) / BK + 1;
   if (MODE == 1 && P.k_splits > 1) {
     t_base = (int)((long long)n_sweep * split / P.k_splits);
     n_sweep = (int)((long long)n_sweep * (split + 1) / P.k_splits) - t_base;
   }
+  int n_sched = (MODE == 2 && !SWEEP) ? (n_col_tiles + n_rng) : n_sweep;
+  if (PARTS) {
+    t_base = n_sched * split / n_parts;
+    n_sched = n_sched * (split + 1) / n_parts - t_base;
+    if (MODE == 2 && !SWEEP) {           // tile t of this part is tile t + t_base of the schedule
+      const int col_before = min(t_base, n_col_tiles);
+      n_rng -= t_base - col_before;
+      n_col_tiles = min(n_col_tiles - col_before, n_sched);
+      cidx += BK * col_before;
+      kc += (size_t)col_before * BK * kHeadDim;
+      vct += (size_t)col_before * BK;
+    }
+  }
   t_base = __builtin_amdgcn_readfirstlane(t_base);
-  const int n_tiles = __builtin_amdgcn_readfirstlane((MODE == 2 && !SWEEP) ? (n_col_tiles + n_rng) : n_sweep);
+  n_col_tiles = __builtin_amdgcn_readfirstlane(n_col_tiles);
+  n_rng = __builtin_amdgcn_readfirstlane(n_rng);
+  const int n_tiles = __builtin_amdgcn_readfirstlane(n_sched);
+  constexpr bool SHIFTED = MODE == 1 || (PARTS && (MODE == 0 || SWEEP));   // a causal sweep that starts at tile t_base
 
   // Kind of tile t (wave-uniform; no memory access), and whether t lies inside the schedule.
   // `kc` is the Stretch the calling iteration belongs to: what it knows at compile time.
@@ -233,7 +253,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
       return ((const_i32_ptr)(uintptr_t)cidx)[BK * t];                       // first key of the tile's block
     if (SWEEP) {
       // the list holds every diagonal; only block masks need its entry (which waves keep the tile)
-      if (IN_PLACE && is_real(kc, t)) return ((const_i32_ptr)(uintptr_t)dl)[a64 + 3 - t];
+      if (IN_PLACE && is_real(kc, t)) return ((const_i32_ptr)(uintptr_t)dl)[a64 + 3 - t - (SHIFTED ? t_base : 0)];
       return 0;
     }
     if (MODE == 2 && !is_col(kc, t) && is_real(kc, t))
@@ -243,7 +263,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   // first key of tile t
   auto first_key = [&](auto kc, int t, int d) __attribute__((always_inline)) -> int {  // contiguous tiles only; d = list entry
     if (IN_PLACE && is_col(kc, t)) return d;         // the entry of an in-place column tile is its first key
-    return (MODE == 2 && !SWEEP) ? (a64 + 3 - (d & kDiagMask)) * BK : (t + (MODE == 1 ? t_base : 0)) * BK;
+    return (MODE == 2 && !SWEEP) ? (a64 + 3 - (d & kDiagMask)) * BK : (t + (SHIFTED ? t_base : 0)) * BK;
   };
   // array bases as scalars, once
   const uint64_t s_kbase = scalar_ptr(kbase), s_vtbase = scalar_ptr(vtbase);
@@ -796,6 +816,19 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   float l_tot = half_sum(l_run);
   if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
   if (!row_ok) return;
+  if (PARTS) {
+    const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
+    const int r = 32 * wave + ql;
+    if (hf == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run, l_tot);
+    float* po = P.part_o + (slot * BQ + r) * kHeadDim;
+#pragma unroll
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4*>(po + 32 * mb + 8 * g + 4 * hf) =
+            make_float4(o[mb][4 * g], o[mb][4 * g + 1], o[mb][4 * g + 2], o[mb][4 * g + 3]);
+    return;
+  }
   if (P.lse != nullptr && hf == 0) {
     size_t at = (MODE == 1) ? (((size_t)split * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)) : ((size_t)bh * S + i_me);
     P.lse[at] = m_run * kLn2 + __logf(l_tot);
@@ -821,15 +854,26 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   }
 }
 
-template <int MODE, bool OUT_F32, bool IN_PLACE = false>
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS>
 __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
   // ---- which (head, query tile) this workgroup owns ------------------------
   // (the log-sum-exp sweep may also cut the keys of a query tile into k_splits
   // equal parts, one workgroup each, to even out the last round of the launch)
-  int bh, a, split = 0;
+  int bh, a, split = 0, n_parts = 1;
   {
     const int bid = blockIdx.x;
-    if (MODE == 2) {
+    if (PARTS) {
+      // heavy (late) query tiles first, the heads of a part side by side
+      bh = bid % P.n_bh;
+      split = bid / P.n_bh;
+      a = P.qtile0 + P.n_qtiles - 1;
+      n_parts = a / P.part_m + 1;
+      while (split >= n_parts) {         // (ends: the grid has exactly the parts of these tiles)
+        split -= n_parts;
+        --a;
+        n_parts = a / P.part_m + 1;
+      }
+    } else if (MODE == 2) {
       // heads are sliced over the 8 XCDs (workgroups go round-robin to XCDs) and an
       // XCD works through one head at a time, heavy (late) query tiles first: the
       // workgroups resident on it then stream the gathered columns of the same head,
@@ -864,11 +908,45 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
     // (diagonal 0 is in every list, and its entry is the first)
     const int first = P.dlist[(size_t)bh * P.dlist_stride];
     if (__builtin_amdgcn_readfirstlane(first) & kSweepBit) {
-      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2>(P, bh, a, split);
+      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS>(P, bh, a, split, n_parts);
       return;
     }
   }
-  flash_body<MODE, OUT_F32, IN_PLACE, false>(P, bh, a, split);
+  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS>(P, bh, a, split, n_parts);
+}
+
+// The parts of a query tile brought to one reference maximum, added in fixed order and
+// normalised.  Eight rows per workgroup, 32 lanes of four columns each.
+template <bool OUT_F32>
+__global__ __launch_bounds__(256) void parts_combine_kernel(FlashParams P) {
+  const int bh = blockIdx.y, tid = threadIdx.x;
+  const int r_launch = blockIdx.x * 8 + (tid >> 5);
+  const int a = P.qtile0 + r_launch / BQ, r = r_launch % BQ;
+  const int i = a * BQ + r, c4 = tid & 31;
+  if (i < P.row_lo || i >= P.n_qrows) return;
+  const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a);
+  const int n_parts = a / P.part_m + 1;
+  const float2* ml = reinterpret_cast<const float2*>(P.part_ml) + slot * BQ + r;
+  const float4* po = reinterpret_cast<const float4*>(P.part_o + (slot * BQ + r) * kHeadDim) + c4;
+  float m = ml[0].x;
+  for (int s = 1; s < n_parts; ++s) m = fmaxf(m, ml[s * BQ].x);
+  float l = 0.f;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s = 0; s < n_parts; ++s) {
+    const float2 e = ml[s * BQ];
+    const float w = fast_exp2(e.x - m);
+    const float4 y = po[(size_t)s * BQ * (kHeadDim / 4)];
+    l = fmaf(e.y, w, l);
+    x.x = fmaf(y.x, w, x.x); x.y = fmaf(y.y, w, x.y); x.z = fmaf(y.z, w, x.z); x.w = fmaf(y.w, w, x.w);
+  }
+  const float inv = 1.0f / l;
+  const size_t at = ((size_t)bh * P.S + i) * kHeadDim + 4 * c4;
+  if (OUT_F32)
+    *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + at) = make_float4(x.x * inv, x.y * inv, x.z * inv, x.w * inv);
+  else
+    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + at) =
+        make_uint2(pack_bf16x2(x.x * inv, x.y * inv), pack_bf16x2(x.z * inv, x.w * inv));
+  if (P.lse != nullptr && c4 == 0) P.lse[(size_t)bh * P.S + i] = m * kLn2 + __logf(l);
 }
 
 // out[i] = log sum_s exp(part[s][i]): the key splits of the log-sum-exp sweep, in fixed order
@@ -910,18 +988,64 @@ int lse_key_splits(int row_first, int n_s, int n_bh, int k_max) {
   return best;
 }
 
-template <int MODE, bool OUT_F32, bool IN_PLACE = false>
+// Parts of the schedules of a dense or strip-masked launch over the query tiles [q0, q1).  A
+// workgroup has a CU to itself, so fewer workgroups than the 256 CUs leave part of the chip
+// idle while the last query tile goes through all its key tiles alone.  Tile a, of 4 (a + 1)
+// key tiles in a causal sweep, is then cut into ceil((a + 1) / m) equal parts of at most 4 m.
+// m is the one with the least estimated time among those that give no more parts than CUs: a
+// key tile takes kTileUs; the partial sums (132 KB a part) are written and read and cost a
+// launch.  The estimate depends on the shape alone, so that a tile's result does not depend on
+// how a call divides heads and queries over its launches.
+// Dense kernel, uncut / cut (parts): 1 head of 1024 tokens 29.5 / 20.9 us (10), of 4096
+// 81 / 32 (72), 4 of 2048 47 / 31 (80), of 8192 156 / 88 (252), 8 of 1500 37 / 31 (96), of 3001
+// 64 / 41 (240); left uncut: 16 of 3000 66.6 / 66.0 (256), 32 of 600 21.7 / 29.8 (192).
+constexpr double kTileUs = 1.1, kCombineUs = 3.0, kPartUs = 0.065;
+int flash_parts(int n_bh, int q0, int q1) {
+  if ((long long)n_bh * (q1 - q0) > kMaxParts) return 0;
+  const double longest = 4.0 * q1, spread = n_bh * 2.0 * ((double)q1 * (q1 + 1) - (double)q0 * (q0 + 1)) / 256;
+  double best_t = longest * kTileUs;
+  int best = 0;
+  for (int m = q1 - 1; m >= 1; --m) {
+    const long long n = (long long)n_bh * parts_before(m, q0, q1);
+    if (n > kMaxParts) break;
+    const double part = 4.0 * m;
+    const double t = (part > spread ? part : spread) * kTileUs + kCombineUs + kPartUs * n;
+    if (t < best_t) { best_t = t; best = m; }
+  }
+  return best;
+}
+
+size_t flash_parts_bytes(int m, int n_heads, int q0, int q1) {
+  return m == 0 ? 0 : (size_t)n_heads * parts_before(m, q0, q1) * BQ * (kHeadDim + 2) * sizeof(float);
+}
+
+template <int MODE, bool OUT_F32, bool IN_PLACE = false, bool PARTS = false>
 static hipError_t launch_one(const FlashParams& P, int grid, hipStream_t st) {
   size_t shmem = (MODE == 1) ? LDS_B_LSE : LDS_B;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE>), dim3(grid), dim3(NT), shmem, st, P);
+  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS>), dim3(grid), dim3(NT), shmem, st, P);
+  return hipGetLastError();
+}
+
+// a launch whose schedules are cut into parts, and the combination
+static hipError_t launch_parts(int mode, bool out_f32, const FlashParams& P0, hipStream_t st) {
+  FlashParams P = P0;
+  const int n = P.n_bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles);
+  P.part_ml = P.part_o + (size_t)n * BQ * kHeadDim;
+  hipError_t e = mode == 0 ? launch_one<0, false, false, true>(P, n, st)
+               : P.cols_in_place ? launch_one<2, false, true, true>(P, n, st) : launch_one<2, false, false, true>(P, n, st);
+  if (e != hipSuccess) return e;
+  const dim3 grid(P.n_qtiles * (BQ / 8), P.n_bh);
+  if (out_f32) hipLaunchKernelGGL(parts_combine_kernel<true>, grid, dim3(256), 0, st, P);
+  else hipLaunchKernelGGL(parts_combine_kernel<false>, grid, dim3(256), 0, st, P);
   return hipGetLastError();
 }
 
 hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_t st) {
   int grid;
+  if (mode != 1 && P.part_m > 0) return launch_parts(mode, out_f32, P, st);
   if (mode == 2) {
     grid = (P.n_bh >= 8) ? 8 * P.n_qtiles * ((P.n_bh + 7) / 8) : P.n_qtiles * P.n_bh;
   } else {

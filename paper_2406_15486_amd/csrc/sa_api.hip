@@ -10,8 +10,9 @@
 #include "sa_kernels.h"
 
 // Static device scratch of the entry point that allocates nothing (sa_dense_attn_static):
-// one copy per GPU that loads the library, held until the process ends.
-static __device__ __align__(256) unsigned char scratch[SA_STATIC_SCRATCH_BYTES];
+// one copy per GPU that loads the library, held until the process ends.  V^T first, then the
+// partial sums of a launch that is cut into parts.
+static __device__ __align__(256) unsigned char scratch[SA_STATIC_SCRATCH_BYTES + sa::kMaxPartsBytes];
 
 namespace {
 
@@ -164,6 +165,10 @@ sa_status check_partition(const sa_partition* p, const Dims& d, int* heads_per_p
   return SA_OK;
 }
 
+// Room for the partial sums of launches that are cut into parts (flash_parts), of all heads, the
+// largest of a call's segments.  It lies behind the rest of the workspace: a workspace that lacks it is
+// accepted, and the launches are then not cut.
+size_t parts_room(const Dims& d, int n_chunks, bool blocks = false);
 size_t dense_ws(const Dims& d) { return align_up((size_t)d.n_bkv * sa::kHeadDim * d.S_pad * 2); }
 
 // rows [*lo, *hi) of query segment m of chunk_n (Algorithm 1: itv = S_q / chunk_n; here
@@ -172,6 +177,34 @@ inline void segment_rows(int S, int n_chunks, int m, int* lo, int* hi) {
   const int itv = S / n_chunks;
   *lo = m * itv;
   *hi = (m + 1 < n_chunks) ? (m + 1) * itv : S;
+}
+
+// parts of the query tiles [q0, q1).  Block lists of less than 2048 tokens are not cut: their
+// workspace, no more than metadata, is to stay a fraction of the strips' (8 us of 80 are at stake).
+int call_parts(const Dims& d, bool blocks, int q0, int q1) {
+  return blocks && d.S < 2048 ? 0 : sa::flash_parts(d.n_bh, q0, q1);
+}
+
+size_t parts_room(const Dims& d, int n_chunks, bool blocks) {
+  size_t most = 0;
+  if (d.n_bh > 256) return 0;
+  for (int m = 0; m < n_chunks; ++m) {
+    int lo, hi;
+    segment_rows(d.S, n_chunks, m, &lo, &hi);
+    const int q0 = lo / sa::kFlashBQ, q1 = (hi + sa::kFlashBQ - 1) / sa::kFlashBQ;
+    const size_t n = sa::flash_parts_bytes(call_parts(d, blocks, q0, q1), d.n_bh, q0, q1);
+    if (n > most) most = n;
+  }
+  return align_up(most);
+}
+
+// cuts the launch P over the query tiles [q0, q1) of the whole call into parts if `room` bytes
+// at `at` hold their sums for n_heads heads
+void set_parts(sa::FlashParams* P, const Dims& d, bool blocks, int n_heads, int q0, int q1, void* at, size_t room) {
+  const int m = call_parts(d, blocks, q0, q1);
+  if (m == 0 || sa::flash_parts_bytes(m, n_heads, q0, q1) > room) return;
+  P->part_m = m;
+  P->part_o = static_cast<float*>(at);
 }
 
 inline sa_status dev(hipError_t e) { return e == hipSuccess ? SA_OK : SA_ERR_DEVICE; }
@@ -245,6 +278,7 @@ extern "C" {
 size_t sa_workspace_bytes(int op, const sa_shape* shape, const sa_sampling* sampling) {
   Dims d;
   if (check_shape(shape, &d) != SA_OK) return 0;
+  const int chunks = (sampling != nullptr && sampling->n_chunks >= 1 && sampling->n_chunks <= d.S) ? sampling->n_chunks : 1;
   switch (op) {
     case SA_OP_SAMPLE_SCORES:
       if (check_sampling(sampling, d) != SA_OK) return 0;
@@ -253,11 +287,11 @@ size_t sa_workspace_bytes(int op, const sa_shape* shape, const sa_sampling* samp
       if (check_sampling(sampling, d) != SA_OK) return 0;
       return sample_ws(pass_dims(d, 1), sampling->n_sample_rows, sampling->granularity).total;
     case SA_OP_SELECT_STRIPS: return 0;
-    case SA_OP_SPARSE_ATTN: return sparse_ws(d, d.n_bh).total;
-    case SA_OP_DENSE_ATTN: return dense_ws(d);
+    case SA_OP_SPARSE_ATTN: return sparse_ws(d, d.n_bh).total + parts_room(d, chunks);
+    case SA_OP_DENSE_ATTN: return dense_ws(d) + parts_room(d, 1);
     case SA_OP_BLOCK_SPARSE_ATTN:
       if (sampling == nullptr || check_granularity(sampling->granularity) != SA_OK) return 0;
-      return block_ws(d, sampling->granularity, d.n_bh).total;
+      return block_ws(d, sampling->granularity, d.n_bh).total + parts_room(d, chunks, true);
     default: return 0;
   }
 }
@@ -513,7 +547,8 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
 // the strip-masked kernel on query tiles [qtile0, qtile0 + n_qtiles) of the heads [h0, h0 + nh)
 sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, int nh, int qtile0, int n_qtiles,
                         int row_lo, int row_hi, const void* q, const void* k, const int32_t* col_cnt,
-                        void* out, int out_dtype, float* out_lse, uint64_t* tiles, char* ws, hipStream_t st) {
+                        void* out, int out_dtype, float* out_lse, uint64_t* tiles, char* ws, size_t parts_at, size_t ws_bytes,
+                        hipStream_t st) {
   sa::FlashParams P = base_flash(d, q, k);
   const size_t head_elems = (size_t)d.S * sa::kHeadDim;
   P.q = static_cast<const uint16_t*>(q) + (size_t)h0 * head_elems;
@@ -539,6 +574,8 @@ sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, i
   P.dcnt = reinterpret_cast<const int32_t*>(ws + w.dcnt);
   P.cidx_stride = d.S_pad; P.cb_words = w.cb_words; P.rb_words = w.rb_words;
   P.dlist_stride = w.dlist_stride; P.off_max = w.off_max;
+  // (decided for all heads and all query tiles of the segment, whatever this launch takes of them)
+  set_parts(&P, d, blocks, nh, row_lo / sa::kFlashBQ, (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ, ws + parts_at, ws_bytes - parts_at);
   Scope sc(SA_K_SPARSE_FLASH, st);
   return dev(sa::launch_flash(2, out_dtype == SA_OUT_F32, P, st));
 }
@@ -605,7 +642,7 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
         const int a0 = qtile0 + (int)((long long)(qtile1 - qtile0) * g / segs);
         const int a1 = qtile0 + (int)((long long)(qtile1 - qtile0) * (g + 1) / segs);
         s = launch_attend(d, bw.sp, blocks, h0, nh, a0, a1 - a0, row_lo, row_hi, q, k, cnt_used, out, out_dtype, out_lse,
-                          tiles, ws, st);
+                          tiles, ws, blocks ? bw.total : bw.sp.total, workspace_bytes, st);
         if (s != SA_OK) return s;
       }
     }
@@ -630,7 +667,7 @@ size_t sa_partitioned_workspace_bytes(const sa_shape* shape, const sa_partition*
   Dims d;
   int hpp = 0, segs = 0;
   if (check_shape(shape, &d) != SA_OK || check_partition(partition, d, &hpp, &segs) != SA_OK) return 0;
-  return sparse_ws(d, hpp).total;
+  return sparse_ws(d, hpp).total + parts_room(d, 1);
 }
 
 sa_status sa_sparse_attn_partitioned(const sa_shape* shape, const sa_partition* partition,
@@ -690,6 +727,7 @@ sa_status sa_dense_attn(const sa_shape* shape, const void* q, const void* k, con
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
+  set_parts(&P, d, false, d.n_bh, 0, P.n_qtiles, static_cast<char*>(workspace) + dense_ws(d), workspace_bytes - dense_ws(d));
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }
@@ -716,6 +754,7 @@ sa_status sa_dense_attn_static(const sa_shape* shape, const void* q, const void*
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
+  set_parts(&P, d, false, d.n_bh, 0, P.n_qtiles, static_cast<char*>(ws) + SA_STATIC_SCRATCH_BYTES, sa::kMaxPartsBytes);
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }

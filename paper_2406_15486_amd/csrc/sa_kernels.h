@@ -30,6 +30,9 @@ struct FlashParams {
                             // (rows [row_lo, n_qrows) of the launch's query tiles are; q_row0 = 0 there)
   int k_splits;             // mode 1: the keys of a query tile are cut into this many workgroups (>= 1);
                             // lse is then [k_splits, n_bh, n_qrows] partial values (launch_lse_combine)
+  int part_m;               // modes 0 and 2: > 0: tile a's schedule is cut into ceil((a + 1) / part_m) workgroups
+  float* part_o;            // ... whose sums [part, 256, 128] and then [part, 256, 2] lie here (flash_parts_bytes)
+  float* part_ml;           // (set by the launch)
   // strip-masked mode only
   const uint16_t* kc;           // [n_bh, S_pad, 128] K rows gathered by column index
   const uint16_t* vct;          // [n_bh, 128, S_pad] V rows gathered and transposed
@@ -46,6 +49,12 @@ struct FlashParams {
 // mode 0: dense causal; 1: row log-sum-exp of rows [q_row0, q_row0+n_qrows); 2: strip mask
 hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_t st);
 int lse_key_splits(int row_first, int n_s, int n_bh, int k_max);
+// part_m of a launch over the query tiles [q0, q1) of n_bh heads (0: not cut), and the bytes of
+// the partial sums of n_heads of them
+constexpr int kMaxParts = 256;
+constexpr size_t kMaxPartsBytes = (size_t)kMaxParts * kFlashBQ * (kHeadDim + 2) * 4;
+int flash_parts(int n_bh, int q0, int q1);
+size_t flash_parts_bytes(int m, int n_heads, int q0, int q1);
 hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hipStream_t st);
 
 // vt[g][d][c] = v[g][c][d], zero up to the 64-key tile that ends the sequence

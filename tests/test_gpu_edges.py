@@ -120,3 +120,63 @@ def test_sample_scores_around_the_key_splits(S, n_s, Hq):
         _score_tol(col[h].cpu().numpy(), wc, f"col h{h}")
         _score_tol(slash[h].cpu().numpy(), ws, f"slash h{h}")
         assert np.abs(lse[h].cpu().numpy() - wl).max() < 2e-3
+
+
+# (path, S, Hq, Hkv, segments or block size): from one tile to the most parts (256), ragged last
+# tiles and parts, a batch of segments
+@pytest.mark.parametrize("path,S,Hq,Hkv,n", [("dense", 513, 1, 1, 0), ("dense", 1100, 3, 1, 0), ("dense", 3001, 8, 2, 0),
+                                             ("strips", 700, 1, 1, 1), ("strips", 2305, 4, 2, 1), ("strips", 2600, 2, 1, 3),
+                                             ("blocks", 2049, 2, 1, 128), ("blocks", 2500, 4, 2, 64)])
+def test_tiles_cut_into_parts(path, S, Hq, Hkv, n):
+    """Small problems: a query tile's keys are cut into parts.  A workspace without room for the
+    partial sums gives uncut tiles; both against the oracle."""
+    import paper_2406_15486_amd as sa
+    B = sa.binding
+    _say(f"parts {path} S={S} Hq={Hq}")
+    _, x = _inputs("glm8k", S=S, Hq=Hq, Hkv=Hkv, n_sinks=8)
+    q, k, v = (_dev(x[t]) for t in "qkv")
+    qf, kf, vf = (_f64(x[t]) for t in "qkv")
+    sh, G = sa.Shape(1, Hq, Hkv, S), Hq // Hkv
+    rng = np.random.default_rng(S)
+    blk, C = (n, 1) if path == "blocks" else (1, max(n, 1))
+    nb = (S + blk - 1) // blk
+    shares = [(0.9, 0.9), (0.3, 0.01), (0.05, 0.3), (0.6, 0.002)]
+    Ic = [[_fill(rng, nb, shares[(h + m) % 4][0]) for h in range(Hq)] for m in range(C)]
+    Is = [[_fill(rng, nb, shares[(h + m) % 4][1]) for h in range(Hq)] for m in range(C)]
+    ci, si = (torch.zeros(C, Hq, nb, dtype=torch.int32) for _ in range(2))
+    for m in range(C):
+        for h in range(Hq):
+            ci[m, h, :len(Ic[m][h])] = torch.from_numpy(Ic[m][h].astype(np.int32))
+            si[m, h, :len(Is[m][h])] = torch.from_numpy(Is[m][h].astype(np.int32))
+    cc, sc = (torch.tensor([[len(a) for a in row] for row in lists], dtype=torch.int32) for lists in (Ic, Is))
+    S_pad = (S + 255) // 256 * 256
+    if path == "dense":
+        need = sa.sa_workspace_bytes(B.SA_OP_DENSE_ATTN, sh)
+        bare = Hkv * 256 * S_pad
+    else:
+        op = B.SA_OP_BLOCK_SPARSE_ATTN if path == "blocks" else B.SA_OP_SPARSE_ATTN
+        need = sa.sa_workspace_bytes(op, sh, granularity=blk, n_chunks=C)
+        up = lambda b: (b + 255) // 256 * 256                                  # noqa: E731
+        bare = Hkv * 256 * S_pad + sum(up(Hq * 4 * w) for w in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24, S_pad // 64 + 8, 1))
+        bare += up(Hq * 4) if path == "blocks" else Hq * 512 * S_pad
+    assert bare < need
+    got = []
+    for size in (need, bare):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")         # NaN patterns
+        if path == "dense":
+            r = sa.sa_dense_attn(q, k, v, workspace=ws, want_lse=True)
+        else:
+            lists = [t.cuda() for t in (ci, cc, si, sc)]
+            r = sa.sa_sparse_attn_chunked(q, k, v, *lists, 3, C, granularity=blk, workspace=ws, want_lse=True)
+        torch.cuda.synchronize()
+        got.append((r[0][0].float().cpu().numpy(), r[1].cpu().numpy()))
+    assert not np.array_equal(got[0][1], got[1][1])                              # two routes
+    for h in range(Hq):
+        if path == "dense":
+            want, wlse = O.dense_attn(qf[h], kf[h // G], vf[h // G])
+        else:
+            want, wlse = O.chunked_masked_attn(qf[h], kf[h // G], vf[h // G], [Ic[m][h] for m in range(C)],
+                                               [Is[m][h] for m in range(C)], 3, C, blk=blk)
+        for (out, lse), route in zip(got, ("parts", "uncut")):
+            _check_out(out[h], want, f"{path} {route} h{h}")
+            assert np.abs(lse[h] - wlse).max() < 2e-3
