@@ -273,9 +273,10 @@ sa_status sa_sparse_attn(const sa_shape* shape, const void* q, const void* k, co
  * sa_sparse_attn's where both calls bring workspaces of the sizes that the
  * library asks for: every (head, query tile) is computed in the same order of
  * operations whatever the partition.  (Of a small problem, fewer query tiles
- * than CUs, a tile's keys are cut into parts by a rule on the shape; a
- * workspace that lacks the room for the partial sums is accepted, the tiles
- * are then not cut, and the last bits of the result differ.)
+ * than CUs, a tile's keys are cut into parts by a rule on the shape, batch and
+ * number of heads included; a workspace that lacks the room for the partial
+ * sums is accepted, the tiles are then not cut.  The last bits of a result
+ * differ between one cut and another.)
  * Workspace: sa_partitioned_workspace_bytes(shape, partition) (0 for invalid
  * arguments; host only).
  */

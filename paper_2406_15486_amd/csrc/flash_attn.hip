@@ -992,27 +992,29 @@ int lse_key_splits(int row_first, int n_s, int n_bh, int k_max) {
 // workgroup has a CU to itself, so fewer workgroups than the 256 CUs leave part of the chip
 // idle while the last query tile goes through all its key tiles alone.  Tile a, of 4 (a + 1)
 // key tiles in a causal sweep, is then cut into ceil((a + 1) / m) equal parts of at most 4 m.
-// m is the one with the least estimated time among those that give no more parts than CUs: a
-// key tile takes kTileUs; the partial sums (132 KB a part) are written and read and cost a
-// launch.  The estimate depends on the shape alone, so that a tile's result does not depend on
-// how a call divides heads and queries over its launches.
+// Short parts fill the chip, but each leaves 132 KB of sums to be written and read: m follows
+// the length (the last tile in six parts) and grows only in coarse steps, until there are no
+// more parts than CUs; then the cut is made if the estimate says that it pays (a key tile takes
+// kTileUs, the combination kCombineUs and kPartUs a part).  All this depends on the shape alone,
+// so that a tile's result does not depend on how a call divides heads and queries over its
+// launches, and through the coarse steps rarely on the size of the batch.
 // Dense kernel, uncut / cut (parts): 1 head of 1024 tokens 29.5 / 20.9 us (10), of 4096
-// 81 / 32 (72), 4 of 2048 47 / 31 (80), of 8192 156 / 88 (252), 8 of 1500 37 / 31 (96), of 3001
+// 81 / 33 (51), 4 of 2048 47 / 31 (80), of 8192 156 / 88 (240), 8 of 1500 37 / 31 (168), of 3001
 // 64 / 41 (240); left uncut: 16 of 3000 66.6 / 66.0 (256), 32 of 600 21.7 / 29.8 (192).
 constexpr double kTileUs = 1.1, kCombineUs = 3.0, kPartUs = 0.065;
 int flash_parts(int n_bh, int q0, int q1) {
   if ((long long)n_bh * (q1 - q0) > kMaxParts) return 0;
   const double longest = 4.0 * q1, spread = n_bh * 2.0 * ((double)q1 * (q1 + 1) - (double)q0 * (q0 + 1)) / 256;
-  double best_t = longest * kTileUs;
-  int best = 0;
-  for (int m = q1 - 1; m >= 1; --m) {
+  const int base = (q1 + 5) / 6;
+  for (int step : {2, 3, 4, 6, 8}) {
+    const int m = (base * step + 1) / 2;
     const long long n = (long long)n_bh * parts_before(m, q0, q1);
-    if (n > kMaxParts) break;
+    if (n > kMaxParts) continue;
     const double part = 4.0 * m;
     const double t = (part > spread ? part : spread) * kTileUs + kCombineUs + kPartUs * n;
-    if (t < best_t) { best_t = t; best = m; }
+    return m < q1 && t < longest * kTileUs ? m : 0;
   }
-  return best;
+  return 0;
 }
 
 size_t flash_parts_bytes(int m, int n_heads, int q0, int q1) {
