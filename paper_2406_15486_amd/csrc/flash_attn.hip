@@ -58,6 +58,11 @@ constexpr int OFF_DUMP_LSE = OFF_V;
 constexpr int LDS_B_LSE = OFF_DUMP_LSE + 8 * 1024;  // 73728 bytes
 constexpr float kSumBound = 256.0f;    // a tile's exponentials may sum to 2^8 per lane before the reference maximum moves
 
+// Query tiles per head up to which a strip-masked launch goes by tile, not by head.  By head / by
+// tile, 32 heads, whole path: 4K tokens 273 / 233 us, 8K 707 / 708, blocks of 128 at 8K 596 / 579,
+// 12K 1422 / 1431.
+constexpr int kByTileMax = 32;
+
 enum TileKind : int { TK_PLAIN = 0, TK_CAUSAL = 1, TK_COLIDX = 2, TK_RANGE = 3 };
 // What a stretch of the tile loop knows at compile time about the tiles it touches
 // (the tile of an iteration, the one before and the four ahead).  KIND: nothing (0),
@@ -879,9 +884,13 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       // workgroups resident on it then stream the gathered columns of the same head,
       // a working set (tens of MB per XCD) that the memory-side cache can hold.
       if (P.n_bh >= 8) {
-        int xcd = bid & 7, slot = bid >> 3;
-        a = P.n_qtiles - 1 - slot % P.n_qtiles;
-        bh = xcd + 8 * (slot / P.n_qtiles);
+        // Where an XCD's heads have few query tiles each, that leaves the last head's heavy
+        // tiles for the end, with no light ones left to even them out (8K tokens: 32 CUs go
+        // through 4 x 32 tiles): there the heavy tiles of all its heads come first.
+        const int xcd = bid & 7, slot = bid >> 3, heads = (P.n_bh + 7) >> 3;
+        const bool by_tile = P.n_qtiles <= kByTileMax;
+        a = P.n_qtiles - 1 - (by_tile ? slot / heads : slot % P.n_qtiles);
+        bh = xcd + 8 * (by_tile ? slot % heads : slot / P.n_qtiles);
         if (bh >= P.n_bh) return;
       } else {
         a = P.n_qtiles - 1 - bid / P.n_bh;

@@ -180,3 +180,21 @@ def test_tiles_cut_into_parts(path, S, Hq, Hkv, n):
         for (out, lse), route in zip(got, ("parts", "uncut")):
             _check_out(out[h], want, f"{path} {route} h{h}")
             assert np.abs(lse[h] - wlse).max() < 2e-3
+
+
+@pytest.mark.parametrize("S,Hq", [(8449, 9), (8193, 17)])
+def test_launch_order_by_tile_and_by_head(S, Hq):
+    """Launches of up to 32 query tiles per head go by tile, longer ones by head: 33 or 34 tiles
+    of heads that do not divide over the eight XCDs, at once and in three launches."""
+    import paper_2406_15486_amd as sa
+    _say(f"launch order S={S} Hq={Hq}")
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, h, S, 128, generator=g, device="cuda").bfloat16() for h in (Hq, 1, 1))
+    col, slash = sa.sa_sample_scores(q, k, 64)
+    lists = sa.sa_select_strips(col, slash, 0.3, 0.2, sa.Shape(1, Hq, 1, S))
+    want = sa.sa_sparse_attn(q, k, v, *lists, 16, want_lse=True, want_tiles=True)
+    got = sa.sa_sparse_attn_partitioned(q, k, v, *lists, 16, Hq, 3, want_lse=True, want_tiles=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(want[1]).all()
+    for a, b in zip(want, got):
+        assert torch.equal(a, b)
