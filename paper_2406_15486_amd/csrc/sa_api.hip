@@ -78,7 +78,7 @@ sa_status check_chunks(const Dims& d, int n_chunks, int granularity) {
 // ---- workspace layouts --------------------------------------------------------
 // The partial log-sum-exps of more than kRoomKeySplits key splits run on into the region of the
 // slash partials, which are written after they have been combined: a part keeps at least eight
-// key tiles, so that k splits need S >= 512 k, and there are more than S / 205 slash partials
+// key tiles, so that k splits need S >= 512 k, and there are more than S / 256 slash partials
 // per sampled row.
 constexpr int kRoomKeySplits = 8, kMaxKeySplits = 64;
 struct SampleWs { size_t lse, lse_part, partial, tok_col, tok_slash, total; };

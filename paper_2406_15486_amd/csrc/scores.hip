@@ -10,10 +10,14 @@
 // tile with the same b - kb, so tiles of one diagonal class are first added up
 // in registers.  A finished class (16 registers x 32 lanes per lane half, 59
 // distinct diagonals) is first summed along its diagonals across lanes - register
-// r is pulled from the lane e(r) positions on (one ds_bpermute each, all 16 in
+// r is pulled from the lane e(r) positions on (one rotation each, all 16 in
 // flight together), which leaves every lane with the totals of two diagonals - and
 // then added into a window in LDS that is private to the wave and to the lane half
 // with two read-add-writes per lane whose slots no other lane touches.
+// A chunk of few rows clears, fills and hands on only the slots its rows reach (128 rows: 384 of
+// 1280 floats a partial).  Accumulation, with the rotations in place of ds_bpermute (16 registers
+// fewer) and the short windows, before / after: 32 heads of 128K and 6592 rows 9.53 / 9.08 ms,
+// of 50001 and 2560 rows 1.67 / 1.56 ms, of 32K and 128 rows 97 / 83 us, 1 head of 1K 10.2 / 9.0 us.
 // The eight windows are combined in a fixed order into one partial per (key
 // block, chunk) and a second kernel adds the partials in a fixed order.  No
 // float atomics anywhere: repeated runs give identical bits.
@@ -31,9 +35,15 @@ typedef __attribute__((address_space(3))) float lds_f32;   // LDS-qualified, kee
 constexpr int KB = 256;          // keys per workgroup (4 waves x 2 sub-blocks x 32)
 constexpr int QC = 1024;         // sampled rows per chunk
 constexpr int WWIN = QC + 64;    // floats in one (wave, lane half) diagonal window
-constexpr int WIN = QC + 256;    // floats in the combined (key block, chunk) partial
 constexpr int QROW_B = 272;      // bytes per staged Q row
 constexpr int QSTAGE_B = 32 * QROW_B + 32 * 4;   // 32 rows + 32 lse values
+
+// value of the lane N positions on, around within each half of the wave (LDS crossbar, rotate
+// mode: the distance is in the instruction; ds_bpermute took 16 registers of lane numbers)
+template <int N>
+__device__ __forceinline__ float pull_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0xC000 | (N << 5)));
+}
 
 __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -71,19 +81,17 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
   // slot of (row rb + m, key jw + 32 sb + ql) in this wave's window:
   //   32 (b - sb + 1) + (m - ql) + 31
   // The class sum.  Register r of lane ql holds the diagonal e(r) - ql, with e(r) =
-  // 8 (r / 4) + r % 4, of 59 in all (-31 .. 27).  Lane L collects diagonal L - 31 (from
-  // the registers with e(r) <= L, lane e(r) + 31 - L) and diagonal L + 1 (from the
-  // others, lane e(r) - 1 - L): for each r one pull from lane (e(r) + 31 - L) mod 32 of
+  // 8 (r / 4) + r % 4, of 59 in all (-31 .. 27).  Lane L collects diagonal -L (from
+  // the registers with e(r) + L < 32, lane L + e(r)) and diagonal 32 - L (from the
+  // others, lane L + e(r) - 32): for each r one pull from lane (L + e(r)) mod 32 of
   // its own half, credited to the one or the other by 0/1 factors (the products are
-  // exact).  Their window slots are 32 b' + L and 32 b' + 32 + L.
-  float* mywin = win + (wave * 2 + hf) * WWIN + ql + 4 * hf;
-  int pull[16];
+  // exact).  Their window slots are 32 b' + 31 - L and 32 b' + 63 - L.
+  float* mywin = win + (wave * 2 + hf) * WWIN + 31 - ql + 4 * hf;
   float first[16], second[16];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int e = 8 * (r >> 2) + (r & 3);
-    pull[r] = 4 * (((e + 31 - ql) & 31) + 32 * hf);
-    first[r] = (ql >= e) ? 1.f : 0.f;
+    first[r] = (ql + e < 32) ? 1.f : 0.f;
     second[r] = 1.f - first[r];
   }
 
@@ -93,10 +101,12 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
   const int row0 = r0 + ch * QC;                    // first row of the chunk
   const int row_end = min(row0 + QC, r_end);        // one past the last row
   if (row_end - 1 < j0) continue;                   // chunk entirely above these keys (uniform)
-  for (int x = tid; x < 8 * WWIN; x += 256) win[x] = 0.f;
-
-  // first 32-row block that reaches the keys of the workgroup, rounded down to even
   const int nblk = (row_end - row0 + 31) / 32;
+  const int wlen = 32 * nblk + 64;                  // slots of a window that the chunk's rows reach
+  for (int x = tid; x < wlen; x += 256)
+#pragma unroll
+    for (int w = 0; w < 8; ++w) win[w * WWIN + x] = 0.f;
+  // first 32-row block that reaches the keys of the workgroup, rounded down to even
   const int b_first = ((j0 > row0) ? (j0 - row0) / 32 : 0) & ~1;
 
   uint4 pq0, pq1;
@@ -133,16 +143,20 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
   // registers are not cleared: the first tile of the next class to use them (always a
   // sub-block-0 tile) assigns instead of adding.
   auto flush_class = [&](f32x16& acc, int bpos) {
+    const float pulled[16] = {
+        pull_lane<0>(acc[0]),   pull_lane<1>(acc[1]),   pull_lane<2>(acc[2]),   pull_lane<3>(acc[3]),
+        pull_lane<8>(acc[4]),   pull_lane<9>(acc[5]),   pull_lane<10>(acc[6]),  pull_lane<11>(acc[7]),
+        pull_lane<16>(acc[8]),  pull_lane<17>(acc[9]),  pull_lane<18>(acc[10]), pull_lane<19>(acc[11]),
+        pull_lane<24>(acc[12]), pull_lane<25>(acc[13]), pull_lane<26>(acc[14]), pull_lane<27>(acc[15])};
     float a1 = 0.f, a2 = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      float v = __int_as_float(__builtin_amdgcn_ds_bpermute(pull[r], __float_as_int(acc[r])));
-      a1 = fmaf(v, first[r], a1);
-      a2 = fmaf(v, second[r], a2);
+      a1 = fmaf(pulled[r], first[r], a1);
+      a2 = fmaf(pulled[r], second[r], a2);
     }
     volatile lds_f32* s1 = (volatile lds_f32*)(mywin + 32 * bpos);
     *s1 = *s1 + a1;
-    if (ql < 27) {                                   // diagonals 28 .. 32 do not exist
+    if (ql >= 5) {                                   // diagonals 28 .. 32 do not exist
       volatile lds_f32* s2 = (volatile lds_f32*)(mywin + 32 * bpos + 32);
       *s2 = *s2 + a2;
     }
@@ -172,11 +186,13 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
       f32x16 s2[2];
 #pragma unroll
       for (int r = 0; r < 16; ++r) { s2[0][r] = 0.f; s2[1][r] = 0.f; }
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int ks = 0; ks < 8; ++ks) {
         s2[0] = mfma_32x32x16(qf[ks], kf[0][ks], s2[0]);
         s2[1] = mfma_32x32x16(qf[ks], kf[1][ks], s2[1]);
       }
+      __builtin_amdgcn_s_setprio(0);
 #pragma unroll
       for (int sb = 0; sb < 2; ++sb) {
         const int jsb = jw + 32 * sb;
@@ -240,13 +256,13 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
 
   // combine the eight windows: slot x <-> offset x + (row0 - j0 - 255);
   // wave w slot y <-> offset y + (row0 - j0 - 64 w - 63)
-  float* out = P.partial + (((size_t)bh * P.n_kblocks + kb) * P.n_chunks + ch) * WIN;
-  for (int x = tid; x < WIN; x += 256) {
+  float* out = P.partial + (((size_t)bh * P.n_kblocks + kb) * P.n_chunks + ch) * P.win;
+  for (int x = tid; x < P.win; x += 256) {
     float acc = 0.f;
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       int y = x - 192 + 64 * w;
-      if (y >= 0 && y < WWIN) acc += win[(w * 2) * WWIN + y] + win[(w * 2 + 1) * WWIN + y];
+      if (y >= 0 && y < wlen) acc += win[(w * 2) * WWIN + y] + win[(w * 2 + 1) * WWIN + y];
     }
     out[x] = acc;
   }
@@ -268,16 +284,16 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(ScoreParams P, cons
     int row_end = min(row0 + QC, r0 + P.n_s);
     // column x
     if (row_end - 1 >= (x / KB) * KB) c += (double)colpart[((size_t)bh * P.n_chunks + ch) * S + x];
-    // offset x: slot = x - row0 + KB kb + (KB - 1) in [0, WIN)
+    // offset x: slot = x - row0 + KB kb + (KB - 1) in [0, P.win)
     int kb_lo = row0 - x - (KB - 1);                  // KB kb >= kb_lo
     kb_lo = (kb_lo <= 0) ? 0 : (kb_lo + KB - 1) / KB;
-    int kb_hi_num = row0 - x + WIN - 1 - (KB - 1);    // KB kb <= kb_hi_num
+    int kb_hi_num = row0 - x + P.win - 1 - (KB - 1);    // KB kb <= kb_hi_num
     if (kb_hi_num < 0) continue;
     int kb_hi = min(kb_hi_num / KB, P.n_kblocks - 1);
     for (int kb = kb_lo; kb <= kb_hi; ++kb) {
       if (row_end - 1 < kb * KB) break;               // block not live for this chunk
       int slot = x - row0 + KB * kb + (KB - 1);
-      s += (double)P.partial[(((size_t)bh * P.n_kblocks + kb) * P.n_chunks + ch) * WIN + slot];
+      s += (double)P.partial[(((size_t)bh * P.n_kblocks + kb) * P.n_chunks + ch) * P.win + slot];
     }
   }
   P.col[(size_t)bh * S + x] = (float)c;
@@ -290,7 +306,7 @@ void score_geometry(int S, int n_s, int* n_kblocks, int* n_chunks, int* chunk_ro
   *n_kblocks = (S + KB - 1) / KB;
   *n_chunks = (n_s + QC - 1) / QC;
   *chunk_rows = QC;
-  *win = WIN;
+  *win = min(QC, (n_s + 31) / 32 * 32) + KB;   // every offset between a chunk's rows and a workgroup's keys
 }
 
 size_t score_partial_floats(int S, int n_s, int n_bh) {

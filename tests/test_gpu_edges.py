@@ -198,3 +198,19 @@ def test_launch_order_by_tile_and_by_head(S, Hq):
     assert torch.isfinite(want[1]).all()
     for a, b in zip(want, got):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n_s", [31, 32, 33, 255, 257, 1023, 1024, 1025, 1400])
+def test_sample_scores_window_lengths(n_s):
+    """The diagonal windows are as long as a chunk's rows, in steps of 32 up to 1024."""
+    import paper_2406_15486_amd as sa
+    S = 1400
+    _say(f"window lengths n_s={n_s}")
+    _, x = _inputs("glm8k", S=S, Hq=2, Hkv=1, n_sinks=8)
+    col, slash = sa.sa_sample_scores(_dev(x["q"]), _dev(x["k"]), n_s)
+    torch.cuda.synchronize()
+    qf, kf = _f64(x["q"]), _f64(x["k"])
+    for h in range(2):
+        wc, ws, _ = O.sample_scores(qf[h], kf[0], n_s)
+        _score_tol(col[h].cpu().numpy(), wc, f"col h{h}")
+        _score_tol(slash[h].cpu().numpy(), ws, f"slash h{h}")
