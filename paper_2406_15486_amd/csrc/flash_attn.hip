@@ -404,6 +404,10 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
       act = (((uint32_t)d >> (24 + wave)) & 1u) && ((w0 & w1) != 0xFFFFFFFFu) && (j0 < S);
     } else {
       act = j0 <= iw0 + 31;                        // else every key of the tile lies after the wave's rows
+      // ... or the wave has no row.  (Half of the waves for 128 sampled rows: left to work on copies
+      // of the last row they took half the vector pipe; 32 heads, 128K keys 276 / 155 us, 32K
+      // 73 / 48 us; 32K with 1664 rows, whose last tile is half full, 478 / 458 us.)
+      if (MODE == 1) act = act && iw0 <= i_last_wg;
     }
     return __builtin_amdgcn_readfirstlane((int)act) != 0;
   };
@@ -764,6 +768,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
   // past the end of the schedule.
   const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
+                                 : (MODE == 1 && i_last_wg - i0 < BQ - 32) ? 0      // (waves without rows look at every tile)
                                  : max(min(a64 - t_base - 1, n_tiles - 4), 0);
   const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
   const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end

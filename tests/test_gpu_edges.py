@@ -200,7 +200,7 @@ def test_launch_order_by_tile_and_by_head(S, Hq):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("n_s", [31, 32, 33, 255, 257, 1023, 1024, 1025, 1400])
+@pytest.mark.parametrize("n_s", [31, 32, 33, 223, 224, 225, 255, 257, 1023, 1024, 1025, 1400])
 def test_sample_scores_window_lengths(n_s):
     """The diagonal windows are as long as a chunk's rows, in steps of 32 up to 1024."""
     import paper_2406_15486_amd as sa
