@@ -395,7 +395,10 @@ hipError_t launch_block_reduce(const float* in, float* out, int n_rows, int S, i
   return hipGetLastError();
 }
 
-// kernels with a sequence-sized LDS array: the limit is raised to what the launch asks for
+// Kernels with a sequence-sized LDS array.  The limit belongs to the kernel, for all threads of
+// the process, so it is the most that any launch asks for, never what this launch asks for.
+constexpr size_t kStripPrepLds = (size_t)kBitSegWords * 4;
+constexpr size_t kBlockPrepLds = (size_t)((kMaxSeqLen / kFlashBK + 1) / 32 + 1) * 4;   // (blocks of 64 keys are the shortest)
 template <typename K>
 static hipError_t allow_lds(K kernel, size_t bytes) {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
@@ -403,7 +406,7 @@ static hipError_t allow_lds(K kernel, size_t bytes) {
 
 hipError_t launch_block_prep(const BlockPrepParams& P, hipStream_t st) {
   const size_t lds = (size_t)((P.nb + 1) / 32 + 1) * 4;
-  hipError_t e = allow_lds(&block_prep_kernel, lds);
+  hipError_t e = allow_lds(&block_prep_kernel, kBlockPrepLds);
   if (e != hipSuccess) return e;
   dim3 grid(1 + (P.idx_pad_stride + kBlockSpan - 1) / kBlockSpan, P.n_bh);
   hipLaunchKernelGGL(block_prep_kernel, grid, dim3(PT), lds, st, P);
@@ -427,7 +430,7 @@ hipError_t launch_gather_strips(const GatherParams& P, hipStream_t st) {
 hipError_t launch_mask_prep(const MaskPrepParams& P, hipStream_t st) {
   const int n_seg = (P.rb_words + kBitSegWords - 1) / kBitSegWords;   // (the column bitmap is the shorter one)
   const size_t lds = (size_t)(n_seg == 1 ? P.rb_words : kBitSegWords) * 4;
-  hipError_t e = allow_lds(&strip_prep_kernel, lds);
+  hipError_t e = allow_lds(&strip_prep_kernel, kStripPrepLds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(strip_prep_kernel, dim3(2 * n_seg, P.n_bh), dim3(PT), lds, st, P, n_seg);
   if (n_seg > 1) {

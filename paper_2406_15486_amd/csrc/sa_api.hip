@@ -32,7 +32,7 @@ sa_status check_shape(const sa_shape* s, Dims* d) {
   if (s->head_dim != sa::kHeadDim) return SA_ERR_UNSUPPORTED;
   if (s->causal != 1) return SA_ERR_UNSUPPORTED;
   if ((long long)s->batch * s->n_q_heads > 65535) return SA_ERR_UNSUPPORTED;
-  if (s->seq_len > (1 << 24)) return SA_ERR_UNSUPPORTED;   // kernels keep 32-bit byte offsets into V^T
+  if (s->seq_len > sa::kMaxSeqLen) return SA_ERR_UNSUPPORTED;
   d->S = s->seq_len;
   d->S_pad = (s->seq_len + sa::kFlashBQ - 1) / sa::kFlashBQ * sa::kFlashBQ;
   d->n_bh = s->batch * s->n_q_heads;

@@ -8,6 +8,7 @@ namespace sa {
 constexpr int kHeadDim = 128;  // the only supported head dimension
 constexpr int kFlashBQ = 256;  // query rows per workgroup of the flash kernels
 constexpr int kFlashBK = 64;   // keys per tile
+constexpr int kMaxSeqLen = 1 << 24;   // kernels keep 32-bit byte offsets into V^T
 constexpr int kSweepBit = 1 << 23;   // in every entry of a tile-diagonal list: the head is swept
 
 struct FlashParams {
