@@ -126,12 +126,14 @@ int32_t sa_rows_from_ratio(int32_t seq_len, float ratio);
  * rows of segment m (rows [(m+1)*itv - n_sample_rows, (m+1)*itv); the last
  * segment ends at seq_len), exactly as above (causal: those rows see keys up to
  * their own position); row_lse must then be NULL.
- * The sums are formed in a fixed order: repeated calls give identical bits.
+ * The sums are formed in a fixed order that follows from seq_len, n_sample_rows
+ * and n_chunks alone: repeated calls give identical bits, and so do calls on
+ * another batch or other heads beside a head's own.
  * Workspace: with sa_workspace_bytes(SA_OP_SAMPLE_SCORES, ..) all heads are
  * processed at once.  Any smaller size down to SA_OP_SAMPLE_SCORES_MIN is
  * accepted as well: the heads are then taken as many at a time as fit (whole
  * KV heads, or an equal part of one KV head's query heads), pass after pass,
- * with the same result - which bounds the workspace for long sequences (it
+ * with the same result, bit for bit - which bounds the workspace for long sequences (it
  * grows with seq_len * n_sample_rows per head, Sec. 5.4).
  */
 sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,

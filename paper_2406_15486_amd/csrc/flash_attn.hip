@@ -213,12 +213,20 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     vct = P.vct + (size_t)bh * kHeadDim * P.S_pad;
   }
   int t_base = 0;                        // first key tile of this workgroup's share of the causal sweep
-  int n_sweep = min(i_last_wg, S - 1) / BK + 1;
-  if (MODE == 1 && P.k_splits > 1) {
-    t_base = (int)((long long)n_sweep * split / P.k_splits);
-    n_sweep = (int)((long long)n_sweep * (split + 1) / P.k_splits) - t_base;
-  }
+  const int n_sweep = min(i_last_wg, S - 1) / BK + 1;
   int n_sched = (MODE == 2 && !SWEEP) ? (n_col_tiles + n_rng) : n_sweep;
+  // Log-sum-exp sweep: the keys of the query tile are cut into lse_parts equal parts, each summed
+  // from nothing, and this workgroup takes the parts [part, part_stop) one after the other.
+  int part = 0, part_stop = 1;
+  if (MODE == 1) {
+    part = P.lse_parts / P.k_splits * split;
+    part_stop = part + P.lse_parts / P.k_splits;
+    t_base = n_sweep * part / P.lse_parts;
+    n_sched = n_sweep * part_stop / P.lse_parts - t_base;
+  }
+  // tile that ends part `part` (counted from t_base); the workgroup's last part ends with the schedule
+  auto end_of_part = [&]() { return part + 1 < part_stop ? n_sweep * (part + 1) / P.lse_parts - t_base - 1 : -1; };
+  int part_last = MODE == 1 ? __builtin_amdgcn_readfirstlane(end_of_part()) : -1;
   if (PARTS) {
     t_base = n_sched * split / n_parts;
     n_sched = n_sched * (split + 1) / n_parts - t_base;
@@ -496,6 +504,13 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     }
   };
 
+  // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
+  // so only makes the vmcnt waits of the loop wait for more than they must.
+  auto store_part_lse = [&]() __attribute__((always_inline)) {
+    const float l_tot = half_sum(l_run);
+    if (row_ok && hf == 0) P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)] = m_run * kLn2 + __logf(l_tot);
+  };
+
   // ---- the softmax phase: mask, online softmax (one query per lane), bf16 --------
   auto step_softmax = [&](auto kc, int t, int d) __attribute__((always_inline)) {
     const int j0 = first_key(kc, t, d);
@@ -629,6 +644,14 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
       exponentials(std::false_type{});
     }
     l_run += rs;
+    // (a part ends well before the diagonal: every wave that has rows works on its last tile)
+    if (MODE == 1 && t == part_last) {
+      store_part_lse();
+      ++part;
+      part_last = __builtin_amdgcn_readfirstlane(end_of_part());
+      m_run = kNegBig;
+      l_run = 0.f;
+    }
   };
 
   // ---- the two-phase pipeline --------------------------------------------------------
@@ -823,6 +846,10 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
 
   // ---- epilogue -------------------------------------------------------------
+  if (MODE == 1) {
+    store_part_lse();
+    return;
+  }
   float l_tot = half_sum(l_run);
   if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
   if (!row_ok) return;
@@ -839,10 +866,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
             make_float4(o[mb][4 * g], o[mb][4 * g + 1], o[mb][4 * g + 2], o[mb][4 * g + 3]);
     return;
   }
-  if (P.lse != nullptr && hf == 0) {
-    size_t at = (MODE == 1) ? (((size_t)split * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)) : ((size_t)bh * S + i_me);
-    P.lse[at] = m_run * kLn2 + __logf(l_tot);
-  }
+  if (P.lse != nullptr && hf == 0) P.lse[(size_t)bh * S + i_me] = m_run * kLn2 + __logf(l_tot);
   if (WITH_V) {
     float inv = 1.0f / l_tot;
     size_t rowoff = ((size_t)bh * S + i_me) * kHeadDim;
@@ -867,8 +891,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
 template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS>
 __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
   // ---- which (head, query tile) this workgroup owns ------------------------
-  // (the log-sum-exp sweep may also cut the keys of a query tile into k_splits
-  // equal parts, one workgroup each, to even out the last round of the launch)
+  // (the log-sum-exp sweep may also give the keys of a query tile to k_splits workgroups)
   int bh, a, split = 0, n_parts = 1;
   {
     const int bid = blockIdx.x;
@@ -963,7 +986,7 @@ __global__ __launch_bounds__(256) void parts_combine_kernel(FlashParams P) {
   if (P.lse != nullptr && c4 == 0) P.lse[(size_t)bh * P.S + i] = m * kLn2 + __logf(l);
 }
 
-// out[i] = log sum_s exp(part[s][i]): the key splits of the log-sum-exp sweep, in fixed order
+// out[i] = log sum_s exp(part[s][i]): the key parts of the log-sum-exp sweep, in fixed order
 __global__ void lse_combine_kernel(const float* part, float* out, size_t n, int k) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -980,28 +1003,40 @@ hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hi
   return hipGetLastError();
 }
 
-// How many workgroups share the keys of a query tile of the log-sum-exp launch (a power of
-// two, at most k_max).  Two things ask for a split: W workgroups fill the 512 slots (256 CUs x
-// 2) unevenly, and a chunk of 128 sampled rows gives one workgroup per head, a serial chain
-// over every key on a chip that is nearly idle.  A part costs its tiles and kPartTiles tiles'
-// worth of start, end and combination; a workgroup that has a CU to itself runs its tiles in
-// 0.6 of the time.  A part keeps kMinPartTiles tiles, more than the four that a query tile
-// spans, so that every row sees a key in every part.
+// The log-sum-exp launch cuts the keys of a query tile into equal parts, which are summed apart
+// and combined in fixed order, and gives them to workgroups, some neighbouring ones to each.
+// How many workgroups: W of them fill the 512 slots (256 CUs x 2) unevenly, and 128 sampled rows
+// are one query tile per head, a serial chain over every key on a chip that is nearly idle.  A
+// workgroup costs its tiles and kStartTiles tiles' worth of start and end; one that has a CU to
+// itself runs its tiles in 0.6 of the time.
+// How many parts: what a call of kFewHeads heads would take as workgroups, whatever the heads of
+// this call or pass, so that a row's bits follow from its sequence alone.  (With the parts left
+// to the workgroups a row's last bits, and with them strips at the selection's cut, followed the
+// batch and the room in the workspace.)  A part keeps kMinPartTiles tiles, more than the five that
+// a query tile can span, so that every row sees a key in every part.
 // Parts of at least 64 tiles / of at least eight, whole path: three segments of two sequences of
-// 5003 tokens 523 / 422 us, blocks at 32K 2535 / 2450 us, 8K 770 / 690 us.
-constexpr int kPartTiles = 6, kMinPartTiles = 8;
-int lse_key_splits(int row_first, int n_s, int n_bh, int k_max) {
-  const int n_qtiles = (n_s + kFlashBQ - 1) / kFlashBQ;
+// 5003 tokens 523 / 422 us, blocks at 32K 2535 / 2450 us, 8K 770 / 690 us.  The sweep alone, parts
+// left to the workgroups / from the sequence: 32 heads of 128K and 6592 rows 6412 / 6387 us, of
+// 50001 and 2560 rows 969 / 984, of 32K and 1664 rows 489 / 487, of 32K and 128 rows 51 / 59; 4 heads
+// of 32K and 1664 rows 72 / 70.
+constexpr int kStartTiles = 6, kMinPartTiles = 8, kFewHeads = 4;
+static int lse_workgroups(int n_qtiles, int n_bh, int min_tiles, int k_max) {
   const long long W = (long long)n_qtiles * n_bh;
-  const int min_tiles = row_first / kFlashBK;       // key tiles the first sampled row sees, at least
   auto cost = [&](int k) {
     const long long n = W * k;
-    return (n <= 256 ? 0.6 : (double)((n + 511) / 512)) * ((double)min_tiles / k + kPartTiles);
+    return (n <= 256 ? 0.6 : (double)((n + 511) / 512)) * ((double)min_tiles / k + kStartTiles);
   };
   int best = 1;
   for (int k = 2; k <= k_max && min_tiles / k >= kMinPartTiles; k *= 2)
     if (cost(k) < cost(best)) best = k;
   return best;
+}
+
+void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int* workgroups) {
+  const int n_qtiles = (n_s + kFlashBQ - 1) / kFlashBQ;
+  const int min_tiles = row_first / kFlashBK;       // key tiles the first sampled row sees, at least
+  *parts = lse_workgroups(n_qtiles, kFewHeads, min_tiles, max_parts);
+  *workgroups = lse_workgroups(n_qtiles, n_bh, min_tiles, *parts);
 }
 
 // Parts of the schedules of a dense or strip-masked launch over the query tiles [q0, q1).  A

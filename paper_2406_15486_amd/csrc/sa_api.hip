@@ -76,17 +76,17 @@ sa_status check_chunks(const Dims& d, int n_chunks, int granularity) {
 }
 
 // ---- workspace layouts --------------------------------------------------------
-// The partial log-sum-exps of more than kRoomKeySplits key splits run on into the region of the
-// slash partials, which are written after they have been combined: a part keeps at least eight
-// key tiles, so that k splits need S >= 512 k, and there are more than S / 256 slash partials
+// The log-sum-exps of more than kRoomKeyParts key parts run on into the region of the slash
+// partials, which are written after they have been combined: a part keeps at least eight
+// key tiles, so that k parts need S >= 512 k, and there are more than S / 256 slash partials
 // per sampled row.
-constexpr int kRoomKeySplits = 8, kMaxKeySplits = 64;
+constexpr int kRoomKeyParts = 8, kMaxKeyParts = 64;
 struct SampleWs { size_t lse, lse_part, partial, tok_col, tok_slash, total; };
 SampleWs sample_ws(const Dims& d, int n_s, int granularity) {
   SampleWs w;
   size_t at = 0;
   w.lse = at;      at += align_up((size_t)d.n_bh * n_s * sizeof(float));
-  w.lse_part = at; at += align_up((size_t)kRoomKeySplits * d.n_bh * n_s * sizeof(float));
+  w.lse_part = at; at += align_up((size_t)kRoomKeyParts * d.n_bh * n_s * sizeof(float));
   w.partial = at; at += align_up(sa::score_partial_floats(d.S, n_s, d.n_bh) * sizeof(float));
   w.tok_col = w.tok_slash = at;
   if (granularity > 1) {   // per-token scores, reduced to blocks afterwards
@@ -263,7 +263,7 @@ sa::FlashParams base_flash(const Dims& d, const void* q, const void* k) {
   P.scale_log2 = d.scale * 1.4426950408889634f;
   P.n_qtiles = (d.S + sa::kFlashBQ - 1) / sa::kFlashBQ;
   P.q_row0 = 0; P.n_qrows = d.S;
-  P.k_splits = 1;
+  P.lse_parts = P.k_splits = 1;
   return P;
 }
 
@@ -347,16 +347,16 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
 
       // pass 1: log-sum-exp of every sampled row (flash sweep without V)
       sa::FlashParams P = base_flash(pd, q_pass, k_pass);
-      P.k_splits = sa::lse_key_splits(row_first, n_s, pd.n_bh, kMaxKeySplits);
-      P.lse = P.k_splits > 1 ? reinterpret_cast<float*>(ws + w.lse_part) : lse;
+      sa::lse_splits(row_first, n_s, pd.n_bh, kMaxKeyParts, &P.lse_parts, &P.k_splits);
+      P.lse = P.lse_parts > 1 ? reinterpret_cast<float*>(ws + w.lse_part) : lse;
       P.q_row0 = row_first;
       P.n_qrows = n_s;
       P.n_qtiles = (n_s + sa::kFlashBQ - 1) / sa::kFlashBQ;
       {
         Scope sc(SA_K_ROW_LSE, st);
         s = dev(sa::launch_flash(1, false, P, st));
-        if (s == SA_OK && P.k_splits > 1)
-          s = dev(sa::launch_lse_combine(P.lse, lse, (size_t)pd.n_bh * n_s, P.k_splits, st));
+        if (s == SA_OK && P.lse_parts > 1)
+          s = dev(sa::launch_lse_combine(P.lse, lse, (size_t)pd.n_bh * n_s, P.lse_parts, st));
       }
       if (s != SA_OK) return s;
 

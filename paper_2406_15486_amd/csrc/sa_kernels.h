@@ -29,8 +29,9 @@ struct FlashParams {
                             // (kc, vct unused); col_idx_pad then holds runs of 64 consecutive keys per tile
   int row_lo;               // strip-masked mode: rows below it are neither computed for nor written
                             // (rows [row_lo, n_qrows) of the launch's query tiles are; q_row0 = 0 there)
-  int k_splits;             // mode 1: the keys of a query tile are cut into this many workgroups (>= 1);
-                            // lse is then [k_splits, n_bh, n_qrows] partial values (launch_lse_combine)
+  int lse_parts;            // mode 1: parts the keys of a query tile are cut into (a power of two); lse is
+                            // [lse_parts, n_bh, n_qrows] partial values, combined by launch_lse_combine
+  int k_splits;             // ... and the workgroups they are given to (a power of two, <= lse_parts)
   int part_m;               // modes 0 and 2: > 0: tile a's schedule is cut into ceil((a + 1) / part_m) workgroups
   float* part_o;            // ... whose sums [part, 256, 128] and then [part, 256, 2] lie here (flash_parts_bytes)
   float* part_ml;           // (set by the launch)
@@ -49,7 +50,9 @@ struct FlashParams {
 
 // mode 0: dense causal; 1: row log-sum-exp of rows [q_row0, q_row0+n_qrows); 2: strip mask
 hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_t st);
-int lse_key_splits(int row_first, int n_s, int n_bh, int k_max);
+// parts of the keys of a query tile (from the sequence alone, at most max_parts) and the workgroups
+// that share them (from the heads of the launch too)
+void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int* workgroups);
 // part_m of a launch over the query tiles [q0, q1) of n_bh heads (0: not cut), and the bytes of
 // the partial sums of n_heads of them
 constexpr int kMaxParts = 256;

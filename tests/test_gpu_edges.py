@@ -107,8 +107,8 @@ def test_swept_segments(S, C, blk):
 
 @pytest.mark.parametrize("S,n_s,Hq", [(1087, 64, 1), (1088, 64, 1), (1111, 65, 2), (4224, 128, 2), (4500, 300, 2), (32896, 128, 1)])
 def test_sample_scores_around_the_key_splits(S, n_s, Hq):
-    """Few sampled rows: the keys of a query tile are cut into parts of eight tiles or more
-    (S - n_s = 1024: the first split; 32768: the most of them)."""
+    """The keys of a query tile are cut into parts of eight tiles or more (S - n_s = 1024: the
+    first cut; 32768: the most of them)."""
     import paper_2406_15486_amd as sa
     _say(f"key splits S={S} n_s={n_s}")
     _, x = _inputs("glm8k", S=S, Hq=Hq, Hkv=1, n_sinks=8)
@@ -120,6 +120,35 @@ def test_sample_scores_around_the_key_splits(S, n_s, Hq):
         _score_tol(col[h].cpu().numpy(), wc, f"col h{h}")
         _score_tol(slash[h].cpu().numpy(), ws, f"slash h{h}")
         assert np.abs(lse[h].cpu().numpy() - wl).max() < 2e-3
+
+
+# many heads: fewer workgroups than parts (8300 x 448 x 64 heads: four for eight parts)
+@pytest.mark.parametrize("S,n_s,Hq,Hkv", [(1100, 65, 8, 2), (4224, 128, 8, 4), (8300, 448, 32, 2), (17000, 832, 8, 2),
+                                          (33000, 1664, 8, 2), (33000, 128, 16, 4)])
+def test_sample_scores_follow_from_the_sequence(S, n_s, Hq, Hkv):
+    """A head's scores and log-sum-exps are the same bits in a batch of two, alone with its
+    sequence, among half of the heads, and in passes over a small workspace."""
+    import paper_2406_15486_amd as sa
+    _say(f"scores by sequence S={S} n_s={n_s} Hq={Hq}")
+    xs = [_inputs("glm8k", S=S, Hq=Hq, Hkv=Hkv, seed=s, n_sinks=8)[1] for s in (31, 32)]
+    q, k = (torch.cat([_dev(x[t]) for x in xs]).contiguous() for t in "qk")
+    both = [t.view(2, Hq, -1) for t in sa.sa_sample_scores(q, k, n_s, want_lse=True)]
+    least = sa.sa_workspace_bytes(sa.binding.SA_OP_SAMPLE_SCORES_MIN, sa.Shape(2, Hq, Hkv, S), n_s)
+    for size in (least, 3 * least):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        for a, b in zip(both, sa.sa_sample_scores(q, k, n_s, workspace=ws, want_lse=True)):
+            assert torch.equal(a.view_as(b), b), f"workspace of {size} bytes"
+    for b in range(2):
+        for heads in (Hq, Hq // 2):
+            one = sa.sa_sample_scores(q[b:b + 1, :heads].contiguous(), k[b:b + 1, :heads * Hkv // Hq].contiguous(), n_s,
+                                      want_lse=True)
+            for x, y in zip(both, one):
+                assert torch.equal(x[b, :heads], y), f"sequence {b}, {heads} heads"
+    col, slash, lse = (t[1, Hq - 1].cpu().numpy() for t in both)
+    wc, ws, wl = O.sample_scores(_f64(xs[1]["q"])[Hq - 1], _f64(xs[1]["k"])[Hkv - 1], n_s)
+    _score_tol(col, wc, "col")
+    _score_tol(slash, ws, "slash")
+    assert np.abs(lse - wl).max() < 2e-3
 
 
 # (path, S, Hq, Hkv, segments or block size): from one tile to the most parts (256), ragged last
