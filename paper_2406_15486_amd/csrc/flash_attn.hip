@@ -1052,9 +1052,15 @@ void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int
 // Dense kernel, uncut / cut (parts): 1 head of 1024 tokens 29.5 / 20.9 us (10), of 4096
 // 81 / 33 (51), 4 of 2048 47 / 31 (80), of 8192 156 / 88 (240), 8 of 1500 37 / 31 (168), of 3001
 // 64 / 41 (240); left uncut: 16 of 3000 66.6 / 66.0 (256), 32 of 600 21.7 / 29.8 (192).
+// Up to two query tiles there are eight key tiles at most to share, and a second launch costs as much.
+// Uncut / cut, whole call: dense 1 head of 257 tokens 20.6 / 25.5 us, 4 of 384 20.8 / 23.8, 1 of
+// 512 25.0 / 24.0; strips 4 of 384 29.6 / 32.9; blocks of 128 4 of 384 28.4 / 29.6, of 512 31.0 / 30.0.
+// Three tiles: dense 8 of 640 25.2 / 26.2, 8 of 768 29.6 / 27.1, strips 4 of 640 35.5 / 34.6, blocks 1 of
+// 640 31.0 / 30.2, 8 of 768 36.0 / 33.5; blocks 4 of 1024 40.2 / 32.9, of 2047 59.2 / 40.6.
+constexpr int kMinCutTiles = 3;
 constexpr double kTileUs = 1.1, kCombineUs = 3.0, kPartUs = 0.065;
 int flash_parts(int n_bh, int q0, int q1) {
-  if ((long long)n_bh * (q1 - q0) > kMaxParts) return 0;
+  if (q1 < kMinCutTiles || (long long)n_bh * (q1 - q0) > kMaxParts) return 0;
   const double longest = 4.0 * q1, spread = n_bh * 2.0 * ((double)q1 * (q1 + 1) - (double)q0 * (q0 + 1)) / 256;
   const int base = (q1 + 5) / 6;
   for (int step : {2, 3, 4, 6, 8}) {

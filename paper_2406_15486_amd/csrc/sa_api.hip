@@ -168,7 +168,7 @@ sa_status check_partition(const sa_partition* p, const Dims& d, int* heads_per_p
 // Room for the partial sums of launches that are cut into parts (flash_parts), of all heads, the
 // largest of a call's segments.  It lies behind the rest of the workspace: a workspace that lacks it is
 // accepted, and the launches are then not cut.
-size_t parts_room(const Dims& d, int n_chunks, bool blocks = false);
+size_t parts_room(const Dims& d, int n_chunks);
 size_t dense_ws(const Dims& d) { return align_up((size_t)d.n_bkv * sa::kHeadDim * d.S_pad * 2); }
 
 // rows [*lo, *hi) of query segment m of chunk_n (Algorithm 1: itv = S_q / chunk_n; here
@@ -179,20 +179,14 @@ inline void segment_rows(int S, int n_chunks, int m, int* lo, int* hi) {
   *hi = (m + 1 < n_chunks) ? (m + 1) * itv : S;
 }
 
-// parts of the query tiles [q0, q1).  Block lists of less than 2048 tokens are not cut: their
-// workspace, no more than metadata, is to stay a fraction of the strips' (8 us of 80 are at stake).
-int call_parts(const Dims& d, bool blocks, int q0, int q1) {
-  return blocks && d.S < 2048 ? 0 : sa::flash_parts(d.n_bh, q0, q1);
-}
-
-size_t parts_room(const Dims& d, int n_chunks, bool blocks) {
+size_t parts_room(const Dims& d, int n_chunks) {
   size_t most = 0;
   if (d.n_bh > 256) return 0;
   for (int m = 0; m < n_chunks; ++m) {
     int lo, hi;
     segment_rows(d.S, n_chunks, m, &lo, &hi);
     const int q0 = lo / sa::kFlashBQ, q1 = (hi + sa::kFlashBQ - 1) / sa::kFlashBQ;
-    const size_t n = sa::flash_parts_bytes(call_parts(d, blocks, q0, q1), d.n_bh, q0, q1);
+    const size_t n = sa::flash_parts_bytes(sa::flash_parts(d.n_bh, q0, q1), d.n_bh, q0, q1);
     if (n > most) most = n;
   }
   return align_up(most);
@@ -200,8 +194,8 @@ size_t parts_room(const Dims& d, int n_chunks, bool blocks) {
 
 // cuts the launch P over the query tiles [q0, q1) of the whole call into parts if `room` bytes
 // at `at` hold their sums for n_heads heads
-void set_parts(sa::FlashParams* P, const Dims& d, bool blocks, int n_heads, int q0, int q1, void* at, size_t room) {
-  const int m = call_parts(d, blocks, q0, q1);
+void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int q0, int q1, void* at, size_t room) {
+  const int m = sa::flash_parts(d.n_bh, q0, q1);
   if (m == 0 || sa::flash_parts_bytes(m, n_heads, q0, q1) > room) return;
   P->part_m = m;
   P->part_o = static_cast<float*>(at);
@@ -291,7 +285,7 @@ size_t sa_workspace_bytes(int op, const sa_shape* shape, const sa_sampling* samp
     case SA_OP_DENSE_ATTN: return dense_ws(d) + parts_room(d, 1);
     case SA_OP_BLOCK_SPARSE_ATTN:
       if (sampling == nullptr || check_granularity(sampling->granularity) != SA_OK) return 0;
-      return block_ws(d, sampling->granularity, d.n_bh).total + parts_room(d, chunks, true);
+      return block_ws(d, sampling->granularity, d.n_bh).total + parts_room(d, chunks);
     default: return 0;
   }
 }
@@ -575,7 +569,7 @@ sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, i
   P.cidx_stride = d.S_pad; P.cb_words = w.cb_words; P.rb_words = w.rb_words;
   P.dlist_stride = w.dlist_stride; P.off_max = w.off_max;
   // (decided for all heads and all query tiles of the segment, whatever this launch takes of them)
-  set_parts(&P, d, blocks, nh, row_lo / sa::kFlashBQ, (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ, ws + parts_at, ws_bytes - parts_at);
+  set_parts(&P, d, nh, row_lo / sa::kFlashBQ, (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ, ws + parts_at, ws_bytes - parts_at);
   Scope sc(SA_K_SPARSE_FLASH, st);
   return dev(sa::launch_flash(2, out_dtype == SA_OUT_F32, P, st));
 }
@@ -727,7 +721,7 @@ sa_status sa_dense_attn(const sa_shape* shape, const void* q, const void* k, con
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
-  set_parts(&P, d, false, d.n_bh, 0, P.n_qtiles, static_cast<char*>(workspace) + dense_ws(d), workspace_bytes - dense_ws(d));
+  set_parts(&P, d, d.n_bh, 0, P.n_qtiles, static_cast<char*>(workspace) + dense_ws(d), workspace_bytes - dense_ws(d));
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }
@@ -754,7 +748,7 @@ sa_status sa_dense_attn_static(const sa_shape* shape, const void* q, const void*
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
-  set_parts(&P, d, false, d.n_bh, 0, P.n_qtiles, static_cast<char*>(ws) + SA_STATIC_SCRATCH_BYTES, sa::kMaxPartsBytes);
+  set_parts(&P, d, d.n_bh, 0, P.n_qtiles, static_cast<char*>(ws) + SA_STATIC_SCRATCH_BYTES, sa::kMaxPartsBytes);
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }

@@ -155,7 +155,8 @@ def test_sample_scores_follow_from_the_sequence(S, n_s, Hq, Hkv):
 # tiles and parts, a batch of segments
 @pytest.mark.parametrize("path,S,Hq,Hkv,n", [("dense", 513, 1, 1, 0), ("dense", 1100, 3, 1, 0), ("dense", 3001, 8, 2, 0),
                                              ("strips", 700, 1, 1, 1), ("strips", 2305, 4, 2, 1), ("strips", 2600, 2, 1, 3),
-                                             ("blocks", 2049, 2, 1, 128), ("blocks", 2500, 4, 2, 64)])
+                                             ("blocks", 577, 1, 1, 64), ("blocks", 1100, 4, 2, 256), ("blocks", 2049, 2, 1, 128),
+                                             ("blocks", 2500, 4, 2, 64)])
 def test_tiles_cut_into_parts(path, S, Hq, Hkv, n):
     """Small problems: a query tile's keys are cut into parts.  A workspace without room for the
     partial sums gives uncut tiles; both against the oracle."""

@@ -69,3 +69,22 @@ def test_lds_limits_do_not_depend_on_the_call(recorder):
     for kind, name, v in log:
         if kind == "launch" and v[4] > 0:
             assert v[4] <= max(limits[name]), name
+
+
+@pytest.mark.parametrize("S,Hq,cut", [(257, 1, False), (512, 1, False), (512, 4, False), (513, 1, True), (768, 8, True),
+                                      (1024, 4, True), (2047, 1, True), (2048, 1, True), (3001, 32, False)])
+def test_small_problems_are_cut_by_length_whatever_the_path(recorder, S, Hq, cut):
+    """Dense, strip and block launches share one rule; up to two query tiles are never cut (a
+    second launch costs more than it gives there), and the room is asked for only where they are."""
+    calls = f"""
+sh = shape({S}, {Hq})
+for path in (strips, blocks):
+    path({S}, {Hq})
+assert lib.sa_dense_attn(ref(sh), P, P, P, P, 0, None, P, room(B.SA_OP_DENSE_ATTN, sh), None) == 0
+assert lib.sa_dense_attn_static(ref(sh), P, P, P, P, 0, None, None) == 0
+pad = (({S} + 255) // 256) * 256
+assert (room(B.SA_OP_DENSE_ATTN, sh) > pad * 256) == {cut}
+"""
+    log = _run(recorder, calls)
+    combined = sum("parts_combine" in name for kind, name, v in log if kind == "launch")
+    assert combined == (4 if cut else 0)
