@@ -36,6 +36,21 @@
  *   they work on a machine without a GPU.  SA_ERR_DEVICE reports a failed
  *   launch (hipGetLastError).
  * - Two calls that share a workspace must not overlap in time.
+ * - Every sum is formed in a fixed order: the same call gives the same bits.
+ *   What else the order depends on:
+ *   scores and lists (sa_sample_scores, sa_block_scores, sa_select_*): the
+ *     sequence alone, not the batch, the other heads or the workspace.
+ *   attention (sa_sparse_attn, _chunked, _partitioned, sa_block_sparse_attn,
+ *     sa_dense_attn, sa_dense_attn_static): the sequence alone where the call's
+ *     batch * n_q_heads heads have more than 256 query tiles of 256 rows (in
+ *     every segment, for n_chunks > 1).  Calls with fewer are small for this
+ *     GPU: they may cut the keys of a query tile into parts, summed apart in
+ *     the workspace, and seq_len and batch * n_q_heads decide whether and how.
+ *     The same sequence in another batch, or beside other heads, then agrees
+ *     to the rounding of bf16 probabilities, not bit for bit.  So does a call
+ *     whose workspace is smaller than what sa_workspace_bytes (or
+ *     sa_partitioned_workspace_bytes) asks for but holds all but the partial
+ *     sums: it is accepted, and nothing is cut.
  */
 #ifndef SA_H
 #define SA_H
@@ -96,10 +111,11 @@ typedef enum {
   SA_OP_SAMPLE_SCORES_MIN = 5 /* the least sa_sample_scores works with */
 } sa_op;
 
-/* Bytes of device workspace `op` needs for this shape (sampling may be NULL
- * for ops that neither sample nor work on blocks; SA_OP_BLOCK_SPARSE_ATTN
- * reads sampling->granularity only).  Returns 0 for invalid arguments.
- * Host only. */
+/* Bytes of device workspace `op` needs for this shape.  SA_OP_SAMPLE_SCORES and
+ * SA_OP_SAMPLE_SCORES_MIN read all of sampling; SA_OP_BLOCK_SPARSE_ATTN reads
+ * granularity and n_chunks, SA_OP_SPARSE_ATTN n_chunks (sampling NULL, or an
+ * n_chunks that no call would accept: one segment); the others read nothing of
+ * it.  Returns 0 for invalid arguments.  Host only. */
 size_t sa_workspace_bytes(int op, const sa_shape* shape, const sa_sampling* sampling);
 
 /* 64 * ceil(ratio * seq_len / 64), clamped to [min(64, seq_len), seq_len]:
@@ -219,8 +235,9 @@ sa_status sa_block_sparse_attn(const sa_shape* shape, int32_t granularity,
  * segment m, [m*itv, (m+1)*itv) with itv = floor(seq_len / C), the last segment
  * running to seq_len: for those rows the mask is that of
  * sa_sparse_attn (granularity 1) or sa_block_sparse_attn with chunk m's lists.
- * Workspace: that of SA_OP_SPARSE_ATTN or SA_OP_BLOCK_SPARSE_ATTN.  `tiles`
- * counts over all segments.
+ * Workspace: that of SA_OP_SPARSE_ATTN or SA_OP_BLOCK_SPARSE_ATTN for the same
+ * sampling (the size for one segment is accepted too, but may not hold the
+ * partial sums of small problems).  `tiles` counts over all segments.
  */
 sa_status sa_select_chunked(const sa_shape* shape, const sa_sampling* sampling,
                             const float* col_scores, const float* slash_scores,
@@ -273,12 +290,8 @@ sa_status sa_sparse_attn(const sa_shape* shape, const void* q, const void* k, co
  * Values larger than the number of heads / query tiles are clamped; both must
  * be >= 1.  The result (out, out_lse, tiles) is bit-identical to
  * sa_sparse_attn's where both calls bring workspaces of the sizes that the
- * library asks for: every (head, query tile) is computed in the same order of
- * operations whatever the partition.  (Of a small problem, fewer query tiles
- * than CUs, a tile's keys are cut into parts by a rule on the shape, batch and
- * number of heads included; a workspace that lacks the room for the partial
- * sums is accepted, the tiles are then not cut.  The last bits of a result
- * differ between one cut and another.)
+ * library asks for: whether and how a query tile is cut into parts follows
+ * from the whole call's shape, whatever the partition.
  * Workspace: sa_partitioned_workspace_bytes(shape, partition) (0 for invalid
  * arguments; host only).
  */
@@ -308,7 +321,8 @@ sa_status sa_dense_attn(const sa_shape* shape, const void* q, const void* k, con
 /*
  * sa_dense_attn for callers that cannot allocate device memory or bring a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments, results and kernels as sa_dense_attn, but
+ * forbid hipMalloc.  Same arguments, kernels and results as sa_dense_attn (with
+ * a workspace of the size that sa_workspace_bytes asks for), but
  * the transposed copy of V lives in a device array that is part of the library
  * (SA_STATIC_SCRATCH_BYTES and, for the partial sums of small problems, 34 MB
  * more per GPU, held until the process ends) instead of a

@@ -1046,9 +1046,14 @@ void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int
 // Short parts fill the chip, but each leaves 132 KB of sums to be written and read: m follows
 // the length (the last tile in six parts) and grows only in coarse steps, until there are no
 // more parts than CUs; then the cut is made if the estimate says that it pays (a key tile takes
-// kTileUs, the combination kCombineUs and kPartUs a part).  All this depends on the shape alone,
-// so that a tile's result does not depend on how a call divides heads and queries over its
-// launches, and through the coarse steps rarely on the size of the batch.
+// kTileUs, the combination kCombineUs and kPartUs a part).  All this depends on the shape of the
+// call alone, so that a tile's result does not depend on how the call divides heads and queries over
+// its launches.  It does depend on the number of heads, batch included: of the 300 shapes of 1, 2, 4 .. 32
+// heads and up to 128 tiles at which a sequence or two of them are cut, 237 are cut differently
+// for one and two, and their results agree to rounding only.  One cut for every batch would have to
+// be made where the chip is full as well, and there the sums would cost more than the work (32
+// sequences of 8 heads and 3001 tokens, computed: 1 GB of them written and read at the rate of a
+// copy 0.45 ms, the key tiles at kTileUs on 256 CUs 0.35 ms).
 // Dense kernel, uncut / cut (parts): 1 head of 1024 tokens 29.5 / 20.9 us (10), of 4096
 // 81 / 33 (51), 4 of 2048 47 / 31 (80), of 8192 156 / 88 (240), 8 of 1500 37 / 31 (168), of 3001
 // 64 / 41 (240); left uncut: 16 of 3000 66.6 / 66.0 (256), 32 of 600 21.7 / 29.8 (192).

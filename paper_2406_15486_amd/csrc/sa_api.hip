@@ -579,8 +579,8 @@ sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, i
 // whole matrix.  Partition (Sec. 5.4, long sequences): the heads are taken
 // heads_per_pass at a time - the workspace holds the metadata and the gathered K / V
 // of one pass only - and the query tiles of a chunk in n_segments consecutive launches.
-// Every (head, query tile) is computed by one workgroup whatever the partition, so the
-// result does not depend on it.
+// Whether and how a query tile is cut into parts (set_parts) follows from all heads and all
+// query tiles of the segment, so the result does not depend on the partition.
 sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, const sa_partition* part,
                       const void* q, const void* k, const void* v,
                       const int32_t* col_idx_all, const int32_t* col_cnt_all,

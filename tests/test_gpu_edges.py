@@ -212,6 +212,39 @@ def test_tiles_cut_into_parts(path, S, Hq, Hkv, n):
             assert np.abs(lse[h] - wlse).max() < 2e-3
 
 
+@pytest.mark.parametrize("S,Hq,Hkv,same", [(300, 4, 2, True), (512, 1, 1, True), (1300, 4, 2, True), (2100, 32, 4, True),
+                                           (16400, 4, 1, True), (2305, 8, 2, False), (3001, 8, 2, False)])
+def test_attention_of_a_batch_element_and_of_the_sequence_alone(S, Hq, Hkv, same):
+    """Bit for bit where neither call cuts its tiles, or both cut them alike; else (a small problem
+    that the larger batch cuts in another way) to the rounding of the probabilities: each is
+    rounded to bf16 against another reference, 2^-9 of its value on either side, so the outputs
+    lie within 2^-8 max |v|.  Selected lists are the same bits in either case."""
+    import paper_2406_15486_amd as sa
+    _say(f"batch element S={S} Hq={Hq}")
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(2, h, S, 128, generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    n_s, w, f32 = min(128, S), 16, sa.SA_OUT_F32
+    def run(q, k, v):
+        sh = sa.Shape(q.shape[0], Hq, Hkv, S)
+        lists = sa.sa_select_strips(*sa.sa_sample_scores(q, k, n_s), 0.9, 0.3, sh)
+        blocks = sa.sa_select_blocks(*sa.sa_sample_scores(q, k, n_s, granularity=128), 0.6, 0.4, 128, sh)
+        return lists, (sa.sa_dense_attn(q, k, v, out_dtype=f32)[0], sa.sa_sparse_attn(q, k, v, *lists, w, out_dtype=f32)[0],
+                       sa.sa_block_sparse_attn(q, k, v, *blocks, w, 128, out_dtype=f32)[0])
+    lists, outs = run(q, k, v)
+    equal = True
+    for b in range(2):
+        lists1, outs1 = run(*(t[b:b + 1].contiguous() for t in (q, k, v)))
+        torch.cuda.synchronize()
+        for idx, cnt, idx1, cnt1 in zip(lists[::2], lists[1::2], lists1[::2], lists1[1::2]):
+            assert torch.equal(cnt.view(2, Hq)[b], cnt1)
+            for h in range(Hq):
+                assert torch.equal(idx.view(2, Hq, S)[b, h, :int(cnt1[h])], idx1[h, :int(cnt1[h])])
+        for x, y in zip(outs, outs1):
+            equal = equal and torch.equal(x[b], y[0])
+            assert (x[b] - y[0]).abs().max().item() <= v.abs().max().item() / 256
+    assert equal == same
+
+
 @pytest.mark.parametrize("S,Hq", [(8449, 9), (8193, 17)])
 def test_launch_order_by_tile_and_by_head(S, Hq):
     """Launches of up to 32 query tiles per head go by tile, longer ones by head: 33 or 34 tiles
