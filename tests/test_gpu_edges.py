@@ -5,6 +5,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+import test_gpu_block as PB                       # noqa: E402
+import test_gpu_parity as P                       # noqa: E402
 from gpu_progress import say as _say              # noqa: E402
 from oracle import sample_attention as O           # noqa: E402
 from test_gpu_block import _block_case            # noqa: E402
@@ -151,6 +153,16 @@ def test_sample_scores_follow_from_the_sequence(S, n_s, Hq, Hkv):
     assert np.abs(lse - wl).max() < 2e-3
 
 
+def _bare(path, Hq, Hkv, S):
+    """Bytes of an attention workspace without room for partial sums."""
+    up = lambda b: (b + 255) // 256 * 256                                      # noqa: E731
+    S_pad = up(S)
+    if path == "dense":
+        return Hkv * 256 * S_pad
+    lists = sum(up(Hq * 4 * w) for w in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24, S_pad // 64 + 8, 1))
+    return Hkv * 256 * S_pad + lists + (up(Hq * 4) if path == "blocks" else Hq * 512 * S_pad)
+
+
 # (path, S, Hq, Hkv, segments or block size): from one tile to the most parts (256), ragged last
 # tiles and parts, a batch of segments
 @pytest.mark.parametrize("path,S,Hq,Hkv,n", [("dense", 513, 1, 1, 0), ("dense", 1100, 3, 1, 0), ("dense", 3001, 8, 2, 0),
@@ -179,16 +191,12 @@ def test_tiles_cut_into_parts(path, S, Hq, Hkv, n):
             ci[m, h, :len(Ic[m][h])] = torch.from_numpy(Ic[m][h].astype(np.int32))
             si[m, h, :len(Is[m][h])] = torch.from_numpy(Is[m][h].astype(np.int32))
     cc, sc = (torch.tensor([[len(a) for a in row] for row in lists], dtype=torch.int32) for lists in (Ic, Is))
-    S_pad = (S + 255) // 256 * 256
     if path == "dense":
         need = sa.sa_workspace_bytes(B.SA_OP_DENSE_ATTN, sh)
-        bare = Hkv * 256 * S_pad
     else:
         op = B.SA_OP_BLOCK_SPARSE_ATTN if path == "blocks" else B.SA_OP_SPARSE_ATTN
         need = sa.sa_workspace_bytes(op, sh, granularity=blk, n_chunks=C)
-        up = lambda b: (b + 255) // 256 * 256                                  # noqa: E731
-        bare = Hkv * 256 * S_pad + sum(up(Hq * 4 * w) for w in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24, S_pad // 64 + 8, 1))
-        bare += up(Hq * 4) if path == "blocks" else Hq * 512 * S_pad
+    bare = _bare(path, Hq, Hkv, S)
     assert bare < need
     got = []
     for size in (need, bare):
@@ -277,3 +285,67 @@ def test_sample_scores_window_lengths(n_s):
         wc, ws, _ = O.sample_scores(qf[h], kf[0], n_s)
         _score_tol(col[h].cpu().numpy(), wc, f"col h{h}")
         _score_tol(slash[h].cpu().numpy(), ws, f"slash h{h}")
+
+
+@pytest.mark.parametrize("test,args", [
+    (P.test_sparse_attn_random_strips, (1024, 1, 1, 64)), (P.test_sparse_attn_random_strips, (1500, 4, 2, 128)),
+    (P.test_sparse_attn_column_counts_around_the_loop_stretches, (0,)),
+    (P.test_sparse_attn_column_counts_around_the_loop_stretches, (2,)),
+    (P.test_sparse_attn_column_counts_around_the_loop_stretches, (40,)),
+    (P.test_sparse_attn_nearly_full_lists, (1500, 0.7, 0.6)), (P.test_sparse_attn_nearly_full_lists, (1024, 0.95, 0.9)),
+    (P.test_sparse_attn_nearly_full_lists, (2304, 0.5, 0.8)), (P.test_sparse_attn_degenerate_strip_sets, ()),
+    (PB.test_block_sparse_attn_random_blocks, (1500, 4, 2, 128, 128)),
+    (PB.test_block_sparse_attn_random_blocks, (1300, 2, 2, 1, 64)),
+    (PB.test_block_sparse_attn_random_blocks, (2000, 2, 1, 300, 256)), (PB.test_block_sparse_attn_degenerate_sets, ()),
+    (test_swept_heads_beside_two_pass_heads, (1279,)), (test_swept_heads_beside_two_pass_heads, (1281,)),
+    (test_swept_heads_block_lists, (1280, 64)), (test_swept_heads_block_lists, (1333, 128)),
+    (test_swept_heads_block_lists, (2100, 256)), (test_swept_segments, (1000, 3, 1)), (test_swept_segments, (1901, 5, 128)),
+    (P.test_large_logits_exercise_the_reference_maximum, ("rising",)),
+    (P.test_large_logits_exercise_the_reference_maximum, ("falling",)),
+    (P.test_large_logits_exercise_the_reference_maximum, ("spiky",))])
+def test_uncut_tiles(test, args, monkeypatch):
+    """Cases whose point is the tile loop of a whole query tile (where its stretches meet, the
+    reference maximum that rises from tile to tile) are small enough to be cut into parts: here
+    on workspaces without the room for that, as the long problems run them.  Every call is made
+    both ways; the log-sum-exps show that they are two routes."""
+    import paper_2406_15486_amd as sa
+    calls = []
+    for name in ("sa_sparse_attn", "sa_block_sparse_attn", "sa_sparse_attn_chunked", "sa_dense_attn"):
+        def both(q, k, v, *a, real=getattr(sa, name), name=name, **kw):
+            blocks = name == "sa_block_sparse_attn" or kw.get("granularity", 1) > 1
+            path = "dense" if name == "sa_dense_attn" else "blocks" if blocks else "strips"
+            kw["want_lse"] = True
+            ws = torch.full((_bare(path, q.shape[1], k.shape[1], q.shape[2]),), 0xFF, dtype=torch.uint8, device="cuda")
+            cut, uncut = real(q, k, v, *a, **kw), real(q, k, v, *a, workspace=ws, **kw)
+            calls.append(not torch.equal(cut[1], uncut[1]))
+            return uncut
+        monkeypatch.setattr(sa, name, both)
+    test(*args)
+    assert calls and all(calls)
+
+
+# empty lists leave a query tile the four key tiles that hold its window, for up to six parts
+@pytest.mark.parametrize("S,C", [(1281, 1), (1536, 1), (2600, 2), (3300, 3)])
+@pytest.mark.parametrize("n_col,n_off", [(0, 0), (1, 0), (0, 1), (65, 2)])
+def test_parts_without_tiles(S, C, n_col, n_off):
+    """More parts than key tiles in the schedule: the parts left over must add nothing (the
+    workspace holds NaN patterns), also in segments that start at a later query tile."""
+    import paper_2406_15486_amd as sa
+    _say(f"parts without tiles S={S} C={C} {n_col} columns {n_off} offsets")
+    _, x = _inputs("glm8k", S=S, Hq=1, Hkv=1, n_sinks=8)
+    rng = np.random.default_rng(S + n_col + n_off)
+    Ic, Is = ([np.sort(rng.choice(S, n, replace=False)) for _ in range(C)] for n in (n_col, n_off))
+    ci, si = (torch.zeros(C, 1, S, dtype=torch.int32) for _ in range(2))
+    for m in range(C):
+        ci[m, 0, :n_col] = torch.from_numpy(Ic[m].astype(np.int32))
+        si[m, 0, :n_off] = torch.from_numpy(Is[m].astype(np.int32))
+    cc, sc = (torch.full((C, 1), n, dtype=torch.int32) for n in (n_col, n_off))
+    need = sa.sa_workspace_bytes(sa.binding.SA_OP_SPARSE_ATTN, sa.Shape(1, 1, 1, S), n_chunks=C)
+    assert need > _bare("strips", 1, 1, S)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    lists = [t.cuda() for t in (ci, cc, si, sc)]
+    out, lse, _ = sa.sa_sparse_attn_chunked(*(_dev(x[t]) for t in "qkv"), *lists, 1, C, workspace=ws, want_lse=True)
+    torch.cuda.synchronize()
+    want, wlse = O.chunked_masked_attn(*(_f64(x[t])[0] for t in "qkv"), Ic, Is, 1, C)
+    _check_out(out[0, 0].float().cpu().numpy(), want, "parts without tiles")
+    assert np.abs(lse[0].cpu().numpy() - wlse).max() < 2e-3
