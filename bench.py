@@ -77,7 +77,8 @@ def mask_density(S: int, cols: np.ndarray, offs: np.ndarray, window: int) -> flo
 def schedule_slots(S: int, cols: np.ndarray, offs: np.ndarray, window: int) -> int:
     """Wave-tile slots the strip-masked kernel's schedule spends on one head: for every
     256-row query tile, 8 waves times (64-key tiles of gathered columns at or before its
-    last row + 64-key tiles whose 319 offsets against the tile's rows hold a kept one).
+    last row + 64-key tiles whose 319 offsets against the tile's rows hold a kept one), or,
+    where the kernel's list is so full that it sweeps the head, times all its causal key tiles.
     A slot is spent whether or not the wave has work on the tile (counting only)."""
     keep = np.zeros(S, dtype=bool)
     keep[np.asarray(offs, dtype=np.int64)] = True
@@ -92,6 +93,14 @@ def schedule_slots(S: int, cols: np.ndarray, offs: np.ndarray, window: int) -> i
     last_row = np.minimum(256 * np.arange(nq) + 255, S - 1)
     n_col = (np.searchsorted(np.asarray(cols, dtype=np.int64), last_row, side="right") + 63) // 64
     n_rng = n_rng_upto[np.minimum(4 * np.arange(nq) + 4, nd)]           # diagonals d <= 4 a + 3
+    # the rule of csrc/prep.hip: a gathered tile costs 132, a range tile 76 + 7 for every wave (32 rows,
+    # 95 offsets) that works on it, a swept tile 140; diagonal d is met by the query tiles a >= d // 4
+    w = np.arange(8)[:, None]
+    w_lo, w_hi = np.clip(64 * d - 255 + 32 * w, 0, S), np.clip(64 * d - 161 + 32 * w, -1, S - 1)
+    waves = ((c[w_hi + 1] - c[np.minimum(w_lo, w_hi + 1)] > 0) & (w_hi >= w_lo)).sum(0)
+    met = np.maximum(nq - d // 4, 0)
+    if 132 * n_col.sum() + ((76 + 7 * waves) * met)[waves > 0].sum() > 140 * met.sum():
+        return int(8 * np.minimum(4 * np.arange(nq) + 4, (S + 63) // 64).sum())
     return int(8 * (n_col.sum() + n_rng.sum()))
 
 

@@ -50,16 +50,19 @@ def test_block_mask_density_matches_brute_force(S, blk, w, seed):
     assert bench.block_mask_density(S, Ic, Is, w, blk) == pytest.approx(kept / (nb * (nb + 1) / 2.0), rel=1e-12)
 
 
-@pytest.mark.parametrize("S,seed", [(700, 1), (1024, 2), (2000, 3)])
-def test_schedule_slots_match_brute_force(S, seed):
+@pytest.mark.parametrize("S,seed,n_col,n_off,swept", [(700, 1, 150, 6, True), (1024, 2, 150, 6, False), (2000, 3, 150, 6, False),
+                                                      (700, 4, 650, 600, True), (1985, 5, 1700, 1900, True),
+                                                      (2000, 6, 2000, 0, True), (2000, 7, 0, 2000, False),
+                                                      (1500, 8, 700, 1400, True), (3000, 9, 1200, 40, True)])
+def test_schedule_slots_match_brute_force(S, seed, n_col, n_off, swept):
     rng = np.random.default_rng(seed)
-    cols = np.sort(rng.choice(S, 150, replace=False))
-    offs = np.sort(rng.choice(S, 6, replace=False))
+    cols = np.sort(rng.choice(S, n_col, replace=False))
+    offs = np.sort(rng.choice(S, n_off, replace=False))
     w = 5
     keep = np.zeros(S, dtype=bool)
     keep[offs] = True
     keep[:w] = True
-    slots = 0
+    slots = two_pass = sweep = sweep_slots = 0
     for a in range((S + 255) // 256):
         last = min(256 * a + 255, S - 1)
         n_col = -(-int((cols <= last).sum()) // 64)
@@ -67,5 +70,15 @@ def test_schedule_slots_match_brute_force(S, seed):
         for d in range(4 * a + 4):                      # key tile 4 a + 3 - d >= 0
             lo, hi = max(64 * d - 255, 0), min(64 * d + 63, S - 1)
             n_rng += bool(lo <= hi and keep[lo:hi + 1].any())
+            waves = 0                                   # of the tile's eight, 32 rows each: with a kept offset
+            for u in range(8):
+                o = np.arange(64 * d - 255 + 32 * u, 64 * d - 160 + 32 * u)
+                waves += bool(keep[o[(o >= 0) & (o < S)]].any())
+            two_pass += 76 + 7 * waves if waves else 0
+            sweep += 140
+        two_pass += 132 * n_col
         slots += 8 * (n_col + n_rng)
+        sweep_slots += 8 * (last // 64 + 1)
+    assert (two_pass > sweep) == swept
+    slots = sweep_slots if swept else slots
     assert bench.schedule_slots(S, cols, offs, w) == slots

@@ -153,6 +153,27 @@ def test_sample_scores_follow_from_the_sequence(S, n_s, Hq, Hkv):
     assert np.abs(lse - wl).max() < 2e-3
 
 
+def test_heads_are_swept_where_the_bench_says():
+    """bench.py counts the slots of a swept head or of the two passes by the kernel's own rule: the
+    tiles that the kernel reports are those of a sweep on exactly these heads."""
+    import bench
+    S, w = 2900, 5
+    _say(f"swept heads in the bench S={S}")
+    wl, x = _inputs("glm8k", S=S, Hq=8, Hkv=1, n_sinks=8)
+    rng = np.random.default_rng(1)
+    Ic = [_fill(rng, S, f) for f in (0.05, 0.3, 0.3, 0.6, 0.6, 0.9, 1.0, 0.0)]
+    Is = [_fill(rng, S, f) for f in (0.002, 0.001, 0.003, 0.0, 0.001, 0.005, 0.0, 1.0)]
+    tiles = _sparse_case(wl, x, Ic, Is, w, "bench rule")
+    last = np.minimum(256 * np.arange((S + 255) // 256) + 255, S - 1)
+    rows = 256 * np.arange(len(last))[:, None] + 32 * np.arange(8)[None, :] + 31
+    sweep_tiles, sweep_slots = int(np.minimum(last[:, None] // 64 + 1, rows // 64 + 1).sum()), int(8 * (last // 64 + 1).sum())
+    swept = [bench.schedule_slots(S, Ic[h], Is[h], w) == sweep_slots for h in range(8)]
+    assert any(swept) and not all(swept)
+    for h in range(8):
+        assert (int(tiles[h]) == sweep_tiles) == swept[h], h
+        assert tiles[h] <= bench.schedule_slots(S, Ic[h], Is[h], w)
+
+
 def _bare(path, Hq, Hkv, S):
     """Bytes of an attention workspace without room for partial sums."""
     up = lambda b: (b + 255) // 256 * 256                                      # noqa: E731
