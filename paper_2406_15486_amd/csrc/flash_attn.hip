@@ -986,13 +986,17 @@ __global__ __launch_bounds__(256) void parts_combine_kernel(FlashParams P) {
   if (P.lse != nullptr && c4 == 0) P.lse[(size_t)bh * P.S + i] = m * kLn2 + __logf(l);
 }
 
-// out[i] = log sum_s exp(part[s][i]): the key parts of the log-sum-exp sweep, in fixed order
+// out[i] = log sum_s exp(part[s][i]): the key parts of the log-sum-exp sweep, in fixed order.  A few
+// blocks with up to 64 loads a thread: bound by their latency unless several are in flight (32 parts
+// of 4096 rows one by one / eight at a time: sweep and combination 58.5 / 49.7 us).
 __global__ void lse_combine_kernel(const float* part, float* out, size_t n, int k) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   float m = part[i];
+#pragma unroll 8
   for (int s = 1; s < k; ++s) m = fmaxf(m, part[(size_t)s * n + i]);
   float z = 0.f;
+#pragma unroll 8
   for (int s = 0; s < k; ++s) z += __expf(part[(size_t)s * n + i] - m);
   out[i] = m + __logf(z);
 }
@@ -1016,9 +1020,9 @@ hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hi
 // a query tile can span, so that every row sees a key in every part.
 // Parts of at least 64 tiles / of at least eight, whole path: three segments of two sequences of
 // 5003 tokens 523 / 422 us, blocks at 32K 2535 / 2450 us, 8K 770 / 690 us.  The sweep alone, parts
-// left to the workgroups / from the sequence: 32 heads of 128K and 6592 rows 6412 / 6387 us, of
-// 50001 and 2560 rows 969 / 984, of 32K and 1664 rows 489 / 487, of 32K and 128 rows 51 / 59; 4 heads
-// of 32K and 1664 rows 72 / 70.
+// left to the workgroups / from the sequence: 32 heads of 128K and 6592 rows 6235 / 6233 us, of
+// 50001 and 2560 rows 949 / 952, of 32K and 1664 rows 486 / 476, of 32K and 128 rows 50 / 50, of 128K
+// and 128 rows 150 / 155.
 constexpr int kStartTiles = 6, kMinPartTiles = 8, kFewHeads = 4;
 static int lse_workgroups(int n_qtiles, int n_bh, int min_tiles, int k_max) {
   const long long W = (long long)n_qtiles * n_bh;
