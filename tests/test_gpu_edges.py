@@ -174,6 +174,23 @@ def test_heads_are_swept_where_the_bench_says():
         assert tiles[h] <= bench.schedule_slots(S, Ic[h], Is[h], w)
 
 
+@pytest.mark.parametrize("copies", [16, 32, 48])
+def test_sample_scores_of_many_heads(copies):
+    """So many heads that two workgroups, or one, go through all parts of a query tile: the bits of
+    one sequence alone, in every copy of it."""
+    import paper_2406_15486_amd as sa
+    S, n_s, Hq = 4224, 300, 8
+    _say(f"scores of many heads, {copies} copies")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q, k = (torch.randn(1, h, S, 128, generator=g, device="cuda").bfloat16() for h in (Hq, 2))
+    one = sa.sa_sample_scores(q, k, n_s, want_lse=True)
+    many = sa.sa_sample_scores(q.repeat(copies, 1, 1, 1), k.repeat(copies, 1, 1, 1), n_s, want_lse=True)
+    for a, b in zip(one, many):
+        assert torch.isfinite(a).all()
+        for x in b.view(copies, Hq, -1):
+            assert torch.equal(a, x)
+
+
 def _bare(path, Hq, Hkv, S):
     """Bytes of an attention workspace without room for partial sums."""
     up = lambda b: (b + 255) // 256 * 256                                      # noqa: E731
