@@ -13,6 +13,9 @@ FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     "-munsafe-fp-atomics",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # Wave-uniform branches stay branches: the structurizer otherwise turns the uniform if / else of the tile
+    # loops into flag chains, whose joins hold every array twice (360 to 570 bytes of spills per lane).
+    "-mllvm", "-structurizecfg-skip-uniform-regions=1",
     "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]
 

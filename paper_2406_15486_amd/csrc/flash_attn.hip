@@ -4,16 +4,24 @@
 //
 // A workgroup owns 256 query rows of one head; each of its 8 waves owns 32 of
 // them.  Keys are visited in tiles of 64, one K/V stream per workgroup.  For every
-// tile a wave forms S^T = K Q^T (keys x queries) with 32x32x16 bf16 MFMAs, so that
-// one lane holds scores of ONE query (lane % 32) for 16 keys per 32-key half
-// tile: the row-wise online softmax is then in-lane arithmetic plus a single
-// exchange between lanes l and l^32.  The probabilities, rounded to bf16, are
+// tile a wave forms S^T = K Q^T (keys x queries) with bf16 MFMAs, so that one lane
+// holds scores of one or two queries: the row-wise online softmax is then in-lane
+// arithmetic plus a rare exchange between lanes.  The probabilities, rounded to bf16, are
 // directly the B operand of O^T += V^T P^T, so the accumulators (O^T, head_dim x
-// queries) again keep one query per lane and the rescale is a per-lane scalar.
+// queries) again keep their queries per lane and the rescale is a per-lane scalar.
 // K tiles live in LDS as [key][d]; V is read from a pre-transposed copy
-// (V^T, [d][key]) so both MFMA A operands are 16-byte LDS reads.
+// (V^T, [d][key]) so both MFMA A operands are 16-byte LDS reads.  Four stages of each are
+// resident in LDS, filled by direct global->LDS loads two and three tiles ahead.
 //
-// Schedule.  The waves form two groups of four (rows 0..127 and 128..255); waves
+// What bounds it.  Long launches run at the card's power limit: the clock falls to 1.5 to 2 GHz,
+// and taking instructions or waits out of the loop returns little unless it saves energy.
+// Launches whose waves often have no work run at 2.3 GHz and are bound by one wave's chain of
+// instructions from barrier to barrier.  Hence two cores (parameter CORE of flash_body):
+//
+// Core 0, 16x16x32 MFMAs (two groups of 16 queries per wave, one LDS operand for both): the same
+// products as 32x32x16 at 14 % less energy (an MFMA loop 2038 against 1752 TFLOP/s, with an LDS
+// operand each 1790 against 1565), but a vector port that is blocked ~9 cycles by twice as many
+// MFMAs.  The waves form two groups of four (rows 0..127 and 128..255); waves
 // w and w+4 share a SIMD.  Left alone, two waves that alternate an MFMA section
 // and a vector-ALU (softmax) section fall into step - both on the matrix pipe,
 // then both on the vector pipe - and each pipe idles half the time.  Here the
@@ -21,9 +29,16 @@
 // P V(t-1) and K Q^T(t) and then the softmax of tile t, group 1 the softmax of
 // tile t-1 and then the same MFMAs - and one workgroup barrier per tile re-aligns
 // them, so every SIMD always has one wave feeding the matrix pipe and one feeding
-// the vector pipe.  Both groups read the same K/V tiles; four stages of each are
-// resident in LDS, filled by direct global->LDS loads two and three tiles ahead.
-// The log-sum-exp sweep stages no V and needs half the registers: two of its
+// the vector pipe.
+//
+// Core 1, 32x32x16 MFMAs (32 queries per wave): every wave issues the softmax of one 32-key half
+// between the MFMAs of the next, so that a tile is one chain of about half the length.
+//
+// Both against core 0 with 32x32x16 MFMAs as it was before, whole path or kernel: dense 16K 1948 / 1860 us
+// (core 0) and 1961 (core 1); 8K swept 672 / 620, 652; blocks of 128 at 32K 3261 / 3040, 3146; 64K head
+// patterns 35.2 / 34.1, 35.2 ms; 50001 tokens at alpha = 0.8 5383 / 5430, 5230 us; runs of four offsets
+// every 300 of 64K 20.6 / 20.4, 16.2 ms, every 1000 6.97 / 6.85, 5.47 ms.
+// The log-sum-exp sweep (core 0) stages no V and needs half the registers: two of its
 // workgroups share a CU.
 #include <type_traits>
 
@@ -39,7 +54,7 @@ constexpr int BK = kFlashBK;          // 64 keys per tile
 constexpr int NT = 512;               // two groups of four waves
 constexpr int NSTAGE = 4;             // K and V^T tiles resident in LDS
 constexpr int NAUX = 8;               // ring of aux-word slots
-constexpr int kDiagMask = 0x007FFFFF;  // a tile-diagonal list entry: diagonal in bits 0..22, kSweepBit, one bit per wave above
+constexpr int kDiagMask = 0x003FFFFF;  // a tile-diagonal list entry: diagonal in bits 0..21, kSparseBit, kSweepBit, one bit per wave above
 // LDS tiles are unpadded (the direct global->LDS loads write 1 KB runs); bank
 // conflicts are avoided by XOR-swizzling the 16-byte chunk index with the row.
 constexpr int KROW_B = 256;           // bytes per K row in LDS: 16 chunks, chunk c of row p stored at c ^ (p & 15)
@@ -71,11 +86,21 @@ enum TileKind : int { TK_PLAIN = 0, TK_CAUSAL = 1, TK_COLIDX = 2, TK_RANGE = 3 }
 // workgroup's first row, so every wave works on them and nothing is masked.  The loop
 // runs in stretches, so that the long ones carry no per-tile choice between the two kinds
 // of addressing, aux words and activity tests, and no stand-ins for tiles past the end.
-template <int KIND_, bool REAL_, bool INTERIOR_ = false>
+template <int KIND_, bool REAL_, bool INTERIOR_ = false, bool FIRST_ = false>
 struct Stretch {
   static constexpr int KIND = KIND_;
   static constexpr bool REAL = REAL_;
   static constexpr bool INTERIOR = INTERIOR_;
+  static constexpr bool FIRST = FIRST_;      // iteration 0: there is no tile before this one
+  using AtFirst = Stretch<KIND_, REAL_, INTERIOR_, true>;
+};
+// The MFMA operands of one iteration (see flash_body): V^T operands if V, K operands if K, in two
+// halves; where there are both they take turns.
+template <bool V, bool K>
+struct Steps {
+  static constexpr int HALF = 8 * (V + K);
+  static constexpr bool is_v(int i) { return V && (!K || (i & 1)); }
+  static constexpr int index(int i) { return V && K ? (i % HALF) / 2 : i & 7; }   // of the eight of its kind in a half
 };
 using AnyTiles = Stretch<0, false>;
 using PlainTiles = Stretch<0, true, true>;       // dense / log-sum-exp sweep below the diagonal
@@ -119,7 +144,13 @@ __device__ __forceinline__ void vm_wait() {
   static_assert(N >= 0 && N < 16, "vmcnt immediate");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
-// workgroup barrier; LDS reads issued before it have returned
+// workgroup barrier
+__device__ __forceinline__ void wg_meet() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// ... LDS reads issued before it have returned
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0), as the builtin: the compiler's own counters see it too
@@ -145,7 +176,7 @@ __host__ __device__ inline int parts_before(int m, int q0, int q1) { return part
 // body of its own it knows at compile time that interior tiles are active.
 // PARTS (dense and strip-masked modes): the workgroup takes part `split` of the `n_parts` equal
 // parts of its query tile's schedule and leaves unnormalised sums for parts_combine_kernel.
-template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP, bool PARTS>
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP, bool PARTS, int CORE>
 __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, const int a, const int split, const int n_parts) {
   static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
@@ -162,8 +193,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // 0..7, wave-uniform, kept in an SGPR
   const int grp = wave >> 2;           // phase group
   const int lane = tid & 63;
-  const int ql = lane & 31;   // query within the wave / row within a 32-row operand
-  const int hf = lane >> 5;   // which half of the contraction block this lane feeds
   const uint32_t smem_lds = __builtin_amdgcn_readfirstlane((int)(uintptr_t)(__attribute__((address_space(3))) char*)smem);
 
   const int bkv = ((MODE == 2 ? P.head0 : 0) + bh) / P.group;
@@ -171,8 +200,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   const int i0 = P.q_row0 + a * BQ;                     // first query row of the workgroup
   const int i_last_wg = min(i0 + BQ, P.q_row0 + P.n_qrows) - 1;  // last valid row
   const int iw0 = i0 + 32 * wave;                        // first query row of the wave
-  const int i_me = iw0 + ql;                             // this lane's query row
-  const bool row_ok = i_me <= i_last_wg && (MODE != 2 || i_me >= P.row_lo);
   const int a64 = i0 / BK;   // index of the 64-key tile that holds row i0 (i0 % 256 == 0 in MODE 2)
   const uint16_t* kbase = P.k + (size_t)bkv * S * kHeadDim;
   const uint16_t* vtbase = WITH_V ? P.vt + (size_t)bkv * kHeadDim * P.S_pad : nullptr;
@@ -283,30 +310,11 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   const uint64_t s_kc = scalar_ptr(kc), s_vct = scalar_ptr(vct), s_cidx = scalar_ptr(cidx);
   const uint64_t s_cbits = scalar_ptr(cbits), s_obits = scalar_ptr(obits);
 
-  // ---- Q^T operand: 8 contraction steps of 16, resident in registers -------
-  bf16x8 qf[8];
-  {
-    int qr = row_ok ? i_me : max(min(i_last_wg, S - 1), 0);
-    const uint16_t* qrow = P.q + ((size_t)bh * S + qr) * kHeadDim;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks)
-      qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 16 + hf * 8));
-  }
-
-  f32x16 o[4];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
-  float m_run = kNegBig;   // reference maximum, in log2 units (score * scale * log2 e)
-  float l_run = 0.f;       // running sum of exp2 for this lane's keys
-  const float c2 = P.scale_log2;
-
   // ---- staging ---------------------------------------------------------------------
   // One wave instruction writes a 1 KB run of LDS, lane l its bytes [16 l, 16 l + 16):
   // for K that is 4 physical rows, for V^T 8 rows.  Each lane therefore fetches the
-  // global chunk that belongs at its LDS position: the K row whose slot it is (bits 2
-  // and 3 of the row index exchanged, see krow_slot) and the chunk that the XOR
+  // global chunk that belongs at its LDS position: the K row whose slot it is (see krow_slot16)
+  // and the chunk that the XOR
   // swizzle maps there.  A tile is 16 runs of K and 16 of V^T; wave w issues runs w
   // and w + 8 of each.  The lane's byte offset inside a run is fixed for the whole
   // kernel, and run w + 8 lies a constant 32 K rows / 64 V^T rows after run w
@@ -316,7 +324,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   {
     int p = 4 * wave + (lane >> 4);                // physical K row of run `wave`
     int c = (lane & 15) ^ (p & 15);                // logical 16-byte chunk stored there
-    koff0 = krow_slot(p) * KROW_B + c * 16;        // key row within the tile, byte in the row
+    koff0 = (CORE == 0 ? krow_slot16(p) : krow_slot32(p)) * KROW_B + c * 16;   // key row within the tile, byte in the row
     int d = 8 * wave + (lane >> 3);                // V^T row
     int cv = (lane & 7) ^ ((d >> 1) & 7);
     voff0 = (uint32_t)d * (uint32_t)P.S_pad * 2u + cv * 16;
@@ -380,36 +388,42 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   };
 
   // Whether this wave has anything to do on tile t.
-  //  - gathered tile: its first key index (an aux word) must not lie after the wave's rows;
+  //  - gathered tile: its first key index (an aux word) must not lie after the wave's rows.
+  //    The word is read early (act_word) and looked at later (tile_active), so that the wait
+  //    for it hides behind MFMAs;
   //  - range tile: one of the 95 offsets between the wave's 32 rows and the tile's 64
   //    keys must be kept.  That depends on the tile diagonal and the wave only, not on
   //    the query tile, so the list entry carries it as a bit per wave (bits 24..31; a
   //    key after a row gives a negative offset, never kept).  Also not all 64 keys may
-  //    be selected columns (the column pass covered those: two aux words), and the
-  //    tile must start before the sequence end.
-  // The aux words are read early (act_words) and looked at later (tile_active), so
-  // that the wait for them hides behind MFMAs.
-  auto act_words = [&](auto kc, int t, uint32_t& w0, uint32_t& w1) __attribute__((always_inline)) {
-    if (MODE != 2 || decltype(kc)::INTERIOR || (SWEEP && !IN_PLACE)) return;
-    const uint32_t* ax = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
-    if (is_col(kc, t)) {
-      w0 = ax[0];
-    } else {
-      w0 = ax[16];
-      w1 = ax[17];
-    }
+  //    be selected columns (the column pass covered those), and the tile must start
+  //    before the sequence end: settle() clears the bits of such an entry.  (A sweep that needs
+  //    the entries keeps tiles of selected columns instead: there it sets them.)  The two words
+  //    of the column bitmap are fetched like the entries, as scalars and a tile later, so that
+  //    activity is scalar arithmetic: read from the aux words it cost a wait for every LDS read
+  //    in flight in the middle of the P V sweep.
+  constexpr bool kBits = MODE == 2 && (!SWEEP || IN_PLACE);      // range tiles have list entries
+  auto fetch_cols = [&](auto kc, int t, int d) __attribute__((always_inline)) -> uint64_t {
+    typedef const __attribute__((address_space(4))) uint64_t* const_u64_ptr;
+    if (!kBits || is_col(kc, t) || !is_real(kc, t)) return 0;
+    return *(const_u64_ptr)(uintptr_t)(s_cbits + (uint64_t)((uint32_t)(first_key(kc, t, d) >> 5) * 4u));
   };
-  auto tile_active = [&](auto kc, int t, int d, uint32_t w0, uint32_t w1) __attribute__((always_inline)) -> bool {
+  auto settle = [&](auto kc, int t, int d, uint64_t cols) __attribute__((always_inline)) -> int {
+    if (!kBits || is_col(kc, t)) return d;
+    if (SWEEP) return cols == ~0ull ? (int)((uint32_t)d | 0xFF000000u) : d;
+    return (cols == ~0ull || first_key(kc, t, d) >= S) ? (int)((uint32_t)d & 0x00FFFFFFu) : d;
+  };
+  auto act_word = [&](auto kc, int t, int& w0) __attribute__((always_inline)) {
+    if (MODE != 2 || SWEEP || decltype(kc)::INTERIOR || !is_col(kc, t)) return;
+    w0 = *reinterpret_cast<const int*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+  };
+  auto tile_active = [&](auto kc, int t, int d, int w0) __attribute__((always_inline)) -> bool {
     if (decltype(kc)::INTERIOR) return true;
     bool act;
     const int j0 = first_key(kc, t, d);
     if (is_col(kc, t)) {
-      act = (int)w0 <= iw0 + 31;
-    } else if (SWEEP && IN_PLACE) {
-      // the wave's block diagonal is kept, or the tile lies in a selected key block
-      act = ((((uint32_t)d >> (24 + wave)) & 1u) || (w0 & w1) == 0xFFFFFFFFu) && j0 <= iw0 + 31;
-    } else if (MODE == 2 && !SWEEP) {
-      act = (((uint32_t)d >> (24 + wave)) & 1u) && ((w0 & w1) != 0xFFFFFFFFu) && (j0 < S);
+      act = w0 <= iw0 + 31;
+    } else if (kBits) {
+      act = (((uint32_t)d >> (24 + wave)) & 1u) && (!SWEEP || j0 <= iw0 + 31);
     } else {
       act = j0 <= iw0 + 31;                        // else every key of the tile lies after the wave's rows
       // ... or the wave has no row.  (Half of the waves for 128 sampled rows: left to work on copies
@@ -420,472 +434,924 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     return __builtin_amdgcn_readfirstlane((int)act) != 0;
   };
 
-  // ---- operand ring and the MFMA phase -------------------------------------------
-  // A phase issues up to 32 MFMAs: 16 of P V(t-1) (keys in groups of 16, head-dim
-  // blocks 0..3 within a group) and 16 of K Q^T(t) (8 contraction steps for each
-  // of two 32-key halves).  Their A operands come from LDS through a ring of 8
-  // registers x 16 bytes: after MFMA i has consumed slot i % 8, the operand of MFMA
-  // i + 8 is read into it, so every read has 7 MFMAs (~250 cycles) to return and the
-  // matrix pipe does not wait on LDS round trips.  sched_barrier pins the order: the
-  // compiler would otherwise sink each read down to its use.
-  f32x16 s[2];
-  uint32_t pk[2][8];
-  uint4 R[8];
 #define SA_PIN() __builtin_amdgcn_sched_barrier(0)
-  // K operand i = 2 ks + sb: contraction step ks, 32-key half sb (the halves alternate
-  // so that consecutive MFMAs of the sweep accumulate into different registers)
-  auto ld_k = [&](int slot, int i, int buf) {
-    // row p = 32 sb + ql; logical chunk 2 ks + hf lives at physical chunk (2 ks + hf) ^ (p & 15)
-    const int sb = i & 1, ks = i >> 1;
-    const char* kp = smem + OFF_K + buf * KTILE_B + (32 * sb + ql) * KROW_B;
-    R[slot] = *reinterpret_cast<const uint4*>(kp + (((2 * ks + hf) ^ (ql & 15)) << 4));
-  };
-  // V^T operand i = 8 sb + 4 u + mb: keys 32 sb + 16 u .., head-dim block mb
-  auto ld_v = [&](int slot, int i, int buf) {
-    // row d = 32 mb + ql; logical chunk 4 sb + 2 u + hf lives at physical chunk (..) ^ ((d >> 1) & 7)
-    const int sb = i >> 3, u = (i >> 2) & 1, mb = i & 3;
-    const char* vp = smem + OFF_V + buf * VTILE_B + (32 * mb + ql) * VROW_B;
-    R[slot] = *reinterpret_cast<const uint4*>(vp + (((4 * sb + 2 * u + hf) ^ ((ql >> 1) & 7)) << 4));
-  };
-  // P V: on entry the ring holds V operands 0..7 (read during the softmax phase);
-  // the second half of the sweep re-fills it with the first 8 K operands of the next
-  // tile (read even when that tile turns out to need no work from this wave).  The
-  // loads of the tiles further ahead go out under the MFMAs, one per 3 MFMAs.
-  auto mm_pv = [&](int bufp, int bufq, auto&& setup_a, auto&& setup_v, auto&& setup_k, auto&& look, auto&& decide) {
+  if constexpr (CORE == 0) {
+    const int ql = lane & 15;   // query within a group of 16 / row within a 16-row operand
+    const int kg = lane >> 4;   // which quarter of the contraction block this lane feeds
+    const int i_me = iw0 + ql;                             // this lane's first query row; the second is 16 on
+    auto row_ok = [&](int n) { const int i = i_me + 16 * n; return i <= i_last_wg && (MODE != 2 || i >= P.row_lo); };
+    // ---- Q^T operand: two groups of 16 queries, 4 contraction steps of 32, resident in registers
+    bf16x8 qf[2][4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      // scalar bookkeeping in small pieces, so that no gap between two MFMAs grows long
-      if (!kLoadsInSoftmax) {
-        if (i == 1) setup_a();
-        if (i == 2) setup_v();
-        if (i == 4) load_v_one(0);
-        if (i == 5) setup_k();
-        if (i == 7) load_v_one(1);
-        if (i == 10) load_k_one(0);
-        if (i == 13) load_k_one(1);
-      }
-      if (i == 3) look();                          // read the words that say whether the next tile needs this wave
-      if (i == 9) decide();                        // ... and decide, under the MFMAs
-      const int sb = i >> 3, u = (i >> 2) & 1, mb = i & 3;
-      uint4 pw = {pk[sb][4 * u], pk[sb][4 * u + 1], pk[sb][4 * u + 2], pk[sb][4 * u + 3]};
-      o[mb] = mfma_32x32x16(as_bf16x8(R[i & 7]), as_bf16x8(pw), o[mb]);      // O^T += V^T P^T
-      SA_PIN();
-      if (i + 8 < 16) ld_v(i & 7, i + 8, bufp); else ld_k(i & 7, i - 8, bufq);
-      SA_PIN();
+    for (int n = 0; n < 2; ++n) {
+      int qr = row_ok(n) ? i_me + 16 * n : max(min(i_last_wg, S - 1), 0);
+      const uint16_t* qrow = P.q + ((size_t)bh * S + qr) * kHeadDim;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        qf[n][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 32 + kg * 8));
     }
-  };
-  // first 8 K operands of a tile into the ring (when no P V sweep did it)
-  auto warm_k = [&](int bufq) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ld_k(i, i, bufq);
-    SA_PIN();
-  };
-  // K Q^T: the ring holds K operands 0..7.  `with_loads`: no P V sweep went before,
-  // so this sweep issues the loads of the tiles further ahead.
-  // Element r of s[sb] is key j0 + 32*sb + 16*(r/8) + 8*hf + r%8 against query i_me.
-  auto mm_qk = [&](int bufq, bool with_loads) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (with_loads && !kLoadsInSoftmax) {
-        if (i == 2) load_v_one(0);
-        if (i == 5) load_v_one(1);
-        if (i == 8) load_k_one(0);
-        if (i == 11) load_k_one(1);
-      }
-      const int sb = i & 1, ks = i >> 1;
-      if (ks == 0) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[sb][r] = 0.f;
-      }
-      s[sb] = mfma_32x32x16(as_bf16x8(R[i & 7]), qf[ks], s[sb]);
-      SA_PIN();
-      if (i + 8 < 16) ld_k(i & 7, i + 8, bufq);
-      SA_PIN();
-    }
-  };
 
-  // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
-  // so only makes the vmcnt waits of the loop wait for more than they must.
-  auto store_part_lse = [&]() __attribute__((always_inline)) {
-    const float l_tot = half_sum(l_run);
-    if (row_ok && hf == 0) P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)] = m_run * kLn2 + __logf(l_tot);
-  };
-
-  // ---- the softmax phase: mask, online softmax (one query per lane), bf16 --------
-  auto step_softmax = [&](auto kc, int t, int d) __attribute__((always_inline)) {
-    const int j0 = first_key(kc, t, d);
-    constexpr bool INTERIOR = decltype(kc)::INTERIOR;
-    const int kind = is_col(kc, t) ? TK_COLIDX : (MODE == 2 && !(SWEEP && IN_PLACE)) ? TK_RANGE : (!INTERIOR && j0 + BK - 1 > i0) ? TK_CAUSAL : TK_PLAIN;
-    const int buf = t & (NSTAGE - 1);
-    // Mask: one 32-bit pattern per lane and 32-key half, bit b <-> key
-    // j0 + 32 sb + 8 hf + b of the lane's 16 (b = 0..7, 16..23), set = keep.  The
-    // pattern is built per tile kind; one loop applies it (a 1-bit signed extract and
-    // a bitwise select between the score and -inf per element).
-    bool masked = false;                   // wave-uniform
-    uint32_t km[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
-    if (kind == TK_CAUSAL) {
-      if (j0 + BK - 1 > iw0) {             // keep key <= query, i.e. b <= tl
-        masked = true;
+    f32x4 o[2][8];
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-          const int tl = i_me - (j0 + 32 * sb + 8 * hf);
-          km[sb] = tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u);
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[n][mb][r] = 0.f;
+    float m_run[2] = {kNegBig, kNegBig};   // reference maximum, in log2 units (score * scale * log2 e)
+    float l_run[2] = {0.f, 0.f};           // running sum of exp2 for this lane's keys
+    const float c2 = P.scale_log2;
+
+    // ---- operand ring and the MFMA phase -------------------------------------------
+    // A phase takes up to 32 operands of 16 rows from LDS, each for one MFMA per group of 16
+    // queries: 16 of P V(t-1) (head-dim blocks 0..7 for each of two 32-key halves) and 16 of
+    // K Q^T(t) (16-key blocks 0..3 for each of 4 contraction steps).  They come through a ring of
+    // 8 registers x 16 bytes: after the MFMAs of operand i have consumed slot i % 8, operand
+    // i + 8 is read into it, so every read has 14 MFMAs (~250 cycles) to return and the
+    // matrix pipe does not wait on LDS round trips.  sched_barrier pins the order: the
+    // compiler would otherwise sink each read down to its use.
+    f32x4 s[2][4];
+    uint4 pk[2][2];
+    uint4 R[8];
+    // K operand i = 4 ks + b: contraction step ks, 16-key block b
+    auto ld_k = [&](int slot, int i, int buf) {
+      // row p = 16 b + ql; logical chunk 4 ks + kg lives at physical chunk (4 ks + kg) ^ (p & 15)
+      const int b = i & 3, ks = i >> 2;
+      const char* kp = smem + OFF_K + buf * KTILE_B + (16 * b + ql) * KROW_B;
+      R[slot] = *reinterpret_cast<const uint4*>(kp + (((4 * ks + kg) ^ ql) << 4));
+    };
+    // V^T operand i = 8 sb + mb: keys 32 sb .., head-dim block mb
+    auto ld_v = [&](int slot, int i, int buf) {
+      // row d = 16 mb + ql; logical chunk 4 sb + kg lives at physical chunk (..) ^ ((d >> 1) & 7)
+      const int sb = i >> 3, mb = i & 7;
+      const char* vp = smem + OFF_V + buf * VTILE_B + (16 * mb + ql) * VROW_B;
+      R[slot] = *reinterpret_cast<const uint4*>(vp + (((4 * sb + kg) ^ (ql >> 1)) << 4));
+    };
+    // P V: on entry the ring holds V operands 0..7 (read during the softmax phase);
+    // the second half of the sweep re-fills it with the first 8 K operands of the next
+    // tile (read even when that tile turns out to need no work from this wave).  The
+    // loads of the tiles further ahead go out under the MFMAs, one per 3 MFMAs.
+    auto mm_pv = [&](int bufp, int bufq, auto&& setup_a, auto&& setup_v, auto&& setup_k, auto&& look, auto&& decide) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        // scalar bookkeeping in small pieces, so that no gap between two MFMAs grows long
+        if (!kLoadsInSoftmax) {
+          if (i == 1) setup_a();
+          if (i == 2) setup_v();
+          if (i == 4) load_v_one(0);
+          if (i == 5) setup_k();
+          if (i == 7) load_v_one(1);
+          if (i == 10) load_k_one(0);
+          if (i == 13) load_k_one(1);
         }
+        if (i == 3) look();                          // read the words that say whether the next tile needs this wave
+        if (i == 9) decide();                        // ... and decide, under the MFMAs
+        const int sb = i >> 3, mb = i & 7;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {                                        // O^T += V^T P^T
+          const int n = (i & 1) ? 1 - m : m;
+          o[n][mb] = mfma_16x16x32(as_bf16x8(R[i & 7]), as_bf16x8(pk[n][sb]), o[n][mb]);
+        }
+        SA_PIN();
+        if (i + 8 < 16) ld_v(i & 7, i + 8, bufp); else ld_k(i & 7, i - 8, bufq);
+        SA_PIN();
       }
-    } else if (MODE == 2 && kind == TK_COLIDX) {
-      const int32_t* il = reinterpret_cast<const int32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
-      if (!INTERIOR && il[BK - 1] > iw0) {   // only the last gathered tiles reach past a row: keep index <= query
-        masked = true;
+    };
+    // first 8 K operands of a tile into the ring (when no P V sweep did it)
+    auto warm_k = [&](int bufq) {
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-          uint32_t m = 0;
+      for (int i = 0; i < 8; ++i) ld_k(i, i, bufq);
+      SA_PIN();
+    };
+    // K Q^T: the ring holds K operands 0..7.  `with_loads`: no P V sweep went before,
+    // so this sweep issues the loads of the tiles further ahead.
+    // Element r of s[n][b] is key j0 + 32 (b / 2) + 8 kg + 4 (b % 2) + r against query i_me + 16 n.
+    auto mm_qk = [&](int bufq, bool with_loads) {
 #pragma unroll
-          for (int u = 0; u < 2; ++u) {
-            const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 16 * u + 8 * hf);
+      for (int i = 0; i < 16; ++i) {
+        if (with_loads && !kLoadsInSoftmax) {
+          if (i == 2) load_v_one(0);
+          if (i == 5) load_v_one(1);
+          if (i == 8) load_k_one(0);
+          if (i == 11) load_k_one(1);
+        }
+        const int b = i & 3, ks = i >> 2;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+          const int n = (i & 1) ? 1 - m : m;
+          if (ks == 0) s[n][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+          s[n][b] = mfma_16x16x32(as_bf16x8(R[i & 7]), qf[n][ks], s[n][b]);
+        }
+        SA_PIN();
+        if (i + 8 < 16) ld_k(i & 7, i + 8, bufq);
+        SA_PIN();
+      }
+    };
+
+    // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
+    // so only makes the vmcnt waits of the loop wait for more than they must.
+    auto store_part_lse = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int n = 0; n < 2; ++n) {
+        const float l_tot = quad_sum(l_run[n]);
+        if (row_ok(n) && kg == 0)
+          P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me + 16 * n - P.q_row0)] = m_run[n] * kLn2 + __logf(l_tot);
+      }
+    };
+
+    // ---- the softmax phase: mask, online softmax (two queries per lane), bf16 --------
+    auto step_softmax = [&](auto kc, int t, int d, auto&& fetch) __attribute__((always_inline)) {
+      const int j0 = first_key(kc, t, d);
+      constexpr bool INTERIOR = decltype(kc)::INTERIOR;
+      const int kind = is_col(kc, t) ? TK_COLIDX : (MODE == 2 && !(SWEEP && IN_PLACE)) ? TK_RANGE : (!INTERIOR && j0 + BK - 1 > i0) ? TK_CAUSAL : TK_PLAIN;
+      const int buf = t & (NSTAGE - 1);
+      // Mask: one 32-bit pattern per lane and 32-key half, set = keep: bit e (e = 0..7) <-> key
+      // j0 + 32 sb + 8 kg + e against the lane's SECOND query, bit 16 + e against its first.  (The
+      // offset of the second query is the larger one by 16, so a window of the reversed offset
+      // bitmap has its bits 16 places lower.)  The pattern is built per tile kind; one loop
+      // applies it (a 1-bit signed extract and a bitwise select between the score and -inf per element).
+      bool masked = false;                   // wave-uniform
+      uint32_t km[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+      // keep key <= query, i.e. e <= tl for the first query, e <= tl + 16 for the second
+      auto causal = [](int tl) -> uint32_t {
+        auto low = [](int n) { return (1u << min(max(n, 0), 8)) - 1u; };   // the lowest n of 8 bits
+        return (low(tl + 1) << 16) | low(tl + 17);
+      };
+      if (kind == TK_CAUSAL) {
+        if (j0 + BK - 1 > iw0) {
+          masked = true;
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb) km[sb] = causal(i_me - (j0 + 32 * sb + 8 * kg));
+        }
+      } else if (MODE == 2 && kind == TK_COLIDX) {
+        const int32_t* il = reinterpret_cast<const int32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+        if (!INTERIOR && il[BK - 1] > iw0) {   // only the last gathered tiles reach past a row: keep index <= query
+          masked = true;
+#pragma unroll
+          for (int sb = 0; sb < 2; ++sb) {
+            uint32_t m = 0;
+            const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 8 * kg);
             int4 x0 = ip[0], x1 = ip[1];
             int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m |= (jj[e] <= i_me ? 1u : 0u) << (16 * u + e);
+            for (int e = 0; e < 8; ++e) m |= ((jj[e] <= i_me ? 1u : 0u) << (16 + e)) | ((jj[e] <= i_me + 16 ? 1u : 0u) << e);
+            km[sb] = m;
           }
-          km[sb] = m;
         }
-      }
-    } else if (MODE == 2 && kind == TK_RANGE) {
-      masked = true;
-      const uint32_t* mw = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
-      const int wb = (P.off_max - (i0 - j0 + BQ - 1)) >> 5;
+      } else if (MODE == 2 && kind == TK_RANGE) {
+        masked = true;
+        const uint32_t* mw = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+        const int wb = (P.off_max - (i0 - j0 + BQ - 1)) >> 5;
+        const int tl = i_me - (j0 + 8 * kg);                 // offset of the first query and key e = 0
+        const int x0 = P.off_max - (tl + 16);                // >= 0: the window starts with the second query's
+        const int k = (x0 >> 5) - wb;                        // 0 .. 9: word of the staged window
+        const uint32_t w0 = mw[k], w1 = mw[k + 1], w2 = mw[k + 2];
 #pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        int tl = i_me - (j0 + 32 * sb + 8 * hf);
-        int x0 = P.off_max - tl;                       // >= 0 by construction of the bitmap
-        int k = (x0 >> 5) - wb;                        // 0 .. 10: word of the staged window
-        uint32_t lo = mw[k], hi = mw[k + 1];
-        uint32_t ow = __builtin_amdgcn_alignbit(hi, lo, x0 & 31);  // bit b <-> offset tl - b
-        uint32_t cw = mw[16 + sb] >> (8 * hf);                     // bit 16u+e <-> key is a selected column
-        // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
-        // column bit, unlike an offset bit, says nothing about j <= i)
-        km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
-        if (SWEEP && !INTERIOR) km[sb] &= tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u);
+        for (int sb = 0; sb < 2; ++sb) {
+          // bit b of the window <-> offset tl + 16 - 32 sb - b
+          const uint32_t ow = __builtin_amdgcn_alignbit(sb == 0 ? w1 : w2, sb == 0 ? w0 : w1, x0 & 31);
+          const uint32_t cb = __builtin_amdgcn_ubfe(mw[16 + sb], 8 * kg, 8);   // bit e <-> key is a selected column
+          const uint32_t cw = cb | (cb << 16);
+          // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
+          // column bit, unlike an offset bit, says nothing about j <= i)
+          km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
+          if (SWEEP && !INTERIOR) km[sb] &= causal(tl - 32 * sb);
+        }
+        // a tile that keeps every pair (a whole block of the block mask, the inside of a
+        // band of offsets) needs no masking at all
+        masked = __builtin_amdgcn_ballot_w64((km[0] & km[1] & 0x00FF00FFu) != 0x00FF00FFu) != 0ull;
       }
-      // a tile that keeps every pair (a whole block of the block mask, the inside of a
-      // band of offsets) needs no masking at all
-      masked = __builtin_amdgcn_ballot_w64((km[0] & km[1]) != 0xFFFFFFFFu) != 0ull;
+      if (masked) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(km[b >> 1], (n == 0 ? 16 : 0) + 4 * (b & 1) + r, 1);   // all-ones where kept
+              s[n][b][r] = __uint_as_float((__float_as_uint(s[n][b][r]) & keep) | (0xFF800000u & ~keep));
+            }
+      }
+
+      // the operand ring is idle: fetch the first 8 V operands of this tile's P V now,
+      // so that the reads return under the exponentials
+      SA_PIN();
+      fetch();
+      if (WITH_V) {
+        SA_PIN();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ld_v(i, i, buf);
+        SA_PIN();
+      }
+      // Online softmax, optimistic: the exponentials are taken against the reference
+      // maximum the row already has, and only their sum is looked at.  A sum within
+      // 2^8 means that no probability exceeds 2^8, which is all the reference is
+      // for (exact in fp32 and bf16 alike); then the tile costs no maximum at all.
+      // Otherwise (first tiles of a row, or a score far above what the row has seen: the
+      // sum is large, inf or NaN) the row maximum of the tile is formed, the reference
+      // moved up to it, the accumulators rescaled and the exponentials taken again.
+      float rs[2];
+      auto exponentials = [&](auto first_tag) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        rs[0] = rs[1] = 0.f;
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+#pragma unroll
+          for (int n = 0; n < 2; ++n) {
+            float p[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              if (kLoadsInSoftmax && FIRST && e == 4) {   // the loads of the tiles ahead, spread over the exponentials
+                if (sb == 0) load_v_one(n); else load_k_one(n);
+              }
+              p[e] = fast_exp2(fmaf(s[n][2 * sb + (e >> 2)][e & 3], c2, -m_run[n]));
+              rs[n] += p[e];
+            }
+            pk[n][sb] = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
+          }
+      };
+      exponentials(std::true_type{});
+      if (__any(!(rs[0] <= kSumBound && rs[1] <= kSumBound))) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n) {
+          // (the maximum starts from a value the compiler cannot see through: otherwise it
+          // forms the whole maximum ahead of the branch, on every tile)
+          float mx = s[n][0][0];
+          asm volatile("" : "+v"(mx));
+#pragma unroll
+          for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[n][b][r]);
+          mx = quad_max(mx);                     // the four lanes of a row agree on its reference
+          const float m_cand = mx * c2;
+          const float m_new = (m_cand > m_run[n]) ? m_cand : m_run[n];
+          const float alpha = fast_exp2(m_run[n] - m_new);
+          m_run[n] = m_new;
+          l_run[n] *= alpha;
+          if (WITH_V) {
+#pragma unroll
+            for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) o[n][mb][r] *= alpha;
+          }
+        }
+        exponentials(std::false_type{});
+      }
+      l_run[0] += rs[0];
+      l_run[1] += rs[1];
+      // (a part ends well before the diagonal: every wave that has rows works on its last tile)
+      if (MODE == 1 && t == part_last) {
+        store_part_lse();
+        ++part;
+        part_last = __builtin_amdgcn_readfirstlane(end_of_part());
+        m_run[0] = m_run[1] = kNegBig;
+        l_run[0] = l_run[1] = 0.f;
+      }
+    };
+
+    // ---- the two-phase pipeline --------------------------------------------------------
+    // MFMA phase(u):    P V(u-1), K Q^T(u)
+    // softmax phase(u): softmax(u)
+    // Iteration u also issues the loads of aux(u+3), V(u+2), K(u+3): from its softmax phase
+    // (dense and strip-masked kernels) or from its MFMA phase (log-sum-exp sweep).
+    // Group 0 runs MFMA phase u in the first half of iteration u, group 1 in the second.
+    // Slot t % 4 of the K (V^T) ring is re-filled with tile t + 4 only after the barrier
+    // that follows its last reader - K Q^T(t) (P V(t)) of group 1; a load is waited for
+    // by the wave that issued it before the barrier that precedes its first reader.  Loads complete
+    // in order, so "at most n in flight" means everything but the last n has landed: at
+    // the end of iteration u the loads of iteration u - 1 that feed the next softmax and
+    // K Q^T (V(u+1), and K(u+1) from iteration u - 2) must be in, the rest may still fly.
+    unsigned long long tiles_done = 0;
+    bool act_t = false;                        // this wave has work on the tile whose softmax comes next
+    // list entries of tiles u .. u+3, settled up to u+2
+    int dq0 = fetch_d(AnyTiles{}, 0), dq1 = fetch_d(AnyTiles{}, 1), dq2 = fetch_d(AnyTiles{}, 2), dq3 = fetch_d(AnyTiles{}, 3);
+    int dq4 = 0;                               // fetched by the iteration: the entry of tile u+4
+    uint64_t cols3 = 0;                        // ... and the column words of tile u+3
+    // The scores, the probabilities and the operand ring are written on some paths only
+    // (a wave may have no work on a tile).  An empty asm that "defines" them where their
+    // old contents are dead tells the compiler so; without it every path that skips a
+    // write carries the old value along, and the register allocator copies whole arrays
+    // between two homes inside the loop.
+    auto forget_ring = [&]() {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(R[i]));
+    };
+    auto forget_ring_and_p = [&]() {
+      forget_ring();
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "=v"(pk[i >> 1][i & 1]));
+    };
+    auto forget_scores = [&]() {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(s[i >> 2][i & 3]));
+    };
+    // (An interior stretch knows that the wave works on every tile: as a run-time flag the answer
+    // left a join in front of the K Q^T sweep, at which the compiler waited for the whole ring.)
+    auto softmax_phase = [&](auto kc, int u, int d_u, int it) __attribute__((always_inline)) {   // list entry of tile u; iteration
+      const bool act = decltype(kc)::INTERIOR ? !(decltype(kc)::FIRST && u < it) : act_t;   // (u < it: group 1)
+      forget_ring_and_p();                     // consumed by the MFMA phase before
+      if (kLoadsInSoftmax) {
+        // the loads of iteration `it`: aux(it + 3), V(it + 2), K(it + 3)
+        dma_aux(kc, it + 3, dq3);
+        load_v_begin(kc, it + 2, dq2);
+        load_k_begin(kc, it + 3, dq3);
+        if (!act) { load_v_one(0); load_v_one(1); load_k_one(0); load_k_one(1); }
+      }
+      // The scalar loads are collected by the barrier's lgkmcnt(0).  While one is in flight every wait for
+      // an LDS read waits for everything, so they go out where the next such wait is far away.
+      auto fetch = [&]() {
+        dq4 = fetch_d(kc, it + 4);
+        cols3 = fetch_cols(kc, it + 3, dq3);
+      };
+      if (act) step_softmax(kc, u, d_u, fetch); else fetch();
+    };
+    auto mfma_phase = [&](auto kc, int u) __attribute__((always_inline)) {
+      forget_scores();                         // consumed by the softmax phase before
+      const bool have = is_real(kc, u);
+      auto setup_a = [&]() { dma_aux(kc, u + 3, dq3); };
+      auto setup_v = [&]() { load_v_begin(kc, u + 2, dq2); };
+      auto setup_k = [&]() { load_k_begin(kc, u + 3, dq3); };
+      auto ahead_setup = [&]() { setup_a(); setup_v(); setup_k(); };
+      // (nothing is in flight: the V operands were requested a softmax ago.  Told so, the compiler does not
+      // wait for the whole ring where the paths below meet in front of the K Q^T sweep.)
+      if (WITH_V && !decltype(kc)::INTERIOR) __builtin_amdgcn_s_waitcnt(0xc07f);
+      __builtin_amdgcn_s_setprio(1);
+      const bool pv = WITH_V && (decltype(kc)::INTERIOR ? !decltype(kc)::FIRST : act_t);
+      const bool late = MODE == 2 && !SWEEP && !decltype(kc)::INTERIOR && is_col(kc, u);   // activity from an aux word
+      int aw0 = 0;
+      bool act_n = !late && have && tile_active(kc, u, dq0, 0);
+      if (pv) {
+        auto look = [&]() { if (late && have) act_word(kc, u, aw0); };
+        auto decide = [&]() { if (late) act_n = have && tile_active(kc, u, dq0, aw0); };
+        mm_pv((u - 1) & (NSTAGE - 1), u & (NSTAGE - 1), setup_a, setup_v, setup_k, look, decide);
+      } else {
+        if (!kLoadsInSoftmax) ahead_setup();
+        if (late && have) {
+          act_word(kc, u, aw0);
+          act_n = tile_active(kc, u, dq0, aw0);
+        }
+        if (act_n) warm_k(u & (NSTAGE - 1)); else forget_ring();
+      }
+      if (act_n) mm_qk(u & (NSTAGE - 1), !pv);
+      __builtin_amdgcn_s_setprio(0);
+      if (!kLoadsInSoftmax && !pv && !act_n) {
+        load_v_one(0); load_v_one(1); load_k_one(0); load_k_one(1);
+      }
+      tiles_done += act_n ? 1 : 0;
+      act_t = act_n;
+      // everything but this phase's loads and the K loads of the one before has landed
+      // (the wave that also fetched aux words waits for one load more than it must)
+      if (!kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
+    };
+    // before the barrier that ends an iteration everything has landed but that iteration's
+    // loads and the K loads of the one before
+    auto end_of_iteration_wait = [&]() {
+      if (kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
+    };
+
+    // prologue: K(0..2), V(0..1) and the aux words of tiles 0..2
+    {
+      const AnyTiles any{};
+      dma_aux(any, 0, dq0); dma_aux(any, 1, dq1); dma_aux(any, 2, dq2);
+      load_k_begin(any, 0, dq0); load_k_one(0); load_k_one(1);
+      load_k_begin(any, 1, dq1); load_k_one(0); load_k_one(1);
+      load_k_begin(any, 2, dq2); load_k_one(0); load_k_one(1);
+      load_v_begin(any, 0, dq0); load_v_one(0); load_v_one(1);
+      load_v_begin(any, 1, dq1); load_v_one(0); load_v_one(1);
+      const uint64_t c0 = fetch_cols(any, 0, dq0), c1 = fetch_cols(any, 1, dq1), c2w = fetch_cols(any, 2, dq2);
+      dq0 = settle(any, 0, dq0, c0); dq1 = settle(any, 1, dq1, c1); dq2 = settle(any, 2, dq2, c2w);
     }
-    if (masked) {
+    // vmcnt(0), as the builtin: the compiler then also knows that the Q loads above have
+    // landed and places no waits of its own for them inside the loop, where they would
+    // wait for the loads in flight there as well
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    wg_barrier();
+    // Iteration n: group 0 runs MFMA phase n, then softmax phase n; group 1 runs softmax
+    // phase n - 1, then MFMA phase n; one workgroup barrier ends the iteration.  The
+    // barrier is all the LDS traffic needs (a stage is re-filled, and a landed tile is
+    // first read, at least one iteration after the other side touched it - see above);
+    // starting the two groups on opposite phases after each barrier is what keeps one
+    // wave of every SIMD on the matrix pipe while the other is on the vector pipe.
+    // (The loop is written out once per group: one loop that picks the phase at run
+    // time keeps the registers of both phases alive everywhere and spills.)
+    // Iteration n touches tiles n - 1 .. n + 4 and decides on the work of tiles n and n + 1.
+    // Strip-masked kernel: the selected keys that are not before the workgroup's first row
+    // (at most 256) lie in the last five gathered tiles, so the iterations n + 1 <
+    // n_col_tiles - 5 see gathered tiles only, with work for every wave and nothing to mask;
+    // the iterations n > n_col_tiles see range tiles only; the few in between take the
+    // general form.  Dense and log-sum-exp sweeps: the tiles below key tile a64 (the one
+    // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
+    // past the end of the schedule.
+    const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
+                                   : (MODE == 1 && i_last_wg - i0 < BQ - 32) ? 0      // (waves without rows look at every tile)
+                                   : max(min(a64 - t_base - 1, n_tiles - 4), 0);
+    const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
+    const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
+    if (grp == 0) {
+      auto iteration = [&](auto kc, int n) __attribute__((always_inline)) {
+        mfma_phase(kc, n);                     // n = 0: K Q^T(0) only; n = n_tiles: the last P V
+        softmax_phase(kc, n, dq0, n);
+        end_of_iteration_wait();
+        wg_barrier();
+        SA_PIN();
+        dq0 = dq1; dq1 = dq2; dq2 = settle(kc, n + 3, dq3, cols3); dq3 = dq4;
+      };
+      int n = 0;
+      auto interior = [&](auto kc) __attribute__((always_inline)) {
+        if (n_gen0 > 0) iteration(typename decltype(kc)::AtFirst{}, n++);
+        for (; n < n_gen0; ++n) iteration(kc, n);
+      };
+      if (SWEEP && IN_PLACE) {
+        for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+        for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+      } else if (MODE == 2 && !SWEEP) {
+        interior(ColTiles{});
+        for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
+        for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+        for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+      } else {
+        interior(PlainTiles{});
+        for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
+      }
+    } else {
+      int dprev = 0;                           // tile diagonal of tile n - 1
+      auto iteration = [&](auto kc, int n) __attribute__((always_inline)) {
+        softmax_phase(kc, n - 1, dprev, n);
+        mfma_phase(kc, n);
+        end_of_iteration_wait();
+        wg_barrier();
+        SA_PIN();
+        dprev = dq0; dq0 = dq1; dq1 = dq2; dq2 = settle(kc, n + 3, dq3, cols3); dq3 = dq4;
+      };
+      int n = 0;
+      auto interior = [&](auto kc) __attribute__((always_inline)) {
+        if (n_gen0 > 0) iteration(typename decltype(kc)::AtFirst{}, n++);
+        for (; n < n_gen0; ++n) iteration(kc, n);
+      };
+      if (SWEEP && IN_PLACE) {
+        for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+        for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+      } else if (MODE == 2 && !SWEEP) {
+        interior(ColTiles{});
+        for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
+        for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
+        for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
+      } else {
+        interior(PlainTiles{});
+        for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
+      }
+    }
+    vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
+
+    // ---- epilogue -------------------------------------------------------------
+    if (MODE == 1) {
+      store_part_lse();
+      return;
+    }
+    if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
+    // a lane holds d = 16 mb + 4 kg .. + 3 of its two rows: the lanes of a row write 32 (bf16) or 64 bytes in a run
 #pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
+    for (int n = 0; n < 2; ++n) {
+      const float l_tot = quad_sum(l_run[n]);
+      if (!row_ok(n)) continue;
+      const int i = i_me + 16 * n;
+      if (PARTS) {
+        const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
+        const int r = 32 * wave + 16 * n + ql;
+        if (kg == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run[n], l_tot);
+        float* po = P.part_o + (slot * BQ + r) * kHeadDim + 4 * kg;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int bit = 16 * (r >> 3) + (r & 7);
-          const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(km[sb], bit, 1);   // all-ones where kept
-          s[sb][r] = __uint_as_float((__float_as_uint(s[sb][r]) & keep) | (0xFF800000u & ~keep));
-        }
+        for (int mb = 0; mb < 8; ++mb)
+          *reinterpret_cast<float4*>(po + 16 * mb) = make_float4(o[n][mb][0], o[n][mb][1], o[n][mb][2], o[n][mb][3]);
+        continue;
+      }
+      if (P.lse != nullptr && kg == 0) P.lse[(size_t)bh * S + i] = m_run[n] * kLn2 + __logf(l_tot);
+      const float inv = 1.0f / l_tot;
+      const size_t at = ((size_t)bh * S + i) * kHeadDim + 4 * kg;
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        const float x0 = o[n][mb][0] * inv, x1 = o[n][mb][1] * inv, x2 = o[n][mb][2] * inv, x3 = o[n][mb][3] * inv;
+        if (OUT_F32)
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + at + 16 * mb) = make_float4(x0, x1, x2, x3);
+        else
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + at + 16 * mb) = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+      }
+    }
+  } else {
+    const int ql = lane & 31;   // query within the wave / row within a 32-row operand
+    const int hf = lane >> 5;   // which half of the contraction block this lane feeds
+    const int i_me = iw0 + ql;                             // this lane's query row
+    const bool row_ok = i_me <= i_last_wg && (MODE != 2 || i_me >= P.row_lo);
+    // ---- Q^T operand: 8 contraction steps of 16, resident in registers -------
+    bf16x8 qf[8];
+    {
+      int qr = row_ok ? i_me : max(min(i_last_wg, S - 1), 0);
+      const uint16_t* qrow = P.q + ((size_t)bh * S + qr) * kHeadDim;
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks)
+        qf[ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 16 + hf * 8));
     }
 
-    // the operand ring is idle: fetch the first 8 V operands of this tile's P V now,
-    // so that the reads return under the exponentials
-    if (WITH_V) {
-      SA_PIN();
+    f32x16 o[4];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) ld_v(i, i, buf);
-      SA_PIN();
-    }
+    for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[mb][r] = 0.f;
+    float m_run = kNegBig;   // reference maximum, in log2 units (score * scale * log2 e)
+    float l_run = 0.f;       // running sum of exp2 for this lane's keys
+    const float c2 = P.scale_log2;
+
+    // list entries of tiles u .. u+3 of iteration u, settled up to u+2
+    int dq0 = fetch_d(AnyTiles{}, 0), dq1 = fetch_d(AnyTiles{}, 1), dq2 = fetch_d(AnyTiles{}, 2), dq3 = fetch_d(AnyTiles{}, 3);
+    int dq4 = 0;                               // fetched by the iteration: the entry of tile u+4
+    uint64_t cols3 = 0;                        // ... and the column words of tile u+3
+
+    // ---- operands ----------------------------------------------------------------------
+    // The MFMAs of an iteration take up to 32 operands of 32 rows from LDS: 16 of P V(u-1) (head-dim
+    // blocks 0..3 for each of four 16-key groups) and 16 of K Q^T(u) (8 contraction steps for each of
+    // two 32-key halves).  They come through a ring of 8 registers x 16 bytes: after the MFMA of operand
+    // i has consumed slot i % 8, operand i + 8 is read into it, so every read has 7 MFMAs (~250 cycles)
+    // to return and the matrix pipe does not wait on LDS round trips.  sched_barrier pins the order: the
+    // compiler would otherwise sink each read down to its use.
+    // Element r of s[sb] is key j0 + 32 sb + 16 (r / 8) + 8 hf + r % 8 against query i_me.
+    f32x16 s[2];
+    uint32_t pk[2][8];                         // probabilities of half sb as bf16
+    uint4 R[8];
+    // operand i of iteration u; `st` (Steps) says which operands there are
+    auto load_operand = [&](auto st, int i, int u) __attribute__((always_inline)) {
+      using St = decltype(st);
+      const int h = i / St::HALF, j = St::index(i);
+      if (St::is_v(i)) {
+        // row d = 32 mb + ql of V^T; logical chunk 4 h + 2 g + hf lives at physical chunk (..) ^ ((d >> 1) & 7)
+        const int g = j >> 2, mb = j & 3;
+        const char* vp = smem + OFF_V + ((u - 1) & (NSTAGE - 1)) * VTILE_B + (32 * mb + ql) * VROW_B;
+        R[i & 7] = *reinterpret_cast<const uint4*>(vp + (((4 * h + 2 * g + hf) ^ ((ql >> 1) & 7)) << 4));
+      } else {
+        // row p = 32 h + ql of K; logical chunk 2 j + hf lives at physical chunk (..) ^ (p & 15)
+        const char* kp = smem + OFF_K + (u & (NSTAGE - 1)) * KTILE_B + (32 * h + ql) * KROW_B;
+        R[i & 7] = *reinterpret_cast<const uint4*>(kp + (((2 * j + hf) ^ (ql & 15)) << 4));
+      }
+    };
+    auto multiply = [&](auto st, int i) __attribute__((always_inline)) {
+      using St = decltype(st);
+      const int h = i / St::HALF, j = St::index(i);
+      if (St::is_v(i)) {                         // O^T += V^T P^T
+        const int g = j >> 2, mb = j & 3;
+        const uint4 pw = {pk[h][4 * g], pk[h][4 * g + 1], pk[h][4 * g + 2], pk[h][4 * g + 3]};
+        o[mb] = mfma_32x32x16(as_bf16x8(R[i & 7]), as_bf16x8(pw), o[mb]);
+      } else {                                   // S^T = K Q^T
+        if (j == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[h][r] = 0.f;
+        }
+        s[h] = mfma_32x32x16(as_bf16x8(R[i & 7]), qf[j], s[h]);
+      }
+    };
+
+    // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
+    // so only makes the vmcnt waits of the loop wait for more than they must.
+    auto store_part_lse = [&]() __attribute__((always_inline)) {
+      const float l_tot = half_sum(l_run);
+      if (row_ok && hf == 0) P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)] = m_run * kLn2 + __logf(l_tot);
+    };
+
+    // ---- masks ---------------------------------------------------------------------------
+    // One 32-bit pattern per lane and 32-key half, bit b <-> key j0 + 32 sb + 8 hf + b of the lane's 16
+    // (b = 0..7, 16..23), set = keep.  The pattern is built per tile kind when the tile's
+    // scores are under way; that of half 1 is used an iteration later.  A score is masked by a 1-bit
+    // signed extract and a bitwise select between it and -inf: with its exponential (where every
+    // tile is masked), or in a pass of its own that is left out where the half keeps every pair (a
+    // whole block of the block mask, the inside of a band, tiles away from the causal edge).
+    uint32_t km[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+    auto masked_score = [&](int sb, int r) __attribute__((always_inline)) -> float {
+      const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(km[sb], 16 * (r >> 3) + (r & 7), 1);   // all-ones where kept
+      return __uint_as_float((__float_as_uint(s[sb][r]) & keep) | (0xFF800000u & ~keep));
+    };
+    auto mask_half = [&](int sb) __attribute__((always_inline)) {
+      if (__builtin_amdgcn_ballot_w64((km[sb] & 0x00FF00FFu) != 0x00FF00FFu) == 0ull) return;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[sb][r] = masked_score(sb, r);
+    };
+    // words of a range tile's pattern, read a half iteration before they are used
+    uint32_t rw[5] = {0, 0, 0, 0, 0};
+    auto is_range = [&](auto kc, int t) __attribute__((always_inline)) -> bool {
+      return MODE == 2 && !(SWEEP && IN_PLACE) && !is_col(kc, t);
+    };
+    auto read_range_words = [&](auto kc, int t, int d) __attribute__((always_inline)) {
+      if (!is_range(kc, t)) return;
+      const uint32_t* mw = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+      const int j0 = first_key(kc, t, d);
+      const int wb = (P.off_max - (i0 - j0 + BQ - 1)) >> 5;
+      const int x0 = P.off_max - (i_me - (j0 + 8 * hf));        // >= 0 by construction of the bitmap
+      const int k = (x0 >> 5) - wb;                             // 0 .. 9: word of the staged window
+      rw[0] = mw[k]; rw[1] = mw[k + 1]; rw[2] = mw[k + 2];
+      rw[3] = mw[16]; rw[4] = mw[17];                           // the column words
+    };
+    auto build_masks = [&](auto kc, int t, int d) __attribute__((always_inline)) {
+      const int j0 = first_key(kc, t, d);
+      constexpr bool INTERIOR = decltype(kc)::INTERIOR;
+      // keep key <= query, i.e. b <= tl
+      auto causal = [](int tl) -> uint32_t { return tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u); };
+      const int tl = i_me - (j0 + 8 * hf);                      // offset of the lane's first key
+      if (is_range(kc, t)) {
+        const int x0 = P.off_max - tl;
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) {
+          const uint32_t ow = __builtin_amdgcn_alignbit(rw[sb + 1], rw[sb], x0 & 31);  // bit b <-> offset tl - 32 sb - b
+          const uint32_t cw = rw[3 + sb] >> (8 * hf);                                  // bit 16u+e <-> key is a selected column
+          // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
+          // column bit, unlike an offset bit, says nothing about j <= i)
+          km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
+          if (SWEEP && !INTERIOR) km[sb] &= causal(tl - 32 * sb);
+        }
+      } else {
+        km[0] = km[1] = 0xFFFFFFFFu;
+        if (is_col(kc, t)) {
+          const int32_t* il = reinterpret_cast<const int32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+          if (!INTERIOR && il[BK - 1] > iw0) {     // only the last gathered tiles reach past a row: keep index <= query
+#pragma unroll
+            for (int sb = 0; sb < 2; ++sb) {
+              uint32_t m = 0;
+#pragma unroll
+              for (int g = 0; g < 2; ++g) {
+                const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 16 * g + 8 * hf);
+                int4 x0 = ip[0], x1 = ip[1];
+                int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m |= (jj[e] <= i_me ? 1u : 0u) << (16 * g + e);
+              }
+              km[sb] = m;
+            }
+          }
+        } else if (!INTERIOR && j0 + BK - 1 > iw0) {
+          km[0] = causal(tl);
+          km[1] = causal(tl - 32);
+        }
+      }
+    };
+
+    // ---- one iteration of a wave ------------------------------------------------------------
+    // Iteration u issues the MFMAs of P V(u-1) and of K Q^T(u), and with them, in the same
+    // instruction stream, the softmax of the scores that are there: half 1 (keys 32..63) of tile u-1
+    // beside the first half of the MFMAs (P V of half 0, K Q^T of half 0), half 0 of tile u beside the
+    // second (P V of half 1, K Q^T of half 1).  So a wave feeds the matrix and the vector pipe
+    // at once, whatever the other wave of its SIMD does.
+    //
     // Online softmax, optimistic: the exponentials are taken against the reference
     // maximum the row already has, and only their sum is looked at.  A sum within
     // 2^8 means that no probability exceeds 2^8, which is all the reference is
     // for (exact in fp32 and bf16 alike); then the tile costs no maximum at all.
     // Otherwise (first tiles of a row, or a score far above what the row has seen: the
-    // sum is large, inf or NaN) the row maximum of the tile is formed, the reference
+    // sum is large, inf or NaN) the row maximum of the half is formed, the reference
     // moved up to it, the accumulators rescaled and the exponentials taken again.
-    float rs = 0.f;
-    auto exponentials = [&](auto first_tag) {
-      constexpr bool FIRST = decltype(first_tag)::value;
-      rs = 0.f;
+    //
+    // PREV, CUR: tile u-1 / u has work for this wave.  MM: masks are applied not at all (0), with
+    // the exponentials (1), in a pass (2).  AHEAD: the ring holds the first eight operands already and
+    // is left with those of the next iteration (which has work on both tiles too).
+    auto run = [&](auto kc, auto prev_tag, auto cur_tag, auto ahead_tag, int u, auto&& fetch) __attribute__((always_inline)) {
+      constexpr bool PREV = decltype(prev_tag)::value, CUR = decltype(cur_tag)::value, AHEAD = decltype(ahead_tag)::value;
+      constexpr int KIND = decltype(kc)::KIND;
+      constexpr int MM = (MODE == 2 && !IN_PLACE && (KIND == 2 || (SWEEP && decltype(kc)::INTERIOR))) ? 1 : decltype(kc)::INTERIOR ? 0 : 2;
+      using St = Steps<PREV && WITH_V, CUR>;
+      constexpr int H = St::HALF;
+      if (!AHEAD) {
 #pragma unroll
-      for (int sb = 0; sb < 2; ++sb) {
-        float p[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (kLoadsInSoftmax && FIRST) {          // the loads of the tiles ahead, spread over the exponentials
-            if (sb == 0 && r == 4) load_v_one(0);
-            if (sb == 0 && r == 12) load_v_one(1);
-            if (sb == 1 && r == 4) load_k_one(0);
-            if (sb == 1 && r == 12) load_k_one(1);
-          }
-          p[r] = fast_exp2(fmaf(s[sb][r], c2, -m_run));
+        for (int i = 0; i < (H > 0 ? 8 : 0); ++i) load_operand(St{}, i, u);
+        SA_PIN();
+      }
+      if (CUR && MM != 0) read_range_words(kc, u, dq0);
+      auto half = [&](auto h_tag) __attribute__((always_inline)) {
+        constexpr int h = decltype(h_tag)::value, sb = 1 - h;
+        constexpr bool SM = h == 0 ? PREV : CUR;
+        if (SM && MM == 2) mask_half(sb);
+        auto score = [&](int r) __attribute__((always_inline)) -> float { return MM == 1 ? masked_score(sb, r) : s[sb][r]; };
+        float rs = 0.f, p[16];
+        auto element = [&](int r) __attribute__((always_inline)) {
+          p[r] = fast_exp2(fmaf(score(r), c2, -m_run));
           rs += p[r];
+          if (r & 1) pk[sb][r >> 1] = pack_bf16x2(p[r - 1], p[r]);
+        };
+        // the loads of the tiles ahead, one at a time: V in the first half, K in the second
+        if (h == 0) load_v_begin(kc, u + 2, dq2); else load_k_begin(kc, u + 3, dq3);
+        auto load_one = [&](int n) __attribute__((always_inline)) { if (h == 0) load_v_one(n); else load_k_one(n); };
+        if (H == 0) { load_one(0); load_one(1); }
+        if (h == 1) fetch();
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+          const int x = h * H + i;
+          multiply(St{}, x);
+          SA_PIN();
+          if (x + 8 < 2 * H) load_operand(St{}, x + 8, u);
+          else if (AHEAD) load_operand(St{}, x + 8 - 2 * H, u + 1);
+          if (i == H / 4) load_one(0);
+          if (i == H / 4 + H / 2) load_one(1);
+          SA_PIN();
+          if (SM) {
+#pragma unroll
+            for (int e = 16 * i / H; e < 16 * (i + 1) / H; ++e) element(e);
+            SA_PIN();
+          }
         }
+        if (SM && H == 0) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r) pk[sb][r] = pack_bf16x2(p[2 * r], p[2 * r + 1]);
-      }
-    };
-    exponentials(std::true_type{});
-    if (__any(!(rs <= kSumBound))) {
-      // (the maximum starts from a value the compiler cannot see through: otherwise it
-      // forms the whole maximum ahead of the branch, on every tile)
-      float mx = s[0][0];
-      asm volatile("" : "+v"(mx));
-#pragma unroll
-      for (int sb = 0; sb < 2; ++sb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sb][r]);
-      mx = half_max(mx);                     // the two lanes of a row agree on its reference
-      const float m_cand = mx * c2;
-      const float m_new = (m_cand > m_run) ? m_cand : m_run;
-      const float alpha = fast_exp2(m_run - m_new);
-      m_run = m_new;
-      l_run *= alpha;
-      if (WITH_V) {
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
-      }
-      exponentials(std::false_type{});
-    }
-    l_run += rs;
-    // (a part ends well before the diagonal: every wave that has rows works on its last tile)
-    if (MODE == 1 && t == part_last) {
-      store_part_lse();
-      ++part;
-      part_last = __builtin_amdgcn_readfirstlane(end_of_part());
-      m_run = kNegBig;
-      l_run = 0.f;
-    }
-  };
-
-  // ---- the two-phase pipeline --------------------------------------------------------
-  // MFMA phase(u):    P V(u-1), K Q^T(u)
-  // softmax phase(u): softmax(u)
-  // Iteration u also issues the loads of aux(u+3), V(u+2), K(u+3): from its softmax phase
-  // (dense and strip-masked kernels) or from its MFMA phase (log-sum-exp sweep).
-  // Group 0 runs MFMA phase u in the first half of iteration u, group 1 in the second.
-  // Slot t % 4 of the K (V^T) ring is re-filled with tile t + 4 only after the barrier
-  // that follows its last reader - K Q^T(t) (P V(t)) of group 1; a load is waited for
-  // by the wave that issued it before the barrier that precedes its first reader.  Loads complete
-  // in order, so "at most n in flight" means everything but the last n has landed: at
-  // the end of iteration u the loads of iteration u - 1 that feed the next softmax and
-  // K Q^T (V(u+1), and K(u+1) from iteration u - 2) must be in, the rest may still fly.
-  unsigned long long tiles_done = 0;
-  bool act_t = false;                        // this wave has work on the tile whose softmax comes next
-  bool pre_done = false, pre_act = false;    // the next tile was already looked at (and the ring warmed for it)
-  int dq0 = fetch_d(AnyTiles{}, 0), dq1 = fetch_d(AnyTiles{}, 1), dq2 = fetch_d(AnyTiles{}, 2), dq3 = fetch_d(AnyTiles{}, 3);   // tile diagonals of tiles u .. u+3
-  // The scores, the probabilities and the operand ring are written on some paths only
-  // (a wave may have no work on a tile).  An empty asm that "defines" them where their
-  // old contents are dead tells the compiler so; without it every path that skips a
-  // write carries the old value along, and the register allocator copies whole arrays
-  // between two homes inside the loop.
-  auto forget_ring_and_p = [&]() {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(R[i]));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(pk[0][i]), "=v"(pk[1][i]));
-  };
-  auto forget_scores = [&]() { asm volatile("" : "=v"(s[0]), "=v"(s[1])); };
-  auto softmax_phase = [&](auto kc, int u, int d_u, int d_next, int it) __attribute__((always_inline)) {   // tile diagonals of tiles u and u + 1; iteration
-    forget_ring_and_p();                     // consumed by the MFMA phase before
-    if (kLoadsInSoftmax) {
-      // the loads of iteration `it`: aux(it + 3), V(it + 2), K(it + 3)
-      dma_aux(kc, it + 3, dq3);
-      load_v_begin(kc, it + 2, dq2);
-      load_k_begin(kc, it + 3, dq3);
-      if (!act_t) { load_v_one(0); load_v_one(1); load_k_one(0); load_k_one(1); }
-    }
-    if (act_t) step_softmax(kc, u, d_u);
-    // A wave with nothing to do here looks at the next tile now, so that its next MFMA
-    // phase knows at once whether it has work.
-    if (!act_t && is_real(kc, u + 1)) {
-      uint32_t w0 = 0, w1 = 0;
-      act_words(kc, u + 1, w0, w1);
-      pre_act = tile_active(kc, u + 1, d_next, w0, w1);
-      pre_done = true;
-    }
-  };
-  auto mfma_phase = [&](auto kc, int u) __attribute__((always_inline)) {
-    forget_scores();                         // consumed by the softmax phase before
-    const bool have = is_real(kc, u);
-    auto setup_a = [&]() { dma_aux(kc, u + 3, dq3); };
-    auto setup_v = [&]() { load_v_begin(kc, u + 2, dq2); };
-    auto setup_k = [&]() { load_k_begin(kc, u + 3, dq3); };
-    auto ahead_setup = [&]() { setup_a(); setup_v(); setup_k(); };
-    __builtin_amdgcn_s_setprio(1);
-    const bool pv = WITH_V && act_t;
-    bool act_n = false;
-    if (pv) {
-      uint32_t aw0 = 0, aw1 = 0;
-      auto look = [&]() { if (have) act_words(kc, u, aw0, aw1); };
-      auto decide = [&]() { act_n = have && tile_active(kc, u, dq0, aw0, aw1); };
-      mm_pv((u - 1) & (NSTAGE - 1), u & (NSTAGE - 1), setup_a, setup_v, setup_k, look, decide);
-    } else {
-      if (!kLoadsInSoftmax) ahead_setup();
-      if (MODE == 1) {
-        // one call site for the warm-up: with two, the ring gets two homes in the
-        // log-sum-exp kernel and 32 register copies per tile (-6 % there; the other
-        // two kernels measured 1 % slower with this form, so they keep the one below)
-        if (pre_done) {
-          act_n = pre_act;
-        } else if (have) {
-          uint32_t aw0 = 0, aw1 = 0;
-          act_words(kc, u, aw0, aw1);
-          act_n = tile_active(kc, u, dq0, aw0, aw1);
+          for (int e = 0; e < 16; ++e) element(e);
         }
-        if (act_n) warm_k(u & (NSTAGE - 1));
-      } else if (pre_done) {
-        act_n = pre_act;
-        if (act_n) warm_k(u & (NSTAGE - 1));
-      } else if (have) {
-        uint32_t aw0 = 0, aw1 = 0;
-        act_words(kc, u, aw0, aw1);
-        act_n = tile_active(kc, u, dq0, aw0, aw1);
-        if (act_n) warm_k(u & (NSTAGE - 1));
-      }
-    }
-    pre_done = false;
-    if (act_n) mm_qk(u & (NSTAGE - 1), !pv);
-    __builtin_amdgcn_s_setprio(0);
-    if (!kLoadsInSoftmax && !pv && !act_n) {
-      load_v_one(0); load_v_one(1); load_k_one(0); load_k_one(1);
-    }
-    tiles_done += act_n ? 1 : 0;
-    act_t = act_n;
-    // everything but this phase's loads and the K loads of the one before has landed
-    // (the wave that also fetched aux words waits for one load more than it must)
-    if (!kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
-  };
-  // before the barrier that ends an iteration everything has landed but that iteration's
-  // loads and the K loads of the one before
-  auto end_of_iteration_wait = [&]() {
-    if (kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
-  };
-#undef SA_PIN
-
-  // prologue: K(0..2), V(0..1) and the aux words of tiles 0..2
-  {
-    const AnyTiles any{};
-    dma_aux(any, 0, dq0); dma_aux(any, 1, dq1); dma_aux(any, 2, dq2);
-    load_k_begin(any, 0, dq0); load_k_one(0); load_k_one(1);
-    load_k_begin(any, 1, dq1); load_k_one(0); load_k_one(1);
-    load_k_begin(any, 2, dq2); load_k_one(0); load_k_one(1);
-    load_v_begin(any, 0, dq0); load_v_one(0); load_v_one(1);
-    load_v_begin(any, 1, dq1); load_v_one(0); load_v_one(1);
-  }
-  // vmcnt(0), as the builtin: the compiler then also knows that the Q loads above have
-  // landed and places no waits of its own for them inside the loop, where they would
-  // wait for the loads in flight there as well
-  __builtin_amdgcn_s_waitcnt(0x0f70);
-  wg_barrier();
-  // Iteration n: group 0 runs MFMA phase n, then softmax phase n; group 1 runs softmax
-  // phase n - 1, then MFMA phase n; one workgroup barrier ends the iteration.  The
-  // barrier is all the LDS traffic needs (a stage is re-filled, and a landed tile is
-  // first read, at least one iteration after the other side touched it - see above);
-  // starting the two groups on opposite phases after each barrier is what keeps one
-  // wave of every SIMD on the matrix pipe while the other is on the vector pipe.
-  // (The loop is written out once per group: one loop that picks the phase at run
-  // time keeps the registers of both phases alive everywhere and spills.)
-  // Iteration n touches tiles n - 1 .. n + 4 and decides on the work of tiles n and n + 1.
-  // Strip-masked kernel: the selected keys that are not before the workgroup's first row
-  // (at most 256) lie in the last five gathered tiles, so the iterations n + 1 <
-  // n_col_tiles - 5 see gathered tiles only, with work for every wave and nothing to mask;
-  // the iterations n > n_col_tiles see range tiles only; the few in between take the
-  // general form.  Dense and log-sum-exp sweeps: the tiles below key tile a64 (the one
-  // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
-  // past the end of the schedule.
-  const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
-                                 : (MODE == 1 && i_last_wg - i0 < BQ - 32) ? 0      // (waves without rows look at every tile)
-                                 : max(min(a64 - t_base - 1, n_tiles - 4), 0);
-  const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
-  const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
-  if (grp == 0) {
-    auto iteration = [&](auto kc, int n) __attribute__((always_inline)) {
-      // the scalar load is issued here and collected by the barrier's lgkmcnt(0): waited
-      // for anywhere else, it would drain the LDS reads in flight as well
-      const int dq4 = fetch_d(kc, n + 4);
-      mfma_phase(kc, n);                     // n = 0: K Q^T(0) only; n = n_tiles: the last P V
-      softmax_phase(kc, n, dq0, dq1, n);
-      end_of_iteration_wait();
-      wg_barrier();
-      dq0 = dq1; dq1 = dq2; dq2 = dq3; dq3 = dq4;
+        if (SM) {
+          if (__builtin_expect(__any(!(rs <= kSumBound)), 0)) {
+            // (the maximum starts from a value the compiler cannot see through: otherwise it
+            // forms the whole maximum ahead of the branch, on every tile)
+            float mx = score(0);
+            asm volatile("" : "+v"(mx));
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, score(r));
+            mx = half_max(mx);                     // the two lanes of a row agree on its reference
+            const float m_cand = mx * c2;
+            const float m_new = (m_cand > m_run) ? m_cand : m_run;
+            const float alpha = fast_exp2(m_run - m_new);
+            m_run = m_new;
+            l_run *= alpha;
+            if (WITH_V) {
+#pragma unroll
+              for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
+            }
+            rs = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) element(r);
+          }
+          l_run += rs;
+        }
+        // (a part ends well before the diagonal: every wave that has rows works on its last tile)
+        if (MODE == 1 && h == 0 && PREV && u - 1 == part_last) {
+          store_part_lse();
+          ++part;
+          part_last = __builtin_amdgcn_readfirstlane(end_of_part());
+          m_run = kNegBig;
+          l_run = 0.f;
+        }
+      };
+      half(std::integral_constant<int, 0>{});
+      if (CUR && MM != 0) build_masks(kc, u, dq0);
+      half(std::integral_constant<int, 1>{});
     };
-    int n = 0;
-    if (SWEEP && IN_PLACE) {
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
-    } else if (MODE == 2 && !SWEEP) {
-      for (; n < n_gen0; ++n) iteration(ColTiles{}, n);
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
-    } else {
-      for (; n < n_gen0; ++n) iteration(PlainTiles{}, n);
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
-    }
-  } else {
-    int dprev = 0;                           // tile diagonal of tile n - 1
-    auto iteration = [&](auto kc, int n) __attribute__((always_inline)) {
-      const int dq4 = fetch_d(kc, n + 4);
-      softmax_phase(kc, n - 1, dprev, dq0, n);
-      mfma_phase(kc, n);
-      end_of_iteration_wait();
-      wg_barrier();
-      dprev = dq0; dq0 = dq1; dq1 = dq2; dq2 = dq3; dq3 = dq4;
-    };
-    int n = 0;
-    if (SWEEP && IN_PLACE) {
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
-    } else if (MODE == 2 && !SWEEP) {
-      for (; n < n_gen0; ++n) iteration(ColTiles{}, n);
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, n);
-    } else {
-      for (; n < n_gen0; ++n) iteration(PlainTiles{}, n);
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, n);
-    }
-  }
-  vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
 
-  // ---- epilogue -------------------------------------------------------------
-  if (MODE == 1) {
-    store_part_lse();
-    return;
-  }
-  float l_tot = half_sum(l_run);
-  if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
-  if (!row_ok) return;
-  if (PARTS) {
-    const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
-    const int r = 32 * wave + ql;
-    if (hf == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run, l_tot);
-    float* po = P.part_o + (slot * BQ + r) * kHeadDim;
+    // ---- the tile loop -------------------------------------------------------------------
+    // Iteration u reads V(u-1) and K(u) and issues the loads of aux(u+3), V(u+2), K(u+3); one
+    // workgroup barrier ends it.  Slot t % 4 of the K (V^T) ring is re-filled with tile t + 4 from
+    // iteration t + 1 (t + 2) on, after the barrier that follows its last reader.  A load is waited for
+    // by the wave that issued it before a barrier: loads complete in order, and before the barrier that
+    // ends iteration u everything has landed but that iteration's four (two) loads, so that V(u+1)
+    // and K(u+2) are there: what iteration u+1 reads, and the first operands of the next that it
+    // reads ahead.
+    unsigned long long tiles_done = 0;
+    bool act_prev = false;                     // this wave has work on the tile before
+    // prologue: K(0..2), V(0..1) and the aux words of tiles 0..2
+    {
+      const AnyTiles any{};
+      dma_aux(any, 0, dq0); dma_aux(any, 1, dq1); dma_aux(any, 2, dq2);
+      load_k_begin(any, 0, dq0); load_k_one(0); load_k_one(1);
+      load_k_begin(any, 1, dq1); load_k_one(0); load_k_one(1);
+      load_k_begin(any, 2, dq2); load_k_one(0); load_k_one(1);
+      load_v_begin(any, 0, dq0); load_v_one(0); load_v_one(1);
+      load_v_begin(any, 1, dq1); load_v_one(0); load_v_one(1);
+      const uint64_t c0 = fetch_cols(any, 0, dq0), c1 = fetch_cols(any, 1, dq1), c2w = fetch_cols(any, 2, dq2);
+      dq0 = settle(any, 0, dq0, c0); dq1 = settle(any, 1, dq1, c1); dq2 = settle(any, 2, dq2, c2w);
+    }
+    // vmcnt(0), as the builtin: the compiler then also knows that the Q loads above have
+    // landed and places no waits of its own for them inside the loop, where they would
+    // wait for the loads in flight there as well
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    wg_barrier();
+    constexpr std::true_type YES{};
+    constexpr std::false_type NO{};
+    // The arrays are written on some paths only (a wave may have no work on a tile).  An empty asm
+    // that "defines" what an iteration hands on, where its contents are dead, tells the compiler so;
+    // without it every path that skips a write carries the old values along, and the register
+    // allocator copies whole arrays between two homes inside the loop.
+    auto hand_on_nothing = [&]() __attribute__((always_inline)) {
+      asm volatile("" : "=v"(s[1]));
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<float4*>(po + 32 * mb + 8 * g + 4 * hf) =
-            make_float4(o[mb][4 * g], o[mb][4 * g + 1], o[mb][4 * g + 2], o[mb][4 * g + 3]);
-    return;
-  }
-  if (P.lse != nullptr && hf == 0) P.lse[(size_t)bh * S + i_me] = m_run * kLn2 + __logf(l_tot);
-  if (WITH_V) {
-    float inv = 1.0f / l_tot;
-    size_t rowoff = ((size_t)bh * S + i_me) * kHeadDim;
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        int d = 32 * mb + 8 * g + 4 * hf;
-        float x0 = o[mb][4 * g] * inv, x1 = o[mb][4 * g + 1] * inv;
-        float x2 = o[mb][4 * g + 2] * inv, x3 = o[mb][4 * g + 3] * inv;
-        if (OUT_F32) {
-          float4 v4 = {x0, x1, x2, x3};
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + rowoff + d) = v4;
+      for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(pk[0][i]));
+    };
+    auto iteration = [&](auto kc, auto ahead, int u) __attribute__((always_inline)) {
+      using Kc = decltype(kc);
+      // The scalar loads are collected at the barrier.  While one is in flight every wait for
+      // an LDS read waits for everything.
+      auto fetch = [&]() __attribute__((always_inline)) {
+        dq4 = fetch_d(kc, u + 4);
+        cols3 = fetch_cols(kc, u + 3, dq3);
+      };
+      dma_aux(kc, u + 3, dq3);
+      bool act = true;
+      if constexpr (Kc::INTERIOR) {
+        if constexpr (Kc::FIRST) run(kc, NO, YES, NO, u, fetch); else run(kc, YES, YES, ahead, u, fetch);
+      } else {
+        int w0 = 0;
+        if (is_real(kc, u)) act_word(kc, u, w0);
+        act = is_real(kc, u) && tile_active(kc, u, dq0, w0);
+        if (act_prev && act) {
+          run(kc, YES, YES, NO, u, fetch);
+        } else if (act) {
+          run(kc, NO, YES, NO, u, fetch);
         } else {
-          uint2 v2 = {pack_bf16x2(x0, x1), pack_bf16x2(x2, x3)};
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + rowoff + d) = v2;
+          if (act_prev) {
+            run(kc, YES, NO, NO, u, fetch);
+          } else {
+            load_v_begin(kc, u + 2, dq2); load_v_one(0); load_v_one(1);
+            load_k_begin(kc, u + 3, dq3); load_k_one(0); load_k_one(1);
+            fetch();
+          }
+          hand_on_nothing();
         }
       }
+      tiles_done += act ? 1 : 0;
+      act_prev = act;
+      if (WITH_V) vm_wait<4>(); else vm_wait<2>();
+      // (the operands read ahead stay in flight: their stages are not re-filled in the next iteration)
+      if constexpr (decltype(ahead)::value) wg_meet(); else wg_barrier();
+      SA_PIN();
+      dq0 = dq1; dq1 = dq2; dq2 = settle(kc, u + 3, dq3, cols3); dq3 = dq4;
+    };
+    // Iteration n touches tiles n - 1 .. n + 4 and decides on the work of tile n.
+    // Strip-masked kernel: the selected keys that are not before the workgroup's first row
+    // (at most 256) lie in the last five gathered tiles, so the iterations n + 1 <
+    // n_col_tiles - 5 see gathered tiles only, with work for every wave and nothing to mask;
+    // the iterations n > n_col_tiles see range tiles only; the few in between take the
+    // general form.  Dense and log-sum-exp sweeps: the tiles below key tile a64 (the one
+    // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
+    // past the end of the schedule.
+    const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
+                                   : (MODE == 1 && i_last_wg - i0 < BQ - 32) ? 0      // (waves without rows look at every tile)
+                                   : max(min(a64 - t_base - 1, n_tiles - 4), 0);
+    const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
+    const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
+    int n = 0;
+    auto interior = [&](auto kc) __attribute__((always_inline)) {
+      if (n_gen0 <= 0) return;
+      iteration(typename decltype(kc)::AtFirst{}, NO, n++);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_operand(Steps<WITH_V, true>{}, i, n);
+      for (; n < n_gen0; ++n) iteration(kc, YES, n);
+      act_prev = true;
+    };
+    if (SWEEP && IN_PLACE) {
+      for (; n < n_real; ++n) iteration(RngRealTiles{}, NO, n);
+      for (; n <= n_tiles; ++n) iteration(RngTiles{}, NO, n);
+    } else if (MODE == 2 && !SWEEP) {
+      interior(ColTiles{});
+      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, NO, n);
+      for (; n < n_real; ++n) iteration(RngRealTiles{}, NO, n);
+      for (; n <= n_tiles; ++n) iteration(RngTiles{}, NO, n);
+    } else {
+      interior(PlainTiles{});
+      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, NO, n);
+    }
+    vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
+
+    // ---- epilogue -------------------------------------------------------------
+    if (MODE == 1) {
+      store_part_lse();
+      return;
+    }
+    float l_tot = half_sum(l_run);
+    if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
+    if (!row_ok) return;
+    if (PARTS) {
+      const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
+      const int r = 32 * wave + ql;
+      if (hf == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run, l_tot);
+      float* po = P.part_o + (slot * BQ + r) * kHeadDim;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<float4*>(po + 32 * mb + 8 * g + 4 * hf) =
+              make_float4(o[mb][4 * g], o[mb][4 * g + 1], o[mb][4 * g + 2], o[mb][4 * g + 3]);
+      return;
+    }
+    if (P.lse != nullptr && hf == 0) P.lse[(size_t)bh * S + i_me] = m_run * kLn2 + __logf(l_tot);
+    if (WITH_V) {
+      float inv = 1.0f / l_tot;
+      size_t rowoff = ((size_t)bh * S + i_me) * kHeadDim;
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          int d = 32 * mb + 8 * g + 4 * hf;
+          float x0 = o[mb][4 * g] * inv, x1 = o[mb][4 * g + 1] * inv;
+          float x2 = o[mb][4 * g + 2] * inv, x3 = o[mb][4 * g + 3] * inv;
+          if (OUT_F32) {
+            float4 v4 = {x0, x1, x2, x3};
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + rowoff + d) = v4;
+          } else {
+            uint2 v2 = {pack_bf16x2(x0, x1), pack_bf16x2(x2, x3)};
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + rowoff + d) = v2;
+          }
+        }
+    }
   }
+#undef SA_PIN
 }
 
 template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS>
@@ -941,15 +1407,24 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       bh = bkv * P.group + hg;
     }
   }
+  // Which core a head is for.  Whole query tiles: the one of 16-row operands for sweeps, block lists and
+  // strips that keep most waves busy, the other for strips of few and scattered offsets (decided with
+  // the list, on the device).  Parts: the other, whose tiles are the shorter ones on a chip that is not
+  // full.
+  constexpr int SWEEP_CORE = PARTS ? 1 : 0;
   if (MODE == 2) {
     // (diagonal 0 is in every list, and its entry is the first)
-    const int first = P.dlist[(size_t)bh * P.dlist_stride];
-    if (__builtin_amdgcn_readfirstlane(first) & kSweepBit) {
-      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS>(P, bh, a, split, n_parts);
+    const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)bh * P.dlist_stride]);
+    if (first & kSweepBit) {
+      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, SWEEP_CORE>(P, bh, a, split, n_parts);
+      return;
+    }
+    if (!PARTS && !IN_PLACE && (first & kSparseBit)) {
+      flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, bh, a, split, n_parts);
       return;
     }
   }
-  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS>(P, bh, a, split, n_parts);
+  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, SWEEP_CORE>(P, bh, a, split, n_parts);
 }
 
 // The parts of a query tile brought to one reference maximum, added in fixed order and

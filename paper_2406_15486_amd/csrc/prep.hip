@@ -152,6 +152,10 @@ __device__ __forceinline__ long long block_sum(long long x, long long* scratch) 
 // 32 runs 19.2 ms in two passes / 30.9 swept, 218 runs 29.7 / 30.9, 436 runs 35.7 / 30.9,
 // 1638 runs 45.2 / 31.1.
 constexpr int kColTileCost = 132, kRangeTileCost = 76, kRangeWaveCost = 7, kSweepTileCost = 140;
+// Which core a head in two passes is for (kSparseBit: the one of 32-row operands): what the other
+// gains on a gathered tile and on every wave that works on a range tile, against what it loses on a
+// range tile.
+constexpr int kCoreColTile = 33, kCoreWave = 10, kCoreRangeTile = 68;
 
 // Written by one workgroup: `active(d, w)` says whether wave w has work on diagonal d.  A
 // thread takes one (d, w) pair, a wave eight diagonals at a time (one ballot is eight
@@ -175,7 +179,7 @@ __device__ __forceinline__ void write_dlist(int nd, int q_lo, int q_hi, long lon
   // diagonal d is met by the query tiles a with 4 a + 3 >= d
   auto met = [&](int d) { return (long long)max(q_hi - max(q_lo, d / 4), 0); };
   int n = 0;
-  long long two_pass = kColTileCost * col_tiles, sweep = 0;
+  long long two_pass = kColTileCost * col_tiles, sweep = 0, core = kCoreColTile * col_tiles;
   for (int g = g_lo; g < g_hi; ++g) {
     const uint32_t mask = mask_of(g);
     const int d = 8 * g + (lane >> 3);
@@ -184,6 +188,7 @@ __device__ __forceinline__ void write_dlist(int nd, int q_lo, int q_hi, long lon
     if (first) {
       sweep += kSweepTileCost * met(d);
       if (mask != 0u) two_pass += (kRangeTileCost + kRangeWaveCost * __popc(mask)) * met(d);
+      if (mask != 0u) core += (kCoreWave * (int)__popc(mask) - kCoreRangeTile) * met(d);
     }
   }
   if (lane == 0) wave_cnt[wave] = n;
@@ -197,6 +202,7 @@ __device__ __forceinline__ void write_dlist(int nd, int q_lo, int q_hi, long lon
     if (tid == 0) *dcnt = nd;
     return;
   }
+  const uint32_t flag = block_sum(core, sums) < 0 ? (uint32_t)kSparseBit : 0u;
   int at = 0, total = 0;
   for (int w = 0; w < PT / 64; ++w) {
     at += w < wave ? wave_cnt[w] : 0;
@@ -206,7 +212,7 @@ __device__ __forceinline__ void write_dlist(int nd, int q_lo, int q_hi, long lon
     const uint32_t mask = mask_of(g);
     const bool mine = (lane & 7) == 0 && mask != 0u;
     const unsigned long long b = __ballot(mine);
-    if (mine) dl[at + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)((uint32_t)(8 * g + (lane >> 3)) | (mask << 24));
+    if (mine) dl[at + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)((uint32_t)(8 * g + (lane >> 3)) | flag | (mask << 24));
     at += __popcll(b);
   }
   if (tid == 0) *dcnt = total;

@@ -10,6 +10,7 @@ constexpr int kFlashBQ = 256;  // query rows per workgroup of the flash kernels
 constexpr int kFlashBK = 64;   // keys per tile
 constexpr int kMaxSeqLen = 1 << 24;   // kernels keep 32-bit byte offsets into V^T
 constexpr int kSweepBit = 1 << 23;   // in every entry of a tile-diagonal list: the head is swept
+constexpr int kSparseBit = 1 << 22;  // ... or its tiles leave many waves without work
 
 struct FlashParams {
   const uint16_t* q;        // [n_bh, S, 128] bf16

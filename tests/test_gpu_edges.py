@@ -362,6 +362,40 @@ def test_uncut_tiles(test, args, monkeypatch):
     assert calls and all(calls)
 
 
+@pytest.mark.parametrize("S,n_col", [(1279, 0), (1280, 0), (1281, 65), (2305, 448), (2816, 700)])
+def test_cores_of_the_two_passes(S, n_col):
+    """Heads whose tiles leave many waves without work take the core of 32-row operands, the others
+    that of 16-row operands, in one launch: scattered offsets and offsets in runs on whole
+    query tiles (no room for parts), with and without columns, at lengths around the tiles."""
+    import paper_2406_15486_amd as sa
+    _say(f"cores S={S} columns={n_col}")
+    H, KV, pad = 4, 2, (S + 255) // 256 * 256
+    wl, x = _inputs("glm8k", S=S, Hq=H, Hkv=KV, n_sinks=8)
+    rng = np.random.default_rng(S)
+    Ic = [np.sort(rng.choice(S, n, replace=False)) for n in (n_col, 0, n_col, min(n_col, S // 8))]
+    Is = [np.arange(300, S, 613), np.arange(0, S, 2), np.unique(np.r_[310:314, 930:933, S - 1]), np.arange(0, S // 2)]
+    lists = []
+    for L in (Ic, Is):
+        idx = torch.zeros(H, S, dtype=torch.int32)
+        for h in range(H):
+            idx[h, :len(L[h])] = torch.from_numpy(L[h].astype(np.int32))
+        lists += [idx.cuda(), torch.tensor([len(y) for y in L], dtype=torch.int32, device="cuda")]
+    q, k, v = (_dev(x[n]) for n in "qkv")
+    ws = torch.full((_bare("strips", H, KV, S),), 0xFF, dtype=torch.uint8, device="cuda")
+    out, lse, _ = sa.sa_sparse_attn(q, k, v, *lists, 16, workspace=ws, want_lse=True, out_dtype=sa.SA_OUT_F32)
+    torch.cuda.synchronize()
+    # the lists of tile diagonals lie behind V^T, the gathered K and V^T, the padded columns and two bitmaps
+    up = lambda n: (n + 255) // 256 * 256
+    at = up(KV * 256 * pad) + 2 * up(H * 256 * pad) + up(H * pad * 4) + up(H * (pad // 32 + 2) * 4) + up(H * (pad // 32 + 24) * 4)
+    first = ws[at:at + 4 * H * (pad // 64 + 8)].view(torch.int32).view(H, -1)[:, 0].cpu().numpy()
+    assert [bool(e & (1 << 22)) for e in first] == [True, False, True, S < 2000] and not any(e & (1 << 23) for e in first)
+    qf, kf, vf = _f64(x["q"]), _f64(x["k"]), _f64(x["v"])
+    for h in range(H):
+        want, wlse = O.masked_attn(qf[h], kf[h // 2], vf[h // 2], Ic[h], Is[h], 16)
+        _check_out(out[0, h].cpu().numpy(), want, f"cores h{h}")
+        assert np.abs(lse[h].cpu().numpy() - wlse).max() < 2e-3
+
+
 # empty lists leave a query tile the four key tiles that hold its window, for up to six parts
 @pytest.mark.parametrize("S,C", [(1281, 1), (1536, 1), (2600, 2), (3300, 3)])
 @pytest.mark.parametrize("n_col,n_off", [(0, 0), (1, 0), (0, 1), (65, 2)])
