@@ -1354,7 +1354,11 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
 #undef SA_PIN
 }
 
-template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS>
+// Which core (see the top of the file) a workgroup takes: core 1 in parts and where !LONG.  In a LONG launch of
+// strips or block lists, swept heads take core 0 (their mask costs vector instructions on every tile), the
+// others too where the sequence is long and the head's list does not leave too many waves without work
+// (kSparseBit; strips only).
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
 __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
   // ---- which (head, query tile) this workgroup owns ------------------------
   // (the log-sum-exp sweep may also give the keys of a query tile to k_splits workgroups)
@@ -1407,24 +1411,20 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       bh = bkv * P.group + hg;
     }
   }
-  // Which core a head is for.  Whole query tiles: the one of 16-row operands for sweeps, block lists and
-  // strips that keep most waves busy, the other for strips of few and scattered offsets (decided with
-  // the list, on the device).  Parts: the other, whose tiles are the shorter ones on a chip that is not
-  // full.
-  constexpr int SWEEP_CORE = PARTS ? 1 : 0;
+  constexpr int CORE = LONG ? 0 : 1;
   if (MODE == 2) {
     // (diagonal 0 is in every list, and its entry is the first)
     const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)bh * P.dlist_stride]);
     if (first & kSweepBit) {
-      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, SWEEP_CORE>(P, bh, a, split, n_parts);
+      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, CORE>(P, bh, a, split, n_parts);
       return;
     }
-    if (!PARTS && !IN_PLACE && (first & kSparseBit)) {
+    if (CORE == 0 && (P.short_lists || (!IN_PLACE && (first & kSparseBit)))) {
       flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, bh, a, split, n_parts);
       return;
     }
   }
-  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, SWEEP_CORE>(P, bh, a, split, n_parts);
+  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, bh, a, split, n_parts);
 }
 
 // The parts of a query tile brought to one reference maximum, added in fixed order and
@@ -1562,23 +1562,38 @@ size_t flash_parts_bytes(int m, int n_heads, int q0, int q1) {
   return m == 0 ? 0 : (size_t)n_heads * parts_before(m, q0, q1) * BQ * (kHeadDim + 2) * sizeof(float);
 }
 
-template <int MODE, bool OUT_F32, bool IN_PLACE = false, bool PARTS = false>
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
 static hipError_t launch_one(const FlashParams& P, int grid, hipStream_t st) {
   size_t shmem = (MODE == 1) ? LDS_B_LSE : LDS_B;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, LONG>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS>), dim3(grid), dim3(NT), shmem, st, P);
+  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, LONG>), dim3(grid), dim3(NT), shmem, st, P);
   return hipGetLastError();
 }
+template <int MODE, bool IN_PLACE>
+static hipError_t launch_whole(bool out_f32, bool long_run, const FlashParams& P, int grid, hipStream_t st) {
+  if (long_run) return out_f32 ? launch_one<MODE, true, IN_PLACE, false, true>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, true>(P, grid, st);
+  return out_f32 ? launch_one<MODE, true, IN_PLACE, false, false>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, false>(P, grid, st);
+}
+
+// Which launches are LONG: of more tiles than CUs, of sequences long enough.  By the length alone, so that
+// a head's bits above 256 query tiles do not follow the batch.  Gain over the kernel before the two
+// cores, core 0 / core 1: dense, 32 heads of 4096 1.03 / 0.99, of 8192 1.034 / 0.986, 16 of 8192 1.05 / 0.99, 8 of 16384
+// 1.05 / 0.99; up to some 340 tiles on the 256 CUs one tile's chain decides, 16 of 4500 0.95 / 0.98, 8 of 8500
+// 0.94 / 0.98, of 9500 0.96 / 0.98, 4 of 17000 0.95 / 0.99: rare shapes, left to the rule.  Swept heads: 32 of 8192
+// 1.08 / 1.03, of 4500 1.04 / 0.99, 8 of 8500 1.02 / 0.97, 16 of 8000 1.05 / 0.96, but 32 of 2048 in blocks 0.94 / 1.01, 4
+// segments of 4000 0.93 / 1.03.  Strips in two passes: 32 heads of 3000 0.95 / 1.02, of 6001 0.93 / 1.05, 16 of 20000
+// 0.97 / 1.05, 8 of 40000 0.99 / 1.02, but 32 of 65536 1.04 / 1.00.  Block lists in two: 32 of 16384 1.02 / 1.06, of 32768 1.06 / 1.04.
+constexpr int kLongDense = 4096, kLongStrips = 49152, kLongBlocks = 24576;
 
 // a launch whose schedules are cut into parts, and the combination
 static hipError_t launch_parts(int mode, bool out_f32, const FlashParams& P0, hipStream_t st) {
   FlashParams P = P0;
   const int n = P.n_bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles);
   P.part_ml = P.part_o + (size_t)n * BQ * kHeadDim;
-  hipError_t e = mode == 0 ? launch_one<0, false, false, true>(P, n, st)
-               : P.cols_in_place ? launch_one<2, false, true, true>(P, n, st) : launch_one<2, false, false, true>(P, n, st);
+  hipError_t e = mode == 0 ? launch_one<0, false, false, true, false>(P, n, st)
+               : P.cols_in_place ? launch_one<2, false, true, true, false>(P, n, st) : launch_one<2, false, false, true, false>(P, n, st);
   if (e != hipSuccess) return e;
   const dim3 grid(P.n_qtiles * (BQ / 8), P.n_bh);
   if (out_f32) hipLaunchKernelGGL(parts_combine_kernel<true>, grid, dim3(256), 0, st, P);
@@ -1597,12 +1612,14 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
   }
   if (grid <= 0) return hipSuccess;
   switch (mode) {
-    case 0: return out_f32 ? launch_one<0, true>(P, grid, st) : launch_one<0, false>(P, grid, st);
-    case 1: return launch_one<1, false>(P, grid, st);
-    default:
-      if (P.cols_in_place)
-        return out_f32 ? launch_one<2, true, true>(P, grid, st) : launch_one<2, false, true>(P, grid, st);
-      return out_f32 ? launch_one<2, true>(P, grid, st) : launch_one<2, false>(P, grid, st);
+    case 0: return launch_whole<0, false>(out_f32, P.S >= kLongDense && P.all_tiles > kMaxParts, P, grid, st);
+    case 1: return launch_one<1, false, false, false, true>(P, grid, st);
+    default: {
+      FlashParams L = P;
+      L.short_lists = P.S < (P.cols_in_place ? kLongBlocks : kLongStrips);
+      const bool long_run = P.all_tiles > kMaxParts;
+      return P.cols_in_place ? launch_whole<2, true>(out_f32, long_run, L, grid, st) : launch_whole<2, false>(out_f32, long_run, L, grid, st);
+    }
   }
 }
 

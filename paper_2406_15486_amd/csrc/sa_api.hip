@@ -192,10 +192,11 @@ size_t parts_room(const Dims& d, int n_chunks) {
   return align_up(most);
 }
 
-// cuts the launch P over the query tiles [q0, q1) of the whole call into parts if `room` bytes
-// at `at` hold their sums for n_heads heads
+// tells the launch P how large the call is (query tiles [q0, q1) of all heads), and cuts it into
+// parts if `room` bytes at `at` hold their sums for n_heads heads
 void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int q0, int q1, void* at, size_t room) {
   const int m = sa::flash_parts(d.n_bh, q0, q1);
+  P->all_tiles = d.n_bh * (q1 - q0);
   if (m == 0 || sa::flash_parts_bytes(m, n_heads, q0, q1) > room) return;
   P->part_m = m;
   P->part_o = static_cast<float*>(at);

@@ -33,6 +33,8 @@ struct FlashParams {
   int lse_parts;            // mode 1: parts the keys of a query tile are cut into (a power of two); lse is
                             // [lse_parts, n_bh, n_qrows] partial values, combined by launch_lse_combine
   int k_splits;             // ... and the workgroups they are given to (a power of two, <= lse_parts)
+  int all_tiles;            // modes 0 and 2: query tiles of all heads of the call (of the segment), whatever this launch takes
+  int short_lists;          // mode 2 (set by the launch): heads in two passes take core 1
   int part_m;               // modes 0 and 2: > 0: tile a's schedule is cut into ceil((a + 1) / part_m) workgroups
   float* part_o;            // ... whose sums [part, 256, 128] and then [part, 256, 2] lie here (flash_parts_bytes)
   float* part_ml;           // (set by the launch)

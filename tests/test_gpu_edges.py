@@ -362,38 +362,60 @@ def test_uncut_tiles(test, args, monkeypatch):
     assert calls and all(calls)
 
 
-@pytest.mark.parametrize("S,n_col", [(1279, 0), (1280, 0), (1281, 65), (2305, 448), (2816, 700)])
-def test_cores_of_the_two_passes(S, n_col):
-    """Heads whose tiles leave many waves without work take the core of 32-row operands, the others
-    that of 16-row operands, in one launch: scattered offsets and offsets in runs on whole
-    query tiles (no room for parts), with and without columns, at lengths around the tiles."""
+# just below and above the lengths and the tiles of a call at which a launch changes core
+@pytest.mark.parametrize("path,S,H", [("dense", 4095, 17), ("dense", 4097, 17), ("dense", 4097, 15), ("strips", 49151, 2), ("strips", 49153, 2),
+                                      ("strips", 49153, 1), ("blocks", 24575, 3), ("blocks", 24577, 3), ("blocks", 24577, 2)])
+def test_cores_of_the_attention_kernels(path, S, H):
+    """Uncut tiles take one of two cores, by the length, the query tiles and (strips) the list of the
+    head: scattered strips, every other one, nearly full lists that are swept.  Rows around the
+    tiles against their fp64 softmax (probabilities and V are bf16, as elsewhere)."""
     import paper_2406_15486_amd as sa
-    _say(f"cores S={S} columns={n_col}")
-    H, KV, pad = 4, 2, (S + 255) // 256 * 256
-    wl, x = _inputs("glm8k", S=S, Hq=H, Hkv=KV, n_sinks=8)
+    _say(f"cores {path} S={S} H={H}")
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, h, S, 128, generator=g, device="cuda").bfloat16() for h in (H, 1, 1))
     rng = np.random.default_rng(S)
-    Ic = [np.sort(rng.choice(S, n, replace=False)) for n in (n_col, 0, n_col, min(n_col, S // 8))]
-    Is = [np.arange(300, S, 613), np.arange(0, S, 2), np.unique(np.r_[310:314, 930:933, S - 1]), np.arange(0, S // 2)]
+    blk = 128 if path == "blocks" else 1
+    n, w = (S + blk - 1) // blk, 16
+    Is = [np.arange(3, n, 613 if blk == 1 else 17), np.arange(0, n, 2), np.sort(rng.choice(n, n * 19 // 20, replace=False))]
+    Ic = [np.sort(rng.choice(n, m, replace=False)) for m in (n // 5, n // 40, n * 9 // 10)]
+    Ic, Is = ([L[(h + (H == 2)) % 3] for h in range(H)] for L in (Ic, Is))
     lists = []
     for L in (Ic, Is):
-        idx = torch.zeros(H, S, dtype=torch.int32)
+        idx = torch.zeros(H, n, dtype=torch.int32)
         for h in range(H):
             idx[h, :len(L[h])] = torch.from_numpy(L[h].astype(np.int32))
         lists += [idx.cuda(), torch.tensor([len(y) for y in L], dtype=torch.int32, device="cuda")]
-    q, k, v = (_dev(x[n]) for n in "qkv")
-    ws = torch.full((_bare("strips", H, KV, S),), 0xFF, dtype=torch.uint8, device="cuda")
-    out, lse, _ = sa.sa_sparse_attn(q, k, v, *lists, 16, workspace=ws, want_lse=True, out_dtype=sa.SA_OUT_F32)
+    kw = dict(out_dtype=sa.SA_OUT_F32, want_lse=True, workspace=torch.full((_bare(path, H, 1, S),), 0xFF, dtype=torch.uint8, device="cuda"))
+    if path == "dense":
+        out, lse = sa.sa_dense_attn(q, k, v, **kw)
+    elif path == "strips":
+        out, lse, _ = sa.sa_sparse_attn(q, k, v, *lists, w, **kw)
+    else:
+        out, lse, _ = sa.sa_block_sparse_attn(q, k, v, *lists, w, blk, **kw)
     torch.cuda.synchronize()
-    # the lists of tile diagonals lie behind V^T, the gathered K and V^T, the padded columns and two bitmaps
-    up = lambda n: (n + 255) // 256 * 256
-    at = up(KV * 256 * pad) + 2 * up(H * 256 * pad) + up(H * pad * 4) + up(H * (pad // 32 + 2) * 4) + up(H * (pad // 32 + 24) * 4)
-    first = ws[at:at + 4 * H * (pad // 64 + 8)].view(torch.int32).view(H, -1)[:, 0].cpu().numpy()
-    assert [bool(e & (1 << 22)) for e in first] == [True, False, True, S < 2000] and not any(e & (1 << 23) for e in first)
-    qf, kf, vf = _f64(x["q"]), _f64(x["k"]), _f64(x["v"])
-    for h in range(H):
-        want, wlse = O.masked_attn(qf[h], kf[h // 2], vf[h // 2], Ic[h], Is[h], 16)
-        _check_out(out[0, h].cpu().numpy(), want, f"cores h{h}")
-        assert np.abs(lse[h].cpu().numpy() - wlse).max() < 2e-3
+    kk, vv = k[0, 0].double(), v[0, 0].double()
+    j = torch.arange(S, device="cuda")
+    for h in range(0, H, 1 if H < 4 else 5):
+        cols, offs = (torch.zeros(n, dtype=torch.bool, device="cuda") for _ in range(2))
+        cols[lists[0][h, :len(Ic[h])].long()] = True
+        offs[lists[2][h, :len(Is[h])].long()] = True
+        for i in (0, 1, 63, 64, 255, 256, 1000, 2111, S // 2, S - 258, S - 257, S - 2, S - 1):
+            d = i - j
+            if path == "dense":
+                keep = d >= 0
+            elif path == "strips":
+                keep = (d >= 0) & (cols | offs[d.clamp(min=0)] | (d < w))
+            else:      # block diagonals: an offset block b lies on the diagonals b and b + 1, the window on those it reaches
+                t = i // blk - j // blk
+                diag = torch.zeros(n + 1, dtype=torch.bool, device="cuda")
+                diag[:n] |= offs
+                diag[1:] |= offs
+                diag[:(w + blk - 2) // blk + 1] = True
+                keep = (d >= 0) & (cols[j // blk] | diag[t.clamp(min=0)])
+            s = (kk @ q[0, h, i].double()) / np.sqrt(128.0)
+            s = torch.where(keep, s, torch.tensor(-float("inf"), dtype=torch.float64, device="cuda"))
+            assert abs(float(torch.logsumexp(s, 0)) - float(lse[h, i])) < 2e-3, (h, i)
+            assert float((torch.softmax(s, 0) @ vv - out[0, h, i].double()).abs().max()) < 2e-2, (h, i)
 
 
 # empty lists leave a query tile the four key tiles that hold its window, for up to six parts
