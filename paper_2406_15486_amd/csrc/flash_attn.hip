@@ -160,6 +160,18 @@ __device__ __forceinline__ void wg_barrier() {
 
 // Parts of the query tiles [q0, q1) of a head, ceil((a + 1) / m) for tile a.
 __host__ __device__ inline int parts_upto(int m, int n) { return m * (n / m) * (n / m + 1) / 2 + (n % m) * (n / m + 1); }
+// What a workgroup does: part `split` of n_parts of query tile a of head bh, rows [row_lo, row_hi) of
+// segment seg.  Log-sum-exp: the sampled rows of the segment (a counts from the first of them), and
+// how its keys are cut.  part0: the tile's first part among those of its head.
+struct TileJob {
+  int bh, a, seg, row_lo, row_hi, split, n_parts, part0, lse_parts, k_splits;
+};
+// tile f of the launch (segments one after the other): its segment, and the tile
+__host__ __device__ inline int segment_of(const FlashParams& P, int f) {
+  int m = 0;
+  while (m + 1 < P.n_seg && f >= P.seg[m + 1].tile0) ++m;
+  return m;
+}
 __host__ __device__ inline int parts_before(int m, int q0, int q1) { return parts_upto(m, q1) - parts_upto(m, q0); }
 
 }  // namespace
@@ -177,7 +189,9 @@ __host__ __device__ inline int parts_before(int m, int q0, int q1) { return part
 // PARTS (dense and strip-masked modes): the workgroup takes part `split` of the `n_parts` equal
 // parts of its query tile's schedule and leaves unnormalised sums for parts_combine_kernel.
 template <int MODE, bool OUT_F32, bool IN_PLACE, bool SWEEP, bool PARTS, int CORE>
-__device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, const int a, const int split, const int n_parts) {
+__device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& J) {
+  const int bh = J.bh, a = J.a, split = J.split, n_parts = J.n_parts;
+  const int hs = MODE == 2 ? J.seg * P.n_bh + bh : bh;   // the head's metadata: one set for every segment
   static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -197,8 +211,8 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
 
   const int bkv = ((MODE == 2 ? P.head0 : 0) + bh) / P.group;
   const int S = P.S;
-  const int i0 = P.q_row0 + a * BQ;                     // first query row of the workgroup
-  const int i_last_wg = min(i0 + BQ, P.q_row0 + P.n_qrows) - 1;  // last valid row
+  const int i0 = (MODE == 1 ? J.row_lo : 0) + a * BQ;                     // first query row of the workgroup
+  const int i_last_wg = min(i0 + BQ, J.row_hi) - 1;      // last valid row
   const int iw0 = i0 + 32 * wave;                        // first query row of the wave
   const int a64 = i0 / BK;   // index of the 64-key tile that holds row i0 (i0 % 256 == 0 in MODE 2)
   const uint16_t* kbase = P.k + (size_t)bkv * S * kHeadDim;
@@ -214,30 +228,30 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   const uint16_t* vct = nullptr;
   int n_col_tiles = 0, n_rng = 0;
   if (SWEEP) {
-    dl = P.dlist + (size_t)bh * P.dlist_stride;
-    cbits = P.col_bits + (size_t)bh * P.cb_words;
-    obits = P.off_bits + (size_t)bh * P.rb_words;
+    dl = P.dlist + (size_t)hs * P.dlist_stride;
+    cbits = P.col_bits + (size_t)hs * P.cb_words;
+    obits = P.off_bits + (size_t)hs * P.rb_words;
   } else if (MODE == 2) {
-    cidx = P.col_idx_pad + (size_t)bh * P.cidx_stride;
-    int cnt = min(max(P.col_cnt[bh], 0), S);
+    cidx = P.col_idx_pad + (size_t)hs * P.cidx_stride;
+    int cnt = min(max(P.col_cnt[hs], 0), S);
     int lo = 0, hi = cnt;          // selected columns j <= last row of the tile (ascending list)
     while (lo < hi) {
       int mid = (lo + hi) >> 1;
       if (cidx[mid] <= i_last_wg) lo = mid + 1; else hi = mid;
     }
     n_col_tiles = (lo + BK - 1) / BK;
-    dl = P.dlist + (size_t)bh * P.dlist_stride;
-    int dc = min(max(P.dcnt[bh], 0), P.dlist_stride);
+    dl = P.dlist + (size_t)hs * P.dlist_stride;
+    int dc = min(max(P.dcnt[hs], 0), P.dlist_stride);
     lo = 0; hi = dc;               // tile diagonals d whose key tile a64 + 3 - d is >= 0
     while (lo < hi) {
       int mid = (lo + hi) >> 1;
       if ((dl[mid] & kDiagMask) <= a64 + 3) lo = mid + 1; else hi = mid;
     }
     n_rng = lo;
-    cbits = P.col_bits + (size_t)bh * P.cb_words;
-    obits = P.off_bits + (size_t)bh * P.rb_words;
-    kc = P.kc + (size_t)bh * P.S_pad * kHeadDim;
-    vct = P.vct + (size_t)bh * kHeadDim * P.S_pad;
+    cbits = P.col_bits + (size_t)hs * P.cb_words;
+    obits = P.off_bits + (size_t)hs * P.rb_words;
+    kc = P.kc + (size_t)hs * P.S_pad * kHeadDim;
+    vct = P.vct + (size_t)hs * kHeadDim * P.S_pad;
   }
   int t_base = 0;                        // first key tile of this workgroup's share of the causal sweep
   const int n_sweep = min(i_last_wg, S - 1) / BK + 1;
@@ -246,13 +260,13 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
   // from nothing, and this workgroup takes the parts [part, part_stop) one after the other.
   int part = 0, part_stop = 1;
   if (MODE == 1) {
-    part = P.lse_parts / P.k_splits * split;
-    part_stop = part + P.lse_parts / P.k_splits;
-    t_base = n_sweep * part / P.lse_parts;
-    n_sched = n_sweep * part_stop / P.lse_parts - t_base;
+    part = J.lse_parts / J.k_splits * split;
+    part_stop = part + J.lse_parts / J.k_splits;
+    t_base = n_sweep * part / J.lse_parts;
+    n_sched = n_sweep * part_stop / J.lse_parts - t_base;
   }
   // tile that ends part `part` (counted from t_base); the workgroup's last part ends with the schedule
-  auto end_of_part = [&]() { return part + 1 < part_stop ? n_sweep * (part + 1) / P.lse_parts - t_base - 1 : -1; };
+  auto end_of_part = [&]() { return part + 1 < part_stop ? n_sweep * (part + 1) / J.lse_parts - t_base - 1 : -1; };
   int part_last = MODE == 1 ? __builtin_amdgcn_readfirstlane(end_of_part()) : -1;
   if (PARTS) {
     t_base = n_sched * split / n_parts;
@@ -439,7 +453,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     const int ql = lane & 15;   // query within a group of 16 / row within a 16-row operand
     const int kg = lane >> 4;   // which quarter of the contraction block this lane feeds
     const int i_me = iw0 + ql;                             // this lane's first query row; the second is 16 on
-    auto row_ok = [&](int n) { const int i = i_me + 16 * n; return i <= i_last_wg && (MODE != 2 || i >= P.row_lo); };
+    auto row_ok = [&](int n) { const int i = i_me + 16 * n; return i <= i_last_wg && (MODE != 2 || i >= J.row_lo); };
     // ---- Q^T operand: two groups of 16 queries, 4 contraction steps of 32, resident in registers
     bf16x8 qf[2][4];
 #pragma unroll
@@ -555,7 +569,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
       for (int n = 0; n < 2; ++n) {
         const float l_tot = quad_sum(l_run[n]);
         if (row_ok(n) && kg == 0)
-          P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me + 16 * n - P.q_row0)] = m_run[n] * kLn2 + __logf(l_tot);
+          P.lse[((size_t)part * P.n_slots + J.seg * P.n_bh + bh) * P.n_qrows + (i_me + 16 * n - J.row_lo)] = m_run[n] * kLn2 + __logf(l_tot);
       }
     };
 
@@ -916,7 +930,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
       if (!row_ok(n)) continue;
       const int i = i_me + 16 * n;
       if (PARTS) {
-        const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
+        const size_t slot = (size_t)bh * P.parts_per_head + J.part0 + split;
         const int r = 32 * wave + 16 * n + ql;
         if (kg == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run[n], l_tot);
         float* po = P.part_o + (slot * BQ + r) * kHeadDim + 4 * kg;
@@ -941,7 +955,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     const int ql = lane & 31;   // query within the wave / row within a 32-row operand
     const int hf = lane >> 5;   // which half of the contraction block this lane feeds
     const int i_me = iw0 + ql;                             // this lane's query row
-    const bool row_ok = i_me <= i_last_wg && (MODE != 2 || i_me >= P.row_lo);
+    const bool row_ok = i_me <= i_last_wg && (MODE != 2 || i_me >= J.row_lo);
     // ---- Q^T operand: 8 contraction steps of 16, resident in registers -------
     bf16x8 qf[8];
     {
@@ -1012,7 +1026,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     // so only makes the vmcnt waits of the loop wait for more than they must.
     auto store_part_lse = [&]() __attribute__((always_inline)) {
       const float l_tot = half_sum(l_run);
-      if (row_ok && hf == 0) P.lse[((size_t)part * P.n_bh + bh) * P.n_qrows + (i_me - P.q_row0)] = m_run * kLn2 + __logf(l_tot);
+      if (row_ok && hf == 0) P.lse[((size_t)part * P.n_slots + J.seg * P.n_bh + bh) * P.n_qrows + (i_me - J.row_lo)] = m_run * kLn2 + __logf(l_tot);
     };
 
     // ---- masks ---------------------------------------------------------------------------
@@ -1318,7 +1332,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const int bh, c
     if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
     if (!row_ok) return;
     if (PARTS) {
-      const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a) + split;
+      const size_t slot = (size_t)bh * P.parts_per_head + J.part0 + split;
       const int r = 32 * wave + ql;
       if (hf == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run, l_tot);
       float* po = P.part_o + (slot * BQ + r) * kHeadDim;
@@ -1362,20 +1376,40 @@ template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
 __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
   // ---- which (head, query tile) this workgroup owns ------------------------
   // (the log-sum-exp sweep may also give the keys of a query tile to k_splits workgroups)
-  int bh, a, split = 0, n_parts = 1;
+  TileJob J;
+  J.split = 0; J.n_parts = 1; J.part0 = 0; J.lse_parts = J.k_splits = 1;
   {
     const int bid = blockIdx.x;
+    int f = 0;                           // tile, counted over the segments
     if (PARTS) {
       // heavy (late) query tiles first, the heads of a part side by side
-      bh = bid % P.n_bh;
-      split = bid / P.n_bh;
-      a = P.qtile0 + P.n_qtiles - 1;
-      n_parts = a / P.part_m + 1;
-      while (split >= n_parts) {         // (ends: the grid has exactly the parts of these tiles)
-        split -= n_parts;
-        --a;
-        n_parts = a / P.part_m + 1;
+      // (a segment's values are read once: a load for every tile passed over is 1 us of a small call)
+      J.bh = bid % P.n_bh;
+      J.split = bid / P.n_bh;
+      const int pm = P.part_m;
+      int m = P.n_seg - 1, q0, q1;
+      for (;; --m) {                     // (both loops end: the grid has exactly the parts of these tiles)
+        q0 = P.seg[m].qtile0;
+        q1 = q0 + P.seg[m].n_qtiles;
+        const int n = parts_before(pm, q0, q1);
+        if (J.split < n || m == 0) break;
+        J.split -= n;
       }
+      int a = q1 - 1, before = parts_before(pm, q0, q1), rem;
+      J.n_parts = a / pm + 1;
+      rem = a % pm;
+      while (J.split >= J.n_parts && a > q0) {
+        J.split -= J.n_parts;
+        before -= J.n_parts;
+        --a;
+        if (--rem < 0) {
+          rem = pm - 1;
+          --J.n_parts;
+        }
+      }
+      J.seg = m;
+      J.a = a;
+      J.part0 = P.seg[m].part0 + before - J.n_parts;
     } else if (MODE == 2) {
       // heads are sliced over the 8 XCDs (workgroups go round-robin to XCDs) and an
       // XCD works through one head at a time, heavy (late) query tiles first: the
@@ -1387,56 +1421,74 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
         // through 4 x 32 tiles): there the heavy tiles of all its heads come first.
         const int xcd = bid & 7, slot = bid >> 3, heads = (P.n_bh + 7) >> 3;
         const bool by_tile = P.n_qtiles <= kByTileMax;
-        a = P.n_qtiles - 1 - (by_tile ? slot / heads : slot % P.n_qtiles);
-        bh = xcd + 8 * (by_tile ? slot % heads : slot / P.n_qtiles);
-        if (bh >= P.n_bh) return;
+        f = P.n_qtiles - 1 - (by_tile ? slot / heads : slot % P.n_qtiles);
+        J.bh = xcd + 8 * (by_tile ? slot % heads : slot / P.n_qtiles);
+        if (J.bh >= P.n_bh) return;
       } else {
-        a = P.n_qtiles - 1 - bid / P.n_bh;
-        bh = bid % P.n_bh;
-        if (a < 0) return;
+        f = P.n_qtiles - 1 - bid / P.n_bh;
+        J.bh = bid % P.n_bh;
+        if (f < 0) return;
       }
-      a += P.qtile0;
     } else {
       // a bundle = the query heads sharing one KV head at one query tile; the
       // bundle's workgroups land on one XCD so the K/V stream is shared in L2.
+      // (Log-sum-exp: n_qtiles of every segment, cut by each into its own k_splits.)
       int xcd = bid & 7, slot = bid >> 3;
       int bl = slot / P.group, hg = slot % P.group;
       int bundle = bl * 8 + xcd;
-      const int ks = (MODE == 1) ? P.k_splits : 1;
+      int m = 0;
+      if (MODE == 1) {
+        while (m + 1 < P.n_seg && bundle >= P.n_qtiles * P.seg[m].k_splits * P.n_bkv) {
+          bundle -= P.n_qtiles * P.seg[m].k_splits * P.n_bkv;
+          ++m;
+        }
+        J.lse_parts = P.seg[m].lse_parts;
+        J.k_splits = P.seg[m].k_splits;
+      }
+      const int ks = J.k_splits;
       if (bundle >= P.n_qtiles * ks * P.n_bkv) return;
       const int av = P.n_qtiles * ks - 1 - bundle / P.n_bkv;
-      a = av / ks;
-      split = av % ks;
-      int bkv = bundle % P.n_bkv;
-      bh = bkv * P.group + hg;
+      J.split = av % ks;
+      J.bh = bundle % P.n_bkv * P.group + hg;
+      J.seg = m;
+      J.a = av / ks;
     }
+    if (!PARTS && MODE == 2) {
+      J.seg = segment_of(P, f);
+      J.a = P.seg[J.seg].qtile0 + f - P.seg[J.seg].tile0;
+    }
+    J.row_lo = P.seg[J.seg].row_lo;
+    J.row_hi = P.seg[J.seg].row_hi;
   }
   constexpr int CORE = LONG ? 0 : 1;
   if (MODE == 2) {
     // (diagonal 0 is in every list, and its entry is the first)
-    const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)bh * P.dlist_stride]);
+    const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)(J.seg * P.n_bh + J.bh) * P.dlist_stride]);
     if (first & kSweepBit) {
-      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, CORE>(P, bh, a, split, n_parts);
+      flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, CORE>(P, J);
       return;
     }
     if (CORE == 0 && (P.short_lists || (!IN_PLACE && (first & kSparseBit)))) {
-      flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, bh, a, split, n_parts);
+      flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, J);
       return;
     }
   }
-  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, bh, a, split, n_parts);
+  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, J);
 }
 
 // The parts of a query tile brought to one reference maximum, added in fixed order and
 // normalised.  Eight rows per workgroup, 32 lanes of four columns each.
-template <bool OUT_F32>
+// (SEGMENTS: there are several.  Found in a loop over the arguments, the one of most launches cost 1.1 us of
+// the 7.7 that 8 heads of 3001 tokens take.)
+template <bool OUT_F32, bool SEGMENTS>
 __global__ __launch_bounds__(256) void parts_combine_kernel(FlashParams P) {
   const int bh = blockIdx.y, tid = threadIdx.x;
   const int r_launch = blockIdx.x * 8 + (tid >> 5);
-  const int a = P.qtile0 + r_launch / BQ, r = r_launch % BQ;
+  const int seg = SEGMENTS ? segment_of(P, r_launch / BQ) : 0;
+  const int a = P.seg[seg].qtile0 + r_launch / BQ - P.seg[seg].tile0, r = r_launch % BQ;
   const int i = a * BQ + r, c4 = tid & 31;
-  if (i < P.row_lo || i >= P.n_qrows) return;
-  const size_t slot = (size_t)bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles) + parts_before(P.part_m, P.qtile0, a);
+  if (i < P.seg[seg].row_lo || i >= P.seg[seg].row_hi) return;
+  const size_t slot = (size_t)bh * P.parts_per_head + P.seg[seg].part0 + parts_before(P.part_m, P.seg[seg].qtile0, a);
   const int n_parts = a / P.part_m + 1;
   const float2* ml = reinterpret_cast<const float2*>(P.part_ml) + slot * BQ + r;
   const float4* po = reinterpret_cast<const float4*>(P.part_o + (slot * BQ + r) * kHeadDim) + c4;
@@ -1464,9 +1516,12 @@ __global__ __launch_bounds__(256) void parts_combine_kernel(FlashParams P) {
 // out[i] = log sum_s exp(part[s][i]): the key parts of the log-sum-exp sweep, in fixed order.  A few
 // blocks with up to 64 loads a thread: bound by their latency unless several are in flight (32 parts
 // of 4096 rows one by one / eight at a time: sweep and combination 58.5 / 49.7 us).
-__global__ void lse_combine_kernel(const float* part, float* out, size_t n, int k) {
+// (A segment's values [heads, rows] lie behind each other, its parts n apart; k of them each.)
+struct LseParts { int per_seg, k[kMaxSegs]; };
+__global__ void lse_combine_kernel(const float* part, float* out, size_t n, LseParts L) {
   size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
+  const int k = L.k[i / L.per_seg];
   float m = part[i];
 #pragma unroll 8
   for (int s = 1; s < k; ++s) m = fmaxf(m, part[(size_t)s * n + i]);
@@ -1476,9 +1531,13 @@ __global__ void lse_combine_kernel(const float* part, float* out, size_t n, int 
   out[i] = m + __logf(z);
 }
 
-hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hipStream_t st) {
+hipError_t launch_lse_combine(const FlashParams& P, float* out, hipStream_t st) {
+  const size_t n = (size_t)P.n_slots * P.n_qrows;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(lse_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, out, n, k);
+  LseParts L;
+  L.per_seg = P.n_bh * P.n_qrows;
+  for (int m = 0; m < kMaxSegs; ++m) L.k[m] = m < P.n_seg ? P.seg[m].lse_parts : 1;
+  hipLaunchKernelGGL(lse_combine_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, P.lse, out, n, L);
   return hipGetLastError();
 }
 
@@ -1543,13 +1602,22 @@ void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int
 // 640 31.0 / 30.2, 8 of 768 36.0 / 33.5; blocks 4 of 1024 40.2 / 32.9, of 2047 59.2 / 40.6.
 constexpr int kMinCutTiles = 3;
 constexpr double kTileUs = 1.1, kCombineUs = 3.0, kPartUs = 0.065;
-int flash_parts(int n_bh, int q0, int q1) {
-  if (q1 < kMinCutTiles || (long long)n_bh * (q1 - q0) > kMaxParts) return 0;
-  const double longest = 4.0 * q1, spread = n_bh * 2.0 * ((double)q1 * (q1 + 1) - (double)q0 * (q0 + 1)) / 256;
+// Several segments in one launch are one set of tiles, cut by one m.
+int flash_parts(int n_bh, int n_seg, const SegmentJob* seg) {
+  int q1 = 0, tiles = 0;
+  double spread = 0;
+  for (int k = 0; k < n_seg; ++k) {
+    const int lo = seg[k].qtile0, hi = lo + seg[k].n_qtiles;
+    q1 = q1 > hi ? q1 : hi;
+    tiles += hi - lo;
+    spread += n_bh * 2.0 * ((double)hi * (hi + 1) - (double)lo * (lo + 1)) / 256;
+  }
+  if (q1 < kMinCutTiles || (long long)n_bh * tiles > kMaxParts) return 0;
+  const double longest = 4.0 * q1;
   const int base = (q1 + 5) / 6;
   for (int step : {2, 3, 4, 6, 8}) {
     const int m = (base * step + 1) / 2;
-    const long long n = (long long)n_bh * parts_before(m, q0, q1);
+    const long long n = (long long)n_bh * parts_of(m, n_seg, seg);
     if (n > kMaxParts) continue;
     const double part = 4.0 * m;
     const double t = (part > spread ? part : spread) * kTileUs + kCombineUs + kPartUs * n;
@@ -1558,8 +1626,14 @@ int flash_parts(int n_bh, int q0, int q1) {
   return 0;
 }
 
-size_t flash_parts_bytes(int m, int n_heads, int q0, int q1) {
-  return m == 0 ? 0 : (size_t)n_heads * parts_before(m, q0, q1) * BQ * (kHeadDim + 2) * sizeof(float);
+int parts_of(int m, int n_seg, const SegmentJob* seg) {
+  int n = 0;
+  for (int k = 0; k < n_seg; ++k) n += parts_before(m, seg[k].qtile0, seg[k].qtile0 + seg[k].n_qtiles);
+  return n;
+}
+
+size_t flash_parts_bytes(int m, int n_heads, int n_seg, const SegmentJob* seg) {
+  return m == 0 ? 0 : (size_t)n_heads * parts_of(m, n_seg, seg) * BQ * (kHeadDim + 2) * sizeof(float);
 }
 
 template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
@@ -1590,14 +1664,21 @@ constexpr int kLongDense = 4096, kLongStrips = 49152, kLongBlocks = 24576;
 // a launch whose schedules are cut into parts, and the combination
 static hipError_t launch_parts(int mode, bool out_f32, const FlashParams& P0, hipStream_t st) {
   FlashParams P = P0;
-  const int n = P.n_bh * parts_before(P.part_m, P.qtile0, P.qtile0 + P.n_qtiles);
+  P.parts_per_head = parts_of(P.part_m, P.n_seg, P.seg);
+  for (int k = 1; k < P.n_seg; ++k) P.seg[k].part0 = parts_of(P.part_m, k, P.seg);
+  const int n = P.n_bh * P.parts_per_head;
   P.part_ml = P.part_o + (size_t)n * BQ * kHeadDim;
   hipError_t e = mode == 0 ? launch_one<0, false, false, true, false>(P, n, st)
                : P.cols_in_place ? launch_one<2, false, true, true, false>(P, n, st) : launch_one<2, false, false, true, false>(P, n, st);
   if (e != hipSuccess) return e;
   const dim3 grid(P.n_qtiles * (BQ / 8), P.n_bh);
-  if (out_f32) hipLaunchKernelGGL(parts_combine_kernel<true>, grid, dim3(256), 0, st, P);
-  else hipLaunchKernelGGL(parts_combine_kernel<false>, grid, dim3(256), 0, st, P);
+  if (P.n_seg > 1) {
+    if (out_f32) hipLaunchKernelGGL((parts_combine_kernel<true, true>), grid, dim3(256), 0, st, P);
+    else hipLaunchKernelGGL((parts_combine_kernel<false, true>), grid, dim3(256), 0, st, P);
+  } else {
+    if (out_f32) hipLaunchKernelGGL((parts_combine_kernel<true, false>), grid, dim3(256), 0, st, P);
+    else hipLaunchKernelGGL((parts_combine_kernel<false, false>), grid, dim3(256), 0, st, P);
+  }
   return hipGetLastError();
 }
 
@@ -1607,7 +1688,8 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
   if (mode == 2) {
     grid = (P.n_bh >= 8) ? 8 * P.n_qtiles * ((P.n_bh + 7) / 8) : P.n_qtiles * P.n_bh;
   } else {
-    int bundles = P.n_qtiles * (mode == 1 ? P.k_splits : 1) * P.n_bkv;
+    int bundles = 0;
+    for (int k = 0; k < P.n_seg; ++k) bundles += P.n_qtiles * (mode == 1 ? P.seg[k].k_splits : 1) * P.n_bkv;
     grid = ((bundles + 7) / 8) * 8 * P.group;
   }
   if (grid <= 0) return hipSuccess;

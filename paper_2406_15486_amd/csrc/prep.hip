@@ -73,8 +73,9 @@ __global__ __launch_bounds__(256) void gather_strips_kernel(GatherParams P) {
   if (c0 >= ((cnt + 63) & ~63)) return;   // nothing reads beyond the last partial tile
   // rows of an earlier segment see no key at or after their end: a tile of the ascending
   // list that starts there is left alone
-  if (P.key_limit > 0 && list[c0] >= P.key_limit) return;
-  const size_t kv = (size_t)((P.head0 + g) / P.group) * P.S * kHeadDim;
+  const int key_limit = P.key_limit[g / P.heads_per_seg];
+  if (key_limit > 0 && list[c0] >= key_limit) return;
+  const size_t kv = (size_t)((P.head0 + g % P.heads_per_seg) / P.group) * P.S * kHeadDim;
   uint4 kr[4], vr[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
@@ -235,8 +236,10 @@ __device__ __forceinline__ long long count_col_tiles(const int32_t* list, int n,
 
 // Strip masks: wave w meets the offsets [64 d - 255 + 32 w, 64 d - 161 + 32 w] on diagonal d.
 __device__ __forceinline__ void write_strip_dlist(const MaskPrepParams& P, int h, const uint32_t* ob) {
-  const long long col = count_col_tiles(P.col_idx + (size_t)h * P.S, min(max(P.col_cnt[h], 0), P.S), P.qtile_lo, P.qtile_hi, P.row_hi);
-  write_dlist((P.S + 63) / 64 + 3, P.qtile_lo, P.qtile_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h,
+  const SegmentJob& J = P.seg[h / P.heads_per_seg];
+  const int q_lo = J.qtile0, q_hi = J.qtile0 + J.n_qtiles;
+  const long long col = count_col_tiles(P.col_idx + (size_t)h * P.S, min(max(P.col_cnt[h], 0), P.S), q_lo, q_hi, J.row_hi);
+  write_dlist((P.S + 63) / 64 + 3, q_lo, q_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h,
               [&](int d, int w) {
                 const int lo = max(0, 64 * d - 255 + 32 * w), hi = min(P.S - 1, 64 * d - 255 + 32 * w + 94);
                 return lo <= hi && any_offset(ob, P.off_max, lo, hi);
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(PT) void strip_prep_kernel(MaskPrepParams P, int n_
   const int words = cols ? P.cb_words : P.rb_words;
   const int nw = min(kBitSegWords, words - w0);
   if (nw <= 0) return;
-  if (blockIdx.x == 0 && tid == 0 && P.tiles != nullptr) P.tiles[h] = 0ull;
+  if (blockIdx.x == 0 && tid == 0 && P.tiles != nullptr && h < P.heads_per_seg) P.tiles[h] = 0ull;
   const int32_t* list = (cols ? P.col_idx : P.slash_idx) + (size_t)h * P.S;
   const int n = min(max((cols ? P.col_cnt : P.slash_cnt)[h], 0), P.S);
   // bit x of the offset bitmap is offset off_max - x: the window is the run of bits up to off_max
@@ -335,7 +338,7 @@ __global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
   extern __shared__ __attribute__((aligned(16))) uint32_t bits[];   // block diagonals / key blocks
   const int h = blockIdx.y, tid = threadIdx.x;
   const bool diag = blockIdx.x == 0;
-  if (diag && tid == 0 && P.tiles != nullptr) P.tiles[h] = 0ull;
+  if (diag && tid == 0 && P.tiles != nullptr && h < P.heads_per_seg) P.tiles[h] = 0ull;
   const int32_t* list = (diag ? P.slash_blk : P.col_blk) + (size_t)h * P.nb;
   const int n = min(max((diag ? P.slash_bcnt : P.col_bcnt)[h], 0), P.nb);
   const int n_words = (P.nb + 1) / 32 + 1;
@@ -353,11 +356,13 @@ __global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
   auto has = [&](int b) { return ((bits[b >> 5] >> (b & 31)) & 1u) != 0u; };
   if (diag) {
     // column tiles: the selected key blocks as runs of blk columns
+    const SegmentJob& J = P.seg[h / P.heads_per_seg];
+    const int q_lo = J.qtile0, q_hi = J.qtile0 + J.n_qtiles;
     long long col = 0;
     const int32_t* cb = P.col_blk + (size_t)h * P.nb;
     const int nc = min(max(P.col_bcnt[h], 0), P.nb);
     for (int c = tid; c < nc; c += PT)
-      col += (long long)(P.blk / kFlashBK) * max(P.qtile_hi - max(P.qtile_lo, (int)((long long)cb[c] * P.blk / kFlashBQ)), 0);
+      col += (long long)(P.blk / kFlashBK) * max(q_hi - max(q_lo, (int)((long long)cb[c] * P.blk / kFlashBQ)), 0);
     auto meets = [&](int d, int w) {       // the offsets of the wave on this tile reach into [0, S)
       const int o_lo = 64 * d - 255 + 32 * w;
       return o_lo + 94 >= 0 && o_lo <= P.S - 1;
@@ -366,7 +371,7 @@ __global__ __launch_bounds__(PT) void block_prep_kernel(BlockPrepParams P) {
       const int delta = (32 * w) / P.blk - floor_div(192 - 64 * d, P.blk);
       return delta >= 0 && delta <= P.nb && meets(d, w) && has(delta);
     };
-    write_dlist((P.S + 63) / 64 + 3, P.qtile_lo, P.qtile_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, kept, kept);
+    write_dlist((P.S + 63) / 64 + 3, q_lo, q_hi, col, P.dlist + (size_t)h * P.dlist_stride, P.dcnt + h, kept, kept);
     return;
   }
   const int span = (int)blockIdx.x - 1, n_span = (int)gridDim.x - 1;

@@ -18,6 +18,7 @@ namespace {
 
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+inline size_t most(size_t a, size_t b) { return a > b ? a : b; }
 
 struct Dims {
   int S, S_pad, n_bh, n_bkv, group;
@@ -179,25 +180,70 @@ inline void segment_rows(int S, int n_chunks, int m, int* lo, int* hi) {
   *hi = (m + 1 < n_chunks) ? (m + 1) * itv : S;
 }
 
-size_t parts_room(const Dims& d, int n_chunks) {
-  size_t most = 0;
-  if (d.n_bh > 256) return 0;
-  for (int m = 0; m < n_chunks; ++m) {
-    int lo, hi;
-    segment_rows(d.S, n_chunks, m, &lo, &hi);
-    const int q0 = lo / sa::kFlashBQ, q1 = (hi + sa::kFlashBQ - 1) / sa::kFlashBQ;
-    const size_t n = sa::flash_parts_bytes(sa::flash_parts(d.n_bh, q0, q1), d.n_bh, q0, q1);
-    if (n > most) most = n;
+// the query segments [m0, m0 + n) as the segments of one launch; returns their query tiles
+int segment_jobs(const Dims& d, int n_chunks, int m0, int n, sa::SegmentJob* seg) {
+  int tiles = 0;
+  for (int k = 0; k < n; ++k) {
+    sa::SegmentJob& J = seg[k];
+    memset(&J, 0, sizeof(J));
+    segment_rows(d.S, n_chunks, m0 + k, &J.row_lo, &J.row_hi);
+    J.qtile0 = J.row_lo / sa::kFlashBQ;
+    J.n_qtiles = (J.row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ - J.qtile0;   // the last tile with a row of the segment
+    J.tile0 = tiles;
+    J.lse_parts = J.k_splits = 1;
+    tiles += J.n_qtiles;
   }
-  return align_up(most);
+  return tiles;
 }
 
-// tells the launch P how large the call is (query tiles [q0, q1) of all heads), and cuts it into
+// Several segments go through one launch per step where a workspace of kBatchBytes holds the lists,
+// gathered keys or partial scores of all of them: segments of a few thousand tokens leave most of
+// the chip idle one by one (8 heads x 2 of 5003 tokens in three segments 333 us one by one).
+constexpr size_t kBatchBytes = (size_t)1 << 30;
+bool batch_chunks(const Dims& d, int n_chunks, size_t bytes) {
+  return n_chunks > 1 && n_chunks <= sa::kMaxSegs && (long long)n_chunks * d.n_bh <= 65535 && bytes <= kBatchBytes;
+}
+Dims all_chunks(const Dims& d, int n_chunks) {
+  Dims e = d;
+  e.n_bh = d.n_bh * n_chunks;
+  return e;
+}
+size_t batched_sample_bytes(const Dims& d, int n_chunks, int n_s, int blk) {
+  if (n_chunks < 2 || n_chunks > sa::kMaxSegs) return 0;
+  const size_t b = sample_ws(all_chunks(d, n_chunks), n_s, blk).total;
+  return batch_chunks(d, n_chunks, b) ? b : 0;
+}
+size_t batched_sparse_bytes(const Dims& d, int n_chunks, int blk) {      // blk 1: strips
+  if (n_chunks < 2 || n_chunks > sa::kMaxSegs) return 0;
+  const size_t b = blk > 1 ? block_ws(d, blk, d.n_bh * n_chunks).total : sparse_ws(d, d.n_bh * n_chunks).total;
+  return batch_chunks(d, n_chunks, b) ? b : 0;
+}
+
+size_t parts_room(const Dims& d, int n_chunks) {
+  size_t bytes = 0;
+  if (d.n_bh > 256) return 0;
+  sa::SegmentJob seg[sa::kMaxSegs];
+  for (int m = 0; m < n_chunks; ++m) {
+    segment_jobs(d, n_chunks, m, 1, seg);
+    const size_t n = sa::flash_parts_bytes(sa::flash_parts(d.n_bh, 1, seg), d.n_bh, 1, seg);
+    bytes = most(bytes, n);
+  }
+  if (n_chunks > 1 && n_chunks <= sa::kMaxSegs) {
+    segment_jobs(d, n_chunks, 0, n_chunks, seg);
+    const size_t n = sa::flash_parts_bytes(sa::flash_parts(d.n_bh, n_chunks, seg), d.n_bh, n_chunks, seg);
+    bytes = most(bytes, n);
+  }
+  return align_up(bytes);
+}
+
+// tells the launch P how large the call is (query tiles of all heads in the shortest segment), and cuts it into
 // parts if `room` bytes at `at` hold their sums for n_heads heads
-void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int q0, int q1, void* at, size_t room) {
-  const int m = sa::flash_parts(d.n_bh, q0, q1);
-  P->all_tiles = d.n_bh * (q1 - q0);
-  if (m == 0 || sa::flash_parts_bytes(m, n_heads, q0, q1) > room) return;
+void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int n_seg, const sa::SegmentJob* seg, void* at, size_t room) {
+  const int m = sa::flash_parts(d.n_bh, n_seg, seg);
+  int fewest = seg[0].n_qtiles;
+  for (int k = 1; k < n_seg; ++k) fewest = seg[k].n_qtiles < fewest ? seg[k].n_qtiles : fewest;
+  P->all_tiles = d.n_bh * fewest;
+  if (m == 0 || sa::flash_parts_bytes(m, n_heads, n_seg, seg) > room) return;
   P->part_m = m;
   P->part_o = static_cast<float*>(at);
 }
@@ -256,9 +302,9 @@ sa::FlashParams base_flash(const Dims& d, const void* q, const void* k) {
   P.S = d.S; P.S_pad = d.S_pad;
   P.n_bh = d.n_bh; P.n_bkv = d.n_bkv; P.group = d.group;
   P.scale_log2 = d.scale * 1.4426950408889634f;
-  P.n_qtiles = (d.S + sa::kFlashBQ - 1) / sa::kFlashBQ;
-  P.q_row0 = 0; P.n_qrows = d.S;
-  P.lse_parts = P.k_splits = 1;
+  P.n_seg = 1;
+  P.n_slots = d.n_bh;
+  P.n_qtiles = segment_jobs(d, 1, 0, 1, P.seg);
   return P;
 }
 
@@ -277,16 +323,18 @@ size_t sa_workspace_bytes(int op, const sa_shape* shape, const sa_sampling* samp
   switch (op) {
     case SA_OP_SAMPLE_SCORES:
       if (check_sampling(sampling, d) != SA_OK) return 0;
-      return sample_ws(d, sampling->n_sample_rows, sampling->granularity).total;
+      return most(sample_ws(d, sampling->n_sample_rows, sampling->granularity).total,
+                  batched_sample_bytes(d, chunks, sampling->n_sample_rows, sampling->granularity));
     case SA_OP_SAMPLE_SCORES_MIN:
       if (check_sampling(sampling, d) != SA_OK) return 0;
       return sample_ws(pass_dims(d, 1), sampling->n_sample_rows, sampling->granularity).total;
     case SA_OP_SELECT_STRIPS: return 0;
-    case SA_OP_SPARSE_ATTN: return sparse_ws(d, d.n_bh).total + parts_room(d, chunks);
+    case SA_OP_SPARSE_ATTN: return most(sparse_ws(d, d.n_bh).total, batched_sparse_bytes(d, chunks, 1)) + parts_room(d, chunks);
     case SA_OP_DENSE_ATTN: return dense_ws(d) + parts_room(d, 1);
     case SA_OP_BLOCK_SPARSE_ATTN:
       if (sampling == nullptr || check_granularity(sampling->granularity) != SA_OK) return 0;
-      return block_ws(d, sampling->granularity, d.n_bh).total + parts_room(d, chunks);
+      return most(block_ws(d, sampling->granularity, d.n_bh).total, batched_sparse_bytes(d, chunks, sampling->granularity)) +
+             parts_room(d, chunks);
     default: return 0;
   }
 }
@@ -323,15 +371,15 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
   const size_t n_cand = (size_t)(d.S + blk - 1) / blk;       // scores per head and direction
   const size_t head_elems = (size_t)d.S * sa::kHeadDim;
 
-  for (int m = 0; m < n_chunks; ++m) {
-    // chunk m: the last n_s rows of the m-th of n_chunks query segments
-    int seg_lo, seg_hi;
-    segment_rows(d.S, n_chunks, m, &seg_lo, &seg_hi);
-    const int row_first = seg_hi - n_s;
+  // all chunks of all heads at once if the workspace allows, else chunk after chunk
+  const size_t batched = batched_sample_bytes(d, n_chunks, n_s, blk);
+  const int n_seg = batched > 0 && workspace_bytes >= batched ? n_chunks : 1;
+  for (int m = 0; m < n_chunks; m += n_seg) {
     for (int h0 = 0; h0 < d.n_bh; h0 += heads_per_pass) {
       const int nh = (d.n_bh - h0 < heads_per_pass) ? d.n_bh - h0 : heads_per_pass;
       const Dims pd = pass_dims(d, nh);
-      const SampleWs w = sample_ws(pd, n_s, blk);
+      const int n_slots = n_seg * nh;                          // heads of every chunk
+      const SampleWs w = sample_ws(all_chunks(pd, n_seg), n_s, blk);
       const void* q_pass = static_cast<const uint16_t*>(q) + (size_t)h0 * head_elems;
       const void* k_pass = static_cast<const uint16_t*>(k) + (size_t)(h0 / d.group) * head_elems;
       float* lse = row_lse ? row_lse + (size_t)h0 * n_s : reinterpret_cast<float*>(ws + w.lse);
@@ -342,16 +390,24 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
 
       // pass 1: log-sum-exp of every sampled row (flash sweep without V)
       sa::FlashParams P = base_flash(pd, q_pass, k_pass);
-      sa::lse_splits(row_first, n_s, pd.n_bh, kMaxKeyParts, &P.lse_parts, &P.k_splits);
-      P.lse = P.lse_parts > 1 ? reinterpret_cast<float*>(ws + w.lse_part) : lse;
-      P.q_row0 = row_first;
+      P.n_seg = n_seg;
+      P.n_slots = n_slots;
       P.n_qrows = n_s;
       P.n_qtiles = (n_s + sa::kFlashBQ - 1) / sa::kFlashBQ;
+      int most_parts = 1;
+      segment_jobs(d, n_chunks, m, n_seg, P.seg);
+      for (int c = 0; c < n_seg; ++c) {
+        // chunk m: the last n_s rows of the m-th of n_chunks query segments
+        sa::SegmentJob& J = P.seg[c];
+        J.row_lo = J.row_hi - n_s;
+        sa::lse_splits(J.row_lo, n_s, n_slots, kMaxKeyParts, &J.lse_parts, &J.k_splits);
+        most_parts = J.lse_parts > most_parts ? J.lse_parts : most_parts;
+      }
+      P.lse = most_parts > 1 ? reinterpret_cast<float*>(ws + w.lse_part) : lse;
       {
         Scope sc(SA_K_ROW_LSE, st);
         s = dev(sa::launch_flash(1, false, P, st));
-        if (s == SA_OK && P.lse_parts > 1)
-          s = dev(sa::launch_lse_combine(P.lse, lse, (size_t)pd.n_bh * n_s, P.lse_parts, st));
+        if (s == SA_OK && most_parts > 1) s = dev(sa::launch_lse_combine(P, lse, st));
       }
       if (s != SA_OK) return s;
 
@@ -363,8 +419,9 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
       C.lse = lse;
       C.col = tok_col; C.slash = tok_slash;
       C.partial = reinterpret_cast<float*>(ws + w.partial);
-      C.S = d.S; C.n_s = n_s; C.n_bh = pd.n_bh; C.n_bkv = pd.n_bkv; C.group = pd.group;
-      C.row_first = row_first;
+      C.S = d.S; C.n_s = n_s; C.n_bh = n_slots; C.n_bkv = pd.n_bkv; C.group = pd.group;
+      C.heads_per_seg = nh;
+      for (int c = 0; c < n_seg; ++c) C.row_first[c] = P.seg[c].row_lo;
       C.scale_log2 = P.scale_log2;
       {
         Scope sc(SA_K_SCORE_ACCUM, st);
@@ -375,8 +432,8 @@ sa_status sa_sample_scores(const sa_shape* shape, const sa_sampling* sampling,
         Scope sc(SA_K_SCORE_FINAL, st);
         s = dev(sa::launch_score_finalize(C, st));
         // block_reduction: the per-token scores summed over blocks of blk keys / offsets
-        if (s == SA_OK && blk > 1) s = dev(sa::launch_block_reduce(tok_col, out_col, pd.n_bh, d.S, blk, st));
-        if (s == SA_OK && blk > 1) s = dev(sa::launch_block_reduce(tok_slash, out_slash, pd.n_bh, d.S, blk, st));
+        if (s == SA_OK && blk > 1) s = dev(sa::launch_block_reduce(tok_col, out_col, n_slots, d.S, blk, st));
+        if (s == SA_OK && blk > 1) s = dev(sa::launch_block_reduce(tok_slash, out_slash, n_slots, d.S, blk, st));
       }
       if (s != SA_OK) return s;
     }
@@ -473,15 +530,16 @@ sa_status sa_select_chunked(const sa_shape* shape, const sa_sampling* sampling,
 }  // extern "C"
 
 namespace {
-// merge_index for the heads [h0, h0 + nh) under one set of lists: bitmaps, tile-diagonal
-// list and the gathered K / V^T of the kept columns, all in workspace slots 0 .. nh-1.
+// merge_index for the heads [h0, h0 + nh) under the lists of n_seg segments: bitmaps, tile-diagonal
+// list and the gathered K / V^T of the kept columns, all in workspace slots 0 .. n_seg * nh - 1.
+// (Several segments: all heads, whose lists lie behind each other.)
 // granularity 1: strip lists (per key / per offset); otherwise lists of blocks.
 // On return *cnt_used points at the column counts the kernel must read (slot-indexed).
 sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h0, int nh, size_t n_cand,
                         const void* k, const void* v,
                         const int32_t* col_idx, const int32_t* col_cnt,
-                        const int32_t* slash_idx, const int32_t* slash_cnt, int32_t local_window, int row_lo, int row_hi,
-                        uint64_t* tiles_to_clear, char* ws, hipStream_t st, const int32_t** cnt_used) {
+                        const int32_t* slash_idx, const int32_t* slash_cnt, int32_t local_window,
+                        int n_seg, const sa::SegmentJob* seg, uint64_t* tiles_to_clear, char* ws, hipStream_t st, const int32_t** cnt_used) {
   const SparseWs& w = bw.sp;
   const bool blocks = granularity != 1;
   Scope sc(SA_K_MASK_PREP, st);
@@ -501,9 +559,9 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     M.col_bits = col_bits; M.off_bits = off_bits; M.dlist = dlist; M.dcnt = dcnt;
     M.col_idx = col_idx; M.col_cnt = col_cnt; M.slash_idx = slash_idx; M.slash_cnt = slash_cnt;
     M.tiles = tiles;
-    M.n_bh = nh; M.S = d.S; M.window = local_window;
+    M.n_bh = n_seg * nh; M.heads_per_seg = nh; M.S = d.S; M.window = local_window;
     M.cb_words = w.cb_words; M.rb_words = w.rb_words; M.dlist_stride = w.dlist_stride; M.off_max = w.off_max;
-    M.qtile_lo = row_lo / sa::kFlashBQ; M.qtile_hi = (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ; M.row_hi = row_hi;
+    memcpy(M.seg, seg, n_seg * sizeof(*seg));
     s = dev(sa::launch_mask_prep(M, st));
   } else {
     // the same metadata from block lists; from here on the selected key blocks are
@@ -515,10 +573,10 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     B.tok_cnt = reinterpret_cast<int32_t*>(ws + bw.tok_cnt);
     B.col_bits = col_bits; B.off_bits = off_bits; B.dlist = dlist; B.dcnt = dcnt;
     B.tiles = tiles;
-    B.n_bh = nh; B.S = d.S; B.window = local_window;
+    B.n_bh = n_seg * nh; B.heads_per_seg = nh; B.S = d.S; B.window = local_window;
     B.cb_words = w.cb_words; B.rb_words = w.rb_words; B.dlist_stride = w.dlist_stride; B.off_max = w.off_max;
     B.blk = granularity; B.nb = bw.nb;
-    B.qtile_lo = row_lo / sa::kFlashBQ; B.qtile_hi = (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ; B.row_hi = row_hi;
+    memcpy(B.seg, seg, n_seg * sizeof(*seg));
     *cnt_used = B.tok_cnt;
     // (key blocks are runs of consecutive keys and are read in place: nothing to gather)
     return dev(sa::launch_block_prep(B, st));
@@ -533,15 +591,17 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
   G.idx = col_idx; G.cnt = col_cnt;
   G.kc = reinterpret_cast<uint16_t*>(ws + w.kc); G.vct = reinterpret_cast<uint16_t*>(ws + w.vct);
   G.idx_pad = reinterpret_cast<int32_t*>(ws + w.cidx);
-  G.n_heads = nh; G.group = d.group; G.head0 = h0; G.S = d.S; G.S_pad = d.S_pad;
+  G.n_heads = n_seg * nh; G.heads_per_seg = nh; G.group = d.group; G.head0 = h0; G.S = d.S; G.S_pad = d.S_pad;
   G.dlist = dlist; G.dlist_stride = w.dlist_stride;
-  G.key_limit = row_hi < d.S ? row_hi : 0;     // the rows of this segment end at row_hi: later keys are never read
+  // the rows of a segment end at row_hi: later keys are never read
+  for (int k = 0; k < n_seg; ++k) G.key_limit[k] = seg[k].row_hi < d.S ? seg[k].row_hi : 0;
   return dev(sa::launch_gather_strips(G, st));
 }
 
-// the strip-masked kernel on query tiles [qtile0, qtile0 + n_qtiles) of the heads [h0, h0 + nh)
+// the strip-masked kernel on query tiles [qtile0, qtile0 + n_qtiles) of the heads [h0, h0 + nh), or on all tiles of
+// several segments
 sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, int nh, int qtile0, int n_qtiles,
-                        int row_lo, int row_hi, const void* q, const void* k, const int32_t* col_cnt,
+                        int n_seg, const sa::SegmentJob* seg, const void* q, const void* k, const int32_t* col_cnt,
                         void* out, int out_dtype, float* out_lse, uint64_t* tiles, char* ws, size_t parts_at, size_t ws_bytes,
                         hipStream_t st) {
   sa::FlashParams P = base_flash(d, q, k);
@@ -551,12 +611,16 @@ sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, i
   P.lse = out_lse ? out_lse + (size_t)h0 * d.S : nullptr;
   P.tiles = tiles ? reinterpret_cast<unsigned long long*>(tiles) + h0 : nullptr;
   P.n_bh = nh; P.head0 = h0;
-  P.qtile0 = qtile0;
+  // only the rows of a segment are computed and written under its lists (a query tile that straddles two
+  // segments is visited for both)
+  P.n_seg = n_seg;
+  P.n_slots = n_seg * nh;
+  memcpy(P.seg, seg, n_seg * sizeof(*seg));
   P.n_qtiles = n_qtiles;
-  // only rows [row_lo, row_hi) are computed and written (a query tile that straddles two
-  // segments is visited by both launches, each writing its own rows)
-  P.row_lo = row_lo;
-  P.n_qrows = row_hi;
+  if (n_seg == 1) {
+    P.seg[0].qtile0 = qtile0;
+    P.seg[0].n_qtiles = n_qtiles;
+  }
   P.vt = reinterpret_cast<const uint16_t*>(ws + w.vt);
   P.cols_in_place = blocks ? 1 : 0;
   P.kc = blocks ? nullptr : reinterpret_cast<const uint16_t*>(ws + w.kc);
@@ -569,8 +633,8 @@ sa_status launch_attend(const Dims& d, const SparseWs& w, bool blocks, int h0, i
   P.dcnt = reinterpret_cast<const int32_t*>(ws + w.dcnt);
   P.cidx_stride = d.S_pad; P.cb_words = w.cb_words; P.rb_words = w.rb_words;
   P.dlist_stride = w.dlist_stride; P.off_max = w.off_max;
-  // (decided for all heads and all query tiles of the segment, whatever this launch takes of them)
-  set_parts(&P, d, nh, row_lo / sa::kFlashBQ, (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ, ws + parts_at, ws_bytes - parts_at);
+  // (decided for all heads and all query tiles of the segments, whatever this launch takes of them)
+  set_parts(&P, d, nh, n_seg, seg, ws + parts_at, ws_bytes - parts_at);
   Scope sc(SA_K_SPARSE_FLASH, st);
   return dev(sa::launch_flash(2, out_dtype == SA_OUT_F32, P, st));
 }
@@ -609,6 +673,13 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
   if (!blocks) bw.sp = sparse_ws(d, heads_per_pass, true);
   s = check_ws(workspace, workspace_bytes, blocks ? bw.total : bw.sp.total);
   if (s != SA_OK) return s;
+  // all segments at once if the workspace allows
+  const size_t batched = part == nullptr ? batched_sparse_bytes(d, n_chunks, granularity) : 0;
+  const int n_seg = batched > 0 && workspace_bytes >= batched ? n_chunks : 1;
+  if (n_seg > 1) {
+    bw = block_ws(d, blocks ? granularity : 64, n_seg * d.n_bh);
+    if (!blocks) bw.sp = sparse_ws(d, n_seg * d.n_bh, true);
+  }
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   {
@@ -618,11 +689,9 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
     if (s != SA_OK) return s;
   }
   const size_t n_cand = (size_t)(d.S + granularity - 1) / granularity;   // list capacity per head
-  for (int m = 0; m < n_chunks; ++m) {
-    int row_lo, row_hi;
-    segment_rows(d.S, n_chunks, m, &row_lo, &row_hi);
-    const int qtile0 = row_lo / sa::kFlashBQ;
-    const int qtile1 = (row_hi + sa::kFlashBQ - 1) / sa::kFlashBQ;    // one past the last tile with a row of the segment
+  for (int m = 0; m < n_chunks; m += n_seg) {
+    sa::SegmentJob seg[sa::kMaxSegs];
+    const int tiles_all = segment_jobs(d, n_chunks, m, n_seg, seg);
     const size_t chunk_off = (size_t)m * d.n_bh;
     for (int h0 = 0; h0 < d.n_bh; h0 += heads_per_pass) {
       const int nh = (d.n_bh - h0 < heads_per_pass) ? d.n_bh - h0 : heads_per_pass;
@@ -630,13 +699,12 @@ sa_status sparse_attn(const sa_shape* shape, int n_chunks, int granularity, cons
       s = prepare_heads(d, bw, granularity, h0, nh, n_cand, k, v,
                         col_idx_all + chunk_off * n_cand, col_cnt_all + chunk_off,
                         slash_idx_all + chunk_off * n_cand, slash_cnt_all + chunk_off,
-                        local_window, row_lo, row_hi, m == 0 ? tiles : nullptr, ws, st, &cnt_used);
+                        local_window, n_seg, seg, m == 0 ? tiles : nullptr, ws, st, &cnt_used);
       if (s != SA_OK) return s;
-      const int segs = (n_segments < qtile1 - qtile0) ? n_segments : (qtile1 - qtile0);
+      const int segs = (n_segments < tiles_all) ? n_segments : tiles_all;
       for (int g = 0; g < segs; ++g) {
-        const int a0 = qtile0 + (int)((long long)(qtile1 - qtile0) * g / segs);
-        const int a1 = qtile0 + (int)((long long)(qtile1 - qtile0) * (g + 1) / segs);
-        s = launch_attend(d, bw.sp, blocks, h0, nh, a0, a1 - a0, row_lo, row_hi, q, k, cnt_used, out, out_dtype, out_lse,
+        const int a0 = (int)((long long)tiles_all * g / segs), a1 = (int)((long long)tiles_all * (g + 1) / segs);
+        s = launch_attend(d, bw.sp, blocks, h0, nh, seg[0].qtile0 + a0, a1 - a0, n_seg, seg, q, k, cnt_used, out, out_dtype, out_lse,
                           tiles, ws, blocks ? bw.total : bw.sp.total, workspace_bytes, st);
         if (s != SA_OK) return s;
       }
@@ -722,7 +790,7 @@ sa_status sa_dense_attn(const sa_shape* shape, const void* q, const void* k, con
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
-  set_parts(&P, d, d.n_bh, 0, P.n_qtiles, static_cast<char*>(workspace) + dense_ws(d), workspace_bytes - dense_ws(d));
+  set_parts(&P, d, d.n_bh, 1, P.seg, static_cast<char*>(workspace) + dense_ws(d), workspace_bytes - dense_ws(d));
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }
@@ -749,7 +817,7 @@ sa_status sa_dense_attn_static(const sa_shape* shape, const void* q, const void*
   if (s != SA_OK) return s;
   sa::FlashParams P = base_flash(d, q, k);
   P.vt = vt; P.out = out; P.lse = out_lse;
-  set_parts(&P, d, d.n_bh, 0, P.n_qtiles, static_cast<char*>(ws) + SA_STATIC_SCRATCH_BYTES, sa::kMaxPartsBytes);
+  set_parts(&P, d, d.n_bh, 1, P.seg, static_cast<char*>(ws) + SA_STATIC_SCRATCH_BYTES, sa::kMaxPartsBytes);
   Scope sc(SA_K_DENSE_FLASH, st);
   return dev(sa::launch_flash(0, out_dtype == SA_OUT_F32, P, st));
 }

@@ -12,6 +12,18 @@ constexpr int kMaxSeqLen = 1 << 24;   // kernels keep 32-bit byte offsets into V
 constexpr int kSweepBit = 1 << 23;   // in every entry of a tile-diagonal list: the head is swept
 constexpr int kSparseBit = 1 << 22;  // ... or its tiles leave many waves without work
 
+// One launch may take up to kMaxSegs query segments (Algorithm 1's chunks), each with lists of its own;
+// tile0, part0: tiles and parts of the segments before.
+constexpr int kMaxSegs = 8;
+struct SegmentJob {
+  int qtile0, n_qtiles, tile0;   // modes 0 and 2: its query tiles of the launch
+  int row_lo, row_hi;            // its rows of the launch: others are neither computed nor written (mode 1: the sampled rows)
+  int part0;                     // (set by the launch)
+  int lse_parts;                 // mode 1: parts the keys of a query tile are cut into (a power of two); lse is
+                                 // [lse_parts, n_slots, n_qrows] partial values, combined by launch_lse_combine
+  int k_splits;                  // ... and the workgroups they are given to (a power of two, <= lse_parts)
+};
+
 struct FlashParams {
   const uint16_t* q;        // [n_bh, S, 128] bf16
   const uint16_t* k;        // [n_bkv, S, 128] bf16
@@ -23,21 +35,19 @@ struct FlashParams {
   int head0;                // strip-masked mode: q, out, lse, tiles and the per-head metadata start at this
                             // (batch*q-)head, n_bh counts the heads of this pass; KV head = (head0 + h) / group
   float scale_log2;         // softmax scale * log2(e)
-  int n_qtiles;             // 256-row query tiles to process
-  int qtile0;               // strip-masked mode: the first of them (a segment of the queries)
-  int q_row0, n_qrows;      // first query row and number of rows (sampled rows in mode 1)
+  int n_seg;                // segments of the launch; per-head metadata and row log-sum-exps are [n_seg, n_bh]
+  SegmentJob seg[kMaxSegs];
+  int n_slots;              // n_seg * n_bh
+  int n_qtiles;             // 256-row query tiles of all segments; mode 1: of each
+  int n_qrows;              // mode 1: sampled rows of a segment
   int cols_in_place;        // strip-masked mode, block lists: column tiles are read from k / vt themselves
                             // (kc, vct unused); col_idx_pad then holds runs of 64 consecutive keys per tile
-  int row_lo;               // strip-masked mode: rows below it are neither computed for nor written
-                            // (rows [row_lo, n_qrows) of the launch's query tiles are; q_row0 = 0 there)
-  int lse_parts;            // mode 1: parts the keys of a query tile are cut into (a power of two); lse is
-                            // [lse_parts, n_bh, n_qrows] partial values, combined by launch_lse_combine
-  int k_splits;             // ... and the workgroups they are given to (a power of two, <= lse_parts)
-  int all_tiles;            // modes 0 and 2: query tiles of all heads of the call (of the segment), whatever this launch takes
+  int all_tiles;            // modes 0 and 2: query tiles of all heads of the call (of its shortest segment here), whatever this launch takes
   int short_lists;          // mode 2 (set by the launch): heads in two passes take core 1
   int part_m;               // modes 0 and 2: > 0: tile a's schedule is cut into ceil((a + 1) / part_m) workgroups
   float* part_o;            // ... whose sums [part, 256, 128] and then [part, 256, 2] lie here (flash_parts_bytes)
   float* part_ml;           // (set by the launch)
+  int parts_per_head;       // (set by the launch)
   // strip-masked mode only
   const uint16_t* kc;           // [n_bh, S_pad, 128] K rows gathered by column index
   const uint16_t* vct;          // [n_bh, 128, S_pad] V rows gathered and transposed
@@ -56,13 +66,14 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
 // parts of the keys of a query tile (from the sequence alone, at most max_parts) and the workgroups
 // that share them (from the heads of the launch too)
 void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int* workgroups);
-// part_m of a launch over the query tiles [q0, q1) of n_bh heads (0: not cut), and the bytes of
-// the partial sums of n_heads of them
+// part_m of a launch over segments of n_bh heads (0: not cut), and the bytes of the partial sums of
+// n_heads of them
 constexpr int kMaxParts = 256;
 constexpr size_t kMaxPartsBytes = (size_t)kMaxParts * kFlashBQ * (kHeadDim + 2) * 4;
-int flash_parts(int n_bh, int q0, int q1);
-size_t flash_parts_bytes(int m, int n_heads, int q0, int q1);
-hipError_t launch_lse_combine(const float* part, float* out, size_t n, int k, hipStream_t st);
+int flash_parts(int n_bh, int n_seg, const SegmentJob* seg);
+int parts_of(int m, int n_seg, const SegmentJob* seg);
+size_t flash_parts_bytes(int m, int n_heads, int n_seg, const SegmentJob* seg);
+hipError_t launch_lse_combine(const FlashParams& P, float* out, hipStream_t st);
 
 // vt[g][d][c] = v[g][c][d], zero up to the 64-key tile that ends the sequence
 hipError_t launch_transpose(const uint16_t* v, uint16_t* vt, int n, int S, int S_pad, hipStream_t st);
@@ -81,7 +92,8 @@ struct GatherParams {
   int S, S_pad;
   const int32_t* dlist;     // [n_heads, dlist_stride]: nothing is gathered for a head that is swept
   int dlist_stride;
-  int key_limit;            // > 0: no reader looks at a key >= key_limit; tiles of 64 list entries
+  int heads_per_seg;        // n_heads counts the heads of every segment
+  int key_limit[kMaxSegs];  // of a segment, > 0: no reader looks at a key >= key_limit; tiles of 64 list entries
                             // that start there are not gathered (their idx_pad entries still are written)
 };
 hipError_t launch_gather_strips(const GatherParams& P, hipStream_t st);
@@ -93,7 +105,8 @@ struct MaskPrepParams {
   int32_t* dlist; int32_t* dcnt;
   unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
-  int qtile_lo, qtile_hi, row_hi;                      // the query tiles this mask is for, and the end of their rows
+  int heads_per_seg;                                   // n_bh counts the heads of every segment
+  SegmentJob seg[kMaxSegs];                            // the query tiles a segment's masks are for, and the end of their rows
 };
 hipError_t launch_mask_prep(const MaskPrepParams& P, hipStream_t st);
 
@@ -107,7 +120,8 @@ struct BlockPrepParams {
   int32_t* dlist; int32_t* dcnt;
   unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
-  int qtile_lo, qtile_hi, row_hi;                      // the query tiles this mask is for, and the end of their rows
+  int heads_per_seg;                                   // n_bh counts the heads of every segment
+  SegmentJob seg[kMaxSegs];                            // the query tiles a segment's masks are for, and the end of their rows
   int blk, nb, idx_pad_stride;
 };
 hipError_t launch_block_prep(const BlockPrepParams& P, hipStream_t st);
@@ -120,8 +134,9 @@ struct ScoreParams {
   float* col;               // [n_bh, S]
   float* slash;             // [n_bh, S]
   float* partial;           // workspace for slash partial sums
-  int S, n_s, n_bh, n_bkv, group;
-  int row_first;            // the sampled rows are [row_first, row_first + n_s)
+  int S, n_s, n_bh, n_bkv, group;   // n_bh: heads of every segment
+  int heads_per_seg;
+  int row_first[kMaxSegs];  // the sampled rows of a segment are [row_first, row_first + n_s)
   float scale_log2;
   int n_kblocks, n_chunks, chunk_rows, win;   // win = floats per (key block, chunk) partial
 };

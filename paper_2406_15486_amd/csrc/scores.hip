@@ -54,12 +54,13 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
   const int ql = lane & 31, hf = lane >> 5;
   const int kb = blockIdx.x, bh = blockIdx.z;
   const int S = P.S;
-  const int r0 = P.row_first;                       // sampled rows [r0, r_end)
+  const int seg = bh / P.heads_per_seg, hq = bh % P.heads_per_seg;   // bh counts the heads of every segment
+  const int r0 = P.row_first[seg];                  // sampled rows [r0, r_end)
   const int r_end = r0 + P.n_s;
   const int j0 = kb * KB;
   if (r_end - 1 < j0) return;                       // every sampled row lies above these keys
   const int jw = j0 + 64 * wave;
-  const int bkv = bh / P.group;
+  const int bkv = hq / P.group;
   const float c2 = P.scale_log2;
 
   // K^T operands of this wave's 2 x 32 keys (zero beyond the sequence end)
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void score_accumulate_kernel(ScoreParams P)
       kf[sb][ks] = as_bf16x8(v);
     }
   }
-  const uint16_t* qbase = P.q + (size_t)bh * S * kHeadDim;
+  const uint16_t* qbase = P.q + (size_t)hq * S * kHeadDim;
   const float* lbase = P.lse + (size_t)bh * P.n_s;
   const int qrow_t = tid >> 4, qcol_t = tid & 15;
   // slot of (row rb + m, key jw + 32 sb + ql) in this wave's window:
@@ -277,7 +278,7 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(ScoreParams P, cons
   const int x = blockIdx.x * 256 + threadIdx.x;
   const int S = P.S;
   if (x >= S) return;
-  const int r0 = P.row_first;
+  const int r0 = P.row_first[bh / P.heads_per_seg];
   double c = 0.0, s = 0.0;
   for (int ch = 0; ch < P.n_chunks; ++ch) {
     int row0 = r0 + ch * QC;

@@ -418,6 +418,38 @@ def test_cores_of_the_attention_kernels(path, S, H):
             assert float((torch.softmax(s, 0) @ vv - out[0, h, i].double()).abs().max()) < 2e-2, (h, i)
 
 
+# segments shorter than a query tile, as long as one, ragged; as many as one launch takes and one more; cut into parts and not
+@pytest.mark.parametrize("S,H,C,blk", [(1301, 2, 8, 1), (1301, 2, 9, 1), (768, 1, 3, 1), (2600, 4, 3, 128), (4611, 17, 2, 1), (4611, 16, 4, 64)])
+def test_segments_in_one_launch(S, H, C, blk):
+    """The segments of a call go through one launch per step where the workspace holds the lists of
+    all of them, and one after the other where it does not: the same scores bit for bit, and
+    attention to the rounding of the probabilities (other cuts of the tiles, another core)."""
+    import paper_2406_15486_amd as sa
+    B = sa.binding
+    _say(f"segments S={S} C={C} blk={blk}")
+    g = torch.Generator(device="cuda").manual_seed(S + C)
+    q, k, v = (torch.randn(2, h, S, 128, generator=g, device="cuda").bfloat16() for h in (H, 1, 1))
+    sh, n_s = sa.Shape(2, H, 1, S), min(65, S // C)
+    one = sa.sa_workspace_bytes(B.SA_OP_SAMPLE_SCORES, sh, n_s, granularity=blk)
+    need = sa.sa_workspace_bytes(B.SA_OP_SAMPLE_SCORES, sh, n_s, n_chunks=C, granularity=blk)
+    assert (need > one) == (C <= 8)
+    scores = [sa.sa_sample_scores(q, k, n_s, granularity=blk, n_chunks=C,
+                                  workspace=torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")) for size in (need, one)]
+    for a, b in zip(*scores):
+        assert torch.equal(a, b)
+    lists = sa.sa_select_chunked(*scores[0], 0.8, 0.3, sh, C, blk)
+    outs = []
+    op = B.SA_OP_SPARSE_ATTN if blk == 1 else B.SA_OP_BLOCK_SPARSE_ATTN
+    bare = _bare("strips" if blk == 1 else "blocks", 2 * H, 2, S)
+    for size in (sa.sa_workspace_bytes(op, sh, n_chunks=C, granularity=blk), bare):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+        outs.append(sa.sa_sparse_attn_chunked(q, k, v, *lists, 5, C, blk, out_dtype=sa.SA_OUT_F32, workspace=ws, want_lse=True, want_tiles=True))
+    torch.cuda.synchronize()
+    (x, lx, tx), (y, ly, ty) = outs
+    assert (x - y).abs().max().item() <= v.abs().max().item() / 256 and (lx - ly).abs().max().item() < 1e-3
+    assert torch.isfinite(x).all() and (S != 4611 or torch.equal(tx, ty))
+
+
 # empty lists leave a query tile the four key tiles that hold its window, for up to six parts
 @pytest.mark.parametrize("S,C", [(1281, 1), (1536, 1), (2600, 2), (3300, 3)])
 @pytest.mark.parametrize("n_col,n_off", [(0, 0), (1, 0), (0, 1), (65, 2)])
