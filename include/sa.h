@@ -45,12 +45,16 @@
  *     batch * n_q_heads heads have more than 256 query tiles of 256 rows (in
  *     every segment, for n_chunks > 1).  Calls with fewer are small for this
  *     GPU: they may cut the keys of a query tile into parts, summed apart in
- *     the workspace, and seq_len and batch * n_q_heads decide whether and how.
+ *     the workspace, or form a row's products in another order, and seq_len
+ *     and batch * n_q_heads decide whether and how.
  *     The same sequence in another batch, or beside other heads, then agrees
  *     to the rounding of bf16 probabilities, not bit for bit.  So does a call
  *     whose workspace is smaller than what sa_workspace_bytes (or
  *     sa_partitioned_workspace_bytes) asks for but holds all but the partial
  *     sums: it is accepted, and nothing is cut.
+ *   n_chunks > 1: sa_workspace_bytes asks for room to work on all segments at
+ *     once (up to eight segments and 1 GiB); a call with less, down to the size
+ *     for one segment, takes them one after the other.
  */
 #ifndef SA_H
 #define SA_H
@@ -236,8 +240,8 @@ sa_status sa_block_sparse_attn(const sa_shape* shape, int32_t granularity,
  * running to seq_len: for those rows the mask is that of
  * sa_sparse_attn (granularity 1) or sa_block_sparse_attn with chunk m's lists.
  * Workspace: that of SA_OP_SPARSE_ATTN or SA_OP_BLOCK_SPARSE_ATTN for the same
- * sampling (the size for one segment is accepted too, but may not hold the
- * partial sums of small problems).  `tiles` counts over all segments.
+ * sampling (the size for one segment is accepted too: the segments then go one
+ * after the other, and the partial sums of small problems may not fit).  `tiles` counts over all segments.
  */
 sa_status sa_select_chunked(const sa_shape* shape, const sa_sampling* sampling,
                             const float* col_scores, const float* slash_scores,
