@@ -13,8 +13,9 @@
 // (V^T, [d][key]) so both MFMA A operands are 16-byte LDS reads.  Four stages of each are
 // resident in LDS, filled by direct global->LDS loads two and three tiles ahead.
 //
-// What bounds it.  Long launches run at the card's power limit: the clock falls to 1.5 to 2 GHz,
-// and taking instructions or waits out of the loop returns little unless it saves energy.
+// What bounds it.  Long launches run at the card's power limit: the clock falls to 1.5 to 2 GHz (dense
+// 1.5 with 32x32x16 MFMAs, 1.9 with 16x16x32), and taking instructions or waits out of the loop returns
+// little unless it saves energy.
 // Launches whose waves often have no work run at 2.3 GHz and are bound by one wave's chain of
 // instructions from barrier to barrier.  Hence two cores (parameter CORE of flash_body):
 //
