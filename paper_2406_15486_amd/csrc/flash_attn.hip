@@ -195,13 +195,15 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
   const int hs = MODE == 2 ? J.seg * P.n_bh + bh : bh;   // the head's metadata: one set for every segment
   static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
+  static_assert(CORE == 0 || MODE != 1, "the log-sum-exp sweep runs on core 0");
+  static_assert(CORE == 1 || !PARTS, "cut tiles run on core 1");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool WITH_V = (MODE != 1);
   // Where a wave issues its share of the tile loads.  Each direct load stalls the wave
   // 40-100 cycles; the two MFMA phases of a SIMD hardly overlap, so a stall there costs
   // the iteration, while the softmax phase is the shorter one and has room.  The
   // log-sum-exp sweep is the other way round (short MFMA phase, no P V).
-  constexpr bool kLoadsInSoftmax = (MODE != 1);
+  constexpr bool kLoadsInSoftmax = WITH_V;
   constexpr int kOffDump = WITH_V ? OFF_DUMP : OFF_DUMP_LSE;
 
   const int tid = threadIdx.x;
@@ -504,21 +506,10 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     };
     // P V: on entry the ring holds V operands 0..7 (read during the softmax phase);
     // the second half of the sweep re-fills it with the first 8 K operands of the next
-    // tile (read even when that tile turns out to need no work from this wave).  The
-    // loads of the tiles further ahead go out under the MFMAs, one per 3 MFMAs.
-    auto mm_pv = [&](int bufp, int bufq, auto&& setup_a, auto&& setup_v, auto&& setup_k, auto&& look, auto&& decide) {
+    // tile (read even when that tile turns out to need no work from this wave).
+    auto mm_pv = [&](int bufp, int bufq, auto&& look, auto&& decide) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        // scalar bookkeeping in small pieces, so that no gap between two MFMAs grows long
-        if (!kLoadsInSoftmax) {
-          if (i == 1) setup_a();
-          if (i == 2) setup_v();
-          if (i == 4) load_v_one(0);
-          if (i == 5) setup_k();
-          if (i == 7) load_v_one(1);
-          if (i == 10) load_k_one(0);
-          if (i == 13) load_k_one(1);
-        }
         if (i == 3) look();                          // read the words that say whether the next tile needs this wave
         if (i == 9) decide();                        // ... and decide, under the MFMAs
         const int sb = i >> 3, mb = i & 7;
@@ -538,15 +529,13 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       for (int i = 0; i < 8; ++i) ld_k(i, i, bufq);
       SA_PIN();
     };
-    // K Q^T: the ring holds K operands 0..7.  `with_loads`: no P V sweep went before,
-    // so this sweep issues the loads of the tiles further ahead.
+    // K Q^T: the ring holds K operands 0..7.  Without P V this sweep issues the loads of the tiles
+    // further ahead, one every six MFMAs.
     // Element r of s[n][b] is key j0 + 32 (b / 2) + 8 kg + 4 (b % 2) + r against query i_me + 16 n.
-    auto mm_qk = [&](int bufq, bool with_loads) {
+    auto mm_qk = [&](int bufq) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        if (with_loads && !kLoadsInSoftmax) {
-          if (i == 2) load_v_one(0);
-          if (i == 5) load_v_one(1);
+        if (!kLoadsInSoftmax) {
           if (i == 8) load_k_one(0);
           if (i == 11) load_k_one(1);
         }
@@ -783,10 +772,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     auto mfma_phase = [&](auto kc, int u) __attribute__((always_inline)) {
       forget_scores();                         // consumed by the softmax phase before
       const bool have = is_real(kc, u);
-      auto setup_a = [&]() { dma_aux(kc, u + 3, dq3); };
-      auto setup_v = [&]() { load_v_begin(kc, u + 2, dq2); };
-      auto setup_k = [&]() { load_k_begin(kc, u + 3, dq3); };
-      auto ahead_setup = [&]() { setup_a(); setup_v(); setup_k(); };
       // (nothing is in flight: the V operands were requested a softmax ago.  Told so, the compiler does not
       // wait for the whole ring where the paths below meet in front of the K Q^T sweep.)
       if (WITH_V && !decltype(kc)::INTERIOR) __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -798,30 +783,28 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       if (pv) {
         auto look = [&]() { if (late && have) act_word(kc, u, aw0); };
         auto decide = [&]() { if (late) act_n = have && tile_active(kc, u, dq0, aw0); };
-        mm_pv((u - 1) & (NSTAGE - 1), u & (NSTAGE - 1), setup_a, setup_v, setup_k, look, decide);
+        mm_pv((u - 1) & (NSTAGE - 1), u & (NSTAGE - 1), look, decide);
       } else {
-        if (!kLoadsInSoftmax) ahead_setup();
+        if (!kLoadsInSoftmax) load_k_begin(kc, u + 3, dq3);
         if (late && have) {
           act_word(kc, u, aw0);
           act_n = tile_active(kc, u, dq0, aw0);
         }
         if (act_n) warm_k(u & (NSTAGE - 1)); else forget_ring();
       }
-      if (act_n) mm_qk(u & (NSTAGE - 1), !pv);
+      if (act_n) mm_qk(u & (NSTAGE - 1));
       __builtin_amdgcn_s_setprio(0);
-      if (!kLoadsInSoftmax && !pv && !act_n) {
-        load_v_one(0); load_v_one(1); load_k_one(0); load_k_one(1);
-      }
+      if (!kLoadsInSoftmax && !act_n) { load_k_one(0); load_k_one(1); }
       tiles_done += act_n ? 1 : 0;
       act_t = act_n;
       // everything but this phase's loads and the K loads of the one before has landed
-      // (the wave that also fetched aux words waits for one load more than it must)
-      if (!kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
+      if (!kLoadsInSoftmax) vm_wait<4>();
     };
     // before the barrier that ends an iteration everything has landed but that iteration's
     // loads and the K loads of the one before
+    // (the wave that also fetched aux words waits for one load more than it must)
     auto end_of_iteration_wait = [&]() {
-      if (kLoadsInSoftmax) { if (WITH_V) vm_wait<6>(); else vm_wait<4>(); }
+      if (kLoadsInSoftmax) vm_wait<6>();
     };
 
     // prologue: K(0..2), V(0..1) and the aux words of tiles 0..2
@@ -930,16 +913,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       const float l_tot = quad_sum(l_run[n]);
       if (!row_ok(n)) continue;
       const int i = i_me + 16 * n;
-      if (PARTS) {
-        const size_t slot = (size_t)bh * P.parts_per_head + J.part0 + split;
-        const int r = 32 * wave + 16 * n + ql;
-        if (kg == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run[n], l_tot);
-        float* po = P.part_o + (slot * BQ + r) * kHeadDim + 4 * kg;
-#pragma unroll
-        for (int mb = 0; mb < 8; ++mb)
-          *reinterpret_cast<float4*>(po + 16 * mb) = make_float4(o[n][mb][0], o[n][mb][1], o[n][mb][2], o[n][mb][3]);
-        continue;
-      }
       if (P.lse != nullptr && kg == 0) P.lse[(size_t)bh * S + i] = m_run[n] * kLn2 + __logf(l_tot);
       const float inv = 1.0f / l_tot;
       const size_t at = ((size_t)bh * S + i) * kHeadDim + 4 * kg;
@@ -1021,13 +994,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
         }
         s[h] = mfma_32x32x16(as_bf16x8(R[i & 7]), qf[j], s[h]);
       }
-    };
-
-    // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
-    // so only makes the vmcnt waits of the loop wait for more than they must.
-    auto store_part_lse = [&]() __attribute__((always_inline)) {
-      const float l_tot = half_sum(l_run);
-      if (row_ok && hf == 0) P.lse[((size_t)part * P.n_slots + J.seg * P.n_bh + bh) * P.n_qrows + (i_me - J.row_lo)] = m_run * kLn2 + __logf(l_tot);
     };
 
     // ---- masks ---------------------------------------------------------------------------
@@ -1127,7 +1093,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       constexpr bool PREV = decltype(prev_tag)::value, CUR = decltype(cur_tag)::value, AHEAD = decltype(ahead_tag)::value;
       constexpr int KIND = decltype(kc)::KIND;
       constexpr int MM = (MODE == 2 && !IN_PLACE && (KIND == 2 || (SWEEP && decltype(kc)::INTERIOR))) ? 1 : decltype(kc)::INTERIOR ? 0 : 2;
-      using St = Steps<PREV && WITH_V, CUR>;
+      using St = Steps<PREV, CUR>;
       constexpr int H = St::HALF;
       if (!AHEAD) {
 #pragma unroll
@@ -1185,25 +1151,15 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
             const float alpha = fast_exp2(m_run - m_new);
             m_run = m_new;
             l_run *= alpha;
-            if (WITH_V) {
 #pragma unroll
-              for (int mb = 0; mb < 4; ++mb)
+            for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
-            }
+              for (int r = 0; r < 16; ++r) o[mb][r] *= alpha;
             rs = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; ++r) element(r);
           }
           l_run += rs;
-        }
-        // (a part ends well before the diagonal: every wave that has rows works on its last tile)
-        if (MODE == 1 && h == 0 && PREV && u - 1 == part_last) {
-          store_part_lse();
-          ++part;
-          part_last = __builtin_amdgcn_readfirstlane(end_of_part());
-          m_run = kNegBig;
-          l_run = 0.f;
         }
       };
       half(std::integral_constant<int, 0>{});
@@ -1216,7 +1172,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     // workgroup barrier ends it.  Slot t % 4 of the K (V^T) ring is re-filled with tile t + 4 from
     // iteration t + 1 (t + 2) on, after the barrier that follows its last reader.  A load is waited for
     // by the wave that issued it before a barrier: loads complete in order, and before the barrier that
-    // ends iteration u everything has landed but that iteration's four (two) loads, so that V(u+1)
+    // ends iteration u everything has landed but that iteration's four loads, so that V(u+1)
     // and K(u+2) are there: what iteration u+1 reads, and the first operands of the next that it
     // reads ahead.
     unsigned long long tiles_done = 0;
@@ -1282,7 +1238,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       }
       tiles_done += act ? 1 : 0;
       act_prev = act;
-      if (WITH_V) vm_wait<4>(); else vm_wait<2>();
+      vm_wait<4>();
       // (the operands read ahead stay in flight: their stages are not re-filled in the next iteration)
       if constexpr (decltype(ahead)::value) wg_meet(); else wg_barrier();
       SA_PIN();
@@ -1293,11 +1249,10 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     // (at most 256) lie in the last five gathered tiles, so the iterations n + 1 <
     // n_col_tiles - 5 see gathered tiles only, with work for every wave and nothing to mask;
     // the iterations n > n_col_tiles see range tiles only; the few in between take the
-    // general form.  Dense and log-sum-exp sweeps: the tiles below key tile a64 (the one
+    // general form.  Dense and swept tiles: the tiles below key tile a64 (the one
     // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
     // past the end of the schedule.
     const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
-                                   : (MODE == 1 && i_last_wg - i0 < BQ - 32) ? 0      // (waves without rows look at every tile)
                                    : max(min(a64 - t_base - 1, n_tiles - 4), 0);
     const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
     const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
@@ -1306,7 +1261,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       if (n_gen0 <= 0) return;
       iteration(typename decltype(kc)::AtFirst{}, NO, n++);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_operand(Steps<WITH_V, true>{}, i, n);
+      for (int i = 0; i < 8; ++i) load_operand(Steps<true, true>{}, i, n);
       for (; n < n_gen0; ++n) iteration(kc, YES, n);
       act_prev = true;
     };
@@ -1325,10 +1280,6 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
 
     // ---- epilogue -------------------------------------------------------------
-    if (MODE == 1) {
-      store_part_lse();
-      return;
-    }
     float l_tot = half_sum(l_run);
     if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
     if (!row_ok) return;
@@ -1346,25 +1297,23 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       return;
     }
     if (P.lse != nullptr && hf == 0) P.lse[(size_t)bh * S + i_me] = m_run * kLn2 + __logf(l_tot);
-    if (WITH_V) {
-      float inv = 1.0f / l_tot;
-      size_t rowoff = ((size_t)bh * S + i_me) * kHeadDim;
+    float inv = 1.0f / l_tot;
+    size_t rowoff = ((size_t)bh * S + i_me) * kHeadDim;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+    for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          int d = 32 * mb + 8 * g + 4 * hf;
-          float x0 = o[mb][4 * g] * inv, x1 = o[mb][4 * g + 1] * inv;
-          float x2 = o[mb][4 * g + 2] * inv, x3 = o[mb][4 * g + 3] * inv;
-          if (OUT_F32) {
-            float4 v4 = {x0, x1, x2, x3};
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + rowoff + d) = v4;
-          } else {
-            uint2 v2 = {pack_bf16x2(x0, x1), pack_bf16x2(x2, x3)};
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + rowoff + d) = v2;
-          }
+      for (int g = 0; g < 4; ++g) {
+        int d = 32 * mb + 8 * g + 4 * hf;
+        float x0 = o[mb][4 * g] * inv, x1 = o[mb][4 * g + 1] * inv;
+        float x2 = o[mb][4 * g + 2] * inv, x3 = o[mb][4 * g + 3] * inv;
+        if (OUT_F32) {
+          float4 v4 = {x0, x1, x2, x3};
+          *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + rowoff + d) = v4;
+        } else {
+          uint2 v2 = {pack_bf16x2(x0, x1), pack_bf16x2(x2, x3)};
+          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + rowoff + d) = v2;
         }
-    }
+      }
   }
 #undef SA_PIN
 }
@@ -1462,16 +1411,18 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
     J.row_hi = P.seg[J.seg].row_hi;
   }
   constexpr int CORE = LONG ? 0 : 1;
-  if (MODE == 2) {
+  if constexpr (MODE == 2) {
     // (diagonal 0 is in every list, and its entry is the first)
     const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)(J.seg * P.n_bh + J.bh) * P.dlist_stride]);
     if (first & kSweepBit) {
       flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, CORE>(P, J);
       return;
     }
-    if (CORE == 0 && (P.short_lists || (!IN_PLACE && (first & kSparseBit)))) {
-      flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, J);
-      return;
+    if constexpr (CORE == 0) {
+      if (P.short_lists || (!IN_PLACE && (first & kSparseBit))) {
+        flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, J);
+        return;
+      }
     }
   }
   flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, J);
