@@ -17,12 +17,15 @@
 // 1.5 with 32x32x16 MFMAs, 1.9 with 16x16x32), and taking instructions or waits out of the loop returns
 // little unless it saves energy.
 // Launches whose waves often have no work run at 2.3 GHz and are bound by one wave's chain of
-// instructions from barrier to barrier.  Hence two cores (parameter CORE of flash_body):
+// instructions from barrier to barrier.  Hence two cores, one of them in two shapes (parameter CORE of
+// flash_body):
 //
 // Core 0, 16x16x32 MFMAs (two groups of 16 queries per wave, one LDS operand for both): the same
 // products as 32x32x16 at 14 % less energy (an MFMA loop 2038 against 1752 TFLOP/s, with an LDS
 // operand each 1790 against 1565), but a vector port that is blocked ~9 cycles by twice as many
-// MFMAs.  The waves form two groups of four (rows 0..127 and 128..255); waves
+// MFMAs.  Core 2, the same schedule with 32x32x16 MFMAs (32 queries per wave), for launches that do not
+// reach the power limit; its results are those of core 0 bit for bit.
+// The waves form two groups of four (rows 0..127 and 128..255); waves
 // w and w+4 share a SIMD.  Left alone, two waves that alternate an MFMA section
 // and a vector-ALU (softmax) section fall into step - both on the matrix pipe,
 // then both on the vector pipe - and each pipe idles half the time.  Here the
@@ -35,12 +38,13 @@
 // Core 1, 32x32x16 MFMAs (32 queries per wave): every wave issues the softmax of one 32-key half
 // between the MFMAs of the next, so that a tile is one chain of about half the length.
 //
-// Both against core 0 with 32x32x16 MFMAs as it was before, whole path or kernel: dense 16K 1948 / 1860 us
-// (core 0) and 1961 (core 1); 8K swept 672 / 620, 652; blocks of 128 at 32K 3261 / 3040, 3146; 64K head
-// patterns 35.2 / 34.1, 35.2 ms; 50001 tokens at alpha = 0.8 5383 / 5430, 5230 us; runs of four offsets
-// every 300 of 64K 20.6 / 20.4, 16.2 ms, every 1000 6.97 / 6.85, 5.47 ms.
-// The log-sum-exp sweep (core 0) stages no V and needs half the registers: two of its
-// workgroups share a CU.
+// Core 2 / core 0 / core 1, whole path or kernel: dense 16K 1948 / 1860 / 1961 us, 8 heads of 8300 174 / 187 / 177;
+// 8K swept 672 / 620 / 652; blocks of 128 at 32K 3261 / 3040 / 3146, swept, 16 heads of 4500 165 / 176 / 170; 64K head
+// patterns 35.2 / 34.1 / 35.2 ms; 50001 tokens at alpha = 0.8 5383 / 5430 / 5230 us; runs of four offsets
+// every 300 of 64K 20.6 / 20.4 / 16.2 ms, every 1000 6.97 / 6.85 / 5.47 ms.
+// The log-sum-exp sweep (core 2) stages no V and needs half the registers: two of its
+// workgroups share a CU, and it is bound by their vector instructions.  On core 0 16 heads of 4000 tokens and 256
+// rows 19.7 / 22.8 us, 32 of 16384 and 832 132 / 143, but of 65536 and 3328 1628 / 1582.
 #include <type_traits>
 
 #include "sa_device.h"
@@ -195,8 +199,8 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
   const int hs = MODE == 2 ? J.seg * P.n_bh + bh : bh;   // the head's metadata: one set for every segment
   static_assert(!SWEEP || MODE == 2, "only the strip mask is swept");
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
-  static_assert(CORE == 0 || MODE != 1, "the log-sum-exp sweep runs on core 0");
-  static_assert(CORE == 1 || !PARTS, "cut tiles run on core 1");
+  static_assert(CORE == 2 || MODE != 1, "the log-sum-exp sweep runs on core 2");
+  static_assert(CORE != 0 || !PARTS, "cut tiles run on cores 1 and 2");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool WITH_V = (MODE != 1);
   // Where a wave issues its share of the tile loads.  Each direct load stalls the wave
@@ -452,57 +456,72 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
   };
 
 #define SA_PIN() __builtin_amdgcn_sched_barrier(0)
-  if constexpr (CORE == 0) {
-    const int ql = lane & 15;   // query within a group of 16 / row within a 16-row operand
-    const int kg = lane >> 4;   // which quarter of the contraction block this lane feeds
+  if constexpr (CORE != 1) {
+    // Two shapes of the MFMAs, the same results bit for bit: both form a score and an element of O by the same
+    // additions in the same order (eight products after eight), and the sums and references below are kept
+    // for the same groups of keys.
+    // CORE 0, 16x16x32: a lane has two queries, 16 apart, and eight keys of each 32.
+    // CORE 2, 32x32x16: a lane has one query, and two groups of eight keys of each 32, 16 apart.
+    // `n` is the query of a lane or the group of its keys.
+    constexpr bool WIDE = CORE == 2;
+    constexpr int NQ = WIDE ? 1 : 2;                       // queries of a lane
+    using Acc = std::conditional_t<WIDE, f32x16, f32x4>;
+    constexpr int NR = WIDE ? 16 : 4, NO = WIDE ? 4 : 16, NS = WIDE ? 2 : 8;   // elements of an accumulator, accumulators of O and of S
+    const int ql = WIDE ? lane & 31 : lane & 15;   // query within a group / row within an operand
+    const int kg = WIDE ? lane >> 5 : lane >> 4;   // which part of the contraction block this lane feeds
     const int i_me = iw0 + ql;                             // this lane's first query row; the second is 16 on
     auto row_ok = [&](int n) { const int i = i_me + 16 * n; return i <= i_last_wg && (MODE != 2 || i >= J.row_lo); };
-    // ---- Q^T operand: two groups of 16 queries, 4 contraction steps of 32, resident in registers
-    bf16x8 qf[2][4];
+    // ---- Q^T operand: two groups of 16 queries and 4 contraction steps of 32 (or 32 queries and 8 of 16), resident in registers
+    constexpr int KS = 8 / NQ;
+    bf16x8 qf[8];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
+    for (int n = 0; n < NQ; ++n) {
       int qr = row_ok(n) ? i_me + 16 * n : max(min(i_last_wg, S - 1), 0);
       const uint16_t* qrow = P.q + ((size_t)bh * S + qr) * kHeadDim;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        qf[n][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * 32 + kg * 8));
+      for (int ks = 0; ks < KS; ++ks)
+        qf[KS * n + ks] = as_bf16x8(*reinterpret_cast<const uint4*>(qrow + ks * (kHeadDim / KS) + kg * 8));
     }
 
-    f32x4 o[2][8];
+    Acc o[NO];                             // query n: o[8 n ..]
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int x = 0; x < NO; ++x)
 #pragma unroll
-      for (int mb = 0; mb < 8; ++mb)
+      for (int r = 0; r < NR; ++r) o[x][r] = 0.f;
+    float m_run[NQ];                       // reference maximum, in log2 units (score * scale * log2 e)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[n][mb][r] = 0.f;
-    float m_run[2] = {kNegBig, kNegBig};   // reference maximum, in log2 units (score * scale * log2 e)
-    float l_run[2] = {0.f, 0.f};           // running sum of exp2 for this lane's keys
+    for (int n = 0; n < NQ; ++n) m_run[n] = kNegBig;
+    constexpr int NL = MODE == 1 ? 1 : 2;  // (the log-sum-exp sweep, bound by vector instructions, has one shape and one sum)
+    float l_run[2] = {0.f, 0.f};           // running sums of exp2 for this lane's keys
     const float c2 = P.scale_log2;
 
     // ---- operand ring and the MFMA phase -------------------------------------------
-    // A phase takes up to 32 operands of 16 rows from LDS, each for one MFMA per group of 16
-    // queries: 16 of P V(t-1) (head-dim blocks 0..7 for each of two 32-key halves) and 16 of
-    // K Q^T(t) (16-key blocks 0..3 for each of 4 contraction steps).  They come through a ring of
-    // 8 registers x 16 bytes: after the MFMAs of operand i have consumed slot i % 8, operand
-    // i + 8 is read into it, so every read has 14 MFMAs (~250 cycles) to return and the
-    // matrix pipe does not wait on LDS round trips.  sched_barrier pins the order: the
+    // A phase takes up to 32 operands from LDS: 16 of P V(t-1) (16 rows: head-dim blocks 0..7 for each of
+    // two 32-key halves; 32 rows: blocks 0..3 for each of four 16-key groups) and 16 of
+    // K Q^T(t) (16-key blocks 0..3 for each of 4 contraction steps; 32-key halves for each of 8).  They
+    // come through a ring of 8 registers x 16 bytes: after the MFMAs of operand i (one per group of 16
+    // queries, or one) have consumed slot i % 8, operand i + 8 is read into it, so every read has the MFMAs of seven
+    // operands (~250 cycles) to return and the matrix pipe does not wait on LDS round trips.  sched_barrier pins the order: the
     // compiler would otherwise sink each read down to its use.
-    f32x4 s[2][4];
+    Acc s[NS];
     uint4 pk[2][2];
     uint4 R[8];
-    // K operand i = 4 ks + b: contraction step ks, 16-key block b
+    // score e of 32-key half sb and query / key group n: see mm_qk
+    auto score_at = [](int sb, int n, int e) { return WIDE ? sb : 4 * n + 2 * sb + (e >> 2); };
+    auto score_el = [](int n, int e) { return WIDE ? 8 * n + e : e & 3; };
+    // K operand i = 4 ks + b: contraction step ks, 16-key block b (2 ks + b: step ks, half b)
     auto ld_k = [&](int slot, int i, int buf) {
-      // row p = 16 b + ql; logical chunk 4 ks + kg lives at physical chunk (4 ks + kg) ^ (p & 15)
-      const int b = i & 3, ks = i >> 2;
-      const char* kp = smem + OFF_K + buf * KTILE_B + (16 * b + ql) * KROW_B;
-      R[slot] = *reinterpret_cast<const uint4*>(kp + (((4 * ks + kg) ^ ql) << 4));
+      // row p = 16 b + ql (32 b + ql); logical chunk 4 ks + kg (2 ks + kg) lives at physical chunk (..) ^ (p & 15)
+      const int b = WIDE ? i & 1 : i & 3, ks = WIDE ? i >> 1 : i >> 2;
+      const char* kp = smem + OFF_K + buf * KTILE_B + ((WIDE ? 32 : 16) * b + ql) * KROW_B;
+      R[slot] = *reinterpret_cast<const uint4*>(kp + ((((WIDE ? 2 : 4) * ks + kg) ^ (WIDE ? ql & 15 : ql)) << 4));
     };
-    // V^T operand i = 8 sb + mb: keys 32 sb .., head-dim block mb
+    // V^T operand i = 8 sb + mb: keys 32 sb .., head-dim block mb (8 sb + 4 n + mb: keys 32 sb + 16 n ..)
     auto ld_v = [&](int slot, int i, int buf) {
-      // row d = 16 mb + ql; logical chunk 4 sb + kg lives at physical chunk (..) ^ ((d >> 1) & 7)
-      const int sb = i >> 3, mb = i & 7;
-      const char* vp = smem + OFF_V + buf * VTILE_B + (16 * mb + ql) * VROW_B;
-      R[slot] = *reinterpret_cast<const uint4*>(vp + (((4 * sb + kg) ^ (ql >> 1)) << 4));
+      // row d = 16 mb + ql (32 mb + ql); logical chunk 4 sb + kg (4 sb + 2 n + kg) lives at physical chunk (..) ^ ((d >> 1) & 7)
+      const int sb = i >> 3, mb = WIDE ? i & 3 : i & 7, n = WIDE ? (i >> 2) & 1 : 0;
+      const char* vp = smem + OFF_V + buf * VTILE_B + ((WIDE ? 32 : 16) * mb + ql) * VROW_B;
+      R[slot] = *reinterpret_cast<const uint4*>(vp + (((4 * sb + 2 * n + kg) ^ (WIDE ? (ql >> 1) & 7 : ql >> 1)) << 4));
     };
     // P V: on entry the ring holds V operands 0..7 (read during the softmax phase);
     // the second half of the sweep re-fills it with the first 8 K operands of the next
@@ -512,11 +531,15 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       for (int i = 0; i < 16; ++i) {
         if (i == 3) look();                          // read the words that say whether the next tile needs this wave
         if (i == 9) decide();                        // ... and decide, under the MFMAs
-        const int sb = i >> 3, mb = i & 7;
+        const int sb = i >> 3;
+        if constexpr (WIDE) {                                                // O^T += V^T P^T
+          o[i & 3] = mfma_32x32x16(as_bf16x8(R[i & 7]), as_bf16x8(pk[(i >> 2) & 1][sb]), o[i & 3]);
+        } else {
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {                                        // O^T += V^T P^T
-          const int n = (i & 1) ? 1 - m : m;
-          o[n][mb] = mfma_16x16x32(as_bf16x8(R[i & 7]), as_bf16x8(pk[n][sb]), o[n][mb]);
+          for (int m = 0; m < 2; ++m) {
+            const int n = (i & 1) ? 1 - m : m, x = 8 * n + (i & 7);
+            o[x] = mfma_16x16x32(as_bf16x8(R[i & 7]), as_bf16x8(pk[n][sb]), o[x]);
+          }
         }
         SA_PIN();
         if (i + 8 < 16) ld_v(i & 7, i + 8, bufp); else ld_k(i & 7, i - 8, bufq);
@@ -530,8 +553,9 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       SA_PIN();
     };
     // K Q^T: the ring holds K operands 0..7.  Without P V this sweep issues the loads of the tiles
-    // further ahead, one every six MFMAs.
-    // Element r of s[n][b] is key j0 + 32 (b / 2) + 8 kg + 4 (b % 2) + r against query i_me + 16 n.
+    // further ahead, one every three operands.
+    // Element r of s[4 n + b] is key j0 + 32 (b / 2) + 8 kg + 4 (b % 2) + r against query i_me + 16 n.
+    // (WIDE: of s[b] key j0 + 32 b + 16 (r / 8) + 8 kg + r % 8 against query i_me.)
     auto mm_qk = [&](int bufq) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -539,12 +563,16 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
           if (i == 8) load_k_one(0);
           if (i == 11) load_k_one(1);
         }
-        const int b = i & 3, ks = i >> 2;
+        const int b = WIDE ? i & 1 : i & 3, ks = WIDE ? i >> 1 : i >> 2;
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const int n = (i & 1) ? 1 - m : m;
-          if (ks == 0) s[n][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-          s[n][b] = mfma_16x16x32(as_bf16x8(R[i & 7]), qf[n][ks], s[n][b]);
+        for (int m = 0; m < NQ; ++m) {
+          const int n = (!WIDE && (i & 1)) ? 1 - m : m, x = 4 * n + b;
+          if (ks == 0) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) s[x][r] = 0.f;
+          }
+          if constexpr (WIDE) s[x] = mfma_32x32x16(as_bf16x8(R[i & 7]), qf[ks], s[x]);
+          else s[x] = mfma_16x16x32(as_bf16x8(R[i & 7]), qf[KS * n + ks], s[x]);
         }
         SA_PIN();
         if (i + 8 < 16) ld_k(i & 7, i + 8, bufq);
@@ -554,10 +582,16 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
 
     // log-sum-exp of part `part` of this lane's row (mode 1).  The store joins the loads in flight and
     // so only makes the vmcnt waits of the loop wait for more than they must.
+    // (one order of the four groups of keys in both shapes)
+    auto row_sum = [&](int n) __attribute__((always_inline)) -> float {
+      if constexpr (NL == 1) return half_sum(l_run[0]);
+      else if constexpr (WIDE) return half_sum(l_run[0]) + half_sum(l_run[1]);
+      else return quad_sum(l_run[n]);
+    };
     auto store_part_lse = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int n = 0; n < 2; ++n) {
-        const float l_tot = quad_sum(l_run[n]);
+      for (int n = 0; n < NQ; ++n) {
+        const float l_tot = row_sum(n);
         if (row_ok(n) && kg == 0)
           P.lse[((size_t)part * P.n_slots + J.seg * P.n_bh + bh) * P.n_qrows + (i_me + 16 * n - J.row_lo)] = m_run[n] * kLn2 + __logf(l_tot);
       }
@@ -572,12 +606,15 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       // Mask: one 32-bit pattern per lane and 32-key half, set = keep: bit e (e = 0..7) <-> key
       // j0 + 32 sb + 8 kg + e against the lane's SECOND query, bit 16 + e against its first.  (The
       // offset of the second query is the larger one by 16, so a window of the reversed offset
-      // bitmap has its bits 16 places lower.)  The pattern is built per tile kind; one loop
+      // bitmap has its bits 16 places lower.)  WIDE: bit 16 n + e <-> key j0 + 32 sb + 16 n + 8 kg + e.
+      // Either way bit b is offset first_off - 32 sb - b.  The pattern is built per tile kind; one loop
       // applies it (a 1-bit signed extract and a bitwise select between the score and -inf per element).
       bool masked = false;                   // wave-uniform
       uint32_t km[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+      const int first_off = i_me - (j0 + 8 * kg) + (WIDE ? 0 : 16);
       // keep key <= query, i.e. e <= tl for the first query, e <= tl + 16 for the second
       auto causal = [](int tl) -> uint32_t {
+        if (WIDE) return tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u);
         auto low = [](int n) { return (1u << min(max(n, 0), 8)) - 1u; };   // the lowest n of 8 bits
         return (low(tl + 1) << 16) | low(tl + 17);
       };
@@ -594,11 +631,17 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
 #pragma unroll
           for (int sb = 0; sb < 2; ++sb) {
             uint32_t m = 0;
-            const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 8 * kg);
-            int4 x0 = ip[0], x1 = ip[1];
-            int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m |= ((jj[e] <= i_me ? 1u : 0u) << (16 + e)) | ((jj[e] <= i_me + 16 ? 1u : 0u) << e);
+            for (int g = 0; g < (WIDE ? 2 : 1); ++g) {
+              const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 16 * g + 8 * kg);
+              int4 x0 = ip[0], x1 = ip[1];
+              int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                if (WIDE) m |= (jj[e] <= i_me ? 1u : 0u) << (16 * g + e);
+                else m |= ((jj[e] <= i_me ? 1u : 0u) << (16 + e)) | ((jj[e] <= i_me + 16 ? 1u : 0u) << e);
+              }
+            }
             km[sb] = m;
           }
         }
@@ -606,20 +649,18 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
         masked = true;
         const uint32_t* mw = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
         const int wb = (P.off_max - (i0 - j0 + BQ - 1)) >> 5;
-        const int tl = i_me - (j0 + 8 * kg);                 // offset of the first query and key e = 0
-        const int x0 = P.off_max - (tl + 16);                // >= 0: the window starts with the second query's
+        const int x0 = P.off_max - first_off;                // >= 0 by construction of the bitmap
         const int k = (x0 >> 5) - wb;                        // 0 .. 9: word of the staged window
         const uint32_t w0 = mw[k], w1 = mw[k + 1], w2 = mw[k + 2];
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
-          // bit b of the window <-> offset tl + 16 - 32 sb - b
           const uint32_t ow = __builtin_amdgcn_alignbit(sb == 0 ? w1 : w2, sb == 0 ? w0 : w1, x0 & 31);
           const uint32_t cb = __builtin_amdgcn_ubfe(mw[16 + sb], 8 * kg, 8);   // bit e <-> key is a selected column
-          const uint32_t cw = cb | (cb << 16);
+          const uint32_t cw = WIDE ? mw[16 + sb] >> (8 * kg) : cb | (cb << 16);
           // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
           // column bit, unlike an offset bit, says nothing about j <= i)
           km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
-          if (SWEEP && !INTERIOR) km[sb] &= causal(tl - 32 * sb);
+          if (SWEEP && !INTERIOR) km[sb] &= causal(first_off - (WIDE ? 0 : 16) - 32 * sb);
         }
         // a tile that keeps every pair (a whole block of the block mask, the inside of a
         // band of offsets) needs no masking at all
@@ -629,23 +670,27 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
 #pragma unroll
         for (int n = 0; n < 2; ++n)
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
+          for (int sb = 0; sb < 2; ++sb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(km[b >> 1], (n == 0 ? 16 : 0) + 4 * (b & 1) + r, 1);   // all-ones where kept
-              s[n][b][r] = __uint_as_float((__float_as_uint(s[n][b][r]) & keep) | (0xFF800000u & ~keep));
+            for (int e = 0; e < 8; ++e) {
+              const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(km[sb], ((WIDE ? n == 1 : n == 0) ? 16 : 0) + e, 1);   // all-ones where kept
+              const int x = score_at(sb, n, e), r = score_el(n, e);
+              s[x][r] = __uint_as_float((__float_as_uint(s[x][r]) & keep) | (0xFF800000u & ~keep));
             }
       }
 
       // the operand ring is idle: fetch the first 8 V operands of this tile's P V now,
       // so that the reads return under the exponentials
-      SA_PIN();
-      fetch();
+      // (the log-sum-exp sweep fetches nothing: a pin alone costs it 4 %)
       if (WITH_V) {
+        SA_PIN();
+        fetch();
         SA_PIN();
 #pragma unroll
         for (int i = 0; i < 8; ++i) ld_v(i, i, buf);
         SA_PIN();
+      } else {
+        fetch();
       }
       // Online softmax, optimistic: the exponentials are taken against the reference
       // maximum the row already has, and only their sum is looked at.  A sum within
@@ -668,48 +713,49 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
               if (kLoadsInSoftmax && FIRST && e == 4) {   // the loads of the tiles ahead, spread over the exponentials
                 if (sb == 0) load_v_one(n); else load_k_one(n);
               }
-              p[e] = fast_exp2(fmaf(s[n][2 * sb + (e >> 2)][e & 3], c2, -m_run[n]));
-              rs[n] += p[e];
+              p[e] = fast_exp2(fmaf(s[score_at(sb, n, e)][score_el(n, e)], c2, -m_run[n % NQ]));
+              rs[n % NL] += p[e];
             }
             pk[n][sb] = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]), pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
           }
       };
       exponentials(std::true_type{});
-      if (__any(!(rs[0] <= kSumBound && rs[1] <= kSumBound))) {
+      if (__any(!(rs[0] <= kSumBound && (NL == 1 || rs[1] <= kSumBound)))) {
 #pragma unroll
-        for (int n = 0; n < 2; ++n) {
+        for (int n = 0; n < NQ; ++n) {
           // (the maximum starts from a value the compiler cannot see through: otherwise it
           // forms the whole maximum ahead of the branch, on every tile)
-          float mx = s[n][0][0];
+          float mx = s[4 * n][0];
           asm volatile("" : "+v"(mx));
 #pragma unroll
-          for (int b = 0; b < 4; ++b)
+          for (int x = 0; x < NS / NQ; ++x)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[n][b][r]);
-          mx = quad_max(mx);                     // the four lanes of a row agree on its reference
+            for (int r = 0; r < NR; ++r) mx = fmaxf(mx, s[4 * n + x][r]);
+          if constexpr (WIDE) mx = half_max(mx); else mx = quad_max(mx);   // the lanes of a row agree on its reference
           const float m_cand = mx * c2;
           const float m_new = (m_cand > m_run[n]) ? m_cand : m_run[n];
           const float alpha = fast_exp2(m_run[n] - m_new);
           m_run[n] = m_new;
           l_run[n] *= alpha;
+          if (WIDE && NL > 1) l_run[1] *= alpha;
           if (WITH_V) {
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb)
+            for (int x = 0; x < NO / NQ; ++x)
 #pragma unroll
-              for (int r = 0; r < 4; ++r) o[n][mb][r] *= alpha;
+              for (int r = 0; r < NR; ++r) o[8 * n + x][r] *= alpha;
           }
         }
         exponentials(std::false_type{});
       }
       l_run[0] += rs[0];
-      l_run[1] += rs[1];
+      if (NL > 1) l_run[1] += rs[1];
       // (a part ends well before the diagonal: every wave that has rows works on its last tile)
       if (MODE == 1 && t == part_last) {
         store_part_lse();
         ++part;
         part_last = __builtin_amdgcn_readfirstlane(end_of_part());
-        m_run[0] = m_run[1] = kNegBig;
-        l_run[0] = l_run[1] = 0.f;
+        m_run[0] = kNegBig;
+        l_run[0] = 0.f;
       }
     };
 
@@ -747,7 +793,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     };
     auto forget_scores = [&]() {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) asm volatile("" : "=v"(s[i >> 2][i & 3]));
+      for (int i = 0; i < NS; ++i) asm volatile("" : "=v"(s[i]));
     };
     // (An interior stretch knows that the wave works on every tile: as a run-time flag the answer
     // left a join in front of the K Q^T sweep, at which the compiler waited for the whole ring.)
@@ -907,23 +953,41 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       return;
     }
     if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
-    // a lane holds d = 16 mb + 4 kg .. + 3 of its two rows: the lanes of a row write 32 (bf16) or 64 bytes in a run
+    // four d in a run: 16 mb + 4 kg .. + 3 of both rows of a lane (WIDE: 32 mb + 8 g + 4 kg .. + 3 of its row)
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      const float l_tot = quad_sum(l_run[n]);
+    for (int n = 0; n < NQ; ++n) {
+      const float l_tot = row_sum(n);
       if (!row_ok(n)) continue;
       const int i = i_me + 16 * n;
+      if (PARTS) {
+        const size_t slot = (size_t)bh * P.parts_per_head + J.part0 + split;
+        const int r = 32 * wave + 16 * n + ql;
+        if (kg == 0) reinterpret_cast<float2*>(P.part_ml)[slot * BQ + r] = make_float2(m_run[n], l_tot);
+        float* po = P.part_o + (slot * BQ + r) * kHeadDim + 4 * kg;
+#pragma unroll
+        for (int x = 0; x < NO / NQ; ++x)
+#pragma unroll
+          for (int g = 0; g < NR / 4; ++g) {
+            const Acc& a = o[8 * n + x];
+            *reinterpret_cast<float4*>(po + (WIDE ? 32 * x + 8 * g : 16 * x)) = make_float4(a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]);
+          }
+        continue;
+      }
       if (P.lse != nullptr && kg == 0) P.lse[(size_t)bh * S + i] = m_run[n] * kLn2 + __logf(l_tot);
       const float inv = 1.0f / l_tot;
       const size_t at = ((size_t)bh * S + i) * kHeadDim + 4 * kg;
 #pragma unroll
-      for (int mb = 0; mb < 8; ++mb) {
-        const float x0 = o[n][mb][0] * inv, x1 = o[n][mb][1] * inv, x2 = o[n][mb][2] * inv, x3 = o[n][mb][3] * inv;
-        if (OUT_F32)
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + at + 16 * mb) = make_float4(x0, x1, x2, x3);
-        else
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + at + 16 * mb) = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
-      }
+      for (int x = 0; x < NO / NQ; ++x)
+#pragma unroll
+        for (int g = 0; g < NR / 4; ++g) {
+          const Acc& a = o[8 * n + x];
+          const float x0 = a[4 * g] * inv, x1 = a[4 * g + 1] * inv, x2 = a[4 * g + 2] * inv, x3 = a[4 * g + 3] * inv;
+          const size_t d = at + (WIDE ? 32 * x + 8 * g : 16 * x);
+          if (OUT_F32)
+            *reinterpret_cast<float4*>(reinterpret_cast<float*>(P.out) + d) = make_float4(x0, x1, x2, x3);
+          else
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(P.out) + d) = make_uint2(pack_bf16x2(x0, x1), pack_bf16x2(x2, x3));
+        }
     }
   } else {
     const int ql = lane & 31;   // query within the wave / row within a 32-row operand
@@ -1318,11 +1382,10 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
 #undef SA_PIN
 }
 
-// Which core (see the top of the file) a workgroup takes: core 1 in parts and where !LONG.  In a LONG launch of
-// strips or block lists, swept heads take core 0 (their mask costs vector instructions on every tile), the
-// others too where the sequence is long and the head's list does not leave too many waves without work
-// (kSparseBit; strips only).
-template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
+// CORE: the core (see the top of the file) of dense and swept tiles.  Heads in two passes take core 1, or
+// core 0 where the call is large and long (short_lists) and the head's list does not leave too many waves without
+// work (kSparseBit; strips only).
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, int CORE>
 __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashParams P) {
   // ---- which (head, query tile) this workgroup owns ------------------------
   // (the log-sum-exp sweep may also give the keys of a query tile to k_splits workgroups)
@@ -1331,20 +1394,24 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
   {
     const int bid = blockIdx.x;
     int f = 0;                           // tile, counted over the segments
+    SegmentJob seg = P.seg[0];
+    J.seg = 0;
     if (PARTS) {
       // heavy (late) query tiles first, the heads of a part side by side
       // (a segment's values are read once: a load for every tile passed over is 1 us of a small call)
       J.bh = bid % P.n_bh;
       J.split = bid / P.n_bh;
       const int pm = P.part_m;
-      int m = P.n_seg - 1, q0, q1;
-      for (;; --m) {                     // (both loops end: the grid has exactly the parts of these tiles)
-        q0 = P.seg[m].qtile0;
-        q1 = q0 + P.seg[m].n_qtiles;
-        const int n = parts_before(pm, q0, q1);
-        if (J.split < n || m == 0) break;
+      for (int m = P.n_seg - 1; m > 0; --m) {   // (both loops end: the grid has exactly the parts of these tiles)
+        const int n = parts_before(pm, P.seg[m].qtile0, P.seg[m].qtile0 + P.seg[m].n_qtiles);
+        if (J.split < n) {
+          seg = P.seg[m];
+          J.seg = m;
+          break;
+        }
         J.split -= n;
       }
+      const int q0 = seg.qtile0, q1 = q0 + seg.n_qtiles;
       int a = q1 - 1, before = parts_before(pm, q0, q1), rem;
       J.n_parts = a / pm + 1;
       rem = a % pm;
@@ -1357,9 +1424,8 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
           --J.n_parts;
         }
       }
-      J.seg = m;
       J.a = a;
-      J.part0 = P.seg[m].part0 + before - J.n_parts;
+      J.part0 = seg.part0 + before - J.n_parts;
     } else if (MODE == 2) {
       // heads are sliced over the 8 XCDs (workgroups go round-robin to XCDs) and an
       // XCD works through one head at a time, heavy (late) query tiles first: the
@@ -1386,46 +1452,44 @@ __global__ __launch_bounds__(NT, (MODE == 1) ? 4 : 1) void flash_kernel(FlashPar
       int xcd = bid & 7, slot = bid >> 3;
       int bl = slot / P.group, hg = slot % P.group;
       int bundle = bl * 8 + xcd;
-      int m = 0;
       if (MODE == 1) {
-        while (m + 1 < P.n_seg && bundle >= P.n_qtiles * P.seg[m].k_splits * P.n_bkv) {
-          bundle -= P.n_qtiles * P.seg[m].k_splits * P.n_bkv;
-          ++m;
+        while (J.seg + 1 < P.n_seg && bundle >= P.n_qtiles * seg.k_splits * P.n_bkv) {
+          bundle -= P.n_qtiles * seg.k_splits * P.n_bkv;
+          seg = P.seg[++J.seg];
         }
-        J.lse_parts = P.seg[m].lse_parts;
-        J.k_splits = P.seg[m].k_splits;
+        J.lse_parts = seg.lse_parts;
+        J.k_splits = seg.k_splits;
       }
       const int ks = J.k_splits;
       if (bundle >= P.n_qtiles * ks * P.n_bkv) return;
       const int av = P.n_qtiles * ks - 1 - bundle / P.n_bkv;
       J.split = av % ks;
       J.bh = bundle % P.n_bkv * P.group + hg;
-      J.seg = m;
       J.a = av / ks;
     }
     if (!PARTS && MODE == 2) {
-      J.seg = segment_of(P, f);
-      J.a = P.seg[J.seg].qtile0 + f - P.seg[J.seg].tile0;
+      if (P.n_seg > 1) {
+        J.seg = segment_of(P, f);
+        seg = P.seg[J.seg];
+      }
+      J.a = seg.qtile0 + f - seg.tile0;
     }
-    J.row_lo = P.seg[J.seg].row_lo;
-    J.row_hi = P.seg[J.seg].row_hi;
+    J.row_lo = seg.row_lo;
+    J.row_hi = seg.row_hi;
   }
-  constexpr int CORE = LONG ? 0 : 1;
   if constexpr (MODE == 2) {
     // (diagonal 0 is in every list, and its entry is the first)
     const int first = __builtin_amdgcn_readfirstlane(P.dlist[(size_t)(J.seg * P.n_bh + J.bh) * P.dlist_stride]);
     if (first & kSweepBit) {
       flash_body<MODE, OUT_F32, IN_PLACE, MODE == 2, PARTS, CORE>(P, J);
-      return;
+    } else if (PARTS || P.short_lists || (!IN_PLACE && (first & kSparseBit))) {
+      flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, J);
+    } else if constexpr (!PARTS) {
+      flash_body<MODE, OUT_F32, IN_PLACE, false, false, 0>(P, J);
     }
-    if constexpr (CORE == 0) {
-      if (P.short_lists || (!IN_PLACE && (first & kSparseBit))) {
-        flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, 1>(P, J);
-        return;
-      }
-    }
+  } else {
+    flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, J);
   }
-  flash_body<MODE, OUT_F32, IN_PLACE, false, PARTS, CORE>(P, J);
 }
 
 // The parts of a query tile brought to one reference maximum, added in fixed order and
@@ -1588,40 +1652,62 @@ size_t flash_parts_bytes(int m, int n_heads, int n_seg, const SegmentJob* seg) {
   return m == 0 ? 0 : (size_t)n_heads * parts_of(m, n_seg, seg) * BQ * (kHeadDim + 2) * sizeof(float);
 }
 
-template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, bool LONG>
+template <int MODE, bool OUT_F32, bool IN_PLACE, bool PARTS, int CORE>
 static hipError_t launch_one(const FlashParams& P, int grid, hipStream_t st) {
   size_t shmem = (MODE == 1) ? LDS_B_LSE : LDS_B;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, LONG>),
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, CORE>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, LONG>), dim3(grid), dim3(NT), shmem, st, P);
+  hipLaunchKernelGGL((flash_kernel<MODE, OUT_F32, IN_PLACE, PARTS, CORE>), dim3(grid), dim3(NT), shmem, st, P);
   return hipGetLastError();
 }
 template <int MODE, bool IN_PLACE>
-static hipError_t launch_whole(bool out_f32, bool long_run, const FlashParams& P, int grid, hipStream_t st) {
-  if (long_run) return out_f32 ? launch_one<MODE, true, IN_PLACE, false, true>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, true>(P, grid, st);
-  return out_f32 ? launch_one<MODE, true, IN_PLACE, false, false>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, false>(P, grid, st);
+static hipError_t launch_whole(bool out_f32, int core, const FlashParams& P, int grid, hipStream_t st) {
+  switch (core) {
+    case 0: return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 0>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 0>(P, grid, st);
+    case 1:
+      if constexpr (MODE == 0) return out_f32 ? launch_one<0, true, false, false, 1>(P, grid, st) : launch_one<0, false, false, false, 1>(P, grid, st);
+    default: return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 2>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 2>(P, grid, st);
+  }
 }
 
-// Which launches are LONG: of more tiles than CUs, of sequences long enough.  By the length alone, so that
-// a head's bits above 256 query tiles do not follow the batch.  Gain over the kernel before the two
-// cores, core 0 / core 1: dense, 32 heads of 4096 1.03 / 0.99, of 8192 1.034 / 0.986, 16 of 8192 1.05 / 0.99, 8 of 16384
-// 1.05 / 0.99; up to some 340 tiles on the 256 CUs one tile's chain decides, 16 of 4500 0.95 / 0.98, 8 of 8500
-// 0.94 / 0.98, of 9500 0.96 / 0.98, 4 of 17000 0.95 / 0.99: rare shapes, left to the rule.  Swept heads: 32 of 8192
-// 1.08 / 1.03, of 4500 1.04 / 0.99, 8 of 8500 1.02 / 0.97, 16 of 8000 1.05 / 0.96, but 32 of 2048 in blocks 0.94 / 1.01, 4
-// segments of 4000 0.93 / 1.03.  Strips in two passes: 32 heads of 3000 0.95 / 1.02, of 6001 0.93 / 1.05, 16 of 20000
-// 0.97 / 1.05, 8 of 40000 0.99 / 1.02, but 32 of 65536 1.04 / 1.00.  Block lists in two: 32 of 16384 1.02 / 1.06, of 32768 1.06 / 1.04.
-constexpr int kLongDense = 4096, kLongStrips = 49152, kLongBlocks = 24576;
+// The core of a launch's dense and swept tiles.  Core 0 and core 2 give the same bits, so this choice may
+// follow the launch.  Up to some 1.5 rounds of the 256 CUs the chain of the heaviest tile decides and core 2
+// is faster, above them the power.  Core 0 / core 2 against the faster one, whole path: dense, 8 heads of 8300 (264 tiles) 186 /
+// 174 us, of 10800 (344) 255 / 249, of 12000 (376) 293 / 290, of 14000 (440) 348 / 355, 32 of 2100 (288) 58.6 / 57.6, 64 of 2100
+// (576) 100 / 98.6, 32 of 3500 (448) 118.6 / 120; swept strips, 4 of 15000 (236) 431 / 416, 16 of 4500 (288) 184 / 181, of 5003 (320) 199 /
+// 199, of 6000 (384) 233 / 236; swept blocks of 128, whose sweep has no interior stretch, 16 of 4500 176 / 165, 8 of 12000
+// 364 / 355, of 14000 420 / 421, 32 of 5000 (640) 277 / 276, of 7000 (896) 435 / 439.
+// Short calls and short parts: core 1, the shortest chain.  Core 1 / core 2: dense, 32 of 500 21.5 / 22.2 us, of 1000 30.2 / 31.0, of 1500
+// 42.2 / 42.0; in parts, dense 4 of 2000 30.6 / 31.1, strips 32 of 500 67.5 / 67.5, 8 of 3001 120 / 121, 4 of 8192 181 / 176, of 12000
+// 313 / 291, blocks 4 of 8192 151 / 149, of 12000 259 / 251.
+constexpr int kWideDense = 384, kWideStrips = 320, kWideBlocks = 640, kWideLength = 3072, kShortDense = 1024, kShortParts = 5000;
+static int sweep_core(int mode, const FlashParams& P) {
+  if (P.part_m > 0) return P.S < kShortParts ? 1 : 2;
+  const long long tiles = (long long)P.n_bh * P.n_qtiles;
+  if (mode == 0) return P.S < kShortDense ? 1 : P.S < kWideLength || tiles <= kWideDense ? 2 : 0;
+  return tiles <= (P.cols_in_place ? kWideBlocks : kWideStrips) ? 2 : 0;
+}
+
+// Which calls have heads in two passes on core 0 (if their lists are not sparse): of more tiles than CUs, of
+// sequences long enough.  By the length alone, so that a head's bits above 256 query tiles do not follow the
+// batch.  Gain over core 2, core 0 / core 1: strips 32 heads of 3000 0.95 / 1.02, of 6001 0.93 / 1.05, 16 of 20000
+// 0.97 / 1.05, 8 of 40000 0.99 / 1.02, but 32 of 65536 1.04 / 1.00.  Block lists 32 of 16384 1.02 / 1.06, of 32768 1.06 / 1.04.
+constexpr int kLongStrips = 49152, kLongBlocks = 24576;
 
 // a launch whose schedules are cut into parts, and the combination
+template <int CORE>
+static hipError_t launch_cut(int mode, const FlashParams& P, int grid, hipStream_t st) {
+  if (mode == 0) return launch_one<0, false, false, true, CORE>(P, grid, st);
+  return P.cols_in_place ? launch_one<2, false, true, true, CORE>(P, grid, st) : launch_one<2, false, false, true, CORE>(P, grid, st);
+}
 static hipError_t launch_parts(int mode, bool out_f32, const FlashParams& P0, hipStream_t st) {
   FlashParams P = P0;
   P.parts_per_head = parts_of(P.part_m, P.n_seg, P.seg);
   for (int k = 1; k < P.n_seg; ++k) P.seg[k].part0 = parts_of(P.part_m, k, P.seg);
   const int n = P.n_bh * P.parts_per_head;
   P.part_ml = P.part_o + (size_t)n * BQ * kHeadDim;
-  hipError_t e = mode == 0 ? launch_one<0, false, false, true, false>(P, n, st)
-               : P.cols_in_place ? launch_one<2, false, true, true, false>(P, n, st) : launch_one<2, false, false, true, false>(P, n, st);
+  const hipError_t e = sweep_core(mode, P) == 1 ? launch_cut<1>(mode, P, n, st) : launch_cut<2>(mode, P, n, st);
   if (e != hipSuccess) return e;
   const dim3 grid(P.n_qtiles * (BQ / 8), P.n_bh);
   if (P.n_seg > 1) {
@@ -1645,15 +1731,13 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
     grid = ((bundles + 7) / 8) * 8 * P.group;
   }
   if (grid <= 0) return hipSuccess;
+  FlashParams L = P;
+  if (mode == 2) L.short_lists = P.all_tiles <= kMaxParts || P.S < (P.cols_in_place ? kLongBlocks : kLongStrips);
+  const int core = sweep_core(mode, P);
   switch (mode) {
-    case 0: return launch_whole<0, false>(out_f32, P.S >= kLongDense && P.all_tiles > kMaxParts, P, grid, st);
-    case 1: return launch_one<1, false, false, false, true>(P, grid, st);
-    default: {
-      FlashParams L = P;
-      L.short_lists = P.S < (P.cols_in_place ? kLongBlocks : kLongStrips);
-      const bool long_run = P.all_tiles > kMaxParts;
-      return P.cols_in_place ? launch_whole<2, true>(out_f32, long_run, L, grid, st) : launch_whole<2, false>(out_f32, long_run, L, grid, st);
-    }
+    case 0: return launch_whole<0, false>(out_f32, core, P, grid, st);
+    case 1: return launch_one<1, false, false, false, 2>(P, grid, st);
+    default: return P.cols_in_place ? launch_whole<2, true>(out_f32, core, L, grid, st) : launch_whole<2, false>(out_f32, core, L, grid, st);
   }
 }
 

@@ -475,3 +475,53 @@ def test_parts_without_tiles(S, C, n_col, n_off):
     want, wlse = O.chunked_masked_attn(*(_f64(x[t])[0] for t in "qkv"), Ic, Is, 1, C)
     _check_out(out[0, 0].float().cpu().numpy(), want, "parts without tiles")
     assert np.abs(lse[0].cpu().numpy() - wlse).max() < 2e-3
+
+
+# dense and swept tiles of one sequence alone (289 query tiles: 32x32x16 MFMAs) and in a batch of three (867: 16x16x32);
+# a query's largest logits come first, last, or now and then
+@pytest.mark.parametrize("kind", ["random", "rising", "falling", "spiky"])
+def test_both_shapes_of_the_mfmas_give_the_same_bits(kind):
+    """A score is the same eight products after eight in either shape, and the sums of a row are kept for the
+    same groups of keys: outputs and log-sum-exps are equal, whichever a launch takes."""
+    import paper_2406_15486_amd as sa
+    S, H, w, blk = 4097, 17, 5, 128
+    _say(f"shapes of the MFMAs, {kind} logits")
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, h, S, 128, generator=g, device="cuda") for h in (H, 1, 1))
+    j = torch.arange(S, device="cuda")
+    if kind != "random":
+        gain = {"rising": j / S, "falling": 1 - j / S, "spiky": (j % 97 == 5).float()}[kind]
+        u = torch.randn(128, generator=g, device="cuda")
+        q = q + 4 * u
+        k = k + 6 * gain[:, None] * u
+    q, k, v = (t.bfloat16() for t in (q, k, v))
+    rng = np.random.default_rng(S)
+    def lists(n, shares):
+        idx, cnt = torch.zeros(H, n, dtype=torch.int32), torch.zeros(H, dtype=torch.int32)
+        for h in range(H):
+            x = _fill(rng, n, shares[h % len(shares)])
+            idx[h, :len(x)], cnt[h] = torch.from_numpy(x.astype(np.int32)), len(x)
+        return idx.cuda(), cnt.cuda()
+    n = (S + blk - 1) // blk
+    strips = (*lists(S, (0.9, 0.97, 0.6)), *lists(S, (0.9, 0.3, 0.97)))      # nearly full: swept
+    blocks = (*lists(n, (0.9, 1.0, 0.7)), *lists(n, (0.9, 0.5, 1.0)))
+    def run(B):
+        qq, kk, vv = (t.repeat(B, 1, 1, 1) for t in (q, k, v))
+        kw = dict(out_dtype=sa.SA_OUT_F32, want_lse=True)
+        return (sa.sa_dense_attn(qq, kk, vv, **kw), sa.sa_sparse_attn(qq, kk, vv, *(t.repeat(B, *[1] * (t.dim() - 1)) for t in strips), w, want_tiles=True, **kw),
+                sa.sa_block_sparse_attn(qq, kk, vv, *(t.repeat(B, *[1] * (t.dim() - 1)) for t in blocks), w, blk, **kw))
+    one, three = run(1), run(3)
+    torch.cuda.synchronize()
+    last = np.minimum(256 * np.arange(17) + 255, S - 1)
+    rows = 256 * np.arange(17)[:, None] + 32 * np.arange(8)[None, :] + 31
+    assert (one[1][2] == int(np.minimum(last[:, None] // 64 + 1, rows // 64 + 1).sum())).all()          # every head is swept
+    for a, b in zip(one, three):
+        assert torch.isfinite(a[0]).all() and torch.isfinite(a[1]).all()
+        for x in range(3):
+            assert torch.equal(a[0][0], b[0][x]) and torch.equal(a[1], b[1].view(3, H, S)[x])
+    # rows of the dense call against their fp64 softmax (bf16 probabilities and V, as elsewhere)
+    for h in (0, 7, 16):
+        for i in (0, 31, 64, 300, 2111, S - 2, S - 1):
+            s = (k[0, 0, :i + 1].double() @ q[0, h, i].double()) / np.sqrt(128.0)
+            assert abs(float(torch.logsumexp(s, 0)) - float(one[0][1].view(H, S)[h, i])) < 2e-3, (h, i)
+            assert float((torch.softmax(s, 0) @ v[0, 0, :i + 1].double() - one[0][0][0, h, i].double()).abs().max()) < 2e-2, (h, i)
