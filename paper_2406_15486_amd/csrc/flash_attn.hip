@@ -1694,6 +1694,7 @@ static int sweep_core(int mode, const FlashParams& P) {
 // batch.  Gain over core 2, core 0 / core 1: strips 32 heads of 3000 0.95 / 1.02, of 6001 0.93 / 1.05, 16 of 20000
 // 0.97 / 1.05, 8 of 40000 0.99 / 1.02, but 32 of 65536 1.04 / 1.00.  Block lists 32 of 16384 1.02 / 1.06, of 32768 1.06 / 1.04.
 constexpr int kLongStrips = 49152, kLongBlocks = 24576;
+bool two_cores(bool blocks, int S, int all_tiles) { return all_tiles > kMaxParts && S >= (blocks ? kLongBlocks : kLongStrips); }
 
 // a launch whose schedules are cut into parts, and the combination
 template <int CORE>
@@ -1732,7 +1733,7 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
   }
   if (grid <= 0) return hipSuccess;
   FlashParams L = P;
-  if (mode == 2) L.short_lists = P.all_tiles <= kMaxParts || P.S < (P.cols_in_place ? kLongBlocks : kLongStrips);
+  if (mode == 2) L.short_lists = !two_cores(P.cols_in_place != 0, P.S, P.all_tiles);
   const int core = sweep_core(mode, P);
   switch (mode) {
     case 0: return launch_whole<0, false>(out_f32, core, P, grid, st);

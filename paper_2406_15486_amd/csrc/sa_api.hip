@@ -238,13 +238,17 @@ size_t parts_room(const Dims& d, int n_chunks) {
   return align_up(bytes);
 }
 
-// tells the launch P how large the call is (query tiles of all heads in the shortest segment), and cuts it into
-// parts if `room` bytes at `at` hold their sums for n_heads heads
-void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int n_seg, const sa::SegmentJob* seg, void* at, size_t room) {
-  const int m = sa::flash_parts(d.n_bh, n_seg, seg);
+// how large the call is: query tiles of all heads in the shortest segment
+int call_tiles(const Dims& d, int n_seg, const sa::SegmentJob* seg) {
   int fewest = seg[0].n_qtiles;
   for (int k = 1; k < n_seg; ++k) fewest = seg[k].n_qtiles < fewest ? seg[k].n_qtiles : fewest;
-  P->all_tiles = d.n_bh * fewest;
+  return d.n_bh * fewest;
+}
+
+// tells the launch P how large the call is, and cuts it into parts if `room` bytes at `at` hold their sums for n_heads heads
+void set_parts(sa::FlashParams* P, const Dims& d, int n_heads, int n_seg, const sa::SegmentJob* seg, void* at, size_t room) {
+  const int m = sa::flash_parts(d.n_bh, n_seg, seg);
+  P->all_tiles = call_tiles(d, n_seg, seg);
   if (m == 0 || sa::flash_parts_bytes(m, n_heads, n_seg, seg) > room) return;
   P->part_m = m;
   P->part_o = static_cast<float*>(at);
@@ -563,6 +567,7 @@ sa_status prepare_heads(const Dims& d, const BlockWs& bw, int granularity, int h
     M.tiles = tiles;
     M.n_bh = n_seg * nh; M.heads_per_seg = nh; M.S = d.S; M.window = local_window;
     M.cb_words = w.cb_words; M.rb_words = w.rb_words; M.dlist_stride = w.dlist_stride; M.off_max = w.off_max;
+    M.cores = sa::two_cores(false, d.S, call_tiles(d, n_seg, seg)) ? 1 : 0;
     memcpy(M.seg, seg, n_seg * sizeof(*seg));
     s = dev(sa::launch_mask_prep(M, st));
   } else {

@@ -10,7 +10,7 @@ constexpr int kFlashBQ = 256;  // query rows per workgroup of the flash kernels
 constexpr int kFlashBK = 64;   // keys per tile
 constexpr int kMaxSeqLen = 1 << 24;   // kernels keep 32-bit byte offsets into V^T
 constexpr int kSweepBit = 1 << 23;   // in every entry of a tile-diagonal list: the head is swept
-constexpr int kSparseBit = 1 << 22;  // ... or its tiles leave many waves without work
+constexpr int kSparseBit = 1 << 22;  // ... or (strips, see two_cores) its tiles leave many waves without work
 
 // One launch may take up to kMaxSegs query segments (Algorithm 1's chunks), each with lists of its own;
 // tile0, part0: tiles and parts of the segments before.
@@ -66,6 +66,8 @@ hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_
 // parts of the keys of a query tile (from the sequence alone, at most max_parts) and the workgroups
 // that share them (from the heads of the launch too)
 void lse_splits(int row_first, int n_s, int n_bh, int max_parts, int* parts, int* workgroups);
+// whether heads in two passes may run on either core in a call of S tokens and all_tiles query tiles (core 1 otherwise)
+bool two_cores(bool blocks, int S, int all_tiles);
 // part_m of a launch over segments of n_bh heads (0: not cut), and the bytes of the partial sums of
 // n_heads of them
 constexpr int kMaxParts = 256;
@@ -105,6 +107,7 @@ struct MaskPrepParams {
   int32_t* dlist; int32_t* dcnt;
   unsigned long long* tiles;                           // nullable [n_bh]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
+  int cores;                                           // the attention launch reads kSparseBit
   int heads_per_seg;                                   // n_bh counts the heads of every segment
   SegmentJob seg[kMaxSegs];                            // the query tiles a segment's masks are for, and the end of their rows
 };
