@@ -153,11 +153,12 @@ __device__ __forceinline__ long long block_sum(long long x, long long* scratch) 
 // 32 runs 19.2 ms in two passes / 30.9 swept, 218 runs 29.7 / 30.9, 436 runs 35.7 / 30.9,
 // 1638 runs 45.2 / 31.1.
 constexpr int kColTileCost = 132, kRangeTileCost = 76, kRangeWaveCost = 7, kSweepTileCost = 140;
-// Which core a head in two passes is for (kSparseBit: the one of 32-row operands): what the other
-// gains on a gathered tile and on every wave that works on a range tile, against what it loses on a
-// range tile.  All heads on core 0 / core 1: 64K head patterns 34.1 / 35.2 ms, runs of four offsets every 300 of 64K
-// 20.4 / 16.2, every 1000 6.85 / 5.47.
-constexpr int kCoreColTile = 33, kCoreWave = 10, kCoreRangeTile = 68;
+// Which core a head in two passes is for (kSparseBit: core 1): what core 0 gains on a gathered tile and on
+// every wave that works on a range tile, against what it loses on a range tile whose other waves wait, in
+// the unit of the costs above.  Fitted to 32 heads of 64K on core 0 / core 1: 20 % of the columns 5.9 / 6.2 ms (5 a tile);
+// runs of one offset every 1000 6.6 / 5.1 (-18 a range tile, 2.4 waves at work), four every 300 20.8 / 16.5 (-15), 128 every 1000
+// 10.0 / 9.0 (-9, 4 waves), 400 every 4000 4.7 / 4.8 (+1.6, 5.5 waves), 700 every 4000 6.8 / 7.2, head patterns 34.1 / 35.2 (+4, 7.7 waves).
+constexpr int kCoreColTile = 5, kCoreWave = 5, kCoreRangeTile = 26;
 
 // Written by one workgroup: `active(d, w)` says whether wave w has work on diagonal d.  A
 // thread takes one (d, w) pair, a wave eight diagonals at a time (one ballot is eight

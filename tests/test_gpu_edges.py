@@ -525,3 +525,38 @@ def test_both_shapes_of_the_mfmas_give_the_same_bits(kind):
             s = (k[0, 0, :i + 1].double() @ q[0, h, i].double()) / np.sqrt(128.0)
             assert abs(float(torch.logsumexp(s, 0)) - float(one[0][1].view(H, S)[h, i])) < 2e-3, (h, i)
             assert float((torch.softmax(s, 0) @ v[0, 0, :i + 1].double() - one[0][0][0, h, i].double()).abs().max()) < 2e-2, (h, i)
+
+
+def test_core_of_heads_in_two_passes():
+    """In long calls the list kernel picks the core of a head by its lists: what it wrote into the entry of
+    diagonal 0.  Isolated offsets (with or without some columns) leave most waves of their tiles without work; columns
+    alone and bands of offsets as wide as a workgroup's rows do not."""
+    import paper_2406_15486_amd as sa
+    S, w = 49153, 16
+    _say("core of heads in two passes")
+    a = np.arange(S)
+    def share(f):
+        return a[::int(1 / f)]
+    def runs(r, p):
+        return a[a % p < r]
+    none = a[:0]
+    cases = [(none, runs(1, 1000), "sparse"), (none, runs(4, 300), "sparse"), (share(0.05), runs(1, 8000), "sparse"), (share(0.1), runs(4, 1000), "sparse"),
+             (none, runs(700, 4000), ""), (share(0.2), none, ""), (share(0.9), runs(1, 2), "swept"), (none, none, "sparse")]
+    H = len(cases)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v = (torch.randn(1, h, S, 128, generator=g, device="cuda").bfloat16() for h in (H, 1, 1))
+    lists = []
+    for t in range(2):
+        idx = torch.zeros(H, S, dtype=torch.int32)
+        for h in range(H):
+            idx[h, :len(cases[h][t])] = torch.from_numpy(cases[h][t].astype(np.int32))
+        lists += [idx.cuda(), torch.tensor([len(c[t]) for c in cases], dtype=torch.int32, device="cuda")]
+    ws = torch.full((_bare("strips", H, 1, S),), 0xFF, dtype=torch.uint8, device="cuda")
+    sa.sa_sparse_attn(q, k, v, *lists, w, workspace=ws)
+    torch.cuda.synchronize()
+    up, S_pad = (lambda b: (b + 255) // 256 * 256), (S + 255) // 256 * 256
+    at = 256 * S_pad + H * 512 * S_pad + sum(up(H * 4 * n) for n in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24))
+    first = ws[at:at + H * 4 * (S_pad // 64 + 8)].view(torch.int32).view(H, -1)[:, 0].cpu().numpy()
+    assert (first & 0x3FFFFF == 0).all()
+    got = ["swept" if e >> 23 & 1 else "sparse" if e >> 22 & 1 else "" for e in first]
+    assert got == [c[2] for c in cases]
