@@ -362,13 +362,23 @@ def test_uncut_tiles(test, args, monkeypatch):
     assert calls and all(calls)
 
 
+def _picked(ws, Hq, Hkv, S):
+    """What the list kernel of a strip call wrote into the entries of diagonal 0: swept, sparse (core 1) or neither."""
+    up, S_pad = (lambda b: (b + 255) // 256 * 256), (S + 255) // 256 * 256
+    at = Hkv * 256 * S_pad + Hq * 512 * S_pad + sum(up(Hq * 4 * n) for n in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24))
+    first = ws[at:at + Hq * 4 * (S_pad // 64 + 8)].view(torch.int32).view(Hq, -1)[:, 0].cpu().numpy()
+    assert (first & 0x3FFFFF == 0).all()
+    return ["swept" if e >> 23 & 1 else "sparse" if e >> 22 & 1 else "" for e in first]
+
+
 # just below and above the lengths and the tiles of a call at which a launch changes core
 @pytest.mark.parametrize("path,S,H", [("dense", 4095, 17), ("dense", 4097, 17), ("dense", 4097, 15), ("strips", 49151, 2), ("strips", 49153, 2),
-                                      ("strips", 49153, 1), ("blocks", 24575, 3), ("blocks", 24577, 3), ("blocks", 24577, 2)])
+                                      ("strips", 49153, 1), ("strips", 49153, 3), ("blocks", 24575, 3), ("blocks", 24577, 3), ("blocks", 24577, 2)])
 def test_cores_of_the_attention_kernels(path, S, H):
-    """Uncut tiles take one of two cores, by the length, the query tiles and (strips) the list of the
-    head: scattered strips, every other one, nearly full lists that are swept.  Rows around the
-    tiles against their fp64 softmax (probabilities and V are bf16, as elsewhere)."""
+    """Uncut tiles take one of the cores, by the length, the query tiles and (strips) the list of the
+    head: scattered strips, every other one, nearly full lists that are swept.  With three heads a long
+    launch of strips has all three kinds.  Rows around the tiles against their fp64 softmax (probabilities and
+    V are bf16, as elsewhere)."""
     import paper_2406_15486_amd as sa
     _say(f"cores {path} S={S} H={H}")
     g = torch.Generator(device="cuda").manual_seed(S)
@@ -393,6 +403,8 @@ def test_cores_of_the_attention_kernels(path, S, H):
     else:
         out, lse, _ = sa.sa_block_sparse_attn(q, k, v, *lists, w, blk, **kw)
     torch.cuda.synchronize()
+    if (path, S, H) == ("strips", 49153, 3):
+        assert _picked(kw["workspace"], H, 1, S) == ["sparse", "", "swept"]
     kk, vv = k[0, 0].double(), v[0, 0].double()
     j = torch.arange(S, device="cuda")
     for h in range(0, H, 1 if H < 4 else 5):
@@ -554,9 +566,68 @@ def test_core_of_heads_in_two_passes():
     ws = torch.full((_bare("strips", H, 1, S),), 0xFF, dtype=torch.uint8, device="cuda")
     sa.sa_sparse_attn(q, k, v, *lists, w, workspace=ws)
     torch.cuda.synchronize()
-    up, S_pad = (lambda b: (b + 255) // 256 * 256), (S + 255) // 256 * 256
-    at = 256 * S_pad + H * 512 * S_pad + sum(up(H * 4 * n) for n in (S_pad, S_pad // 32 + 2, S_pad // 32 + 24))
-    first = ws[at:at + H * 4 * (S_pad // 64 + 8)].view(torch.int32).view(H, -1)[:, 0].cpu().numpy()
-    assert (first & 0x3FFFFF == 0).all()
-    got = ["swept" if e >> 23 & 1 else "sparse" if e >> 22 & 1 else "" for e in first]
-    assert got == [c[2] for c in cases]
+    assert _picked(ws, H, 1, S) == [c[2] for c in cases]
+
+
+@pytest.mark.parametrize("path", ["strips", "blocks"])
+@pytest.mark.parametrize("kind", ["random", "rising", "falling", "spiky"])
+def test_heads_in_two_passes_of_long_calls(path, kind):
+    """The tile loop of core 0 on gathered and range tiles (the small cases run on core 1): column counts that put the
+    boundaries of its stretches at the first, a middle and the last iteration, and logits whose
+    maximum keeps rising, is met at once, or comes in isolated keys.  Rows against their fp64 softmax."""
+    import paper_2406_15486_amd as sa
+    _say(f"two passes of long calls, {path}, {kind} logits")
+    blk, S, w = (1, 49153, 16) if path == "strips" else (128, 24577, 16)
+    counts = [0, 1, 64, 65, 255, 257, 320, 321, 384, 640] if blk == 1 else [0, 1, 2, 3, 5, 12]
+    H, n = len(counts), (S + blk - 1) // blk
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v = (torch.randn(1, h, S, 128, generator=g, device="cuda") for h in (H, 1, 1))
+    j = torch.arange(S, device="cuda")
+    if kind != "random":
+        u = torch.randn(128, generator=g, device="cuda")
+        u = u / u.norm()
+        q = q + 6 * u
+        # (40 logits over the sequence, and 40 above the rest)
+        k = k + (75 * (torch.rand(S, generator=g, device="cuda") < 1e-3) if kind == "spiky" else 75 * (j / S if kind == "rising" else 1 - j / S))[:, None] * u
+    q, k, v = (t.bfloat16() for t in (q, k, v))
+    rng = np.random.default_rng(S)
+    Ic = [np.sort(rng.choice(n, c, replace=False)) for c in counts]
+    Ic[3] = np.arange(counts[3])                              # the first keys: every query tile sees all of them
+    Ic[-2] = np.arange(n - counts[-2], n)                     # the last keys: only the last tiles do
+    a = np.arange(n)
+    Is = [a[(a + 97 * h) % (4000 if blk == 1 else 24) < (700 if blk == 1 else 1 + h % 3)] for h in range(H)]
+    lists = []
+    for L in (Ic, Is):
+        idx = torch.zeros(H, n, dtype=torch.int32)
+        for h in range(H):
+            idx[h, :len(L[h])] = torch.from_numpy(L[h].astype(np.int32))
+        lists += [idx.cuda(), torch.tensor([len(y) for y in L], dtype=torch.int32, device="cuda")]
+    ws = torch.full((_bare(path, H, 1, S),), 0xFF, dtype=torch.uint8, device="cuda")
+    kw = dict(out_dtype=sa.SA_OUT_F32, want_lse=True, workspace=ws)
+    if blk == 1:
+        out, lse, _ = sa.sa_sparse_attn(q, k, v, *lists, w, **kw)
+    else:
+        out, lse, _ = sa.sa_block_sparse_attn(q, k, v, *lists, w, blk, **kw)
+    torch.cuda.synchronize()
+    if blk == 1:
+        assert _picked(ws, H, 1, S) == [""] * H
+    kk, vv = k[0, 0].double(), v[0, 0].double()
+    for h in range(H):
+        cols, offs = (torch.zeros(n, dtype=torch.bool, device="cuda") for _ in range(2))
+        cols[lists[0][h, :len(Ic[h])].long()] = True
+        offs[lists[2][h, :len(Is[h])].long()] = True
+        diag = torch.zeros(n + 1, dtype=torch.bool, device="cuda")
+        diag[:n] |= offs
+        diag[1:] |= offs
+        diag[:(w + blk - 2) // blk + 1] = True
+        for i in (0, 31, 64, 255, 256, 1000, 4500, S // 2, S - 322, S - 258, S - 257, S - 65, S - 2, S - 1):
+            d = i - j
+            if blk == 1:
+                keep = (d >= 0) & (cols | offs[d.clamp(min=0)] | (d < w))
+            else:
+                keep = (d >= 0) & (cols[j // blk] | diag[(i // blk - j // blk).clamp(min=0)])
+            x = (kk @ q[0, h, i].double()) / np.sqrt(128.0)
+            x = torch.where(keep, x, torch.tensor(-float("inf"), dtype=torch.float64, device="cuda"))
+            want = float(torch.logsumexp(x, 0))
+            assert abs(want - float(lse[h, i])) < 2e-3 * max(1.0, abs(want) / 10), (h, i)
+            assert float((torch.softmax(x, 0) @ vv - out[0, h, i].double()).abs().max()) < 2e-2, (h, i)
