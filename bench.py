@@ -246,6 +246,20 @@ def sampling_study(sa, torch, wl, q, k, v, shape) -> int:
     return 0
 
 
+def compact(x):
+    """The same result in fewer characters, for a line that tools which keep some thousand of them still hold whole:
+    floats to six digits, tables (lists of dicts with the same keys) as one list of columns and one of rows."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: compact(v) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        if len(x) > 1 and all(isinstance(r, dict) and r.keys() == x[0].keys() for r in x):
+            return {"columns": list(x[0]), "rows": [[compact(v) for v in r.values()] for r in x]}
+        return [compact(v) for v in x]
+    return x
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -658,7 +672,7 @@ def main() -> int:
         "block_granularity_runs": block_runs,
         "alpha_c_alpha_s_grid": grid,
     }
-    print(json.dumps(line), flush=True)
+    print(json.dumps({**compact(line), "value": ms_median, "ms_per_step": ms_per_step}), flush=True)
     return 0
 
 

@@ -82,3 +82,19 @@ def test_schedule_slots_match_brute_force(S, seed, n_col, n_off, swept):
     assert (two_pass > sweep) == swept
     slots = sweep_slots if swept else slots
     assert bench.schedule_slots(S, cols, offs, w) == slots
+
+
+def test_the_result_line_stays_short():
+    """The tables of the default run (16 threshold pairs on three head patterns, sweeps, blocks) in fewer than 6000 characters,
+    nothing lost but digits after the sixth."""
+    import json
+    rng = np.random.default_rng(0)
+    names = ("sparse_flash_ms", "computed_tile_fraction", "mask_density_head0", "mean_k_c", "mean_k_s", "recall_mean", "cra_min")
+    grid = [{"head_pattern": p, "alpha_c": a, "alpha_s": b, **{n: float(rng.random()) * 10 ** int(rng.integers(-2, 5)) for n in names}}
+            for p in ("column", "slash", "composed") for a in (0.0, 0.8, 0.9, 0.95) for b in (0.0, 0.8, 0.9, 0.95)]
+    line = {"grid": grid, "nested": {"t": [1.23456789, 2]}, "one": [{"a": 1}], "none": None}
+    got = bench.compact(line)
+    assert len(json.dumps(line)) > 10000 and len(json.dumps(got)) < 6000
+    rows = [dict(zip(got["grid"]["columns"], r)) for r in got["grid"]["rows"]]
+    assert rows == [{k: v if isinstance(v, str) else pytest.approx(v, rel=1e-5) for k, v in r.items()} for r in grid]
+    assert got["nested"] == {"t": [1.23457, 2]} and got["one"] == [{"a": 1}] and got["none"] is None
