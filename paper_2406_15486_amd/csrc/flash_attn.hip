@@ -201,6 +201,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
   static_assert(!IN_PLACE || MODE == 2, "in-place column tiles belong to the strip-masked mode");
   static_assert(CORE == 2 || MODE != 1, "the log-sum-exp sweep runs on core 2");
   static_assert(CORE != 0 || !PARTS, "cut tiles run on cores 1 and 2");
+  static_assert(CORE != 1 || (MODE == 2 && !SWEEP), "core 1 takes heads in two passes");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   constexpr bool WITH_V = (MODE != 1);
   // Where a wave issues its share of the tile loads.  Each direct load stalls the wave
@@ -993,7 +994,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     const int ql = lane & 31;   // query within the wave / row within a 32-row operand
     const int hf = lane >> 5;   // which half of the contraction block this lane feeds
     const int i_me = iw0 + ql;                             // this lane's query row
-    const bool row_ok = i_me <= i_last_wg && (MODE != 2 || i_me >= J.row_lo);
+    const bool row_ok = i_me <= i_last_wg && i_me >= J.row_lo;
     // ---- Q^T operand: 8 contraction steps of 16, resident in registers -------
     bf16x8 qf[8];
     {
@@ -1028,6 +1029,11 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     // Element r of s[sb] is key j0 + 32 sb + 16 (r / 8) + 8 hf + r % 8 against query i_me.
     f32x16 s[2];
     uint32_t pk[2][8];                         // probabilities of half sb as bf16
+    // What the sum of a tile's second half starts from: infinity on the wave's first tile, so that the reference is looked for
+    // there too and covers a whole tile, as in the other cores.  A row's largest probabilities are then close to 1, where
+    // bf16 is exact; with the first 32 keys alone the error against fp64 was up to 2.5 % larger (8 heads of 3001, 10 %
+    // of the columns, core 2 / first half / whole tile: 1.346e-3 / 1.369e-3 / 1.336e-3).
+    float rs_first = __builtin_huge_valf();
     uint4 R[8];
     // operand i of iteration u; `st` (Steps) says which operands there are
     auto load_operand = [&](auto st, int i, int u) __attribute__((always_inline)) {
@@ -1079,11 +1085,8 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     };
     // words of a range tile's pattern, read a half iteration before they are used
     uint32_t rw[5] = {0, 0, 0, 0, 0};
-    auto is_range = [&](auto kc, int t) __attribute__((always_inline)) -> bool {
-      return MODE == 2 && !(SWEEP && IN_PLACE) && !is_col(kc, t);
-    };
     auto read_range_words = [&](auto kc, int t, int d) __attribute__((always_inline)) {
-      if (!is_range(kc, t)) return;
+      if (is_col(kc, t)) return;
       const uint32_t* mw = reinterpret_cast<const uint32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
       const int j0 = first_key(kc, t, d);
       const int wb = (P.off_max - (i0 - j0 + BQ - 1)) >> 5;
@@ -1093,44 +1096,33 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
       rw[3] = mw[16]; rw[4] = mw[17];                           // the column words
     };
     auto build_masks = [&](auto kc, int t, int d) __attribute__((always_inline)) {
-      const int j0 = first_key(kc, t, d);
       constexpr bool INTERIOR = decltype(kc)::INTERIOR;
-      // keep key <= query, i.e. b <= tl
-      auto causal = [](int tl) -> uint32_t { return tl < 0 ? 0u : (tl >= 31 ? 0xFFFFFFFFu : (2u << tl) - 1u); };
-      const int tl = i_me - (j0 + 8 * hf);                      // offset of the lane's first key
-      if (is_range(kc, t)) {
+      if (!is_col(kc, t)) {
+        const int tl = i_me - (first_key(kc, t, d) + 8 * hf);     // offset of the lane's first key
         const int x0 = P.off_max - tl;
 #pragma unroll
         for (int sb = 0; sb < 2; ++sb) {
           const uint32_t ow = __builtin_amdgcn_alignbit(rw[sb + 1], rw[sb], x0 & 31);  // bit b <-> offset tl - 32 sb - b
           const uint32_t cw = rw[3 + sb] >> (8 * hf);                                  // bit 16u+e <-> key is a selected column
-          // columns were taken by the gathered tiles - or, in a sweep, are kept here as well (a
-          // column bit, unlike an offset bit, says nothing about j <= i)
-          km[sb] = SWEEP ? (ow | cw) : (ow & ~cw);
-          if (SWEEP && !INTERIOR) km[sb] &= causal(tl - 32 * sb);
+          km[sb] = ow & ~cw;                       // columns were taken by the gathered tiles
         }
-      } else {
-        km[0] = km[1] = 0xFFFFFFFFu;
-        if (is_col(kc, t)) {
-          const int32_t* il = reinterpret_cast<const int32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
-          if (!INTERIOR && il[BK - 1] > iw0) {     // only the last gathered tiles reach past a row: keep index <= query
+        return;
+      }
+      km[0] = km[1] = 0xFFFFFFFFu;
+      const int32_t* il = reinterpret_cast<const int32_t*>(smem + OFF_A + (t & (NAUX - 1)) * AUX_B);
+      if (!INTERIOR && il[BK - 1] > iw0) {         // only the last gathered tiles reach past a row: keep index <= query
 #pragma unroll
-            for (int sb = 0; sb < 2; ++sb) {
-              uint32_t m = 0;
+        for (int sb = 0; sb < 2; ++sb) {
+          uint32_t m = 0;
 #pragma unroll
-              for (int g = 0; g < 2; ++g) {
-                const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 16 * g + 8 * hf);
-                int4 x0 = ip[0], x1 = ip[1];
-                int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+          for (int g = 0; g < 2; ++g) {
+            const int4* ip = reinterpret_cast<const int4*>(il + 32 * sb + 16 * g + 8 * hf);
+            int4 x0 = ip[0], x1 = ip[1];
+            int jj[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) m |= (jj[e] <= i_me ? 1u : 0u) << (16 * g + e);
-              }
-              km[sb] = m;
-            }
+            for (int e = 0; e < 8; ++e) m |= (jj[e] <= i_me ? 1u : 0u) << (16 * g + e);
           }
-        } else if (!INTERIOR && j0 + BK - 1 > iw0) {
-          km[0] = causal(tl);
-          km[1] = causal(tl - 32);
+          km[sb] = m;
         }
       }
     };
@@ -1156,7 +1148,7 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     auto run = [&](auto kc, auto prev_tag, auto cur_tag, auto ahead_tag, int u, auto&& fetch) __attribute__((always_inline)) {
       constexpr bool PREV = decltype(prev_tag)::value, CUR = decltype(cur_tag)::value, AHEAD = decltype(ahead_tag)::value;
       constexpr int KIND = decltype(kc)::KIND;
-      constexpr int MM = (MODE == 2 && !IN_PLACE && (KIND == 2 || (SWEEP && decltype(kc)::INTERIOR))) ? 1 : decltype(kc)::INTERIOR ? 0 : 2;
+      constexpr int MM = (!IN_PLACE && KIND == 2) ? 1 : decltype(kc)::INTERIOR ? 0 : 2;
       using St = Steps<PREV, CUR>;
       constexpr int H = St::HALF;
       if (!AHEAD) {
@@ -1170,7 +1162,8 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
         constexpr bool SM = h == 0 ? PREV : CUR;
         if (SM && MM == 2) mask_half(sb);
         auto score = [&](int r) __attribute__((always_inline)) -> float { return MM == 1 ? masked_score(sb, r) : s[sb][r]; };
-        float rs = 0.f, p[16];
+        float rs = h == 0 ? rs_first : 0.f, p[16];
+        if (SM && h == 0) rs_first = 0.f;
         auto element = [&](int r) __attribute__((always_inline)) {
           p[r] = fast_exp2(fmaf(score(r), c2, -m_run));
           rs += p[r];
@@ -1313,39 +1306,26 @@ __device__ __forceinline__ void flash_body(const FlashParams& P, const TileJob& 
     // (at most 256) lie in the last five gathered tiles, so the iterations n + 1 <
     // n_col_tiles - 5 see gathered tiles only, with work for every wave and nothing to mask;
     // the iterations n > n_col_tiles see range tiles only; the few in between take the
-    // general form.  Dense and swept tiles: the tiles below key tile a64 (the one
-    // that holds the first row) are interior.  The iterations n + 4 < n_tiles see no tile
-    // past the end of the schedule.
-    const int n_gen0 = (MODE == 2 && !SWEEP) ? max(n_col_tiles - 6, 0)                 // first iteration of the general form
-                                   : max(min(a64 - t_base - 1, n_tiles - 4), 0);
-    const int n_gen1 = (MODE == 2 && !SWEEP) ? min(n_col_tiles, n_tiles) : n_tiles;    // its last
+    // general form.  The iterations n + 4 < n_tiles see no tile past the end of the schedule.
+    const int n_gen0 = max(n_col_tiles - 6, 0);                              // first iteration of the general form
+    const int n_gen1 = min(n_col_tiles, n_tiles);                            // its last
     const int n_real = n_tiles - 4;                                          // first iteration that may see a tile past the end
     int n = 0;
-    auto interior = [&](auto kc) __attribute__((always_inline)) {
-      if (n_gen0 <= 0) return;
-      iteration(typename decltype(kc)::AtFirst{}, NO, n++);
+    if (n_gen0 > 0) {
+      iteration(ColTiles::AtFirst{}, NO, n++);
 #pragma unroll
       for (int i = 0; i < 8; ++i) load_operand(Steps<true, true>{}, i, n);
-      for (; n < n_gen0; ++n) iteration(kc, YES, n);
+      for (; n < n_gen0; ++n) iteration(ColTiles{}, YES, n);
       act_prev = true;
-    };
-    if (SWEEP && IN_PLACE) {
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, NO, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, NO, n);
-    } else if (MODE == 2 && !SWEEP) {
-      interior(ColTiles{});
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, NO, n);
-      for (; n < n_real; ++n) iteration(RngRealTiles{}, NO, n);
-      for (; n <= n_tiles; ++n) iteration(RngTiles{}, NO, n);
-    } else {
-      interior(PlainTiles{});
-      for (; n <= n_gen1; ++n) iteration(AnyTiles{}, NO, n);
     }
+    for (; n <= n_gen1; ++n) iteration(AnyTiles{}, NO, n);
+    for (; n < n_real; ++n) iteration(RngRealTiles{}, NO, n);
+    for (; n <= n_tiles; ++n) iteration(RngTiles{}, NO, n);
     vm_wait<0>();                              // nothing may still be writing LDS when the workgroup ends
 
     // ---- epilogue -------------------------------------------------------------
     float l_tot = half_sum(l_run);
-    if (MODE == 2 && P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
+    if (P.tiles != nullptr && lane == 0 && tiles_done > 0) atomicAdd(P.tiles + bh, tiles_done);
     if (!row_ok) return;
     if (PARTS) {
       const size_t slot = (size_t)bh * P.parts_per_head + J.part0 + split;
@@ -1670,12 +1650,8 @@ static hipError_t launch_one(const FlashParams& P, int grid, hipStream_t st) {
 }
 template <int MODE, bool IN_PLACE>
 static hipError_t launch_whole(bool out_f32, int core, const FlashParams& P, int grid, hipStream_t st) {
-  switch (core) {
-    case 0: return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 0>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 0>(P, grid, st);
-    case 1:
-      if constexpr (MODE == 0) return out_f32 ? launch_one<0, true, false, false, 1>(P, grid, st) : launch_one<0, false, false, false, 1>(P, grid, st);
-    default: return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 2>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 2>(P, grid, st);
-  }
+  if (core == 0) return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 0>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 0>(P, grid, st);
+  return out_f32 ? launch_one<MODE, true, IN_PLACE, false, 2>(P, grid, st) : launch_one<MODE, false, IN_PLACE, false, 2>(P, grid, st);
 }
 
 // The core of a launch's dense and swept tiles.  Core 0 and core 2 give the same bits, so this choice may
@@ -1685,14 +1661,13 @@ static hipError_t launch_whole(bool out_f32, int core, const FlashParams& P, int
 // (576) 100 / 98.6, 32 of 3500 (448) 118.6 / 120; swept strips, 4 of 15000 (236) 431 / 416, 16 of 4500 (288) 184 / 181, of 5003 (320) 199 /
 // 199, of 6000 (384) 233 / 236; swept blocks of 128, whose sweep has no interior stretch, 16 of 4500 176 / 165, 8 of 12000
 // 364 / 355, of 14000 420 / 421, 32 of 5000 (640) 277 / 276, of 7000 (896) 435 / 439.
-// Short calls and short parts: core 1, the shortest chain.  Core 1 / core 2: dense, 32 of 500 21.5 / 22.2 us, of 1000 30.2 / 31.0, of 1500
-// 42.2 / 42.0; in parts, dense 4 of 2000 30.6 / 31.1, strips 32 of 500 67.5 / 67.5, 8 of 3001 120 / 121, 4 of 8192 181 / 176, of 12000
-// 313 / 291, blocks 4 of 8192 151 / 149, of 12000 259 / 251.
-constexpr int kWideDense = 384, kWideStrips = 320, kWideBlocks = 640, kWideLength = 3072, kShortDense = 1024, kShortParts = 5000;
+// Not core 1, though its chain is the shortest (dense, 32 heads of 500 21.5 / 22.2 us, 4 of 2000 in parts 30.6 / 31.1): its
+// references begin with 32 keys where the others take 64, so a row's largest probabilities are less often close to 1, where
+// bf16 is exact.  Error against fp64, cores 2 / 1: 2 heads of 600 1.177e-3 / 1.214e-3, 8 of 3001 1.200e-3 / 1.219e-3.
+constexpr int kWideDense = 384, kWideStrips = 320, kWideBlocks = 640, kWideLength = 3072;
 static int sweep_core(int mode, const FlashParams& P) {
-  if (P.part_m > 0) return P.S < kShortParts ? 1 : 2;
   const long long tiles = (long long)P.n_bh * P.n_qtiles;
-  if (mode == 0) return P.S < kShortDense ? 1 : P.S < kWideLength || tiles <= kWideDense ? 2 : 0;
+  if (mode == 0) return P.S < kWideLength || tiles <= kWideDense ? 2 : 0;
   return tiles <= (P.cols_in_place ? kWideBlocks : kWideStrips) ? 2 : 0;
 }
 
@@ -1704,18 +1679,14 @@ constexpr int kLongStrips = 49152, kLongBlocks = 24576;
 bool two_cores(bool blocks, int S, int all_tiles) { return all_tiles > kMaxParts && S >= (blocks ? kLongBlocks : kLongStrips); }
 
 // a launch whose schedules are cut into parts, and the combination
-template <int CORE>
-static hipError_t launch_cut(int mode, const FlashParams& P, int grid, hipStream_t st) {
-  if (mode == 0) return launch_one<0, false, false, true, CORE>(P, grid, st);
-  return P.cols_in_place ? launch_one<2, false, true, true, CORE>(P, grid, st) : launch_one<2, false, false, true, CORE>(P, grid, st);
-}
 static hipError_t launch_parts(int mode, bool out_f32, const FlashParams& P0, hipStream_t st) {
   FlashParams P = P0;
   P.parts_per_head = parts_of(P.part_m, P.n_seg, P.seg);
   for (int k = 1; k < P.n_seg; ++k) P.seg[k].part0 = parts_of(P.part_m, k, P.seg);
   const int n = P.n_bh * P.parts_per_head;
   P.part_ml = P.part_o + (size_t)n * BQ * kHeadDim;
-  const hipError_t e = sweep_core(mode, P) == 1 ? launch_cut<1>(mode, P, n, st) : launch_cut<2>(mode, P, n, st);
+  hipError_t e = mode == 0 ? launch_one<0, false, false, true, 2>(P, n, st)
+               : P.cols_in_place ? launch_one<2, false, true, true, 2>(P, n, st) : launch_one<2, false, false, true, 2>(P, n, st);
   if (e != hipSuccess) return e;
   const dim3 grid(P.n_qtiles * (BQ / 8), P.n_bh);
   if (P.n_seg > 1) {

@@ -36,7 +36,7 @@ def test_no_kernel_spills(tmp_path):
     """No scratch, no spilled vector register, no scalar register kept in a vector lane: the attention kernels use up to
     252 registers and lose several times what a spill looks like it costs, in the middle of their loops."""
     kernels = _kernels(sa.lib_path(), tmp_path)
-    assert sum("flash_kernel" in name for name in kernels) >= 20 and any("select_kernel" in name for name in kernels)
+    assert sum("flash_kernel" in name for name in kernels) >= 10 and any("select_kernel" in name for name in kernels)
     for name, k in kernels.items():
         assert (k["private_segment_fixed_size"], k["vgpr_spill_count"], k["sgpr_spill_count"]) == ("0", "0", "0"), (name, k)
         assert int(k["vgpr_count"]) <= (128 if "12flash_kernelILi1E" in name else 256), (name, k["vgpr_count"])

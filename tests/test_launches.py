@@ -92,7 +92,7 @@ assert (room(B.SA_OP_DENSE_ATTN, sh) > pad * 256) == {cut}
 
 # (heads, tokens, core of the dense launch, of swept strips, of swept blocks): below and above the limits
 @pytest.mark.parametrize("Hq,S,cores", [(16, 4500, "222"), (8, 9000, "222"), (16, 5100, "222"), (16, 5300, "202"), (16, 6200, "002"), (16, 10000, "002"),
-                                        (16, 10300, "000"), (32, 16384, "000"), (32, 1000, "122"), (64, 2100, "202"), (4, 16000, "222")])
+                                        (16, 10300, "000"), (32, 16384, "000"), (32, 1000, "222"), (64, 2100, "202"), (4, 16000, "222")])
 def test_core_of_dense_and_swept_tiles_follows_the_launch(recorder, Hq, S, cores):
     """Launches of up to some 1.5 rounds of the CUs are bound by the chain of their heaviest tile, larger ones by
     power: each takes the shape of the MFMAs that is faster there (the results are the same bits)."""
