@@ -18,7 +18,7 @@ FLAGS = [
     "-Wno-unused-command-line-argument", "-Wno-inline-asm",
 ]
 # flash_attn.hip: wave-uniform branches stay branches.  The structurizer otherwise turns the uniform if / else of the
-# tile loops into flag chains, whose joins hold every array twice (360 to 570 bytes of spills per lane;
+# tile loops into flag chains, whose joins hold every array twice (90 to 270 bytes of spills per lane;
 # tests/test_build.py looks for them, should a compiler drop the option).
 EXTRA_FLAGS = {"flash_attn.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions=1"]}
 

@@ -154,11 +154,14 @@ __device__ __forceinline__ long long block_sum(long long x, long long* scratch) 
 // 1638 runs 45.2 / 31.1.
 constexpr int kColTileCost = 132, kRangeTileCost = 76, kRangeWaveCost = 7, kSweepTileCost = 140;
 // Which core a head in two passes is for (kSparseBit: core 1): what core 0 gains on a gathered tile and on
-// every wave that works on a range tile, against what it loses on a range tile whose other waves wait, in
-// the unit of the costs above.  Fitted to 32 heads of 64K on core 0 / core 1: 20 % of the columns 5.9 / 6.2 ms (5 a tile);
-// runs of one offset every 1000 6.6 / 5.1 (-18 a range tile, 2.4 waves at work), four every 300 20.8 / 16.5 (-15), 128 every 1000
-// 10.0 / 9.0 (-9, 4 waves), 400 every 4000 4.7 / 4.8 (+1.6, 5.5 waves), 700 every 4000 6.8 / 7.2, head patterns 34.1 / 35.2 (+4, 7.7 waves).
-constexpr int kCoreColTile = 5, kCoreWave = 5, kCoreRangeTile = 26;
+// every wave that works on a range tile, against what it loses on a range tile whose other waves wait, in the unit of
+// the costs above.  Core 0 / core 1, 32 heads of 64K: 20 % of the columns 5.9 / 6.2 ms (5 a tile), runs of one offset every
+// 1000 6.6 / 5.1 (-18 a range tile, 2.4 waves at work), four every 300 20.8 / 16.5 (-15), 128 every 1000 10.0 / 9.0 (-9, 4 waves), 700
+// every 4000 6.8 / 7.2 (+6, 6.2 waves), head patterns 34.1 / 35.2 (7.7 waves).  The line lies where heads of one layer seldom
+// fall on both sides, because a launch with both cores is slower than either alone (8 heads of 128K, alpha = 0.95, 4.9 waves:
+// 29.3 / 29.3 ms, half and half 30.6): planted slashes at alpha of 0.8 to 0.98 leave 3.4 to 6.1 waves and run up to 5 %
+// faster on core 1 (at 0.98 up to 5 % slower), smeared ones 6.4 to 7.8.
+constexpr int kCoreColTile = 2, kCoreWave = 5, kCoreRangeTile = 33;
 
 // Written by one workgroup: `active(d, w)` says whether wave w has work on diagonal d.  A
 // thread takes one (d, w) pair, a wave eight diagonals at a time (one ballot is eight
