@@ -51,10 +51,13 @@
  *     to the rounding of bf16 probabilities, not bit for bit.  So does a call
  *     whose workspace is smaller than what sa_workspace_bytes (or
  *     sa_partitioned_workspace_bytes) asks for but holds all but the partial
- *     sums: it is accepted, and nothing is cut.
+ *     sums: it is accepted, and (with one segment) nothing is cut.
  *   n_chunks > 1: sa_workspace_bytes asks for room to work on all segments at
  *     once (up to eight segments and 1 GiB); a call with less, down to the size
- *     for one segment, takes them one after the other.
+ *     for one segment, may take them one after the other.  Scores and lists are the
+ *     same either way; attention of a small call (256 query tiles or fewer in
+ *     some segment) agrees to rounding, because n_chunks and whether the segments go
+ *     together then decide the cut and the order of the products as well.
  */
 #ifndef SA_H
 #define SA_H
@@ -240,7 +243,7 @@ sa_status sa_block_sparse_attn(const sa_shape* shape, int32_t granularity,
  * running to seq_len: for those rows the mask is that of
  * sa_sparse_attn (granularity 1) or sa_block_sparse_attn with chunk m's lists.
  * Workspace: that of SA_OP_SPARSE_ATTN or SA_OP_BLOCK_SPARSE_ATTN for the same
- * sampling (the size for one segment is accepted too: the segments then go one
+ * sampling (the size for one segment is accepted too: the segments then may go one
  * after the other, and the partial sums of small problems may not fit).  `tiles` counts over all segments.
  */
 sa_status sa_select_chunked(const sa_shape* shape, const sa_sampling* sampling,

@@ -21,9 +21,9 @@
 // flash_body):
 //
 // Core 0, 16x16x32 MFMAs (two groups of 16 queries per wave, one LDS operand for both): the same
-// products as 32x32x16 at 14 % less energy (an MFMA loop 2038 against 1752 TFLOP/s, with an LDS
-// operand each 1790 against 1565), but a vector port that is blocked ~9 cycles by twice as many
-// MFMAs.  Core 2, the same schedule with 32x32x16 MFMAs (32 queries per wave), for launches that do not
+// products as 32x32x16 at some 12 % less energy (at the power limit an MFMA loop reaches 2003 against 1755
+// TFLOP/s, with an LDS operand each 1790 against 1645, with an exponential beside it 1511 against 1442), but a
+// vector port that is blocked by twice as many MFMAs (four fma in the stream of each 32 MFMA cycles: 46 against 33).  Core 2, the same schedule with 32x32x16 MFMAs (32 queries per wave), for launches that do not
 // reach the power limit; its results are those of core 0 bit for bit.
 // The waves form two groups of four (rows 0..127 and 128..255); waves
 // w and w+4 share a SIMD.  Left alone, two waves that alternate an MFMA section

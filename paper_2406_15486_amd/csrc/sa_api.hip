@@ -198,9 +198,10 @@ int segment_jobs(const Dims& d, int n_chunks, int m0, int n, sa::SegmentJob* seg
 
 // Several segments go through one launch per step where a workspace of kBatchBytes holds the lists,
 // gathered keys or partial scores of all of them: segments of a few thousand tokens leave most of
-// the chip idle one by one (one by one / at once: 8 heads x 2 of 5003 tokens in three segments 333 / 220 us, 8 of 2048 in
-// two 154 / 94, 32 of 20000 in two 1656 / 1637, 16 of 40000 in four blocks 3235 / 2769); more than 1 GiB of them (two
-// segments of 32 heads from 30 thousand tokens on) fill it as they are, and the memory is the caller's.
+// the chip idle one by one (scores and attention, one by one / at once: 8 heads of 5003 tokens in three segments 93 + 272 /
+// 37 + 116 us, 16 of 20000 in four 194 + 1276 / 130 + 802 (0.5 GB more), 32 of 20000 in two 161 + 1483 / 141 + 1442 (0.33 GB more),
+// 16 of 40000 in four of blocks 309 + 2906 / 247 + 2410, 32 of 64K in two of blocks 414 + 7360 / 402 + 7359); more than 1 GiB of
+// them (two segments of 32 heads from 30 thousand tokens on) fill it as they are, and the memory is the caller's.
 constexpr size_t kBatchBytes = (size_t)1 << 30;
 bool batch_chunks(const Dims& d, int n_chunks, size_t bytes) {
   return n_chunks > 1 && n_chunks <= sa::kMaxSegs && (long long)n_chunks * d.n_bh <= 65535 && bytes <= kBatchBytes;

@@ -49,19 +49,19 @@ struct FlashParams {
   float* part_ml;           // (set by the launch)
   int parts_per_head;       // (set by the launch)
   // strip-masked mode only
-  const uint16_t* kc;           // [n_bh, S_pad, 128] K rows gathered by column index
-  const uint16_t* vct;          // [n_bh, 128, S_pad] V rows gathered and transposed
-  const int32_t* col_idx_pad;   // [n_bh, cidx_stride] ascending, padded with INT_MAX
-  const int32_t* col_cnt;       // [n_bh]
-  const uint32_t* col_bits;     // [n_bh, cb_words]  bit j: key j is a selected column
-  const uint32_t* off_bits;     // [n_bh, rb_words]  bit x: offset off_max - x is kept
-  const int32_t* dlist;         // [n_bh, dlist_stride] ascending touched tile-diagonals
-  const int32_t* dcnt;          // [n_bh]
-  unsigned long long* tiles;    // nullable [n_bh]
+  const uint16_t* kc;           // [n_slots, S_pad, 128] K rows gathered by column index
+  const uint16_t* vct;          // [n_slots, 128, S_pad] V rows gathered and transposed
+  const int32_t* col_idx_pad;   // [n_slots, cidx_stride] ascending, padded with INT_MAX
+  const int32_t* col_cnt;       // [n_slots]
+  const uint32_t* col_bits;     // [n_slots, cb_words]  bit j: key j is a selected column
+  const uint32_t* off_bits;     // [n_slots, rb_words]  bit x: offset off_max - x is kept
+  const int32_t* dlist;         // [n_slots, dlist_stride] ascending touched tile-diagonals
+  const int32_t* dcnt;          // [n_slots]
+  unsigned long long* tiles;    // nullable [n_bh]: over all segments
   int cidx_stride, cb_words, rb_words, dlist_stride, off_max;
 };
 
-// mode 0: dense causal; 1: row log-sum-exp of rows [q_row0, q_row0+n_qrows); 2: strip mask
+// mode 0: dense causal; 1: row log-sum-exp of the n_qrows rows from seg[].row_lo on of every segment; 2: strip mask
 hipError_t launch_flash(int mode, bool out_f32, const FlashParams& P, hipStream_t st);
 // parts of the keys of a query tile (from the sequence alone, at most max_parts) and the workgroups
 // that share them (from the heads of the launch too)
@@ -105,7 +105,7 @@ struct MaskPrepParams {
   const int32_t* slash_idx; const int32_t* slash_cnt;
   uint32_t* col_bits; uint32_t* off_bits;
   int32_t* dlist; int32_t* dcnt;
-  unsigned long long* tiles;                           // nullable [n_bh]: cleared
+  unsigned long long* tiles;                           // nullable [heads_per_seg]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
   int cores;                                           // the attention launch reads kSparseBit
   int heads_per_seg;                                   // n_bh counts the heads of every segment
@@ -121,7 +121,7 @@ struct BlockPrepParams {
                                                        // columns, padded with INT_MAX
   uint32_t* col_bits; uint32_t* off_bits;
   int32_t* dlist; int32_t* dcnt;
-  unsigned long long* tiles;                           // nullable [n_bh]: cleared
+  unsigned long long* tiles;                           // nullable [heads_per_seg]: cleared
   int n_bh, S, window, cb_words, rb_words, dlist_stride, off_max;
   int heads_per_seg;                                   // n_bh counts the heads of every segment
   SegmentJob seg[kMaxSegs];                            // the query tiles a segment's masks are for, and the end of their rows
