@@ -23,8 +23,9 @@
 // Core 0, 16x16x32 MFMAs (two groups of 16 queries per wave, one LDS operand for both): the same
 // products as 32x32x16 at some 12 % less energy (at the power limit an MFMA loop reaches 2003 against 1755
 // TFLOP/s, with an LDS operand each 1790 against 1645, with an exponential beside it 1511 against 1442), but a
-// vector port that is blocked by twice as many MFMAs (four fma in the stream of each 32 MFMA cycles: 46 against 33).  Core 2, the same schedule with 32x32x16 MFMAs (32 queries per wave), for launches that do not
-// reach the power limit; its results are those of core 0 bit for bit.
+// vector port that is blocked by twice as many MFMAs (four fma in the stream of each 32 MFMA cycles: 46
+// against 33 cycles).  Core 2, the same schedule with 32x32x16 MFMAs (32 queries per wave), for launches that
+// do not reach the power limit; its results are those of core 0 bit for bit.
 // The waves form two groups of four (rows 0..127 and 128..255); waves
 // w and w+4 share a SIMD.  Left alone, two waves that alternate an MFMA section
 // and a vector-ALU (softmax) section fall into step - both on the matrix pipe,
@@ -35,8 +36,8 @@
 // them, so every SIMD always has one wave feeding the matrix pipe and one feeding
 // the vector pipe.
 //
-// Core 1, 32x32x16 MFMAs (32 queries per wave): every wave issues the softmax of one 32-key half
-// between the MFMAs of the next, so that a tile is one chain of about half the length.
+// Core 1, 32x32x16 MFMAs (32 queries per wave), heads in two passes: every wave issues the softmax of one
+// 32-key half between the MFMAs of the next, so that a tile is one chain of about half the length.
 //
 // Core 2 / core 0 / core 1, whole path or kernel: dense 16K 1948 / 1860 / 1961 us, 8 heads of 8300 174 / 187 / 177;
 // 8K swept 672 / 620 / 652; blocks of 128 at 32K 3261 / 3040 / 3146, swept, 16 heads of 4500 165 / 176 / 170; 64K head
